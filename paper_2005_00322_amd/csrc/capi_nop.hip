@@ -25,7 +25,7 @@ struct pstd_nop_s {
   float *qpre = nullptr, *q = nullptr, *out = nullptr;
   float *Y1 = nullptr, *Ahat = nullptr, *Zt = nullptr, *At2 = nullptr, *T = nullptr;
   float *dv = nullptr, *dvn = nullptr, *dpre = nullptr, *dq = nullptr, *dout = nullptr, *part = nullptr;
-  double* terms = nullptr;
+  double *terms = nullptr, *mid = nullptr;
   std::vector<void*> owned;
   int last_batch = 0;
   bool have_fwd = false;
@@ -154,7 +154,7 @@ int weight_grad(pstd_nop_s* N, const float* X, int M, const float* Y, int Nc, fl
   g.bC1 = static_cast<int64_t>(nch) * M * Nc;
   g.bC2 = static_cast<int64_t>(M) * Nc;
   NOP_RUN(launch_nop_gemm(g, N->stream));
-  NOP_RUN(launch_nop_partial_sum(N->part, G, B * nch, M * Nc, N->stream));
+  NOP_RUN(launch_nop_partial_sum(N->part, G, N->mid, B * nch, M * Nc, N->stream));
   return PSTD_OK;
 }
 
@@ -237,6 +237,9 @@ int pstd_nop_create(const pstd_nop_config* cfg, void* hip_stream, pstd_nop* out)
   A(&N->dout, B * P);
   A(&N->part, partsz);
   if (st == PSTD_OK && nop_alloc(N, reinterpret_cast<void**>(&N->terms), 2 * B * sizeof(double)) != PSTD_OK)
+    st = PSTD_E_OOM;
+  if (st == PSTD_OK && nop_alloc(N, reinterpret_cast<void**>(&N->mid),
+                                 nop_mid_count(std::max(Hp, C), std::max(Hp, C) * std::max(C, 4)) * sizeof(double)) != PSTD_OK)
     st = PSTD_E_OOM;
   if (st != PSTD_OK) {
     nop_free(N);
@@ -366,7 +369,7 @@ int pstd_nop_backward(pstd_nop N, const float* target, double* loss) {
   float* gr = N->grad;
   NOP_RUN(launch_nop_loss(N->out, target, N->terms, N->dout, B, P, s));
   // output layer
-  NOP_RUN(launch_nop_rowsum(N->dout, gr + N->oq2b, B, 1, P, s));
+  NOP_RUN(launch_nop_rowsum(N->dout, gr + N->oq2b, N->mid, B, 1, P, s));
   int st = weight_grad(N, N->dout, 1, N->q, Hp, gr + N->oQ2, B);
   if (st != PSTD_OK) return st;
   // dq = (Q2 outer dout) * GELU'(qpre)
@@ -376,15 +379,14 @@ int pstd_nop_backward(pstd_nop N, const float* target, double* loss) {
   g.bC1 = Hp * P;
   g.dgelu = N->qpre;
   NOP_RUN(launch_nop_gemm(g, s));
-  NOP_RUN(launch_nop_rowsum(N->dq, gr + N->oq1b, B, Hp, P, s));
+  NOP_RUN(launch_nop_rowsum(N->dq, gr + N->oq1b, N->mid, B, Hp, P, s));
   st = weight_grad(N, N->dq, Hp, N->V[c.layers], C, gr + N->oQ1, B);
   if (st != PSTD_OK) return st;
   // dv = Q1^T dq
   NOP_RUN(launch_nop_mix(th + N->oQ1, true, N->dq, N->dv, nullptr, nullptr, nullptr, nullptr, nullptr, 0, C, Hp, H, W,
                          B, false, c.split != 0, 0, s));
   for (int l = c.layers - 1; l >= 0; --l) {
-    NOP_RUN(launch_nop_gelu_bwd(N->dv, N->PRE[l], N->dpre, static_cast<int64_t>(B) * C * P, s));
-    NOP_RUN(launch_nop_rowsum(N->dpre, gr + N->ob[l], B, C, P, s));
+    NOP_RUN(launch_nop_gelu_bwd(N->dv, N->PRE[l], N->dpre, gr + N->ob[l], N->mid, B, C, P, s));
     st = weight_grad(N, N->dpre, C, N->V[l], C, gr + N->oW[l], B);
     if (st != PSTD_OK) return st;
     // dvn = W^T dpre
@@ -427,7 +429,7 @@ int pstd_nop_backward(pstd_nop N, const float* target, double* loss) {
     std::swap(N->dv, N->dvn);
   }
   // lift
-  NOP_RUN(launch_nop_rowsum(N->dv, gr + N->opb, B, C, P, s));
+  NOP_RUN(launch_nop_rowsum(N->dv, gr + N->opb, N->mid, B, C, P, s));
   st = weight_grad(N, N->dv, C, N->F, 4, gr + N->oP, B);
   if (st != PSTD_OK) return st;
   if (loss) {

@@ -299,9 +299,16 @@ hipError_t launch_nop_idct_h(const float* Z, void* T, const void* img, int B, in
                              bool half, hipStream_t s);   // T in bf16 with half
 hipError_t launch_nop_mode_transpose(const float* in, float* out, int B, int C, int Mm, bool to_block, hipStream_t s);
 hipError_t launch_nop_features(const float* p0, const float* c0, float* f, int B, int H, int W, hipStream_t s);
-hipError_t launch_nop_gelu_bwd(const float* gin, const float* pre, float* d, int64_t n, hipStream_t s);
-hipError_t launch_nop_rowsum(const float* x, float* out, int nb, int rows, int64_t P, hipStream_t s);
-hipError_t launch_nop_partial_sum(const float* part, float* out, int nz, int n, hipStream_t s);
+// Sums over the batch run in two stages; `mid` holds the first one's doubles (nop_mid_count of them, for the
+// largest row and column count the caller passes).  gelu_bwd: d = gin GELU'(pre), rowsum[j] = the sum of
+// d's row j over samples and positions (all [nb][rows][P]); rowsum: the same sum of x; partial_sum:
+// out[j] = sum_z part[z n + j].
+constexpr int kNopMidChunks = 64;
+size_t nop_mid_count(int max_rows, int max_cols);
+hipError_t launch_nop_gelu_bwd(const float* gin, const float* pre, float* d, float* rowsum, double* mid, int nb, int rows,
+                               int64_t P, hipStream_t s);
+hipError_t launch_nop_rowsum(const float* x, float* out, double* mid, int nb, int rows, int64_t P, hipStream_t s);
+hipError_t launch_nop_partial_sum(const float* part, float* out, double* mid, int nz, int n, hipStream_t s);
 hipError_t launch_nop_loss(const float* out, const float* tgt, double* terms, float* dout, int B, int64_t P,
                            hipStream_t s);
 hipError_t launch_nop_input_stats(const float* p0, const float* c0, double* stats, int B, int H, int W, int margin,
