@@ -111,7 +111,7 @@ int pstd_state_init(pstd_plan plan, pstd_state* state, int32_t u_mode);
 /* Advance the state by n_steps >= 0 steps of Eq. (dtt_pstd_solution) (§4.3 for 2D/3D): every u_a from
  * p^n first, then p^{n+1} from all u_a^{n+1/2}.  Asynchronous on the plan's stream.  The steps replay
  * captured HIP graphs (whole chunks of 50 steps, then one graph of the remaining steps; 1D plans of at most
- * 1365 nodes with walls on nodes run one kernel instead); a graph is captured on first use for the
+ * 1365 nodes with walls on nodes run the whole call in one or two kernels instead); a graph is captured on first use for the
  * state's buffers and kept by the plan (one full-chunk graph and one of the last other length). */
 int pstd_step(pstd_plan plan, pstd_state* state, int64_t n_steps);
 

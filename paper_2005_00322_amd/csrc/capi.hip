@@ -137,6 +137,7 @@ void free_plan(pstd_plan_s* P) {
   }
   if (P->c2map) (void)hipFree(P->c2map);
   if (P->flag) (void)hipFree(P->flag);
+  if (P->line_work) (void)hipFree(P->line_work);
   drop_graphs(P);
   delete P;
 }
@@ -177,14 +178,20 @@ int ensure_dense(pstd_plan_s* P, int a) {
 }
 
 // Whether axis a runs on the FFT path under the plan's current path setting.  AUTO: axes above 512
-// nodes (1D plans keep the single-workgroup kernel up to 1365 nodes).
+// nodes (1D plans keep the line kernels up to kLineMaxNodes nodes).
 bool axis_fft(const pstd_plan_s* P, int a) {
   if (!P->fft[a].ok) return false;
   if (P->fft[a].periodic && !P->fft_pow2) return false;   // the mixed-radix kernel extends symmetrically
   if (P->path == PSTD_PATH_FFT || P->path == PSTD_PATH_FFT_GENERIC) return true;
   if (P->path != PSTD_PATH_AUTO) return false;
-  if (P->ndim == 1) return P->n[0] > 1365;
+  if (P->ndim == 1) return P->n[0] > kLineMaxNodes;
   return P->n[a] > 512;
+}
+
+// Whether pstd_step runs the whole time loop in the 1D kernels (walls on nodes, at most kLineMaxNodes nodes,
+// not on the FFT path); other 1D plans step through the dense contractions.
+bool use_step1d(const pstd_plan_s* P) {
+  return P->ndim == 1 && !axis_fft(P, 0) && !axis_periodic(P, 0) && !axis_half_wall(P, 0) && P->n[0] <= kLineMaxNodes;
 }
 
 // Make sure every axis has what its path needs (called before any capture).
@@ -194,6 +201,12 @@ int prepare_axes(pstd_plan_s* P) {
       const int st = ensure_dense(P, a);
       if (st != PSTD_OK) return st;
     }
+  const size_t wb = use_step1d(P) && !P->line_work ? step1d_work_bytes(P->prec, static_cast<int>(P->n[0])) : 0;
+  if (wb) {
+    if (hipMalloc(&P->line_work, wb) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of the 1D workspace failed");
+    PSTD_HIP(hipMemset(P->line_work, 0, wb));
+    PSTD_HIP(hipStreamSynchronize(nullptr));
+  }
   return PSTD_OK;
 }
 
@@ -395,12 +408,6 @@ int step_graph(pstd_plan_s* P, const pstd_state* st, int64_t steps, hipGraphExec
   return PSTD_OK;
 }
 
-// Whether pstd_step runs the whole time loop in the single-workgroup 1D kernel (walls on nodes, at most
-// 1365 nodes, not on the FFT path); other 1D plans step through the dense contractions.
-bool use_step1d(const pstd_plan_s* P) {
-  return P->ndim == 1 && !axis_fft(P, 0) && !axis_periodic(P, 0) && !axis_half_wall(P, 0) && P->n[0] <= 1365;
-}
-
 }  // namespace
 }  // namespace pstd
 
@@ -466,7 +473,7 @@ int pstd_plan_create_ex(const pstd_grid* grid, double dx, double dt, double c0, 
   // a single line has no matrix-matrix product for the bf16 matrix cores: a 1D split-bf16 plan (float
   // state) computes as an FP32 plan
   if (grid->ndim == 1 && precision == PSTD_SPLIT_BF16) precision = PSTD_FP32;
-  // 1D walls on nodes: the single-workgroup kernel up to 1365 nodes, above that the FFT path where 2(n-1)
+  // 1D walls on nodes: the line kernels up to kLineMaxNodes nodes, above that the FFT path where 2(n-1)
   // factors and the dense contraction path otherwise (up to 4097 nodes, checked above)
   int64_t total = 1;
   for (int a = 0; a < grid->ndim; ++a) total *= grid->n[a];
@@ -582,7 +589,7 @@ int pstd_step(pstd_plan P, pstd_state* st, int64_t n_steps) {
   if (pst != PSTD_OK) return pst;
   if (use_step1d(P)) {
     PSTD_HIP(launch_step1d(P->prec, P->G[0], P->D[0], st->p, st->u[0], static_cast<int>(P->n[0]), n_steps,
-                           P->c2map, P->stream));
+                           P->c2map, P->line_work, P->line_spins, P->stream));
     st->step += n_steps;
     return PSTD_OK;
   }
@@ -824,6 +831,13 @@ int pstd_apply_axis_operator(pstd_plan P, int32_t axis, int32_t which, const voi
     if (st != PSTD_OK) return st;
   }
   PSTD_HIP(contract(P, op, axis, in, out, 1.0, 0.0, nullptr, P->stream));
+  return PSTD_OK;
+}
+
+// For tests: polls of the 1D kernel's bounded waits (0 sends every step through its fallback).
+int pstd_test_line_spins(pstd_plan P, uint32_t spins) {
+  if (!P) return fail(PSTD_E_INVALID_ARG, "null plan");
+  P->line_spins = spins;
   return PSTD_OK;
 }
 

@@ -133,8 +133,14 @@ struct ContractArgs {
 hipError_t launch_contract_fp32(const ContractArgs& a, bool contiguous, hipStream_t s);
 hipError_t launch_contract_fp64(const ContractArgs& a, bool contiguous, hipStream_t s);
 hipError_t launch_contract_split(const ContractArgs& a, bool contiguous, hipStream_t s);
+// The 1D time loop of lines of at most kLineMaxNodes nodes.  work: step1d_work_bytes of device memory, zeroed
+// once, kept by the plan; spins: polls a workgroup makes for a half step's values before it gives up (the steps
+// then run in one workgroup).
+constexpr int kLineMaxNodes = 1365;
+constexpr unsigned kLineSpins = 1u << 16;
+size_t step1d_work_bytes(int prec, int n);
 hipError_t launch_step1d(int prec, const DevOperator& G, const DevOperator& D, void* p, void* u, int n,
-                         int64_t steps, const void* scale, hipStream_t s);
+                         int64_t steps, const void* scale, void* work, unsigned spins, hipStream_t s);
 hipError_t launch_zero_dirichlet(int prec, void* p, int ndim, const int64_t* n, const int* dir_lo,
                                  const int* dir_hi, hipStream_t s);
 hipError_t launch_fill_zero(int prec, void* x, int64_t count, hipStream_t s);
@@ -332,6 +338,8 @@ struct pstd_plan_s {
   pstd::FftAxis fft[3];
   void* c2map = nullptr;       // c0(x)^2 in the state dtype (owned), null for a homogeneous medium
   int* flag = nullptr;         // device int for reductions (owned)
+  void* line_work = nullptr;   // 1D plans of 129 .. kLineMaxNodes nodes: workspace of launch_step1d (owned)
+  unsigned line_spins = pstd::kLineSpins;
   int path = 0;                // PSTD_PATH_* (0 = automatic)
   bool use_th = true;          // split-bf16 contractions form Toeplitz-plus-Hankel operators on the chip
   bool fft_pow2 = true;        // FP32 power-of-two FFT axes use fft_pow2_kernel

@@ -8,11 +8,12 @@ namespace {
 // transposed, K x M with row stride ldt, so that consecutive lanes read consecutive rows' entries)
 // stream from L2.  Each step is Eq. (dtt_pstd_solution): u += G~ p, then p += D~ u (scaled pointwise by
 // c0(x)^2 when a sound-speed map is given).  Threads split every dot product 4 ways; the sums and the
-// update are formed in FP64 for both state types and rounded once into the state.
+// update are formed in FP64 for both state types and rounded once into the state.  One CU reads its
+// operators at well under the L2 rate (n = 1000, FP32: 509 us per step), so this is only the fallback of
+// step1d_multi_kernel below.
 template <typename T>
-__global__ __launch_bounds__(1024) void step1d_kernel(const T* __restrict__ GT, int ldg, const T* __restrict__ DT,
-                                                      int ldd, T* __restrict__ p, T* __restrict__ u, int n,
-                                                      int64_t steps, const T* __restrict__ scale) {
+__device__ void step1d_one_block(const T* __restrict__ GT, int ldg, const T* __restrict__ DT, int ldd, T* __restrict__ p,
+                                 T* __restrict__ u, int n, int64_t steps, const T* __restrict__ scale) {
   extern __shared__ unsigned char smem_raw[];
   T* sp = reinterpret_cast<T*>(smem_raw);
   T* su = sp + n;
@@ -53,6 +54,177 @@ __global__ __launch_bounds__(1024) void step1d_kernel(const T* __restrict__ GT, 
   __syncthreads();
   for (int i = tid; i < n; i += nt) p[i] = sp[i];
   for (int i = tid; i < n - 1; i += nt) u[i] = su[i];
+}
+
+// ---- 1D lines above 128 nodes: the time loop over many workgroups --------------------------------------
+// Workgroup w owns rows 16 w .. 16 w + 15 of both operators, held in registers (as double) for all steps:
+// half a wave per row, lane l of the half holding columns l + 32 k.  Per half step a workgroup gathers the
+// other field into LDS, forms its 16 dot products (FP64), updates its values and publishes them.  n^2 FP64
+// products are spread over n / 16 CUs (0.2 us of them at n = 1000), so what bounds a half step is the exchange between
+// CUs: a value travels as one 64-bit word holding the float and the half step's number (FP64: two words with half
+// the bits each), so readers poll the values themselves and no barrier, fence or second round trip is needed.
+// A buffer per field is enough: a workgroup publishes step t + 1 of a field only after it has read all of
+// the other field, each value of which was published after its owner had read all of step t.
+// n = 1000, FP32 with a map, 50 steps: 25.5 ms in one workgroup, 0.265 ms here (2.5 us per half step).
+//
+// The workgroups have to be resident together.  A wait is bounded: a workgroup that gives up sets
+// head->abort and ends, and so do the others in turn.  Results go to a copy; the commit kernel that follows
+// either moves them into the state or, after an abort, runs all the steps in one workgroup from the state,
+// which is still untouched.  head->epoch numbers the half steps of successive launches (kept on the device, so
+// a captured launch can be replayed).
+struct LineHead {
+  unsigned epoch, abort;
+};
+constexpr int kLineThreads = 512, kLineRows = 16;
+
+template <typename T>
+__device__ __forceinline__ void line_publish(unsigned long long* x, int n, int i, T v, unsigned tag) {
+  const unsigned long long t = static_cast<unsigned long long>(tag) << 32;
+  if constexpr (sizeof(T) == 4) {
+    __hip_atomic_store(x + i, t | __builtin_bit_cast(unsigned, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    __hip_atomic_store(x + i, t | (b & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(x + n + i, t | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Values x[tid], x[tid + 512], .. below count into LDS once they carry `tag`; false if the wait ran out.
+template <typename T, int PER>
+__device__ __forceinline__ bool line_gather(const unsigned long long* x, int n, int count, unsigned tag, double* lds,
+                                            unsigned spins) {
+  const int tid = threadIdx.x;
+  unsigned long long a[PER], b[PER];
+  for (unsigned k = 0;; ++k) {
+    bool all = true;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int i = tid + q * kLineThreads;
+      if (i < count) {
+        a[q] = __hip_atomic_load(x + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (sizeof(T) == 8) b[q] = __hip_atomic_load(x + n + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      if (tid + q * kLineThreads >= count) continue;
+      all = all && static_cast<unsigned>(a[q] >> 32) == tag;
+      if constexpr (sizeof(T) == 8) all = all && static_cast<unsigned>(b[q] >> 32) == tag;
+    }
+    if (all) break;
+    if (k >= spins) return false;
+  }
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int i = tid + q * kLineThreads;
+    if (i >= count) continue;
+    if constexpr (sizeof(T) == 4)
+      lds[i] = static_cast<double>(__builtin_bit_cast(float, static_cast<unsigned>(a[q])));
+    else
+      lds[i] = __builtin_bit_cast(double, (b[q] << 32) | (a[q] & 0xffffffffull));
+  }
+  return true;
+}
+
+// x plus the value of the lane a DPP control selects (both halves of the double move together)
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double x) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
+  return x + __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
+}
+
+// Sum over the 32 lanes of a half wave, in all of them, in a fixed order: quad_perm [1,0,3,2] and [2,3,0,1],
+// then row_half_mirror and row_mirror (every lane of a quad, then of eight, holds the same sum), then the
+// neighbouring row of 16.
+__device__ __forceinline__ double half_wave_sum(double x) {
+  x = dpp_add<0xB1>(x);
+  x = dpp_add<0x4E>(x);
+  x = dpp_add<0x141>(x);
+  x = dpp_add<0x140>(x);
+  return x + __shfl_xor(x, 16);
+}
+
+// KPL columns per lane: n <= 32 KPL.
+template <typename T, int KPL>
+__global__ __launch_bounds__(kLineThreads) void step1d_multi_kernel(const T* __restrict__ G, int ldg,
+                                                                    const T* __restrict__ D, int ldd,
+                                                                    const T* __restrict__ p, const T* __restrict__ u,
+                                                                    int n, int64_t steps, const T* __restrict__ scale,
+                                                                    LineHead* head, unsigned long long* xp,
+                                                                    unsigned long long* xu, T* __restrict__ p_out,
+                                                                    T* __restrict__ u_out, unsigned spins) {
+  constexpr int PER = (32 * KPL + kLineThreads - 1) / kLineThreads;
+  __shared__ double sp[32 * KPL], su[32 * KPL];
+  __shared__ int gave_up[2];   // one per gather of a step, so a wave's next gather cannot change what others read
+  const int tid = threadIdx.x, l = tid & 31, nm = n - 1;
+  const int i = blockIdx.x * kLineRows + (tid >> 5);   // this half wave's row
+  double g[KPL], d[KPL];
+#pragma unroll
+  for (int k = 0; k < KPL; ++k) {
+    const int c = l + 32 * k;
+    g[k] = (i < nm && c < n) ? static_cast<double>(G[static_cast<int64_t>(i) * ldg + c]) : 0.0;
+    d[k] = (i < n && c < nm) ? static_cast<double>(D[static_cast<int64_t>(i) * ldd + c]) : 0.0;
+  }
+  const double sc = (scale && i < n) ? static_cast<double>(scale[i]) : 1.0;
+  T pi = i < n ? p[i] : T(0), ui = i < nm ? u[i] : T(0);
+  for (int e = tid; e < 32 * KPL; e += kLineThreads) {
+    sp[e] = e < n ? static_cast<double>(p[e]) : 0.0;
+    su[e] = 0.0;
+  }
+  if (tid < 2) gave_up[tid] = 0;
+  bool stop = false;
+  unsigned tag = head->epoch;
+  __syncthreads();
+  auto dot = [&](const double (&a)[KPL], const double* x) {
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) acc[k & 3] = fma(a[k], x[l + 32 * k], acc[k & 3]);
+    return half_wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
+  };
+  for (int64_t s = 0; s < steps; ++s) {
+    if (s) {
+      if (!line_gather<T, PER>(xp, n, n, tag, sp, spins)) gave_up[0] = 1;
+      __syncthreads();
+      if ((stop = gave_up[0] != 0)) break;
+    }
+    ui = static_cast<T>(static_cast<double>(ui) + dot(g, sp));
+    ++tag;
+    if (l == 0 && i < nm) line_publish<T>(xu, n, i, ui, tag);
+    if (!line_gather<T, PER>(xu, n, nm, tag, su, spins)) gave_up[1] = 1;
+    __syncthreads();
+    if ((stop = gave_up[1] != 0)) break;
+    pi = static_cast<T>(static_cast<double>(pi) + dot(d, su) * sc);
+    ++tag;
+    if (l == 0 && i < n) line_publish<T>(xp, n, i, pi, tag);
+  }
+  if (stop) {
+    if (tid == 0) __hip_atomic_store(&head->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  if (l == 0 && i < n) p_out[i] = pi;
+  if (l == 0 && i < nm) u_out[i] = ui;
+}
+
+// One workgroup, after step1d_multi_kernel: its results into the state, or all the steps here if it gave up.
+template <typename T>
+__global__ __launch_bounds__(1024) void step1d_commit_kernel(const T* __restrict__ GT, int ldg, const T* __restrict__ DT,
+                                                             int ldd, T* __restrict__ p, T* __restrict__ u, int n,
+                                                             int64_t steps, const T* __restrict__ scale, LineHead* head,
+                                                             const T* __restrict__ p_out, const T* __restrict__ u_out) {
+  const unsigned abort = head->abort, epoch = head->epoch;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    head->epoch = epoch + static_cast<unsigned>(2 * steps);
+    head->abort = 0;
+  }
+  if (abort) {
+    step1d_one_block<T>(GT, ldg, DT, ldd, p, u, n, steps, scale);
+    return;
+  }
+  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = p_out[i];
+  for (int i = threadIdx.x; i < n - 1; i += blockDim.x) u[i] = u_out[i];
 }
 
 // The same time loop for n <= 128 with both operators in registers for all steps: thread t owns row
@@ -194,33 +366,58 @@ unsigned blocks_for(int64_t count, int threads) {
 
 }  // namespace
 
-hipError_t launch_step1d(int prec, const DevOperator& G, const DevOperator& D, void* p, void* u, int n,
-                         int64_t steps, const void* scale, hipStream_t s) {
+namespace {
+
+// Layout of a plan's line workspace: the head (256 bytes), the exchanged words of p and of u (two per value in
+// FP64), the result copies.
+size_t line_words(int prec, int n) { return static_cast<size_t>(prec == PSTD_FP64 ? 2 : 1) * n; }
+
+template <typename T>
+hipError_t launch_step1d_t(int prec, const DevOperator& Go, const DevOperator& Do, T* p, T* u, int n, int64_t steps,
+                           const T* scale, void* work, unsigned spins, hipStream_t s) {
+  const T *G = static_cast<const T*>(Go.data), *D = static_cast<const T*>(Do.data);
   if (n <= 128) {
-    if (prec == PSTD_FP64)
-      hipLaunchKernelGGL(step1d_reg_kernel<double>, dim3(1), dim3(1024), 0, s, static_cast<const double*>(G.data),
-                         G.Kp, static_cast<const double*>(D.data), D.Kp, static_cast<double*>(p),
-                         static_cast<double*>(u), n, steps, static_cast<const double*>(scale));
-    else
-      hipLaunchKernelGGL(step1d_reg_kernel<float>, dim3(1), dim3(1024), 0, s, static_cast<const float*>(G.data),
-                         G.Kp, static_cast<const float*>(D.data), D.Kp, static_cast<float*>(p),
-                         static_cast<float*>(u), n, steps, static_cast<const float*>(scale));
+    hipLaunchKernelGGL(step1d_reg_kernel<T>, dim3(1), dim3(1024), 0, s, G, Go.Kp, D, Do.Kp, p, u, n, steps, scale);
     return hipGetLastError();
   }
-  const size_t esz = prec == PSTD_FP64 ? 8 : 4;
-  const size_t shmem = ((esz * 2 * static_cast<size_t>(n) + 7) & ~static_cast<size_t>(7)) + 8 * static_cast<size_t>(4) * n;
-  if (shmem > 64 * 1024) return hipErrorInvalidConfiguration;
-  int threads = 4 * n;
-  threads = threads > 1024 ? 1024 : ((threads + 63) / 64) * 64;
-  if (prec == PSTD_FP64)
-    hipLaunchKernelGGL(step1d_kernel<double>, dim3(1), dim3(threads), shmem, s, static_cast<const double*>(G.dataT),
-                       G.Mp, static_cast<const double*>(D.dataT), D.Mp, static_cast<double*>(p),
-                       static_cast<double*>(u), n, steps, static_cast<const double*>(scale));
-  else
-    hipLaunchKernelGGL(step1d_kernel<float>, dim3(1), dim3(threads), shmem, s, static_cast<const float*>(G.dataT),
-                       G.Mp, static_cast<const float*>(D.dataT), D.Mp, static_cast<float*>(p),
-                       static_cast<float*>(u), n, steps, static_cast<const float*>(scale));
+  const size_t shmem = ((sizeof(T) * 2 * static_cast<size_t>(n) + 7) & ~static_cast<size_t>(7)) + 8 * static_cast<size_t>(4) * n;
+  if (shmem > 64 * 1024 || !work || n > kLineMaxNodes) return hipErrorInvalidConfiguration;
+  LineHead* head = static_cast<LineHead*>(work);
+  unsigned long long* xp = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(work) + 256);
+  unsigned long long* xu = xp + line_words(prec, n);
+  T* po = reinterpret_cast<T*>(xu + line_words(prec, n));
+  T* uo = po + n;
+  const dim3 grid((n + kLineRows - 1) / kLineRows), blk(kLineThreads);
+#define PSTD_LINE(KPL)                                                                                                \
+  hipLaunchKernelGGL((step1d_multi_kernel<T, KPL>), grid, blk, 0, s, G, Go.Kp, D, Do.Kp, p, u, n, steps, scale, head, \
+                     xp, xu, po, uo, spins)
+  if (n <= 32 * 8) PSTD_LINE(8);
+  else if (n <= 32 * 16) PSTD_LINE(16);
+  else if (n <= 32 * 24) PSTD_LINE(24);
+  else if (n <= 32 * 32) PSTD_LINE(32);
+  else PSTD_LINE(43);
+#undef PSTD_LINE
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(step1d_commit_kernel<T>, dim3(1), dim3(1024), shmem, s, static_cast<const T*>(Go.dataT), Go.Mp,
+                     static_cast<const T*>(Do.dataT), Do.Mp, p, u, n, steps, scale, head, po, uo);
   return hipGetLastError();
+}
+
+}  // namespace
+
+size_t step1d_work_bytes(int prec, int n) {
+  if (n <= 128) return 0;
+  return 256 + 2 * line_words(prec, n) * 8 + 2 * static_cast<size_t>(prec == PSTD_FP64 ? 8 : 4) * n;
+}
+
+hipError_t launch_step1d(int prec, const DevOperator& G, const DevOperator& D, void* p, void* u, int n,
+                         int64_t steps, const void* scale, void* work, unsigned spins, hipStream_t s) {
+  if (prec == PSTD_FP64)
+    return launch_step1d_t<double>(prec, G, D, static_cast<double*>(p), static_cast<double*>(u), n, steps,
+                                   static_cast<const double*>(scale), work, spins, s);
+  return launch_step1d_t<float>(prec, G, D, static_cast<float*>(p), static_cast<float*>(u), n, steps,
+                                static_cast<const float*>(scale), work, spins, s);
 }
 
 hipError_t launch_zero_dirichlet(int prec, void* p, int ndim, const int64_t* n, const int* lo, const int* hi,
