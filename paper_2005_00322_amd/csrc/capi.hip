@@ -45,8 +45,10 @@ float bf16_to_float(uint16_t h) {
   return f;
 }
 
-// Round the FP64 matrix (M x K, already scaled) to the plan precision and upload it zero padded.
-int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, double scale, DevOperator* op) {
+// Round the FP64 matrix (M x K, already scaled) to the plan precision and upload it zero padded; with frag also
+// in fragment order (FP64 and FP32).
+int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, double scale, DevOperator* op,
+                    bool frag = false) {
   op->M = M;
   op->K = K;
   op->Mp = static_cast<int>(round_up(M, kRowPad));
@@ -69,8 +71,13 @@ int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, 
           if (want_t) reinterpret_cast<float*>(hostT.data())[t] = static_cast<float>(v);
         }
       }
-    if (hipMalloc(&op->data, cnt * esz) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
+    if (hipMalloc(&op->data, (frag ? 2 : 1) * cnt * esz) != hipSuccess)
+      return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
     PSTD_HIP(hipMemcpy(op->data, host.data(), cnt * esz, hipMemcpyHostToDevice));
+    if (frag) {
+      op->frag = static_cast<unsigned char*>(op->data) + cnt * esz;
+      PSTD_HIP(build_fragments(esz == 8, *op, P->stream));
+    }
     if (want_t) {
       if (hipMalloc(&op->dataT, cnt * esz) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
       PSTD_HIP(hipMemcpy(op->dataT, hostT.data(), cnt * esz, hipMemcpyHostToDevice));
@@ -172,8 +179,10 @@ int ensure_dense(pstd_plan_s* P, int a) {
   const AxisCase c = axis_case(P->bc[2 * a], P->bc[2 * a + 1]);
   const AxisTables& t = axis_tables(n, c);
   const int m = staggered_points(n, c);
-  int st = upload_operator(P, t.G, m, n, const_G(P), &P->G[a]);
-  if (st == PSTD_OK) st = upload_operator(P, t.D, n, m, const_D(P), &P->D[a]);
+  const bool frag = P->ndim == 2 && P->prec != PSTD_SPLIT_BF16 &&
+                    phase2d_supported(static_cast<int>(P->n[0]), static_cast<int>(P->n[1]));
+  int st = upload_operator(P, t.G, m, n, const_G(P), &P->G[a], frag);
+  if (st == PSTD_OK) st = upload_operator(P, t.D, n, m, const_D(P), &P->D[a], frag);
   return st;
 }
 
@@ -340,18 +349,16 @@ bool velocity_fft_multi(const pstd_plan_s* P, pstd_state* st, hipStream_t s, hip
 }
 
 bool use_fused2d(const pstd_plan_s* P) {
-  return P->ndim == 2 && P->prec == PSTD_FP32 && (P->path == PSTD_PATH_AUTO || P->path == PSTD_PATH_FUSED) &&
+  return P->ndim == 2 && P->prec != PSTD_SPLIT_BF16 && (P->path == PSTD_PATH_AUTO || P->path == PSTD_PATH_FUSED) &&
          phase2d_supported(static_cast<int>(P->n[0]), static_cast<int>(P->n[1]));
 }
 
 // Enqueue n steps of the 2D/3D scheme: all velocity contractions, then all pressure contractions
-// (two fused phase kernels per step for small 2D FP32 plans, one kernel per axis and phase otherwise).
+// (two fused phase kernels per step for small 2D FP32 and FP64 plans, one kernel per axis and phase otherwise).
 hipError_t enqueue_steps(pstd_plan_s* P, pstd_state* st, int64_t nsteps, hipStream_t s) {
   if (use_fused2d(P))
-    return launch_phase2d(P->G[0], P->G[1], P->D[0], P->D[1], static_cast<float*>(st->p),
-                          static_cast<float*>(st->u[0]), static_cast<float*>(st->u[1]),
-                          static_cast<const float*>(P->c2map), static_cast<int>(P->n[0]), static_cast<int>(P->n[1]),
-                          nsteps, s);
+    return launch_phase2d(P->prec == PSTD_FP64, P->G[0], P->G[1], P->D[0], P->D[1], st->p, st->u[0], st->u[1], P->c2map,
+                          static_cast<int>(P->n[0]), static_cast<int>(P->n[1]), nsteps, s);
   for (int64_t t = 0; t < nsteps; ++t) {
     hipError_t e = hipSuccess;
     if (velocity_fft_multi(P, st, s, &e)) {
@@ -659,10 +666,8 @@ int pstd_apply_axis(pstd_plan P, pstd_state* st, int32_t axis, int32_t which) {
     for (int a = 0; a < P->ndim; ++a)
       if (!st->u[a]) return fail(PSTD_E_INVALID_ARG, "u[%d] is null", a);
     if (use_fused2d(P)) {
-      PSTD_HIP(launch_phase2d_one(which, P->G[0], P->G[1], P->D[0], P->D[1], static_cast<float*>(st->p),
-                                  static_cast<float*>(st->u[0]), static_cast<float*>(st->u[1]),
-                                  static_cast<const float*>(P->c2map), static_cast<int>(P->n[0]),
-                                  static_cast<int>(P->n[1]), P->stream));
+      PSTD_HIP(launch_phase2d_one(P->prec == PSTD_FP64, which, P->G[0], P->G[1], P->D[0], P->D[1], st->p, st->u[0],
+                                  st->u[1], P->c2map, static_cast<int>(P->n[0]), static_cast<int>(P->n[1]), P->stream));
       return PSTD_OK;
     }
     const int pst = prepare_axes(P);

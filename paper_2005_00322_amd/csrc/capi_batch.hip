@@ -44,7 +44,7 @@ namespace {
 
 constexpr int64_t kChunk = 1024;   // steps per persistent launch
 
-int upload_unscaled(const std::vector<double>& m, int M, int K, DevOperator* op) {
+int upload_unscaled(const std::vector<double>& m, int M, int K, bool frag, hipStream_t s, DevOperator* op) {
   op->M = M;
   op->K = K;
   op->Mp = static_cast<int>(round_up(M, kRowPad));
@@ -52,8 +52,13 @@ int upload_unscaled(const std::vector<double>& m, int M, int K, DevOperator* op)
   std::vector<float> h(static_cast<size_t>(op->Mp) * op->Kp, 0.f);
   for (int i = 0; i < M; ++i)
     for (int k = 0; k < K; ++k) h[static_cast<size_t>(i) * op->Kp + k] = static_cast<float>(m[static_cast<size_t>(i) * K + k]);
-  if (hipMalloc(&op->data, h.size() * sizeof(float)) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc failed");
+  if (hipMalloc(&op->data, (frag ? 2 : 1) * h.size() * sizeof(float)) != hipSuccess)
+    return fail(PSTD_E_OOM, "hipMalloc failed");
   PSTD_HIP(hipMemcpy(op->data, h.data(), h.size() * sizeof(float), hipMemcpyHostToDevice));
+  if (frag) {
+    op->frag = static_cast<float*>(op->data) + h.size();
+    PSTD_HIP(build_fragments(false, *op, s));
+  }
   return PSTD_OK;
 }
 
@@ -216,7 +221,7 @@ bool phase_eligible(const pstd_batch_s* B) {
   for (int s = 0; s < B->count; ++s) {
     const BatchSolve& S = B->solves[s];
     if (B->nx[s] != B->nx[0] || B->ny[s] != B->ny[0]) return false;
-    if (!batch2d_phase_fits(S.ldgx, S.ldgy, S.lddx, S.lddy, S.nx, S.ny)) return false;
+    if (!S.fGx || !S.fDx || !S.fGy || !S.fDy || !batch2d_phase_fits(S.ldgx, S.ldgy, S.lddx, S.lddy, S.nx, S.ny)) return false;
   }
   return phase2d_supported(B->nx[0], B->ny[0]);
 }
@@ -353,7 +358,9 @@ int pstd_batch_create(int32_t count, const int64_t* n, const int32_t* bc, const 
     B->dt.push_back(dt[s]);
     B->c0.push_back(c0[s]);
   }
-  // shared operators
+  // shared operators, in fragment order too where tile 16 (which reads them so) is possible
+  bool frag = phase2d_supported(B->nx[0], B->ny[0]);
+  for (int s = 0; s < count; ++s) frag = frag && B->nx[s] == B->nx[0] && B->ny[s] == B->ny[0];
   for (int s = 0; s < count; ++s) {
     const std::pair<int, int> keys[2] = {{B->nx[s], static_cast<int>(axis_case(B->bc[4 * s], B->bc[4 * s + 1]))},
                                          {B->ny[s], static_cast<int>(axis_case(B->bc[4 * s + 2], B->bc[4 * s + 3]))}};
@@ -361,8 +368,8 @@ int pstd_batch_create(int32_t count, const int64_t* n, const int32_t* bc, const 
       if (B->ops.count(k)) continue;
       const AxisTables& t = axis_tables(k.first, static_cast<AxisCase>(k.second));
       pstd_batch_s::Op op;
-      int st = upload_unscaled(t.G, k.first - 1, k.first, &op.G);
-      if (st == PSTD_OK) st = upload_unscaled(t.D, k.first, k.first - 1, &op.D);
+      int st = upload_unscaled(t.G, k.first - 1, k.first, frag, B->stream, &op.G);
+      if (st == PSTD_OK) st = upload_unscaled(t.D, k.first, k.first - 1, frag, B->stream, &op.D);
       B->ops[k] = op;
       if (st != PSTD_OK) {
         free_batch(B);
@@ -376,6 +383,10 @@ int pstd_batch_create(int32_t count, const int64_t* n, const int32_t* bc, const 
     S.Dx = static_cast<const float*>(ox.D.data);
     S.Gy = static_cast<const float*>(oy.G.data);
     S.Dy = static_cast<const float*>(oy.D.data);
+    S.fGx = static_cast<const float*>(ox.G.frag);
+    S.fDx = static_cast<const float*>(ox.D.frag);
+    S.fGy = static_cast<const float*>(oy.G.frag);
+    S.fDy = static_cast<const float*>(oy.D.frag);
     S.ldgx = ox.G.Kp;
     S.lddx = ox.D.Kp;
     S.ldgy = oy.G.Kp;

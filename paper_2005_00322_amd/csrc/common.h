@@ -89,6 +89,7 @@ struct DevOperator {
   int Mp = 0, Kp = 0;      // padded size (row stride = Kp)
   void* data = nullptr;    // FP64: double[Mp*Kp]; FP32: float[Mp*Kp]; SPLIT: bf16 hi[Mp*Kp] then lo[Mp*Kp]
   void* dataT = nullptr;   // 1D plans: transposed copy, Kp x Mp (row stride Mp)
+  void* frag = nullptr;    // FP64 / FP32 operators of the fused 2D phases: data in MFMA fragment order (one allocation)
   // SPLIT only, operators with a Toeplitz-plus-Hankel form and kThRowsMin < M <= kThRowsMax, Kp <= kThColsMax:
   // FP32 f and g windows of th_len values each (see kernels_split.hip) and the end weights
   // {first row, last row, first column, last column}
@@ -148,11 +149,14 @@ hipError_t launch_square(int prec, const float* in, void* out, int64_t count, hi
 hipError_t launch_combine(const float* const* f, const float* w, int nf, float* out, int64_t count,
                           hipStream_t s);
 bool phase2d_supported(int nx, int ny);
-hipError_t launch_phase2d(const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx, const DevOperator& Dy,
-                          float* p, float* ux, float* uy, const float* c2, int nx, int ny, int64_t steps,
-                          hipStream_t s);
-hipError_t launch_phase2d_one(int which, const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx,
-                              const DevOperator& Dy, float* p, float* ux, float* uy, const float* c2, int nx, int ny,
+// Fills op->frag from op->data on stream s.
+hipError_t build_fragments(bool dbl, const DevOperator& op, hipStream_t s);
+// Two fused phases per 2D step (fields and operators double with dbl, float otherwise).
+hipError_t launch_phase2d(bool dbl, const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx,
+                          const DevOperator& Dy, void* p, void* ux, void* uy, const void* c2, int nx, int ny,
+                          int64_t steps, hipStream_t s);
+hipError_t launch_phase2d_one(bool dbl, int which, const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx,
+                              const DevOperator& Dy, void* p, void* ux, void* uy, const void* c2, int nx, int ny,
                               hipStream_t s);
 // ---- batched 2D solves (kernels_batch2d.hip, capi_batch.hip) --------------------------------------
 struct BatchSolve {
@@ -160,6 +164,7 @@ struct BatchSolve {
   float* ux;                // (nx-1) x ny
   float* uy;                // nx x (ny-1)
   const float* Gx; const float* Dx; const float* Gy; const float* Dy;   // unscaled (dx = 1) operators
+  const float* fGx; const float* fDx; const float* fGy; const float* fDy;   // the same in fragment order (tile 16)
   int ldgx, lddx, ldgy, lddy;                                          // their row strides
   int mgx, mdx, mgy, mdy;                                              // their allocated (padded) rows
   int nx, ny;

@@ -1,25 +1,37 @@
-// Two fused phase kernels per step for 2D FP32 plans with at most 512 nodes per axis.
+// Two fused phase kernels per step for 2D plans (FP32 and FP64).
 //
 // Eq. (dtt_pstd_solution) in its 2D form (§4.3) splits into a velocity phase and a pressure phase:
 //   velocity  u_x += G~x p   and   u_y += p G~y^T           (one launch)
 //   pressure  p += c2 .* (D~x u_x + u_y D~y^T)               (one launch)
-// Each block owns one 16 x 16 output tile of the phase: in the velocity phase the u_x and the u_y tile at
+// Each block owns one square output tile of the phase: in the velocity phase the u_x and the u_y tile at
 // the same (i, j) position, in the pressure phase one p tile with both axes' terms.  Both phases are thus
 // two contractions of the same shape,
 //   contraction 0:  out0[i][j] = sum_k A0[i][k] X0[k][j]   (operator rows, columns of a field)
 //   contraction 1:  out1[i][j] = sum_k X1[i][k] A1[j][k]   (rows of a field, operator rows)
-// and the eight waves of a block split them as (contraction, quarter of k).  A box of a few hundred nodes a
-// side is bound by latency, not by bandwidth or MFMA rate, so a block issues every load it needs (four
-// full-k operand slices and the old output values of its epilogue) before the first LDS store: one
-// round trip to memory per phase.  Small tiles give enough blocks to spread the MFMA work over the
-// whole GPU (256 blocks of eight waves for 256 x 256).  The kernel boundary between the phases is the grid-wide
-// dependency of the scheme; graph replay keeps the launch gaps short.
+// and the eight waves of a block split them as (contraction, k chunks h, h + 4, .. of 16).
 //
-// MFMA v_mfma_f32_16x16x4: lane l supplies P[l%16][kslot l/16] and Q[l%16][kslot l/16] and receives
-// C[4*(l/16)+r][l%16] in register r.  A lane reads four consecutive k of each operand with one LDS
-// read and feeds component e to the e-th of four independent MFMAs, so MFMA e contracts the k set
+// A box of a few hundred nodes a side is bound by latency, not by bandwidth or MFMA rate.  As the waves of a block
+// split k and each computes the whole tile, no operand element is used by two waves, so nothing is shared before
+// the partial tiles meet in LDS:
+//   operators  are kept in fragment order (fragment_kernel): the 16 rows x 16 k that one wave feeds to four MFMAs are
+//              one run of 64 lanes x 4 values, loaded straight into the MFMA registers;
+//   X0         16 lanes read 16 neighbouring columns of a row, straight into the registers;
+//   X1         rows are read with neighbouring lanes along k (one value a lane: rows of odd length start at any
+//              value, and 16-byte loads off their alignment cost more than they save) and turned into fragments
+//              through a strip of LDS that belongs to the wave (no block barrier).
+// Loaded as fragments, each quad of lanes would touch four rows, four cache lines for 64 bytes.
+// Loads run NR rounds of RC chunks ahead; the kernel boundary between the phases is the grid-wide dependency of the
+// scheme, and graph replay keeps the launch gaps short.
+//
+// Tile edge 16 MT.  A block reads 2 x 16 MT operand rows for (16 MT)^2 outputs, so at MT = 1 the operands'
+// path into the CU (64 bytes per clock) is exactly as busy as the matrix cores and at MT = 2 half as busy, but MT = 2
+// has a quarter of the blocks: the rule is at tile_edge().
+//
+// MFMA v_mfma_{f32,f64}_16x16x4: lane l supplies P[l%16][kslot l/16] and Q[l%16][kslot l/16] and receives
+// C[4*(l/16)+r][l%16] (f32) or C[4*r+l/16][l%16] (f64) in register r.  A lane holds the four consecutive k
+// 4 (l/16) .. + 3 of a 16-wide chunk and feeds component e to the e-th MFMA, so MFMA e contracts the k set
 // {k0 + 4s + e}; the four together cover k0 .. k0+15 once.  FP32 chain sums are flushed into FP64
-// registers every 32 k, the halves and contractions are added in FP64, and the update is rounded once.
+// registers every 32 k, the waves' shares and the contractions are added in FP64, and the update is rounded once.
 #include <algorithm>
 
 #include "common.h"
@@ -28,354 +40,393 @@ namespace pstd {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 
-constexpr int T = 16;                   // output tile edge
 constexpr int NT = 512;                 // eight waves
 constexpr uint32_t kOOB = 0x80000000u;  // buffer offset past every range: the load returns zero
 
+template <typename T> struct Mma;
+template <> struct Mma<float> {
+  typedef f32x4 v4;
+  static __device__ __forceinline__ v4 mma(float a, float b, v4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
+};
+template <> struct Mma<double> {
+  typedef f64x4 v4;
+  static __device__ __forceinline__ v4 mma(double a, double b, v4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int lane, int r) { return 4 * r + (lane >> 4); }
+};
+
 // mx, my: staggered points along x and y, n - 1 between two walls and n on a periodic axis
+template <typename T>
 struct Phase2DArgs {
-  const float* Gx; int ldgx, mgx;   // mx x nx operator, row stride ldgx, mgx rows allocated (zero padded)
-  const float* Gy; int ldgy, mgy;   // my x ny
-  const float* Dx; int lddx, mdx;   // nx x mx
-  const float* Dy; int lddy, mdy;   // ny x my
-  float* p;                         // nx x ny
-  float* ux;                        // mx x ny
-  float* uy;                        // nx x my
-  const float* c2;                  // nx x ny or null
+  const T* Gx; int ldgx, mgx;   // mx x nx operator in fragment order, ldgx columns, mgx rows (zero padded)
+  const T* Gy; int ldgy, mgy;   // my x ny
+  const T* Dx; int lddx, mdx;   // nx x mx
+  const T* Dy; int lddy, mdy;   // ny x my
+  T* p;                         // nx x ny
+  T* ux;                        // mx x ny
+  T* uy;                        // nx x my
+  const T* c2;                  // nx x ny or null
   int nx, ny, mx, my;
-  double sv, sp;                    // velocity / pressure factors on the contractions (1 for folded operators)
+  double sv, sp;                // velocity / pressure factors on the contractions (1 for folded operators)
 };
 
 __device__ __forceinline__ rsrc_t make_rsrc(const void* ptr, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(ptr), 0, static_cast<int>(bytes), 0x00020000);
 }
-__device__ __forceinline__ float ld_f32(rsrc_t r, uint32_t voff) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, 0, 0));
+__device__ __forceinline__ void ld1(float& v, rsrc_t r, uint32_t o) {
+  v = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0));
 }
-__device__ __forceinline__ f32x4 ld_f32x4(rsrc_t r, uint32_t voff) {
-  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
+__device__ __forceinline__ void ld1(double& v, rsrc_t r, uint32_t o) {
+  v = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, o, 0, 0));
 }
+__device__ __forceinline__ void ld4(f32x4& v, rsrc_t r, uint32_t o) {
+  v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0));
+}
+__device__ __forceinline__ void ld4(f64x4& v, rsrc_t r, uint32_t o) {
+  const f64x2 a = __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0));
+  const f64x2 b = __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(r, o + 16, 0, 0));
+  v = f64x4{a[0], a[1], b[0], b[1]};
+}
+
+// 0, or the bit that takes a byte offset (below 2^31) out of every range.  Arithmetic on purpose: a uniform condition
+// written as a choice between two offsets becomes a branch with the load on either side and a wait in each.
+__device__ __forceinline__ uint32_t oob_unless(bool in) { return (static_cast<uint32_t>(in) - 1u) & kOOB; }
 
 __host__ __device__ __forceinline__ int pad64(int k) { return (k + 63) & ~63; }
 
-// One phase's operands in registers between the loads and the LDS stores (512 threads).
-//   op0, op1: operator rows r0 .. r0+15, k < Kpad, thread t holds k = 4 (t%32) + 128 j of row t/32
-//   col0:     X0[k][c0 + c], thread t holds c = t%16, k = t/16 + 32 u
-//   row1:     X1[r0 + r][k], thread t holds r = t/64 + 8 q, k = t%64 + 64 j
-template <int KMAX>
-struct Slices {
-  static constexpr int KC = KMAX / 64;
-  f32x4 op0[KMAX / 128], op1[KMAX / 128];
-  float col0[KMAX / 32];
-  float row1[2 * KC];
+// Tile shapes: RC chunks of 16 k per round (a row's part of a round is 256 / MT bytes), NR rounds in flight.
+template <typename T, int MT>
+struct Shape {
+  static constexpr int RC = (sizeof(T) == 4 ? 4 : 2) / MT, NR = 1;
+  static constexpr int RL = 16 * RC;                           // lanes along a row
+  static constexpr int RI = 16 * MT * RL / 64;                 // loads of a round (64 / RL rows each)
+  static constexpr int V = 16 / static_cast<int>(sizeof(T));   // values of a 16-byte LDS read
+  static constexpr int LD = 16 * RC + V;                       // LDS row stride: those reads without bank conflicts
+  static constexpr size_t strip = sizeof(T) * 16 * MT * LD;    // LDS of one wave's rows
 };
 
-template <int KMAX>
-__device__ __forceinline__ void load_op(f32x4 (&v)[KMAX / 128], rsrc_t rs, int ld, int r0, int Kpad) {
-  const int t = threadIdx.x;
-  const uint32_t base = 4u * static_cast<uint32_t>((r0 + (t >> 5)) * ld + 4 * (t & 31));
+// This wave's share of one contraction: acc[a][b] (the MT x MT sub-tiles) += sum over its chunks of P Q^T.
+// C = 0: P the operator rows i0 .., Q the columns j0 .. of the field X (row stride ldx);
+// C = 1: P the rows i0 .. of X, Q the operator rows j0 ...  K: contracted length, h: the wave's quarter of it.
+// The operator is zero for k >= K, up to pad64(K); X's rows k >= K lie past its end and read as zero, and the
+// elements of a row past K would be the next row's, so they are not read (a NaN there would not vanish).
+template <typename T, int MT, int C>
+__device__ __forceinline__ void contract_share(rsrc_t rA, int lda, rsrc_t rX, int ldx, int i0, int j0, int K, int h,
+                                               T* strip, double (&acc)[MT][MT][4]) {
+  typedef typename Mma<T>::v4 v4;
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  typedef Shape<T, MT> S;
+  constexpr int RC = S::RC, NR = S::NR, V = S::V, RL = S::RL, RI = S::RI, LD = S::LD;
+  constexpr uint32_t ES = sizeof(T);
+  constexpr bool kFlush = sizeof(T) == 4;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = 4 * (lane >> 4);
+  const int nit = pad64(K) / 64;            // chunks of a wave
+  const int c0 = h * nit;                   // its first
+  v4 A[NR][RC][MT], X0[C == 0 ? NR : 1][RC][MT];
+  T X1[C == 1 ? NR : 1][RI];
+  const int r0 = (C == 0 ? i0 : j0) >> 4, nc = lda >> 4;
+  // in the order of use, kept by the scheduler barriers: the first products start while later chunks are on their way
+  auto load = [&](int slot, int rd) {
+    if constexpr (C == 1) {
+      const int k = 16 * (c0 + rd * RC) + lane % RL;
+      const uint32_t past = oob_unless(k < min(16 * (c0 + nit), K));
 #pragma unroll
-  for (int j = 0; j < KMAX / 128; ++j)
-    if (128 * j < Kpad) v[j] = ld_f32x4(rs, base + 512u * j);
-}
-
-template <int KMAX>
-__device__ __forceinline__ void store_op(float* dst, const f32x4 (&v)[KMAX / 128], int Kpad) {
-  constexpr int LD = KMAX + 4;
-  const int t = threadIdx.x;
-  float* d = dst + (t >> 5) * LD + 4 * (t & 31);
+      for (int i = 0; i < RI; ++i) {
+        const int r = i0 + i * (64 / RL) + lane / RL;
+        ld1(X1[slot][i], rX, past | ES * static_cast<uint32_t>(r * ldx + k));
+      }
+    }
 #pragma unroll
-  for (int j = 0; j < KMAX / 128; ++j)
-    if (128 * j < Kpad) *reinterpret_cast<f32x4*>(d + 128 * j) = v[j];
-}
-
-// columns c0 .. c0+15 of X (row stride ld; valid c < cols, k < K)
-template <int KMAX>
-__device__ __forceinline__ void load_cols(float (&v)[KMAX / 32], rsrc_t rs, int ld, int c0, int cols, int K, int Kpad) {
-  const int t = threadIdx.x;
-  const int c = c0 + (t & 15);
+    for (int q = 0; q < RC; ++q) {
+      const int it = rd * RC + q, ch = c0 + it;
+      const uint32_t past = oob_unless(it < nit);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int u = 0; u < KMAX / 32; ++u) {
-    const int k = (t >> 4) + 32 * u;
-    if (32 * u < Kpad) v[u] = ld_f32(rs, (c < cols && k < K) ? 4u * static_cast<uint32_t>(k * ld + c) : kOOB);
-  }
-}
-
-template <int KMAX>
-__device__ __forceinline__ void store_cols(float* dst, const float (&v)[KMAX / 32], int Kpad) {
-  constexpr int LD = KMAX + 4;
-  const int t = threadIdx.x;
-  float* d = dst + (t & 15) * LD + (t >> 4);
+      for (int a = 0; a < MT; ++a) {
+        ld4(A[slot][q][a], rA, past | ES * static_cast<uint32_t>(((r0 + a) * nc + ch) * 256 + 4 * lane));
+        if constexpr (C == 0) {
 #pragma unroll
-  for (int u = 0; u < KMAX / 32; ++u)
-    if (32 * u < Kpad) d[32 * u] = v[u];
-}
-
-// rows r0 .. r0+15 of X (row stride ld; valid r < rows, k < K)
-template <int KMAX>
-__device__ __forceinline__ void load_rows(float (&v)[2 * (KMAX / 64)], rsrc_t rs, int ld, int r0, int rows, int K,
-                                          int Kpad) {
-  const int t = threadIdx.x;
+          for (int e = 0; e < 4; ++e) {
+            T v;
+            ld1(v, rX, past | ES * static_cast<uint32_t>((16 * ch + lk + e) * ldx + j0 + 16 * a + lr));
+            X0[slot][q][a][e] = v;
+          }
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  v4 c[MT][MT];
+  const v4 zero = {0, 0, 0, 0};
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int r = r0 + (t >> 6) + 8 * q;
+  for (int a = 0; a < MT; ++a)
 #pragma unroll
-    for (int j = 0; j < KMAX / 64; ++j) {
-      const int k = (t & 63) + 64 * j;
-      if (64 * j < Kpad)
-        v[q * (KMAX / 64) + j] = ld_f32(rs, (r < rows && k < K) ? 4u * static_cast<uint32_t>(r * ld + k) : kOOB);
+    for (int b = 0; b < MT; ++b) c[a][b] = zero;
+#pragma unroll
+  for (int s = 0; s < NR; ++s) load(s, s);
+  const int nrd = (nit + RC - 1) / RC;
+  for (int rd = 0; rd < nrd; rd += NR) {
+#pragma unroll
+    for (int s = 0; s < NR; ++s) {
+      if (rd + s >= nrd) break;
+      if constexpr (C == 1) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");   // the last round's reads come first
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < RI; ++i) strip[(i * (64 / RL) + lane / RL) * LD + lane % RL] = X1[s][i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+      }
+#pragma unroll
+      for (int q = 0; q < RC; ++q) {
+        if ((rd + s) * RC + q >= nit) break;
+        v4 X[MT];
+#pragma unroll
+        for (int a = 0; a < MT; ++a) {
+          if constexpr (C == 0) {
+            X[a] = X0[s][q][a];
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; e += V) {
+              const vec v = *reinterpret_cast<const vec*>(strip + (16 * a + lr) * LD + 16 * q + lk + e);
+#pragma unroll
+              for (int f = 0; f < V; ++f) X[a][e + f] = v[f];
+            }
+          }
+        }
+        if constexpr (MT == 1) {
+          // one tile: four independent products, so none waits for the one before it
+          v4 m[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) m[e] = C == 0 ? Mma<T>::mma(A[s][q][0][e], X[0][e], zero)
+                                                    : Mma<T>::mma(X[0][e], A[s][q][0][e], zero);
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            acc[0][0][r] += (static_cast<double>(m[0][r]) + static_cast<double>(m[1][r])) +
+                            (static_cast<double>(m[2][r]) + static_cast<double>(m[3][r]));
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+              for (int b = 0; b < MT; ++b)
+                c[a][b] = C == 0 ? Mma<T>::mma(A[s][q][a][e], X[b][e], c[a][b])
+                                 : Mma<T>::mma(X[a][e], A[s][q][b][e], c[a][b]);
+          if (kFlush && (q % 2 == 1 || RC == 1)) {
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+              for (int b = 0; b < MT; ++b) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[a][b][r] += static_cast<double>(c[a][b][r]);
+                c[a][b] = zero;
+              }
+          }
+        }
+      }
+      if (rd + s + NR < nrd) load(s, rd + s + NR);
     }
   }
-}
-
-template <int KMAX>
-__device__ __forceinline__ void store_rows(float* dst, const float (&v)[2 * (KMAX / 64)], int Kpad) {
-  constexpr int LD = KMAX + 4;
-  const int t = threadIdx.x;
+  if constexpr (MT > 1) {   // FP64, and the last chunk of an odd FP32 share
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    float* d = dst + ((t >> 6) + 8 * q) * LD + (t & 63);
+    for (int a = 0; a < MT; ++a)
 #pragma unroll
-    for (int j = 0; j < KMAX / 64; ++j)
-      if (64 * j < Kpad) d[64 * j] = v[q * (KMAX / 64) + j];
+      for (int b = 0; b < MT; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[a][b][r] += static_cast<double>(c[a][b][r]);
   }
 }
 
-// acc (this lane's four outputs of the 16 x 16 tile) += sum over k in [kb, ke) of P[row][k] Q[col][k];
-// kb and ke multiples of 32.
-template <int KMAX>
-__device__ __forceinline__ void mma_range(const float* P, const float* Q, int kb, int ke, double (&acc)[4]) {
-  constexpr int LD = KMAX + 4;
-  const int lane = threadIdx.x & 63;
-  const float* Pp = P + (lane & 15) * LD + 4 * (lane >> 4);
-  const float* Qp = Q + (lane & 15) * LD + 4 * (lane >> 4);
-  for (int k = kb; k < ke; k += 32) {
-    const f32x4 a0 = *reinterpret_cast<const f32x4*>(Pp + k);
-    const f32x4 b0 = *reinterpret_cast<const f32x4*>(Qp + k);
-    const f32x4 a1 = *reinterpret_cast<const f32x4*>(Pp + k + 16);
-    const f32x4 b1 = *reinterpret_cast<const f32x4*>(Qp + k + 16);
-    const f32x4 z = {0, 0, 0, 0};
-    f32x4 c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[0], b0[0], z, 0, 0, 0);
-    f32x4 c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[1], b0[1], z, 0, 0, 0);
-    f32x4 c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[2], b0[2], z, 0, 0, 0);
-    f32x4 c3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[3], b0[3], z, 0, 0, 0);
-    c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[0], b1[0], c0, 0, 0, 0);
-    c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[1], b1[1], c1, 0, 0, 0);
-    c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[2], b1[2], c2, 0, 0, 0);
-    c3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[3], b1[3], c3, 0, 0, 0);
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      acc[r] += (static_cast<double>(c0[r]) + static_cast<double>(c1[r])) +
-                (static_cast<double>(c2[r]) + static_cast<double>(c3[r]));
-  }
-}
-
-template <int KMAX, bool ALIAS>
-constexpr size_t lds_bytes() {
-  return ALIAS ? std::max(sizeof(float) * 4 * T * (KMAX + 4), sizeof(double) * 8 * 4 * 64)
-               : sizeof(float) * 4 * T * (KMAX + 4) + sizeof(double) * 8 * 4 * 64;
-}
-
-// PH 0: velocity phase, PH 1: pressure phase.
-// ALIAS: the partial tiles reuse the operand slices' LDS once every wave has finished its products (one
-// more barrier, less LDS: two blocks per CU where many blocks queue); otherwise they follow the slices.
-template <int KMAX, int PH, bool ALIAS>
-__device__ __forceinline__ void phase2d_body(const Phase2DArgs& a) {
-  constexpr int SL = T * (KMAX + 4);
-  extern __shared__ float lds[];
-  double* red = reinterpret_cast<double*>(ALIAS ? lds : lds + 4 * SL);   // [wave][reg][lane], eight waves
+// PH 0: velocity phase, PH 1: pressure phase.  tile: index of the block's tile.
+template <typename T, int MT, int PH>
+__device__ __forceinline__ void phase2d_body(const Phase2DArgs<T>& a, int tile) {
+  constexpr int E = 16 * MT, G = MT * MT * 4;   // tile edge, register groups of a tile (64 values each)
+  constexpr uint32_t ES = sizeof(T);
+  // the partial tiles of the eight waves; before that the row strips of waves 4 .. 7
+  constexpr size_t kRed = sizeof(double) * 8 * G * 64, kStrips = 4 * Shape<T, MT>::strip;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kRed > kStrips ? kRed : kStrips];
+  double (*red)[G][64] = reinterpret_cast<double (*)[G][64]>(lds);
   const int nx = a.nx, ny = a.ny, mx = a.mx, my = a.my;
-  const int tiles_y = (ny + T - 1) / T;
-  const int nb = gridDim.x;
-  int b = blockIdx.x;
-  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);   // consecutive tiles on one XCD
-  const int i0 = (b / tiles_y) * T, j0 = (b % tiles_y) * T;
+  const int tiles_y = (ny + E - 1) / E;
+  const int i0 = (tile / tiles_y) * E, j0 = (tile % tiles_y) * E;
   // the wave index through readfirstlane keeps per-wave buffer descriptors in scalar registers
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
-  // the two contractions of this phase
-  const float* A0 = PH == 0 ? a.Gx : a.Dx;
-  const int lda0 = PH == 0 ? a.ldgx : a.lddx, ma0 = PH == 0 ? a.mgx : a.mdx;
-  const float* A1 = PH == 0 ? a.Gy : a.Dy;
-  const int lda1 = PH == 0 ? a.ldgy : a.lddy, ma1 = PH == 0 ? a.mgy : a.mdy;
-  const float* X0 = PH == 0 ? a.p : a.ux;                   // ld ny, K0 rows
-  const float* X1 = PH == 0 ? a.p : a.uy;                   // nx rows of K1
-  const int K0 = PH == 0 ? nx : mx, K1 = PH == 0 ? ny : my;
-  const int ld1 = PH == 0 ? ny : my;
-  const int Kp0 = pad64(K0), Kp1 = pad64(K1);
-
-  const rsrc_t rA0 = make_rsrc(A0, 4u * static_cast<uint32_t>(ma0 * lda0));
-  const rsrc_t rA1 = make_rsrc(A1, 4u * static_cast<uint32_t>(ma1 * lda1));
-  const rsrc_t rX0 = make_rsrc(X0, 4u * static_cast<uint32_t>(K0 * ny));
-  const rsrc_t rX1 = make_rsrc(X1, 4u * static_cast<uint32_t>(nx * ld1));
-
-  // old output value of this wave's share of the epilogue, loaded with the operands
-  //   velocity: wave w finishes register w%4 of the u_x (w < 4) or u_y (w >= 4) tile
-  //   pressure: wave w < 4 finishes register w of the p tile
-  float old = 0.f, cfac = 1.f;
-  const int oj = j0 + (lane & 15);
-  if (PH == 0) {
-    float* Y = wave < 4 ? a.ux : a.uy;
-    const int rows = wave < 4 ? mx : nx, cols = wave < 4 ? ny : my;
-    const rsrc_t rY = make_rsrc(Y, 4u * static_cast<uint32_t>(rows * cols));
-    const int oi = i0 + 4 * (lane >> 4) + (wave & 3);
-    old = ld_f32(rY, (oi < rows && oj < cols) ? 4u * static_cast<uint32_t>(oi * cols + oj) : kOOB);
-  } else if (wave < 4) {
-    const rsrc_t rP = make_rsrc(a.p, 4u * static_cast<uint32_t>(nx * ny));
-    const int oi = i0 + 4 * (lane >> 4) + wave;
-    const bool ok = oi < nx && oj < ny;
-    old = ld_f32(rP, ok ? 4u * static_cast<uint32_t>(oi * ny + oj) : kOOB);
-    if (a.c2) {
-      const rsrc_t rC = make_rsrc(a.c2, 4u * static_cast<uint32_t>(nx * ny));
-      cfac = ld_f32(rC, ok ? 4u * static_cast<uint32_t>(oi * ny + oj) : kOOB);
-    }
-  }
-
-  Slices<KMAX> s;
-  load_op<KMAX>(s.op0, rA0, lda0, i0, Kp0);
-  load_cols<KMAX>(s.col0, rX0, ny, j0, ny, K0, Kp0);
-  load_rows<KMAX>(s.row1, rX1, ld1, i0, nx, K1, Kp1);
-  load_op<KMAX>(s.op1, rA1, lda1, j0, Kp1);
-  float* S0 = lds;            // A0 rows       [i][k]
-  float* S1 = lds + SL;       // X0 columns    [j][k]
-  float* S2 = lds + 2 * SL;   // X1 rows       [i][k]
-  float* S3 = lds + 3 * SL;   // A1 rows       [j][k]
-  store_op<KMAX>(S0, s.op0, Kp0);
-  store_cols<KMAX>(S1, s.col0, Kp0);
-  store_rows<KMAX>(S2, s.row1, Kp1);
-  store_op<KMAX>(S3, s.op1, Kp1);
-  __syncthreads();
-
-  double acc[4] = {0, 0, 0, 0};
-  {
-    // wave w: contraction w / 4, quarter w % 4 of its 32-wide k chunks
-    const int c = wave >> 2, h = wave & 3;
-    const int nch = (c == 0 ? Kp0 : Kp1) >> 5;
-    mma_range<KMAX>(c == 0 ? S0 : S2, c == 0 ? S1 : S3, 32 * ((h * nch) >> 2), 32 * (((h + 1) * nch) >> 2), acc);
-  }
-  if (ALIAS) __syncthreads();
+  // this wave's share of the epilogue: velocity, groups (wave % 4) + 4 g of u_x (wave < 4) or u_y; pressure,
+  // groups wave + 8 g of p (for a 16 x 16 tile waves 0 .. 3 have one each).  Old values and c2 are loaded first.
+  constexpr int NG = PH == 0 ? G / 4 : (G + 7) / 8;
+  const bool ux = wave < 4;
+  T* const Y = PH == 1 ? a.p : (ux ? a.ux : a.uy);
+  const int rows = PH == 1 ? nx : (ux ? mx : nx), cols = PH == 1 ? ny : (ux ? ny : my);
+  const int g0 = PH == 0 ? (wave & 3) : wave, gs = PH == 0 ? 4 : 8;
+  const rsrc_t rY = make_rsrc(Y, ES * static_cast<uint32_t>(rows * cols));
+  const rsrc_t rC = make_rsrc(a.c2, PH == 1 && a.c2 ? ES * static_cast<uint32_t>(nx * ny) : 0u);   // no map: zeros
+  T old[NG], cf[NG];
+  int off[NG];   // element offset, -1 outside the field or past the tile's groups
 #pragma unroll
-  for (int r = 0; r < 4; ++r) red[(wave * 4 + r) * 64 + lane] = acc[r];
-  __syncthreads();
+  for (int g = 0; g < NG; ++g) {
+    const int grp = g0 + gs * g, sub = grp >> 2;
+    const int oi = i0 + 16 * (sub / MT) + Mma<T>::row(lane, grp & 3), oj = j0 + 16 * (sub % MT) + (lane & 15);
+    off[g] = (grp < G && oi < rows && oj < cols) ? oi * cols + oj : -1;
+    const uint32_t o = oob_unless(off[g] >= 0) | ES * static_cast<uint32_t>(off[g]);
+    ld1(old[g], rY, o);
+    if (PH == 1) ld1(cf[g], rC, o);
+  }
 
-  auto part = [&](int w, int r) { return red[(w * 4 + r) * 64 + lane]; };
-  if (PH == 0) {
-    const int c = wave >> 2, r = wave & 3;
-    float* Y = c == 0 ? a.ux : a.uy;
-    const int rows = c == 0 ? mx : nx, cols = c == 0 ? ny : my;
-    const double v = (part(4 * c, r) + part(4 * c + 1, r)) + (part(4 * c + 2, r) + part(4 * c + 3, r));
-    const int oi = i0 + 4 * (lane >> 4) + r;
-    if (oi < rows && oj < cols)
-      Y[static_cast<int64_t>(oi) * cols + oj] = static_cast<float>(static_cast<double>(old) + a.sv * v);
-  } else if (wave < 4) {
-    const int r = wave;
-    const double v = ((part(0, r) + part(1, r)) + (part(2, r) + part(3, r))) +
-                     ((part(4, r) + part(5, r)) + (part(6, r) + part(7, r)));
-    const int oi = i0 + 4 * (lane >> 4) + r;
-    if (oi < nx && oj < ny)
-      a.p[static_cast<int64_t>(oi) * ny + oj] =
-          static_cast<float>(static_cast<double>(old) + a.sp * v * static_cast<double>(cfac));
+  double acc[MT][MT][4] = {};
+  if (ux) {
+    const T* A = PH == 0 ? a.Gx : a.Dx;
+    const int lda = PH == 0 ? a.ldgx : a.lddx, ma = PH == 0 ? a.mgx : a.mdx, K = PH == 0 ? nx : mx;
+    contract_share<T, MT, 0>(make_rsrc(A, ES * static_cast<uint32_t>(ma * lda)), lda,
+                                    make_rsrc(PH == 0 ? a.p : a.ux, ES * static_cast<uint32_t>(K * ny)), ny, i0, j0, K,
+                                    wave, nullptr, acc);
+  } else {
+    const T* A = PH == 0 ? a.Gy : a.Dy;
+    const int lda = PH == 0 ? a.ldgy : a.lddy, ma = PH == 0 ? a.mgy : a.mdy, K = PH == 0 ? ny : my;
+    contract_share<T, MT, 1>(make_rsrc(A, ES * static_cast<uint32_t>(ma * lda)), lda,
+                                    make_rsrc(PH == 0 ? a.p : a.uy, ES * static_cast<uint32_t>(nx * K)), K, i0, j0, K,
+                                    wave - 4, reinterpret_cast<T*>(lds + (wave - 4) * Shape<T, MT>::strip), acc);
+  }
+  lds_barrier();   // the strips are read
+#pragma unroll
+  for (int x = 0; x < MT; ++x)
+#pragma unroll
+    for (int y = 0; y < MT; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][(x * MT + y) * 4 + r][lane] = acc[x][y][r];
+  lds_barrier();
+
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int grp = g0 + gs * g;
+    if (off[g] < 0) continue;
+    auto part = [&](int w) { return red[w][grp][lane]; };
+    const int w0 = PH == 0 && !ux ? 4 : 0;
+    double v = (part(w0) + part(w0 + 1)) + (part(w0 + 2) + part(w0 + 3));
+    if (PH == 1) v += (part(4) + part(5)) + (part(6) + part(7));
+    v *= PH == 0 ? a.sv : a.sp;
+    if (PH == 1 && a.c2) v *= static_cast<double>(cf[g]);
+    Y[off[g]] = static_cast<T>(static_cast<double>(old[g]) + v);
   }
 }
 
-template <int KMAX, int PH>
-__global__ __launch_bounds__(NT) void phase2d_kernel(Phase2DArgs a) {
-  phase2d_body<KMAX, PH, false>(a);
+// Block b of n runs on XCD b % 8: the tile (in the order of the grid) that gives each XCD a run of consecutive
+// ones, whose operator rows and field strips then meet in one L2.
+__device__ __forceinline__ int xcd_tile(int b, int n) {
+  const int x = b & 7, q = n >> 3, r = n & 7;
+  return x * q + min(x, r) + (b >> 3);
 }
 
-// One phase of many solves of one shape: block (tile, solve), the solve's unscaled operators and
-// factors from the batch's solve table.
-template <int KMAX, int PH>
-__global__ __launch_bounds__(NT) void phase2d_batch_kernel(const BatchSolve* __restrict__ solves) {
-  const BatchSolve& S = solves[blockIdx.y];
-  const Phase2DArgs a{S.Gx, S.ldgx, S.mgx, S.Gy, S.ldgy, S.mgy, S.Dx, S.lddx, S.mdx, S.Dy, S.lddy, S.mdy,
-                      S.p, S.ux, S.uy, S.c2, S.nx, S.ny, S.nx - 1, S.ny - 1, S.sG, S.sD};
-  phase2d_body<KMAX, PH, true>(a);
+template <typename T, int MT, int PH>
+__global__ __launch_bounds__(NT, 4) void phase2d_kernel(Phase2DArgs<T> a) {
+  phase2d_body<T, MT, PH>(a, xcd_tile(blockIdx.x, gridDim.x));
 }
 
-// the dynamic LDS size above 64 KB is an attribute of each kernel instance, set once per device
-template <typename F>
-hipError_t configure(F* fn, size_t lds, int* configured) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (*configured == dev) return hipSuccess;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          static_cast<int>(lds));
-  if (e == hipSuccess) *configured = dev;
-  return e;
+// One phase of many solves of one shape: tiles solve after solve, the solve's unscaled operators and factors
+// from the batch's solve table.
+template <int MT, int PH>
+__global__ __launch_bounds__(NT, 4) void phase2d_batch_kernel(const BatchSolve* __restrict__ solves, int tiles) {
+  const int t = xcd_tile(blockIdx.x, gridDim.x);
+  const BatchSolve& S = solves[t / tiles];
+  const Phase2DArgs<float> a{S.fGx, S.ldgx, S.mgx, S.fGy, S.ldgy, S.mgy, S.fDx, S.lddx, S.mdx, S.fDy, S.lddy, S.mdy,
+                             S.p, S.ux, S.uy, S.c2, S.nx, S.ny, S.nx - 1, S.ny - 1, S.sG, S.sD};
+  phase2d_body<float, MT, PH>(a, t % tiles);
 }
 
-template <int KMAX>
-hipError_t launch_one(int which, const Phase2DArgs& a, hipStream_t s) {
-  static int conf[2] = {-1, -1};
-  const int nb = ((a.nx + T - 1) / T) * ((a.ny + T - 1) / T);
-  constexpr size_t lds = lds_bytes<KMAX, false>();
-  hipError_t e = which == 0 ? configure(phase2d_kernel<KMAX, 0>, lds, &conf[0])
-                            : configure(phase2d_kernel<KMAX, 1>, lds, &conf[1]);
-  if (e != hipSuccess) return e;
-  if (which == 0) hipLaunchKernelGGL((phase2d_kernel<KMAX, 0>), dim3(nb), dim3(NT), lds, s, a);
-  else hipLaunchKernelGGL((phase2d_kernel<KMAX, 1>), dim3(nb), dim3(NT), lds, s, a);
+// dst: the Mp x Kp matrix src in fragment order: for every 16 rows and chunk of 16 columns the 64 lanes' four
+// values, lane l those of row l % 16, columns 4 (l / 16) .. + 3.
+template <typename T>
+__global__ __launch_bounds__(256) void fragment_kernel(const T* __restrict__ src, T* __restrict__ dst, int Mp, int Kp) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= Mp * Kp) return;
+  const int e = i & 3, l = (i >> 2) & 63, blk = i >> 8, nc = Kp >> 4;
+  dst[i] = src[(16 * (blk / nc) + (l & 15)) * Kp + 16 * (blk % nc) + 4 * (l >> 4) + e];
+}
+
+int tiles_of(int nx, int ny, int edge) { return ((nx + edge - 1) / edge) * ((ny + edge - 1) / edge); }
+
+// Tile edge for `count` boxes of nx x ny nodes: 16 while its tiles are at most two per CU (each tile is then little more
+// than one round trip to memory), 32 beyond.  us per phase at 16 / 32, FP32 and FP64: 256 x 256 (256 tiles)
+// 4.2 / 6.2 and 4.9 / 8.5; 320 x 320 (400) 6.7 / 7.3 and 8.2 / 10.2; 512 x 300 (608) 10.0 / 8.6 and 12.4 / 12.4;
+// 512 x 512 (1024) 14.1 / 10.3 and 19.9 / 13.8.
+int tile_edge(int nx, int ny, int count) { return static_cast<int64_t>(tiles_of(nx, ny, 16)) * count > 512 ? 32 : 16; }
+
+template <typename T>
+hipError_t launch_one(int which, const Phase2DArgs<T>& a, hipStream_t s) {
+  const int edge = tile_edge(a.nx, a.ny, 1);
+  const dim3 grid(tiles_of(a.nx, a.ny, edge)), blk(NT);
+  if (edge == 16) {
+    if (which == 0) hipLaunchKernelGGL((phase2d_kernel<T, 1, 0>), grid, blk, 0, s, a);
+    else hipLaunchKernelGGL((phase2d_kernel<T, 1, 1>), grid, blk, 0, s, a);
+  } else {
+    if (which == 0) hipLaunchKernelGGL((phase2d_kernel<T, 2, 0>), grid, blk, 0, s, a);
+    else hipLaunchKernelGGL((phase2d_kernel<T, 2, 1>), grid, blk, 0, s, a);
+  }
   return hipGetLastError();
 }
 
-template <int KMAX>
-hipError_t launch_batch(int which, const BatchSolve* solves, int count, int nx, int ny, hipStream_t s) {
-  static int conf[2] = {-1, -1};
-  const int nb = ((nx + T - 1) / T) * ((ny + T - 1) / T);
-  constexpr size_t lds = lds_bytes<KMAX, true>();
-  hipError_t e = which == 0 ? configure(phase2d_batch_kernel<KMAX, 0>, lds, &conf[0])
-                            : configure(phase2d_batch_kernel<KMAX, 1>, lds, &conf[1]);
-  if (e != hipSuccess) return e;
-  if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<KMAX, 0>), dim3(nb, count), dim3(NT), lds, s, solves);
-  else hipLaunchKernelGGL((phase2d_batch_kernel<KMAX, 1>), dim3(nb, count), dim3(NT), lds, s, solves);
-  return hipGetLastError();
+template <typename T>
+Phase2DArgs<T> make_args(const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx, const DevOperator& Dy,
+                         void* p, void* ux, void* uy, const void* c2, int nx, int ny) {
+  return Phase2DArgs<T>{static_cast<const T*>(Gx.frag), Gx.Kp, Gx.Mp, static_cast<const T*>(Gy.frag), Gy.Kp, Gy.Mp,
+                        static_cast<const T*>(Dx.frag), Dx.Kp, Dx.Mp, static_cast<const T*>(Dy.frag), Dy.Kp, Dy.Mp,
+                        static_cast<T*>(p), static_cast<T*>(ux), static_cast<T*>(uy), static_cast<const T*>(c2), nx, ny,
+                        Gx.M, Gy.M, 1.0, 1.0};
 }
 
-Phase2DArgs make_args(const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx, const DevOperator& Dy,
-                      float* p, float* ux, float* uy, const float* c2, int nx, int ny) {
-  return Phase2DArgs{static_cast<const float*>(Gx.data), Gx.Kp, Gx.Mp, static_cast<const float*>(Gy.data), Gy.Kp,
-                     Gy.Mp, static_cast<const float*>(Dx.data), Dx.Kp, Dx.Mp, static_cast<const float*>(Dy.data), Dy.Kp,
-                     Dy.Mp, p, ux, uy, c2, nx, ny, Gx.M, Gy.M, 1.0, 1.0};
-}
-
-// The operator slices are read as 16-byte rows of the zero-padded device matrices: every k < pad64(K)
-// lies inside a row, and rows past the allocation read as zero.  The staggered extent of an axis (the
+// Every k < pad64(K) has its chunk of the zero-padded fragments, and rows past the allocation read as zero.  The staggered extent of an axis (the
 // rows of G, the columns of D) is n - 1 between walls or n on a periodic axis.
 bool operators_fit(const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx, const DevOperator& Dy,
                    int nx, int ny) {
   const int mx = Gx.M, my = Gy.M;
-  return Gx.K == nx && Gy.K == ny && Dx.M == nx && Dy.M == ny && Dx.K == mx && Dy.K == my &&
+  return Gx.frag && Gy.frag && Dx.frag && Dy.frag && Gx.K == nx && Gy.K == ny && Dx.M == nx && Dy.M == ny && Dx.K == mx && Dy.K == my &&
          (mx == nx - 1 || mx == nx) && (my == ny - 1 || my == ny) && Gx.Kp >= pad64(nx) && Gy.Kp >= pad64(ny) &&
-         Dx.Kp >= pad64(mx) && Dy.Kp >= pad64(my) && Gx.Kp % 4 == 0 && Gy.Kp % 4 == 0 && Dx.Kp % 4 == 0 &&
-         Dy.Kp % 4 == 0;
+         Dx.Kp >= pad64(mx) && Dy.Kp >= pad64(my) && Gx.Kp % 16 == 0 && Gy.Kp % 16 == 0 && Dx.Kp % 16 == 0 &&
+         Dy.Kp % 16 == 0;
 }
 
 }  // namespace
 
-bool phase2d_supported(int nx, int ny) { return nx >= 3 && ny >= 3 && nx <= 512 && ny <= 512; }
-
-hipError_t launch_phase2d_one(int which, const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx,
-                              const DevOperator& Dy, float* p, float* ux, float* uy, const float* c2, int nx, int ny,
-                              hipStream_t s) {
-  if (!phase2d_supported(nx, ny) || !operators_fit(Gx, Gy, Dx, Dy, nx, ny)) return hipErrorInvalidValue;
-  const Phase2DArgs a = make_args(Gx, Gy, Dx, Dy, p, ux, uy, c2, nx, ny);
-  return (nx <= 256 && ny <= 256) ? launch_one<256>(which, a, s) : launch_one<512>(which, a, s);
+hipError_t build_fragments(bool dbl, const DevOperator& op, hipStream_t s) {
+  const int cnt = op.Mp * op.Kp;
+  if (!op.frag || op.Mp % 16 || op.Kp % 16) return hipErrorInvalidValue;
+  const dim3 grid((cnt + 255) / 256), blk(256);
+  if (dbl)
+    hipLaunchKernelGGL(fragment_kernel<double>, grid, blk, 0, s, static_cast<const double*>(op.data),
+                       static_cast<double*>(op.frag), op.Mp, op.Kp);
+  else
+    hipLaunchKernelGGL(fragment_kernel<float>, grid, blk, 0, s, static_cast<const float*>(op.data),
+                       static_cast<float*>(op.frag), op.Mp, op.Kp);
+  return hipGetLastError();
 }
 
-hipError_t launch_phase2d(const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx, const DevOperator& Dy,
-                          float* p, float* ux, float* uy, const float* c2, int nx, int ny, int64_t steps,
-                          hipStream_t s) {
+bool phase2d_supported(int nx, int ny) { return nx >= 3 && ny >= 3 && nx <= 512 && ny <= 512; }
+
+hipError_t launch_phase2d_one(bool dbl, int which, const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx,
+                              const DevOperator& Dy, void* p, void* ux, void* uy, const void* c2, int nx, int ny,
+                              hipStream_t s) {
   if (!phase2d_supported(nx, ny) || !operators_fit(Gx, Gy, Dx, Dy, nx, ny)) return hipErrorInvalidValue;
-  const Phase2DArgs a = make_args(Gx, Gy, Dx, Dy, p, ux, uy, c2, nx, ny);
-  const bool small = nx <= 256 && ny <= 256;
-  for (int64_t t = 0; t < steps; ++t) {
-    hipError_t e = small ? launch_one<256>(0, a, s) : launch_one<512>(0, a, s);
-    if (e == hipSuccess) e = small ? launch_one<256>(1, a, s) : launch_one<512>(1, a, s);
-    if (e != hipSuccess) return e;
-  }
+  return dbl ? launch_one(which, make_args<double>(Gx, Gy, Dx, Dy, p, ux, uy, c2, nx, ny), s)
+             : launch_one(which, make_args<float>(Gx, Gy, Dx, Dy, p, ux, uy, c2, nx, ny), s);
+}
+
+hipError_t launch_phase2d(bool dbl, const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx,
+                          const DevOperator& Dy, void* p, void* ux, void* uy, const void* c2, int nx, int ny,
+                          int64_t steps, hipStream_t s) {
+  for (int64_t t = 0; t < steps; ++t)
+    for (int which = 0; which < 2; ++which) {
+      const hipError_t e = launch_phase2d_one(dbl, which, Gx, Gy, Dx, Dy, p, ux, uy, c2, nx, ny, s);
+      if (e != hipSuccess) return e;
+    }
   return hipSuccess;
 }
 
@@ -384,13 +435,21 @@ hipError_t launch_phase2d(const DevOperator& Gx, const DevOperator& Gy, const De
 // operators' padded rows cover pad64(K) columns (batch2d_phase_fits).
 hipError_t launch_phase2d_batch(int which, const BatchSolve* solves, int count, int nx, int ny, hipStream_t s) {
   if (!phase2d_supported(nx, ny) || count < 1 || count > 65535) return hipErrorInvalidValue;
-  return (nx <= 256 && ny <= 256) ? launch_batch<256>(which, solves, count, nx, ny, s)
-                                  : launch_batch<512>(which, solves, count, nx, ny, s);
+  const int edge = tile_edge(nx, ny, count), tiles = tiles_of(nx, ny, edge);
+  const dim3 grid(static_cast<unsigned>(tiles) * static_cast<unsigned>(count)), blk(NT);
+  if (edge == 16) {
+    if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<1, 0>), grid, blk, 0, s, solves, tiles);
+    else hipLaunchKernelGGL((phase2d_batch_kernel<1, 1>), grid, blk, 0, s, solves, tiles);
+  } else {
+    if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<2, 0>), grid, blk, 0, s, solves, tiles);
+    else hipLaunchKernelGGL((phase2d_batch_kernel<2, 1>), grid, blk, 0, s, solves, tiles);
+  }
+  return hipGetLastError();
 }
 
 bool batch2d_phase_fits(int ldgx, int ldgy, int lddx, int lddy, int nx, int ny) {
-  return ldgx >= pad64(nx) && ldgy >= pad64(ny) && lddx >= pad64(nx - 1) && lddy >= pad64(ny - 1) && ldgx % 4 == 0 &&
-         ldgy % 4 == 0 && lddx % 4 == 0 && lddy % 4 == 0;
+  return ldgx >= pad64(nx) && ldgy >= pad64(ny) && lddx >= pad64(nx - 1) && lddy >= pad64(ny - 1) && ldgx % 16 == 0 &&
+         ldgy % 16 == 0 && lddx % 16 == 0 && lddy % 16 == 0;
 }
 
 }  // namespace pstd
