@@ -171,9 +171,14 @@ struct BatchSolve {
   double sG;                // -dt / (rho0 dx)
   double sD;                // -dt rho0 c0^2 / dx, or -dt rho0 / dx with a c0^2 map
   const float* c2;          // nx x ny map of c0(x)^2, or null for a homogeneous medium
+  int walls;                // Dirichlet faces: bit f for face f of {x-, x+, y-, y+}
 };
-// One fused phase of many solves of one shape (kernels_phase2d.hip): grid (tiles, count).
-hipError_t launch_phase2d_batch(int which, const BatchSolve* solves, int count, int nx, int ny, hipStream_t s);
+// One fused phase of many solves of one shape (kernels_phase2d.hip).  start (which = 0): the centred start
+// u^{-1/2} instead of an update.
+hipError_t launch_phase2d_batch(int which, const BatchSolve* solves, int count, int nx, int ny, bool start,
+                                hipStream_t s);
+// Zeroes p on the Dirichlet wall nodes of `count` solves of at most nx x ny nodes.
+hipError_t launch_batch_walls(const BatchSolve* solves, int count, int nx, int ny, hipStream_t s);
 bool batch2d_phase_fits(int ldgx, int ldgy, int lddx, int lddy, int nx, int ny);
 struct BatchTask {
   int solve;

@@ -76,6 +76,7 @@ struct Phase2DArgs {
   const T* c2;                  // nx x ny or null
   int nx, ny, mx, my;
   double sv, sp;                // velocity / pressure factors on the contractions (1 for folded operators)
+  bool fresh;                   // velocity phase: the fields' old values do not count (and are dropped)
 };
 
 __device__ __forceinline__ rsrc_t make_rsrc(const void* ptr, uint32_t bytes) {
@@ -315,6 +316,7 @@ __device__ __forceinline__ void phase2d_body(const Phase2DArgs<T>& a, int tile) 
     if (PH == 1) v += (part(4) + part(5)) + (part(6) + part(7));
     v *= PH == 0 ? a.sv : a.sp;
     if (PH == 1 && a.c2) v *= static_cast<double>(cf[g]);
+    if (PH == 0 && a.fresh) old[g] = T(0);
     Y[off[g]] = static_cast<T>(static_cast<double>(old[g]) + v);
   }
 }
@@ -332,13 +334,14 @@ __global__ __launch_bounds__(NT, 4) void phase2d_kernel(Phase2DArgs<T> a) {
 }
 
 // One phase of many solves of one shape: tiles solve after solve, the solve's unscaled operators and factors
-// from the batch's solve table.
+// from the batch's solve table.  start (velocity phase): u^{-1/2} = -1/2 sG (G p), whatever u holds.
 template <int MT, int PH>
-__global__ __launch_bounds__(NT, 4) void phase2d_batch_kernel(const BatchSolve* __restrict__ solves, int tiles) {
+__global__ __launch_bounds__(NT, 4) void phase2d_batch_kernel(const BatchSolve* __restrict__ solves, int tiles,
+                                                              bool start) {
   const int t = xcd_tile(blockIdx.x, gridDim.x);
   const BatchSolve& S = solves[t / tiles];
   const Phase2DArgs<float> a{S.fGx, S.ldgx, S.mgx, S.fGy, S.ldgy, S.mgy, S.fDx, S.lddx, S.mdx, S.fDy, S.lddy, S.mdy,
-                             S.p, S.ux, S.uy, S.c2, S.nx, S.ny, S.nx - 1, S.ny - 1, S.sG, S.sD};
+                             S.p, S.ux, S.uy, S.c2, S.nx, S.ny, S.nx - 1, S.ny - 1, start ? -0.5 * S.sG : S.sG, S.sD, start};
   phase2d_body<float, MT, PH>(a, t % tiles);
 }
 
@@ -380,7 +383,7 @@ Phase2DArgs<T> make_args(const DevOperator& Gx, const DevOperator& Gy, const Dev
   return Phase2DArgs<T>{static_cast<const T*>(Gx.frag), Gx.Kp, Gx.Mp, static_cast<const T*>(Gy.frag), Gy.Kp, Gy.Mp,
                         static_cast<const T*>(Dx.frag), Dx.Kp, Dx.Mp, static_cast<const T*>(Dy.frag), Dy.Kp, Dy.Mp,
                         static_cast<T*>(p), static_cast<T*>(ux), static_cast<T*>(uy), static_cast<const T*>(c2), nx, ny,
-                        Gx.M, Gy.M, 1.0, 1.0};
+                        Gx.M, Gy.M, 1.0, 1.0, false};
 }
 
 // Every k < pad64(K) has its chunk of the zero-padded fragments, and rows past the allocation read as zero.  The staggered extent of an axis (the
@@ -433,17 +436,42 @@ hipError_t launch_phase2d(bool dbl, const DevOperator& Gx, const DevOperator& Gy
 // One phase of `count` solves of one shape from the batch's device solve table (unscaled operators; the
 // factors sG, sD and the c0^2 maps of the table apply in the epilogue).  The caller checks that the
 // operators' padded rows cover pad64(K) columns (batch2d_phase_fits).
-hipError_t launch_phase2d_batch(int which, const BatchSolve* solves, int count, int nx, int ny, hipStream_t s) {
-  if (!phase2d_supported(nx, ny) || count < 1 || count > 65535) return hipErrorInvalidValue;
+hipError_t launch_phase2d_batch(int which, const BatchSolve* solves, int count, int nx, int ny, bool start,
+                                hipStream_t s) {
+  if (!phase2d_supported(nx, ny) || count < 1 || count > 65535 || (start && which != 0)) return hipErrorInvalidValue;
   const int edge = tile_edge(nx, ny, count), tiles = tiles_of(nx, ny, edge);
   const dim3 grid(static_cast<unsigned>(tiles) * static_cast<unsigned>(count)), blk(NT);
   if (edge == 16) {
-    if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<1, 0>), grid, blk, 0, s, solves, tiles);
-    else hipLaunchKernelGGL((phase2d_batch_kernel<1, 1>), grid, blk, 0, s, solves, tiles);
+    if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<1, 0>), grid, blk, 0, s, solves, tiles, start);
+    else hipLaunchKernelGGL((phase2d_batch_kernel<1, 1>), grid, blk, 0, s, solves, tiles, start);
   } else {
-    if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<2, 0>), grid, blk, 0, s, solves, tiles);
-    else hipLaunchKernelGGL((phase2d_batch_kernel<2, 1>), grid, blk, 0, s, solves, tiles);
+    if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<2, 0>), grid, blk, 0, s, solves, tiles, start);
+    else hipLaunchKernelGGL((phase2d_batch_kernel<2, 1>), grid, blk, 0, s, solves, tiles, start);
   }
+  return hipGetLastError();
+}
+
+namespace {
+
+// Zeroes the Dirichlet wall nodes of every solve's p (block y: solve).
+__global__ __launch_bounds__(256) void batch_walls_kernel(const BatchSolve* __restrict__ solves) {
+  const BatchSolve& S = solves[blockIdx.y];
+  const int nx = S.nx, ny = S.ny, i = blockIdx.x * 256 + threadIdx.x;
+  if (i < ny) {
+    if (S.walls & 1) S.p[i] = 0.f;
+    if (S.walls & 2) S.p[static_cast<int64_t>(nx - 1) * ny + i] = 0.f;
+  }
+  if (i < nx) {
+    if (S.walls & 4) S.p[static_cast<int64_t>(i) * ny] = 0.f;
+    if (S.walls & 8) S.p[static_cast<int64_t>(i) * ny + ny - 1] = 0.f;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_batch_walls(const BatchSolve* solves, int count, int nx, int ny, hipStream_t s) {
+  if (count < 1 || count > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(batch_walls_kernel, dim3((std::max(nx, ny) + 255) / 256, count), dim3(256), 0, s, solves);
   return hipGetLastError();
 }
 
