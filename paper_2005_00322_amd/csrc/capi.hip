@@ -45,10 +45,9 @@ float bf16_to_float(uint16_t h) {
   return f;
 }
 
-// Round the FP64 matrix (M x K, already scaled) to the plan precision and upload it zero padded; with frag also
-// in fragment order (FP64 and FP32).
-int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, double scale, DevOperator* op,
-                    bool frag = false) {
+// Round the FP64 matrix (M x K, already scaled) to the plan precision and upload it zero padded (FP64 and FP32: in
+// fragment order too).
+int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, double scale, DevOperator* op) {
   op->M = M;
   op->K = K;
   op->Mp = static_cast<int>(round_up(M, kRowPad));
@@ -71,13 +70,11 @@ int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, 
           if (want_t) reinterpret_cast<float*>(hostT.data())[t] = static_cast<float>(v);
         }
       }
-    if (hipMalloc(&op->data, (frag ? 2 : 1) * cnt * esz) != hipSuccess)
+    if (hipMalloc(&op->data, 2 * cnt * esz) != hipSuccess)
       return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
     PSTD_HIP(hipMemcpy(op->data, host.data(), cnt * esz, hipMemcpyHostToDevice));
-    if (frag) {
-      op->frag = static_cast<unsigned char*>(op->data) + cnt * esz;
-      PSTD_HIP(build_fragments(esz == 8, *op, P->stream));
-    }
+    op->frag = static_cast<unsigned char*>(op->data) + cnt * esz;
+    PSTD_HIP(build_fragments(esz == 8, *op, P->stream));
     if (want_t) {
       if (hipMalloc(&op->dataT, cnt * esz) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
       PSTD_HIP(hipMemcpy(op->dataT, hostT.data(), cnt * esz, hipMemcpyHostToDevice));
@@ -179,10 +176,8 @@ int ensure_dense(pstd_plan_s* P, int a) {
   const AxisCase c = axis_case(P->bc[2 * a], P->bc[2 * a + 1]);
   const AxisTables& t = axis_tables(n, c);
   const int m = staggered_points(n, c);
-  const bool frag = P->ndim == 2 && P->prec != PSTD_SPLIT_BF16 &&
-                    phase2d_supported(static_cast<int>(P->n[0]), static_cast<int>(P->n[1]));
-  int st = upload_operator(P, t.G, m, n, const_G(P), &P->G[a], frag);
-  if (st == PSTD_OK) st = upload_operator(P, t.D, n, m, const_D(P), &P->D[a], frag);
+  int st = upload_operator(P, t.G, m, n, const_G(P), &P->G[a]);
+  if (st == PSTD_OK) st = upload_operator(P, t.D, n, m, const_D(P), &P->D[a]);
   return st;
 }
 
@@ -224,6 +219,7 @@ hipError_t contract(const pstd_plan_s* P, const DevOperator& op, int a, const vo
   ContractArgs c{};
   c.A = op.data;
   c.A_lo = nullptr;
+  c.frag = op.frag;
   c.lda = op.Kp;
   c.M = op.M;
   c.K = op.K;

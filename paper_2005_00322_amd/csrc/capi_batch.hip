@@ -44,7 +44,7 @@ namespace {
 
 constexpr int64_t kChunk = 1024;   // steps per persistent launch
 
-int upload_unscaled(const std::vector<double>& m, int M, int K, bool frag, hipStream_t s, DevOperator* op) {
+int upload_unscaled(const std::vector<double>& m, int M, int K, hipStream_t s, DevOperator* op) {
   op->M = M;
   op->K = K;
   op->Mp = static_cast<int>(round_up(M, kRowPad));
@@ -52,13 +52,11 @@ int upload_unscaled(const std::vector<double>& m, int M, int K, bool frag, hipSt
   std::vector<float> h(static_cast<size_t>(op->Mp) * op->Kp, 0.f);
   for (int i = 0; i < M; ++i)
     for (int k = 0; k < K; ++k) h[static_cast<size_t>(i) * op->Kp + k] = static_cast<float>(m[static_cast<size_t>(i) * K + k]);
-  if (hipMalloc(&op->data, (frag ? 2 : 1) * h.size() * sizeof(float)) != hipSuccess)
+  if (hipMalloc(&op->data, 2 * h.size() * sizeof(float)) != hipSuccess)
     return fail(PSTD_E_OOM, "hipMalloc failed");
   PSTD_HIP(hipMemcpy(op->data, h.data(), h.size() * sizeof(float), hipMemcpyHostToDevice));
-  if (frag) {
-    op->frag = static_cast<float*>(op->data) + h.size();
-    PSTD_HIP(build_fragments(false, *op, s));
-  }
+  op->frag = static_cast<float*>(op->data) + h.size();
+  PSTD_HIP(build_fragments(false, *op, s));
   return PSTD_OK;
 }
 
@@ -358,9 +356,7 @@ int pstd_batch_create(int32_t count, const int64_t* n, const int32_t* bc, const 
     B->dt.push_back(dt[s]);
     B->c0.push_back(c0[s]);
   }
-  // shared operators, in fragment order too where tile 16 (which reads them so) is possible
-  bool frag = phase2d_supported(B->nx[0], B->ny[0]);
-  for (int s = 0; s < count; ++s) frag = frag && B->nx[s] == B->nx[0] && B->ny[s] == B->ny[0];
+  // shared operators
   for (int s = 0; s < count; ++s) {
     const std::pair<int, int> keys[2] = {{B->nx[s], static_cast<int>(axis_case(B->bc[4 * s], B->bc[4 * s + 1]))},
                                          {B->ny[s], static_cast<int>(axis_case(B->bc[4 * s + 2], B->bc[4 * s + 3]))}};
@@ -368,8 +364,8 @@ int pstd_batch_create(int32_t count, const int64_t* n, const int32_t* bc, const 
       if (B->ops.count(k)) continue;
       const AxisTables& t = axis_tables(k.first, static_cast<AxisCase>(k.second));
       pstd_batch_s::Op op;
-      int st = upload_unscaled(t.G, k.first - 1, k.first, frag, B->stream, &op.G);
-      if (st == PSTD_OK) st = upload_unscaled(t.D, k.first, k.first - 1, frag, B->stream, &op.D);
+      int st = upload_unscaled(t.G, k.first - 1, k.first, B->stream, &op.G);
+      if (st == PSTD_OK) st = upload_unscaled(t.D, k.first, k.first - 1, B->stream, &op.D);
       B->ops[k] = op;
       if (st != PSTD_OK) {
         free_batch(B);
@@ -483,6 +479,7 @@ int pstd_batch_state_init(pstd_batch B, pstd_state* st, int32_t u_mode) {
       // u^{-1/2} = +(dt / (2 rho0)) G p = -1/2 sG (unscaled G) p
       ContractArgs c{};
       c.A = a == 0 ? S.Gx : S.Gy;
+      c.frag = a == 0 ? S.fGx : S.fGy;
       c.lda = a == 0 ? S.ldgx : S.ldgy;
       c.M = (a == 0 ? S.nx : S.ny) - 1;
       c.K = a == 0 ? S.nx : S.ny;

@@ -89,7 +89,9 @@ struct DevOperator {
   int Mp = 0, Kp = 0;      // padded size (row stride = Kp)
   void* data = nullptr;    // FP64: double[Mp*Kp]; FP32: float[Mp*Kp]; SPLIT: bf16 hi[Mp*Kp] then lo[Mp*Kp]
   void* dataT = nullptr;   // 1D plans: transposed copy, Kp x Mp (row stride Mp)
-  void* frag = nullptr;    // FP64 / FP32 operators of the fused 2D phases: data in MFMA fragment order (one allocation)
+  // FP64 / FP32: data in MFMA fragment order (in data's allocation): for every 16 rows and chunk of 16 columns the 64
+  // lanes' four values, lane l those of row l % 16, columns 4 e + l / 16 for e < 4
+  void* frag = nullptr;
   // SPLIT only, operators with a Toeplitz-plus-Hankel form and kThRowsMin < M <= kThRowsMax, Kp <= kThColsMax:
   // FP32 f and g windows of th_len values each (see kernels_split.hip) and the end weights
   // {first row, last row, first column, last column}
@@ -114,6 +116,7 @@ bool toeplitz_hankel(const double* A, int R, int C, double tol, std::vector<doub
 struct ContractArgs {
   const void* A;        // operator, row-major, row stride lda, zero padded
   const void* A_lo;     // SPLIT_BF16 only: low part
+  const void* frag;     // FP64 / FP32: DevOperator::frag
   int lda;
   int M, K;             // output length and input length along the contracted axis
   const void* X;        // input field

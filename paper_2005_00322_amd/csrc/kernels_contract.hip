@@ -9,224 +9,195 @@
 // Two layouts:
 //   strided     the contracted axis is not the last one.  X is viewed as [batch][K][C] and Y as
 //               [batch][M][C] (C = product of the trailing extents, unit stride):
-//               Y[b][m][c] += sum_k A[m][k] X[b][k][c]              (a GEMM  A * X_b)
+//               Y[b][m][c] += sum_k A[m][k] X[b][k][c].  The columns (b, c) of all batches are one range, so a tile may
+//               span several batches and only the last one is partly empty (C = 129: 1 tile in 25800 / 64 against every third).
 //   contiguous  the contracted axis is the last one.  X is [R][K], Y is [R][M]:
-//               Y[r][m] += sum_k X[r][k] A[m][k]                    (a GEMM  X * A^T)
-// Both are computed as C^T-free MFMA tiles: the operator always feeds the MFMA "A" port (rows m) and
-// the field the "B" port (columns c or r), so both layouts share the inner loop.
-//
-// FP32 accuracy: a long FP32 accumulation of the cancelling terms of a spectral derivative loses more than
-// the FP32 rounding of the operator and the state together (about 1e-5 against 2e-6 relative L2 after
-// 2000 steps of a 256 x 256 box).  The FP32 kernel therefore sums each BK-deep K slice on the MFMA in
-// FP32 and adds the slice sums into FP64 registers; the FP64 kernel accumulates in FP64 throughout.
-//
-// MFMA v_mfma_{f32,f64}_16x16x4: lane l holds A[l%16][l/16] and B[l/16][l%16].  Accumulator register
-// r of lane l holds C[4*(l/16)+r][l%16] for f32 but C[4*r+l/16][l%16] for f64 (measured on gfx950).
-#include "common.h"
+//               Y[r][m] += sum_k X[r][k] A[m][k]
+// The tile product is tile_core.h's; the columns of its output run along the unit stride of Y in both layouts.
+// us per launch before (64 x 64 tiles, 16-deep slices, both operands through LDS, one tile range per batch) and now, axes
+// x / y / z: 256^3 FP32 159 / 154 / 196 -> 99 / 98 / 89 (86-96 TFLOP/s of the 150 a large FP32 product reaches here);
+// 161 x 200 x 129 FP32 44 / 71 / 36 -> 28 / 36 / 18; 161 x 200 x 129 FP64 63 / 99 / 53 -> 39 / 50 / 27.
+#include "tile_core.h"
 
 namespace pstd {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-template <typename T> struct Mma;
-template <> struct Mma<float> {
-  using acc_t = f32x4;
-  static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-};
-template <> struct Mma<double> {
-  using acc_t = f64x4;
-  static __device__ __forceinline__ acc_t mma(double a, double b, acc_t c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-};
-
 template <typename T>
 struct KArgs {
-  const T* A;
-  int lda, M, K;
+  const T* op;          // operator fragments
+  int M, K, Kp;
   const T* X;
   T* Y;
-  int64_t ncols, x_bstride, y_bstride;
+  int64_t inner, lines;       // strided: C and batch * C columns; contiguous: rows (inner unused)
+  int64_t x_bstride, y_bstride;
   double alpha, beta;
   const T* scale;
+  int mtiles;
 };
 
-// BM x BN output tile per block, BK-deep K slices staged in LDS; WM x WN waves of 64 lanes.
-template <typename T, bool CONTIG, int BM, int BN, int BK, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void contract_kernel(KArgs<T> a) {
-  constexpr int NT = 64 * WM * WN;
-  constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int TM = WTM / 16, TN = WTN / 16;
-  static_assert(TM >= 1 && TN >= 1 && BK % 4 == 0, "tile shape");
-  using acc_t = typename Mma<T>::acc_t;
-
-  __shared__ T As[BM][BK + 1];
-  __shared__ T Xs[CONTIG ? BN : BK][CONTIG ? BK + 1 : BN + 1];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = wave % WM, wn = wave / WM;
-  const int m0 = blockIdx.y * BM;
-  const int64_t n0 = static_cast<int64_t>(blockIdx.x) * BN;
-  const int64_t b = blockIdx.z;
-  const T* X = a.X + b * a.x_bstride;
-
-  constexpr bool kFlush = sizeof(T) == 4;   // FP32: flush slice sums into FP64 registers
-  acc_t acc[TM][TN];
-  double accd[kFlush ? TM : 1][kFlush ? TN : 1][4];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
-  if (kFlush) {
-#pragma unroll
-    for (int i = 0; i < (kFlush ? TM : 1); ++i)
-#pragma unroll
-      for (int j = 0; j < (kFlush ? TN : 1); ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) accd[i][j][r] = 0.0;
-  }
-
-  for (int k0 = 0; k0 < a.K; k0 += BK) {
-    lds_barrier();
-    // operator and field slices: every load of the slice is issued before the first LDS store.
-    // The operator is zero padded on the host (no bounds checks); the field is zero-filled outside
-    // [0,K) x [0,ncols).
-    constexpr int AIT = BM * BK / NT, XIT = BN * BK / NT;
-    static_assert(AIT * NT == BM * BK && XIT * NT == BN * BK, "tile must split evenly over the block");
-    T av_[AIT], xv_[XIT];
-#pragma unroll
-    for (int it = 0; it < AIT; ++it) {
-      const int e = tid + it * NT;
-      av_[it] = a.A[static_cast<int64_t>(m0 + e / BK) * a.lda + k0 + e % BK];
-    }
-#pragma unroll
-    for (int it = 0; it < XIT; ++it) {
-      const int e = tid + it * NT;
-      if (CONTIG) {
-        const int64_t gr = n0 + e / BK;
-        const int gk = k0 + e % BK;
-        xv_[it] = (gr < a.ncols && gk < a.K) ? X[gr * a.K + gk] : T(0);
-      } else {
-        const int64_t gc = n0 + e % BN;
-        const int gk = k0 + e / BN;
-        xv_[it] = (gc < a.ncols && gk < a.K) ? X[static_cast<int64_t>(gk) * a.ncols + gc] : T(0);
-      }
-    }
-#pragma unroll
-    for (int it = 0; it < AIT; ++it) {
-      const int e = tid + it * NT;
-      As[e / BK][e % BK] = av_[it];
-    }
-#pragma unroll
-    for (int it = 0; it < XIT; ++it) {
-      const int e = tid + it * NT;
-      if (CONTIG) Xs[e / BK][e % BK] = xv_[it];
-      else Xs[e / BN][e % BN] = xv_[it];
-    }
-    lds_barrier();
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      T av[TM], bv[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) av[i] = As[wm * WTM + i * 16 + (lane & 15)][kk + (lane >> 4)];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = wn * WTN + j * 16 + (lane & 15);
-        bv[j] = CONTIG ? Xs[col][kk + (lane >> 4)] : Xs[kk + (lane >> 4)][col];
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = Mma<T>::mma(av[i], bv[j], acc[i][j]);
-    }
-    if (kFlush) {
-#pragma unroll
-      for (int i = 0; i < (kFlush ? TM : 1); ++i)
-#pragma unroll
-        for (int j = 0; j < (kFlush ? TN : 1); ++j) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) accd[i][j][r] += static_cast<double>(acc[i][j][r]);
-          acc[i][j] = acc_t{0, 0, 0, 0};
-        }
-    }
-  }
-
-  // fused update epilogue: every load of Y (and of the map) first, then every store
-  T* Y = a.Y + b * a.y_bstride;
-  const T* S = a.scale ? a.scale + b * a.y_bstride : nullptr;
-  auto out_index = [&](int i, int j, int r) -> int64_t {
-    const int64_t col = n0 + wn * WTN + j * 16 + (lane & 15);
-    const int m = m0 + wm * WTM + i * 16 + (sizeof(T) == 8 ? 4 * r + (lane >> 4) : 4 * (lane >> 4) + r);
-    if (m >= a.M || col >= a.ncols) return -1;
-    return CONTIG ? col * a.M + m : static_cast<int64_t>(m) * a.ncols + col;
+template <typename T, bool ROWS, int MT, int WO>
+__global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_kernel(KArgs<T> a) {
+  typedef Tile<T, MT, WO> TL;
+  __shared__ __attribute__((aligned(16))) T lds[TL::lds_values];
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int m0 = (tile % a.mtiles) * TL::EO;
+  const int64_t l0 = static_cast<int64_t>(tile / a.mtiles) * TL::EL;
+  constexpr uint32_t ES = sizeof(T);
+  const int lane = threadIdx.x & 63;
+  typename TL::template Field<ROWS> X;
+  X.K = a.K;
+  // the first line's batch (strided; every later line's offset from it fits 32 bits: a batch of 4 GiB has no neighbour
+  // within the 2^31 points of a plan)
+  const int64_t b0 = ROWS ? 0 : l0 / a.inner, c0 = ROWS ? 0 : l0 - b0 * a.inner;
+  auto line_off = [&](int64_t l, int64_t bstride) {   // elements from line l0 to line l0 + l (clamped)
+    const int64_t c = c0 + min(l, a.lines - 1 - l0), b = c / a.inner;
+    return b * bstride + (c - b * a.inner) - c0;
   };
-  T yv[TM][TN][4], sv[TM][TN][4];
+  if constexpr (ROWS) {
+    X.x = a.X + l0 * a.K;
+    X.ld = a.K;
+    X.set_rows(static_cast<int>(min(a.lines - l0, static_cast<int64_t>(TL::EL))));
+  } else {
+    X.x = a.X + b0 * a.x_bstride + c0;
+    X.ld = a.inner;
+    X.off[0] = ES * static_cast<uint32_t>(line_off(X.line(0), a.x_bstride));
+  }
+  // Outputs: value (row, column) of the tile, columns along the unit stride.  A lane's column gives a 32-bit offset, its
+  // rows are row_step apart from a wave-uniform start.
+  const int64_t row_step = ROWS ? a.M : a.inner;
+  const int64_t first = (ROWS ? l0 : m0) + (ROWS ? TL::line0() : TL::op0());
+  const int64_t ybase = first * row_step + (ROWS ? m0 + TL::op0() : b0 * a.y_bstride + c0);
+  const int lr = Mma<T>::lane_row(lane);
+  const int rows_left = static_cast<int>(min((ROWS ? a.lines : a.M) - first, static_cast<int64_t>(16 * MT))) - lr;
+  uint32_t coff[MT];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int j = 0; j < MT; ++j) {
+    const int cl = 16 * j + (lane & 15);
+    bool ok;
+    int64_t o;
+    if constexpr (ROWS) {
+      ok = m0 + TL::op0() + cl < a.M;
+      o = cl;
+    } else {
+      ok = l0 + TL::line0() + cl < a.lines;
+      o = line_off(TL::line0() + cl, a.y_bstride);
+    }
+    coff[j] = ok ? ES * static_cast<uint32_t>(o + lr * row_step) : ~0u;
+  }
+  T yv[MT][MT][4];
+  double acc[MT][MT][4] = {};
+  auto valid = [&](int i, int j, int r) { return coff[j] != ~0u && 16 * i + Mma<T>::reg_row(r) < rows_left; };
+  auto at = [&](int i, int r) { return ybase + (16 * i + Mma<T>::reg_row(r)) * row_step; };
+  TL::template contract<ROWS>(a.op + static_cast<int64_t>(m0) * a.Kp, 16 * static_cast<int64_t>(a.Kp), X, lds,
+                               m0 + TL::op0() >= a.M || l0 + TL::line0() >= a.lines, acc, [&] {
+    if (a.beta == 0.0) return;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < MT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (valid(i, j, r)) yv[i][j][r] = ld_at(a.Y + at(i, r), coff[j]);
+  });
+  // fused update epilogue: the product, the map factor and the update are formed in FP64 and rounded once
+  T sv[MT][MT][4];
+  if (a.scale) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < MT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (valid(i, j, r)) sv[i][j][r] = ld_at(a.scale + at(i, r), coff[j]);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < MT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][j][r] *= static_cast<double>(sv[i][j][r]);
+  }
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < MT; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t idx = out_index(i, j, r);
-        yv[i][j][r] = (idx >= 0 && a.beta != 0.0) ? Y[idx] : T(0);
-        sv[i][j][r] = (idx >= 0 && S) ? S[idx] : T(1);
-      }
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t idx = out_index(i, j, r);
-        if (idx < 0) continue;
-        // the product, the map factor and the update are formed in FP64 and rounded once
-        const double prod = kFlush ? accd[kFlush ? i : 0][kFlush ? j : 0][r] : static_cast<double>(acc[i][j][r]);
-        const double v = a.alpha * prod * static_cast<double>(sv[i][j][r]);
-        Y[idx] = static_cast<T>(a.beta * static_cast<double>(yv[i][j][r]) + v);
+        if (!valid(i, j, r)) continue;
+        const double old = a.beta != 0.0 ? a.beta * static_cast<double>(yv[i][j][r]) : 0.0;
+        T* y = reinterpret_cast<T*>(reinterpret_cast<char*>(a.Y + at(i, r)) + coff[j]);
+        *y = static_cast<T>(fma(a.alpha, acc[i][j][r], old));
       }
 }
 
-template <typename T, int BM, int BN, int BK, int WM, int WN>
+template <typename T>
 hipError_t launch_t(const ContractArgs& c, bool contiguous, hipStream_t s) {
+  if (!c.frag || c.batch < 1 || c.ncols < 1 || c.M < 1 || c.K < 1) return hipErrorInvalidValue;
   KArgs<T> a;
-  a.A = static_cast<const T*>(c.A);
-  a.lda = c.lda;
+  a.op = static_cast<const T*>(c.frag);
   a.M = c.M;
   a.K = c.K;
+  a.Kp = c.lda;
   a.X = static_cast<const T*>(c.X);
   a.Y = static_cast<T*>(c.Y);
-  a.ncols = c.ncols;
+  a.inner = c.ncols;
+  a.lines = c.ncols * c.batch;
   a.x_bstride = c.x_bstride;
   a.y_bstride = c.y_bstride;
   a.alpha = c.alpha_d;
   a.beta = c.beta_d;
   a.scale = static_cast<const T*>(c.scale);
-  const int64_t nb = (c.ncols + BN - 1) / BN;
-  const int64_t mb = (c.M + BM - 1) / BM;
-  if (nb > 0x7fffffff || mb > 65535 || c.batch > 65535 || c.batch < 1) return hipErrorInvalidConfiguration;
-  static_assert(kRowPad % BM == 0 && kColPad % BK == 0, "operator padding must cover whole tiles");
-  dim3 grid(static_cast<unsigned>(nb), static_cast<unsigned>(mb), static_cast<unsigned>(c.batch));
-  if (contiguous)
-    hipLaunchKernelGGL((contract_kernel<T, true, BM, BN, BK, WM, WN>), grid, dim3(64 * WM * WN), 0, s, a);
-  else
-    hipLaunchKernelGGL((contract_kernel<T, false, BM, BN, BK, WM, WN>), grid, dim3(64 * WM * WN), 0, s, a);
+  static_assert(kRowPad % 64 == 0 && kColPad % 32 == 0, "operator padding must cover whole tiles and slices");
+  // 64 x 64 tiles from about 400 of them on (1.5 per CU), 32 x 32 before that: four times the blocks, twice the operand
+  // traffic for a product.  us at 32 / 64, FP32: 314 tiles (100 x 100^2) 9.9 / 11.2, 400 (128 x 100^2) 11.9 / 11.0,
+  // 512 (128^3) 14.1 / 12.0; FP64: 314 12.1 / 13.9, 512 19.1 / 16.5.
+  auto tiles = [&](int edge) { return ((c.M + edge - 1) / edge) * ((a.lines + edge - 1) / edge); };
+  const bool big = tiles(64) >= 400;
+  const int edge = big ? 64 : 32;
+  a.mtiles = (c.M + edge - 1) / edge;
+  const int64_t n = tiles(edge);
+  if (n > 0x7fffffff) return hipErrorInvalidConfiguration;
+  const dim3 grid(static_cast<unsigned>(n)), blk(256);
+  if (big) {
+    if (contiguous) hipLaunchKernelGGL((contract_kernel<T, true, 2, 2>), grid, blk, 0, s, a);
+    else hipLaunchKernelGGL((contract_kernel<T, false, 2, 2>), grid, blk, 0, s, a);
+  } else {
+    if (contiguous) hipLaunchKernelGGL((contract_kernel<T, true, 1, 2>), grid, blk, 0, s, a);
+    else hipLaunchKernelGGL((contract_kernel<T, false, 1, 2>), grid, blk, 0, s, a);
+  }
   return hipGetLastError();
+}
+
+// dst: the Mp x Kp matrix src in fragment order (DevOperator::frag).
+template <typename T>
+__global__ __launch_bounds__(256) void fragment_kernel(const T* __restrict__ src, T* __restrict__ dst, int Mp, int Kp) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= static_cast<int64_t>(Mp) * Kp) return;
+  const int e = static_cast<int>(i & 3), l = static_cast<int>(i >> 2) & 63, nc = Kp >> 4;
+  const int blk = static_cast<int>(i >> 8);
+  dst[i] = src[static_cast<int64_t>(16 * (blk / nc) + (l & 15)) * Kp + 16 * (blk % nc) + chunk_k(4 * (l >> 4) + e)];
 }
 
 }  // namespace
 
+hipError_t build_fragments(bool dbl, const DevOperator& op, hipStream_t s) {
+  const int64_t cnt = static_cast<int64_t>(op.Mp) * op.Kp;
+  if (!op.frag || op.Mp % 16 || op.Kp % 16) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>((cnt + 255) / 256)), blk(256);
+  if (dbl)
+    hipLaunchKernelGGL(fragment_kernel<double>, grid, blk, 0, s, static_cast<const double*>(op.data),
+                       static_cast<double*>(op.frag), op.Mp, op.Kp);
+  else
+    hipLaunchKernelGGL(fragment_kernel<float>, grid, blk, 0, s, static_cast<const float*>(op.data),
+                       static_cast<float*>(op.frag), op.Mp, op.Kp);
+  return hipGetLastError();
+}
+
 hipError_t launch_contract_fp32(const ContractArgs& c, bool contiguous, hipStream_t s) {
-  return launch_t<float, 64, 64, 16, 2, 2>(c, contiguous, s);
+  return launch_t<float>(c, contiguous, s);
 }
 
 hipError_t launch_contract_fp64(const ContractArgs& c, bool contiguous, hipStream_t s) {
-  return launch_t<double, 64, 64, 8, 2, 2>(c, contiguous, s);
+  return launch_t<double>(c, contiguous, s);
 }
 
 }  // namespace pstd

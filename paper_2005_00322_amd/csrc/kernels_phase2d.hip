@@ -13,7 +13,7 @@
 // A box of a few hundred nodes a side is bound by latency, not by bandwidth or MFMA rate.  As the waves of a block
 // split k and each computes the whole tile, no operand element is used by two waves, so nothing is shared before
 // the partial tiles meet in LDS:
-//   operators  are kept in fragment order (fragment_kernel): the 16 rows x 16 k that one wave feeds to four MFMAs are
+//   operators  are kept in fragment order (DevOperator::frag): the 16 rows x 16 k that one wave feeds to four MFMAs are
 //              one run of 64 lanes x 4 values, loaded straight into the MFMA registers;
 //   X0         16 lanes read 16 neighbouring columns of a row, straight into the registers;
 //   X1         rows are read with neighbouring lanes along k (one value a lane: rows of odd length start at any
@@ -27,41 +27,21 @@
 // path into the CU (64 bytes per clock) is exactly as busy as the matrix cores and at MT = 2 half as busy, but MT = 2
 // has a quarter of the blocks: the rule is at tile_edge().
 //
-// MFMA v_mfma_{f32,f64}_16x16x4: lane l supplies P[l%16][kslot l/16] and Q[l%16][kslot l/16] and receives
-// C[4*(l/16)+r][l%16] (f32) or C[4*r+l/16][l%16] (f64) in register r.  A lane holds the four consecutive k
-// 4 (l/16) .. + 3 of a 16-wide chunk and feeds component e to the e-th MFMA, so MFMA e contracts the k set
-// {k0 + 4s + e}; the four together cover k0 .. k0+15 once.  FP32 chain sums are flushed into FP64
-// registers every 32 k, the waves' shares and the contractions are added in FP64, and the update is rounded once.
+// A lane's four values of a 16-wide chunk feed four MFMAs, k order and layouts as in tile_core.h.  FP32 chain sums are
+// flushed into FP64 registers every 16 (MT = 1) or 32 k, the waves' shares and the contractions are added in FP64, and the
+// update is rounded once.
 #include <algorithm>
 
-#include "common.h"
+#include "tile_core.h"
 
 namespace pstd {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 
 constexpr int NT = 512;                 // eight waves
 constexpr uint32_t kOOB = 0x80000000u;  // buffer offset past every range: the load returns zero
-
-template <typename T> struct Mma;
-template <> struct Mma<float> {
-  typedef f32x4 v4;
-  static __device__ __forceinline__ v4 mma(float a, float b, v4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
-};
-template <> struct Mma<double> {
-  typedef f64x4 v4;
-  static __device__ __forceinline__ v4 mma(double a, double b, v4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int lane, int r) { return 4 * r + (lane >> 4); }
-};
 
 // mx, my: staggered points along x and y, n - 1 between two walls and n on a periodic axis
 template <typename T>
@@ -157,7 +137,7 @@ __device__ __forceinline__ void contract_share(rsrc_t rA, int lda, rsrc_t rX, in
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             T v;
-            ld1(v, rX, past | ES * static_cast<uint32_t>((16 * ch + lk + e) * ldx + j0 + 16 * a + lr));
+            ld1(v, rX, past | ES * static_cast<uint32_t>((16 * ch + 4 * e + (lane >> 4)) * ldx + j0 + 16 * a + lr));
             X0[slot][q][a][e] = v;
           }
         }
@@ -182,7 +162,8 @@ __device__ __forceinline__ void contract_share(rsrc_t rA, int lda, rsrc_t rX, in
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");   // the last round's reads come first
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int i = 0; i < RI; ++i) strip[(i * (64 / RL) + lane / RL) * LD + lane % RL] = X1[s][i];
+        for (int i = 0; i < RI; ++i)
+          strip[(i * (64 / RL) + lane / RL) * LD + (lane % RL & ~15) + chunk_k(lane & 15)] = X1[s][i];
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
         __builtin_amdgcn_wave_barrier();
       }
@@ -321,13 +302,6 @@ __device__ __forceinline__ void phase2d_body(const Phase2DArgs<T>& a, int tile) 
   }
 }
 
-// Block b of n runs on XCD b % 8: the tile (in the order of the grid) that gives each XCD a run of consecutive
-// ones, whose operator rows and field strips then meet in one L2.
-__device__ __forceinline__ int xcd_tile(int b, int n) {
-  const int x = b & 7, q = n >> 3, r = n & 7;
-  return x * q + min(x, r) + (b >> 3);
-}
-
 template <typename T, int MT, int PH>
 __global__ __launch_bounds__(NT, 4) void phase2d_kernel(Phase2DArgs<T> a) {
   phase2d_body<T, MT, PH>(a, xcd_tile(blockIdx.x, gridDim.x));
@@ -343,16 +317,6 @@ __global__ __launch_bounds__(NT, 4) void phase2d_batch_kernel(const BatchSolve* 
   const Phase2DArgs<float> a{S.fGx, S.ldgx, S.mgx, S.fGy, S.ldgy, S.mgy, S.fDx, S.lddx, S.mdx, S.fDy, S.lddy, S.mdy,
                              S.p, S.ux, S.uy, S.c2, S.nx, S.ny, S.nx - 1, S.ny - 1, start ? -0.5 * S.sG : S.sG, S.sD, start};
   phase2d_body<float, MT, PH>(a, t % tiles);
-}
-
-// dst: the Mp x Kp matrix src in fragment order: for every 16 rows and chunk of 16 columns the 64 lanes' four
-// values, lane l those of row l % 16, columns 4 (l / 16) .. + 3.
-template <typename T>
-__global__ __launch_bounds__(256) void fragment_kernel(const T* __restrict__ src, T* __restrict__ dst, int Mp, int Kp) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= Mp * Kp) return;
-  const int e = i & 3, l = (i >> 2) & 63, blk = i >> 8, nc = Kp >> 4;
-  dst[i] = src[(16 * (blk / nc) + (l & 15)) * Kp + 16 * (blk % nc) + 4 * (l >> 4) + e];
 }
 
 int tiles_of(int nx, int ny, int edge) { return ((nx + edge - 1) / edge) * ((ny + edge - 1) / edge); }
@@ -398,19 +362,6 @@ bool operators_fit(const DevOperator& Gx, const DevOperator& Gy, const DevOperat
 }
 
 }  // namespace
-
-hipError_t build_fragments(bool dbl, const DevOperator& op, hipStream_t s) {
-  const int cnt = op.Mp * op.Kp;
-  if (!op.frag || op.Mp % 16 || op.Kp % 16) return hipErrorInvalidValue;
-  const dim3 grid((cnt + 255) / 256), blk(256);
-  if (dbl)
-    hipLaunchKernelGGL(fragment_kernel<double>, grid, blk, 0, s, static_cast<const double*>(op.data),
-                       static_cast<double*>(op.frag), op.Mp, op.Kp);
-  else
-    hipLaunchKernelGGL(fragment_kernel<float>, grid, blk, 0, s, static_cast<const float*>(op.data),
-                       static_cast<float*>(op.frag), op.Mp, op.Kp);
-  return hipGetLastError();
-}
 
 bool phase2d_supported(int nx, int ny) { return nx >= 3 && ny >= 3 && nx <= 512 && ny <= 512; }
 
