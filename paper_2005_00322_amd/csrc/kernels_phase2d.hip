@@ -83,10 +83,10 @@ __device__ __forceinline__ uint32_t oob_unless(bool in) { return (static_cast<ui
 
 __host__ __device__ __forceinline__ int pad64(int k) { return (k + 63) & ~63; }
 
-// Tile shapes: RC chunks of 16 k per round (a row's part of a round is 256 / MT bytes), NR rounds in flight.
-template <typename T, int MT>
+// Tile shapes: RC chunks of 16 k per round.  NR: rounds in flight (a second one spills at four waves per SIMD).
+template <typename T, int MT, int RC>
 struct Shape {
-  static constexpr int RC = (sizeof(T) == 4 ? 4 : 2) / MT, NR = 1;
+  static constexpr int NR = 1;
   static constexpr int RL = 16 * RC;                           // lanes along a row
   static constexpr int RI = 16 * MT * RL / 64;                 // loads of a round (64 / RL rows each)
   static constexpr int V = 16 / static_cast<int>(sizeof(T));   // values of a 16-byte LDS read
@@ -99,16 +99,16 @@ struct Shape {
 // C = 1: P the rows i0 .. of X, Q the operator rows j0 ...  K: contracted length, h: the wave's quarter of it.
 // The operator is zero for k >= K, up to pad64(K); X's rows k >= K lie past its end and read as zero, and the
 // elements of a row past K would be the next row's, so they are not read (a NaN there would not vanish).
-template <typename T, int MT, int C>
+template <typename T, int MT, int RC, int C>
 __device__ __forceinline__ void contract_share(rsrc_t rA, int lda, rsrc_t rX, int ldx, int i0, int j0, int K, int h,
                                                T* strip, double (&acc)[MT][MT][4]) {
   typedef typename Mma<T>::v4 v4;
   typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
-  typedef Shape<T, MT> S;
-  constexpr int RC = S::RC, NR = S::NR, V = S::V, RL = S::RL, RI = S::RI, LD = S::LD;
+  typedef Shape<T, MT, RC> S;
+  constexpr int NR = S::NR, V = S::V, RL = S::RL, RI = S::RI, LD = S::LD;
   constexpr uint32_t ES = sizeof(T);
   constexpr bool kFlush = sizeof(T) == 4;
-  const int lane = threadIdx.x & 63, lr = lane & 15, lk = 4 * (lane >> 4);
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = 4 * (lane >> 4);   // lk: the lane's place in a chunk
   const int nit = pad64(K) / 64;            // chunks of a wave
   const int c0 = h * nit;                   // its first
   v4 A[NR][RC][MT], X0[C == 0 ? NR : 1][RC][MT];
@@ -229,12 +229,12 @@ __device__ __forceinline__ void contract_share(rsrc_t rA, int lda, rsrc_t rX, in
 }
 
 // PH 0: velocity phase, PH 1: pressure phase.  tile: index of the block's tile.
-template <typename T, int MT, int PH>
+template <typename T, int MT, int RC, int PH>
 __device__ __forceinline__ void phase2d_body(const Phase2DArgs<T>& a, int tile) {
   constexpr int E = 16 * MT, G = MT * MT * 4;   // tile edge, register groups of a tile (64 values each)
   constexpr uint32_t ES = sizeof(T);
   // the partial tiles of the eight waves; before that the row strips of waves 4 .. 7
-  constexpr size_t kRed = sizeof(double) * 8 * G * 64, kStrips = 4 * Shape<T, MT>::strip;
+  constexpr size_t kRed = sizeof(double) * 8 * G * 64, kStrips = 4 * Shape<T, MT, RC>::strip;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kRed > kStrips ? kRed : kStrips];
   double (*red)[G][64] = reinterpret_cast<double (*)[G][64]>(lds);
   const int nx = a.nx, ny = a.ny, mx = a.mx, my = a.my;
@@ -268,15 +268,15 @@ __device__ __forceinline__ void phase2d_body(const Phase2DArgs<T>& a, int tile) 
   if (ux) {
     const T* A = PH == 0 ? a.Gx : a.Dx;
     const int lda = PH == 0 ? a.ldgx : a.lddx, ma = PH == 0 ? a.mgx : a.mdx, K = PH == 0 ? nx : mx;
-    contract_share<T, MT, 0>(make_rsrc(A, ES * static_cast<uint32_t>(ma * lda)), lda,
+    contract_share<T, MT, RC, 0>(make_rsrc(A, ES * static_cast<uint32_t>(ma * lda)), lda,
                                     make_rsrc(PH == 0 ? a.p : a.ux, ES * static_cast<uint32_t>(K * ny)), ny, i0, j0, K,
                                     wave, nullptr, acc);
   } else {
     const T* A = PH == 0 ? a.Gy : a.Dy;
     const int lda = PH == 0 ? a.ldgy : a.lddy, ma = PH == 0 ? a.mgy : a.mdy, K = PH == 0 ? ny : my;
-    contract_share<T, MT, 1>(make_rsrc(A, ES * static_cast<uint32_t>(ma * lda)), lda,
+    contract_share<T, MT, RC, 1>(make_rsrc(A, ES * static_cast<uint32_t>(ma * lda)), lda,
                                     make_rsrc(PH == 0 ? a.p : a.uy, ES * static_cast<uint32_t>(nx * K)), K, i0, j0, K,
-                                    wave - 4, reinterpret_cast<T*>(lds + (wave - 4) * Shape<T, MT>::strip), acc);
+                                    wave - 4, reinterpret_cast<T*>(lds + (wave - 4) * Shape<T, MT, RC>::strip), acc);
   }
   lds_barrier();   // the strips are read
 #pragma unroll
@@ -302,21 +302,21 @@ __device__ __forceinline__ void phase2d_body(const Phase2DArgs<T>& a, int tile) 
   }
 }
 
-template <typename T, int MT, int PH>
+template <typename T, int MT, int RC, int PH>
 __global__ __launch_bounds__(NT, 4) void phase2d_kernel(Phase2DArgs<T> a) {
-  phase2d_body<T, MT, PH>(a, xcd_tile(blockIdx.x, gridDim.x));
+  phase2d_body<T, MT, RC, PH>(a, xcd_tile(blockIdx.x, gridDim.x));
 }
 
 // One phase of many solves of one shape: tiles solve after solve, the solve's unscaled operators and factors
 // from the batch's solve table.  start (velocity phase): u^{-1/2} = -1/2 sG (G p), whatever u holds.
-template <int MT, int PH>
+template <int MT, int RC, int PH>
 __global__ __launch_bounds__(NT, 4) void phase2d_batch_kernel(const BatchSolve* __restrict__ solves, int tiles,
                                                               bool start) {
   const int t = xcd_tile(blockIdx.x, gridDim.x);
   const BatchSolve& S = solves[t / tiles];
   const Phase2DArgs<float> a{S.fGx, S.ldgx, S.mgx, S.fGy, S.ldgy, S.mgy, S.fDx, S.lddx, S.mdx, S.fDy, S.lddy, S.mdy,
                              S.p, S.ux, S.uy, S.c2, S.nx, S.ny, S.nx - 1, S.ny - 1, start ? -0.5 * S.sG : S.sG, S.sD, start};
-  phase2d_body<float, MT, PH>(a, t % tiles);
+  phase2d_body<float, MT, RC, PH>(a, t % tiles);
 }
 
 int tiles_of(int nx, int ny, int edge) { return ((nx + edge - 1) / edge) * ((ny + edge - 1) / edge); }
@@ -327,17 +327,25 @@ int tiles_of(int nx, int ny, int edge) { return ((nx + edge - 1) / edge) * ((ny 
 // 512 x 512 (1024) 14.1 / 10.3 and 19.9 / 13.8.
 int tile_edge(int nx, int ny, int count) { return static_cast<int64_t>(tiles_of(nx, ny, 16)) * count > 512 ? 32 : 16; }
 
+// Chunks per round: 256 / MT bytes of a row, or half of that where it covers a wave's whole share (chunks past the share
+// are still loads, if empty ones: 123 x 123 FP32 3.57 us per phase with four chunks for its two, 3.26 with two).
+template <typename T, int MT>
+constexpr int round_chunks() { return (sizeof(T) == 4 ? 4 : 2) / MT; }
+template <typename T, int MT>
+bool half_round(int nx, int ny) { return MT == 1 && pad64(std::max(nx, ny)) / 64 <= round_chunks<T, MT>() / 2; }
+
 template <typename T>
 hipError_t launch_one(int which, const Phase2DArgs<T>& a, hipStream_t s) {
   const int edge = tile_edge(a.nx, a.ny, 1);
   const dim3 grid(tiles_of(a.nx, a.ny, edge)), blk(NT);
-  if (edge == 16) {
-    if (which == 0) hipLaunchKernelGGL((phase2d_kernel<T, 1, 0>), grid, blk, 0, s, a);
-    else hipLaunchKernelGGL((phase2d_kernel<T, 1, 1>), grid, blk, 0, s, a);
-  } else {
-    if (which == 0) hipLaunchKernelGGL((phase2d_kernel<T, 2, 0>), grid, blk, 0, s, a);
-    else hipLaunchKernelGGL((phase2d_kernel<T, 2, 1>), grid, blk, 0, s, a);
-  }
+#define PSTD_PHASE(MT, RC)                                                                      \
+  if (which == 0) hipLaunchKernelGGL((phase2d_kernel<T, MT, RC, 0>), grid, blk, 0, s, a);       \
+  else hipLaunchKernelGGL((phase2d_kernel<T, MT, RC, 1>), grid, blk, 0, s, a);
+  constexpr int RC1 = round_chunks<T, 1>(), RC2 = round_chunks<T, 2>();
+  if (edge == 32) { PSTD_PHASE(2, RC2) }
+  else if (half_round<T, 1>(a.nx, a.ny)) { PSTD_PHASE(1, RC1 / 2) }
+  else { PSTD_PHASE(1, RC1) }
+#undef PSTD_PHASE
   return hipGetLastError();
 }
 
@@ -392,13 +400,13 @@ hipError_t launch_phase2d_batch(int which, const BatchSolve* solves, int count, 
   if (!phase2d_supported(nx, ny) || count < 1 || count > 65535 || (start && which != 0)) return hipErrorInvalidValue;
   const int edge = tile_edge(nx, ny, count), tiles = tiles_of(nx, ny, edge);
   const dim3 grid(static_cast<unsigned>(tiles) * static_cast<unsigned>(count)), blk(NT);
-  if (edge == 16) {
-    if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<1, 0>), grid, blk, 0, s, solves, tiles, start);
-    else hipLaunchKernelGGL((phase2d_batch_kernel<1, 1>), grid, blk, 0, s, solves, tiles, start);
-  } else {
-    if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<2, 0>), grid, blk, 0, s, solves, tiles, start);
-    else hipLaunchKernelGGL((phase2d_batch_kernel<2, 1>), grid, blk, 0, s, solves, tiles, start);
-  }
+#define PSTD_PHASE(MT, RC)                                                                                          \
+  if (which == 0) hipLaunchKernelGGL((phase2d_batch_kernel<MT, RC, 0>), grid, blk, 0, s, solves, tiles, start);     \
+  else hipLaunchKernelGGL((phase2d_batch_kernel<MT, RC, 1>), grid, blk, 0, s, solves, tiles, start);
+  if (edge == 32) { PSTD_PHASE(2, 2) }
+  else if (half_round<float, 1>(nx, ny)) { PSTD_PHASE(1, 2) }
+  else { PSTD_PHASE(1, 4) }
+#undef PSTD_PHASE
   return hipGetLastError();
 }
 
