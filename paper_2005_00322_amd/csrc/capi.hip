@@ -214,9 +214,11 @@ int prepare_axes(pstd_plan_s* P) {
   return PSTD_OK;
 }
 
-hipError_t contract(const pstd_plan_s* P, const DevOperator& op, int a, const void* X, void* Y, double alpha,
-                    double beta, const void* scale, hipStream_t s) {
-  ContractArgs c{};
+// The launch arguments of Y = beta Y + alpha scale (op X) along dense axis a; true when the axis is the unit-stride one.
+bool contract_args(const pstd_plan_s* P, const DevOperator& op, int a, const void* X, void* Y, double alpha, double beta,
+                   const void* scale, ContractArgs* out) {
+  ContractArgs& c = *out;
+  c = ContractArgs{};
   c.A = op.data;
   c.A_lo = nullptr;
   c.frag = op.frag;
@@ -244,8 +246,13 @@ hipError_t contract(const pstd_plan_s* P, const DevOperator& op, int a, const vo
     c.x_bstride = static_cast<int64_t>(op.K) * inner;
     c.y_bstride = static_cast<int64_t>(op.M) * inner;
   }
-  c.th = nullptr;
-  c.th_len = 0;
+  return contiguous;
+}
+
+hipError_t contract(const pstd_plan_s* P, const DevOperator& op, int a, const void* X, void* Y, double alpha,
+                    double beta, const void* scale, hipStream_t s) {
+  ContractArgs c;
+  const bool contiguous = contract_args(P, op, a, X, Y, alpha, beta, scale, &c);
   if (P->prec == PSTD_FP64) return launch_contract_fp64(c, contiguous, s);
   if (P->prec == PSTD_FP32) return launch_contract_fp32(c, contiguous, s);
   c.A_lo = static_cast<const uint16_t*>(op.data) + static_cast<size_t>(op.Mp) * op.Kp;
@@ -344,6 +351,20 @@ bool velocity_fft_multi(const pstd_plan_s* P, pstd_state* st, hipStream_t s, hip
   return true;
 }
 
+// The velocity half step of every axis as one launch on the FP32 / FP64 contractions (no axis on the FFT path); false: not
+// applicable.
+bool velocity_dense_multi(const pstd_plan_s* P, pstd_state* st, hipStream_t s, hipError_t* err) {
+  if (P->ndim < 2 || P->prec == PSTD_SPLIT_BF16) return false;
+  ContractArgs c[3];
+  bool contiguous[3];
+  for (int a = 0; a < P->ndim; ++a) {
+    if (axis_fft(P, a)) return false;
+    contiguous[a] = contract_args(P, P->G[a], a, st->p, st->u[a], 1.0, 1.0, nullptr, &c[a]);
+  }
+  *err = launch_contract_multi(P->prec == PSTD_FP64, c, contiguous, P->ndim, s);
+  return true;
+}
+
 bool use_fused2d(const pstd_plan_s* P) {
   return P->ndim == 2 && P->prec != PSTD_SPLIT_BF16 && (P->path == PSTD_PATH_AUTO || P->path == PSTD_PATH_FUSED) &&
          phase2d_supported(static_cast<int>(P->n[0]), static_cast<int>(P->n[1]));
@@ -357,7 +378,7 @@ hipError_t enqueue_steps(pstd_plan_s* P, pstd_state* st, int64_t nsteps, hipStre
                           static_cast<int>(P->n[0]), static_cast<int>(P->n[1]), nsteps, s);
   for (int64_t t = 0; t < nsteps; ++t) {
     hipError_t e = hipSuccess;
-    if (velocity_fft_multi(P, st, s, &e)) {
+    if (velocity_fft_multi(P, st, s, &e) || velocity_dense_multi(P, st, s, &e)) {
       if (e != hipSuccess) return e;
     } else {
       for (int a = 0; a < P->ndim; ++a) {
@@ -669,7 +690,7 @@ int pstd_apply_axis(pstd_plan P, pstd_state* st, int32_t axis, int32_t which) {
     const int pst = prepare_axes(P);
     if (pst != PSTD_OK) return pst;
     hipError_t e = hipSuccess;
-    if (which == 0 && velocity_fft_multi(P, st, P->stream, &e)) {
+    if (which == 0 && (velocity_fft_multi(P, st, P->stream, &e) || velocity_dense_multi(P, st, P->stream, &e))) {
       PSTD_HIP(e);
       return PSTD_OK;
     }

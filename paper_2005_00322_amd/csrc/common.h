@@ -136,6 +136,8 @@ struct ContractArgs {
 // Launchers (kernels_*.hip).  contiguous = the contracted axis is the last (unit-stride) one.
 hipError_t launch_contract_fp32(const ContractArgs& a, bool contiguous, hipStream_t s);
 hipError_t launch_contract_fp64(const ContractArgs& a, bool contiguous, hipStream_t s);
+// up to three FP32 / FP64 contractions with different outputs, beta = 1 and no map as one grid
+hipError_t launch_contract_multi(bool dbl, const ContractArgs* a, const bool* contiguous, int count, hipStream_t s);
 hipError_t launch_contract_split(const ContractArgs& a, bool contiguous, hipStream_t s);
 // The 1D time loop of lines of at most kLineMaxNodes nodes.  work: step1d_work_bytes of device memory, zeroed
 // once, kept by the plan; spins: polls a workgroup makes for a half step's values before it gives up (the steps

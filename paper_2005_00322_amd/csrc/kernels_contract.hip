@@ -17,6 +17,8 @@
 // us per launch before (64 x 64 tiles, 16-deep slices, both operands through LDS, one tile range per batch) and now, axes
 // x / y / z: 256^3 FP32 159 / 154 / 196 -> 99 / 98 / 89 (86-96 TFLOP/s of the 150 a large FP32 product reaches here);
 // 161 x 200 x 129 FP32 44 / 71 / 36 -> 28 / 36 / 18; 161 x 200 x 129 FP64 63 / 99 / 53 -> 39 / 50 / 27.
+#include <algorithm>
+
 #include "tile_core.h"
 
 namespace pstd {
@@ -35,11 +37,10 @@ struct KArgs {
   int mtiles;
 };
 
-template <typename T, bool ROWS, int MT, int WO>
-__global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_kernel(KArgs<T> a) {
+// PLAIN: beta = 1 and no map (the velocity update).
+template <typename T, bool ROWS, int MT, int WO, bool PLAIN>
+__device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* lds) {
   typedef Tile<T, MT, WO> TL;
-  __shared__ __attribute__((aligned(16))) T lds[TL::lds_values];
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int m0 = (tile % a.mtiles) * TL::EO;
   const int64_t l0 = static_cast<int64_t>(tile / a.mtiles) * TL::EL;
   constexpr uint32_t ES = sizeof(T);
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_kernel(KArgs<T>
   auto at = [&](int i, int r) { return ybase + (16 * i + Mma<T>::reg_row(r)) * row_step; };
   TL::template contract<ROWS>(a.op + static_cast<int64_t>(m0) * a.Kp, 16 * static_cast<int64_t>(a.Kp), X, lds,
                                m0 + TL::op0() >= a.M || l0 + TL::line0() >= a.lines, acc, [&] {
-    if (a.beta == 0.0) return;
+    if (!PLAIN && a.beta == 0.0) return;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_kernel(KArgs<T>
   });
   // fused update epilogue: the product, the map factor and the update are formed in FP64 and rounded once
   T sv[MT][MT][4];
-  if (a.scale) {
+  if (!PLAIN && a.scale) {
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -123,47 +124,125 @@ __global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_kernel(KArgs<T>
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         if (!valid(i, j, r)) continue;
-        const double old = a.beta != 0.0 ? a.beta * static_cast<double>(yv[i][j][r]) : 0.0;
+        const double y0 = static_cast<double>(yv[i][j][r]);
+        const double old = PLAIN ? y0 : (a.beta != 0.0 ? a.beta * y0 : 0.0);
         T* y = reinterpret_cast<T*>(reinterpret_cast<char*>(a.Y + at(i, r)) + coff[j]);
         *y = static_cast<T>(fma(a.alpha, acc[i][j][r], old));
       }
 }
 
+template <typename T, bool ROWS, int MT>
+__global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_kernel(KArgs<T> a) {
+  __shared__ __attribute__((aligned(16))) T lds[Tile<T, MT, 2>::lds_values];
+  contract_tile<T, ROWS, MT, 2, false>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
+}
+
+// Up to three contractions (beta = 1, no map) with outputs of their own in one grid (the velocity terms of a step: all read p), so that
+// the partly filled last round of blocks comes once instead of once per axis.  tiles[i]: tiles of contraction i; every
+// XCD takes its run of each contraction's tiles in turn (xcd_tile; the counts are rounded up to whole rounds of the
+// XCDs by blocks that end at once).  161 x 200 x 129 FP32: a step of 184 us with one launch per axis takes 178.
+template <typename T>
+struct MultiArgs {
+  KArgs<T> a[3];
+  int tiles[3], rows[3], count;
+};
+
+template <typename T, int MT>
+__global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_multi_kernel(MultiArgs<T> m) {
+  __shared__ __attribute__((aligned(16))) T lds[Tile<T, MT, 2>::lds_values];
+  int b = blockIdx.x;
+  for (int i = 0; i < m.count; ++i) {
+    const int n = (m.tiles[i] + 7) & ~7;
+    if (b >= n) {
+      b -= n;
+      continue;
+    }
+    const int tile = xcd_tile(b, n);
+    if (tile >= m.tiles[i]) return;
+    if (m.rows[i]) contract_tile<T, true, MT, 2, true>(m.a[i], tile, lds);
+    else contract_tile<T, false, MT, 2, true>(m.a[i], tile, lds);
+    return;
+  }
+}
+
+template <typename T>
+bool make_args(const ContractArgs& c, KArgs<T>* a) {
+  if (!c.frag || c.batch < 1 || c.ncols < 1 || c.M < 1 || c.K < 1) return false;
+  a->op = static_cast<const T*>(c.frag);
+  a->M = c.M;
+  a->K = c.K;
+  a->Kp = c.lda;
+  a->X = static_cast<const T*>(c.X);
+  a->Y = static_cast<T*>(c.Y);
+  a->inner = c.ncols;
+  a->lines = c.ncols * c.batch;
+  a->x_bstride = c.x_bstride;
+  a->y_bstride = c.y_bstride;
+  a->alpha = c.alpha_d;
+  a->beta = c.beta_d;
+  a->scale = static_cast<const T*>(c.scale);
+  return true;
+}
+
+template <typename T>
+int64_t tiles_of(const KArgs<T>& a, int edge) {
+  return ((a.M + edge - 1) / edge) * ((a.lines + edge - 1) / edge);
+}
+
+// 64 x 64 tiles from about 400 of them on (1.5 per CU), 32 x 32 before that: four times the blocks, twice the operand
+// traffic for a product.  us at 32 / 64, FP32: 314 tiles (100 x 100^2) 9.9 / 11.2, 400 (128 x 100^2) 11.9 / 11.0,
+// 512 (128^3) 14.1 / 12.0; FP64: 314 12.1 / 13.9, 512 19.1 / 16.5.
+constexpr int64_t kBigTiles = 400;
+
 template <typename T>
 hipError_t launch_t(const ContractArgs& c, bool contiguous, hipStream_t s) {
-  if (!c.frag || c.batch < 1 || c.ncols < 1 || c.M < 1 || c.K < 1) return hipErrorInvalidValue;
-  KArgs<T> a;
-  a.op = static_cast<const T*>(c.frag);
-  a.M = c.M;
-  a.K = c.K;
-  a.Kp = c.lda;
-  a.X = static_cast<const T*>(c.X);
-  a.Y = static_cast<T*>(c.Y);
-  a.inner = c.ncols;
-  a.lines = c.ncols * c.batch;
-  a.x_bstride = c.x_bstride;
-  a.y_bstride = c.y_bstride;
-  a.alpha = c.alpha_d;
-  a.beta = c.beta_d;
-  a.scale = static_cast<const T*>(c.scale);
   static_assert(kRowPad % 64 == 0 && kColPad % 32 == 0, "operator padding must cover whole tiles and slices");
-  // 64 x 64 tiles from about 400 of them on (1.5 per CU), 32 x 32 before that: four times the blocks, twice the operand
-  // traffic for a product.  us at 32 / 64, FP32: 314 tiles (100 x 100^2) 9.9 / 11.2, 400 (128 x 100^2) 11.9 / 11.0,
-  // 512 (128^3) 14.1 / 12.0; FP64: 314 12.1 / 13.9, 512 19.1 / 16.5.
-  auto tiles = [&](int edge) { return ((c.M + edge - 1) / edge) * ((a.lines + edge - 1) / edge); };
-  const bool big = tiles(64) >= 400;
+  KArgs<T> a;
+  if (!make_args(c, &a)) return hipErrorInvalidValue;
+  const bool big = tiles_of(a, 64) >= kBigTiles;
   const int edge = big ? 64 : 32;
   a.mtiles = (c.M + edge - 1) / edge;
-  const int64_t n = tiles(edge);
+  const int64_t n = tiles_of(a, edge);
   if (n > 0x7fffffff) return hipErrorInvalidConfiguration;
   const dim3 grid(static_cast<unsigned>(n)), blk(256);
   if (big) {
-    if (contiguous) hipLaunchKernelGGL((contract_kernel<T, true, 2, 2>), grid, blk, 0, s, a);
-    else hipLaunchKernelGGL((contract_kernel<T, false, 2, 2>), grid, blk, 0, s, a);
+    if (contiguous) hipLaunchKernelGGL((contract_kernel<T, true, 2>), grid, blk, 0, s, a);
+    else hipLaunchKernelGGL((contract_kernel<T, false, 2>), grid, blk, 0, s, a);
   } else {
-    if (contiguous) hipLaunchKernelGGL((contract_kernel<T, true, 1, 2>), grid, blk, 0, s, a);
-    else hipLaunchKernelGGL((contract_kernel<T, false, 1, 2>), grid, blk, 0, s, a);
+    if (contiguous) hipLaunchKernelGGL((contract_kernel<T, true, 1>), grid, blk, 0, s, a);
+    else hipLaunchKernelGGL((contract_kernel<T, false, 1>), grid, blk, 0, s, a);
   }
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_multi_t(const ContractArgs* c, const bool* contiguous, int count, hipStream_t s) {
+  MultiArgs<T> m{};
+  if (count < 1 || count > 3) return hipErrorInvalidValue;
+  int order[3] = {0, 1, 2};
+  std::sort(order, order + count, [&](int x, int y) { return c[x].K > c[y].K; });   // the longest products first
+  int64_t t64 = 0;
+  for (int i = 0; i < count; ++i) {
+    const ContractArgs& ci = c[order[i]];
+    if (!make_args(ci, &m.a[i]) || ci.beta_d != 1.0 || ci.scale) return hipErrorInvalidValue;
+    m.rows[i] = contiguous[order[i]];
+    t64 += tiles_of(m.a[i], 64);
+  }
+  m.count = count;
+  const bool big = t64 >= kBigTiles;
+  const int edge = big ? 64 : 32;
+  int64_t n = 0;
+  for (int i = 0; i < count; ++i) {
+    m.a[i].mtiles = (m.a[i].M + edge - 1) / edge;
+    const int64_t t = tiles_of(m.a[i], edge);
+    if (t > 0x7ffffff0) return hipErrorInvalidConfiguration;
+    m.tiles[i] = static_cast<int>(t);
+    n += round_up(t, 8);
+  }
+  if (n > 0x7fffffff) return hipErrorInvalidConfiguration;
+  const dim3 grid(static_cast<unsigned>(n)), blk(256);
+  if (big) hipLaunchKernelGGL((contract_multi_kernel<T, 2>), grid, blk, 0, s, m);
+  else hipLaunchKernelGGL((contract_multi_kernel<T, 1>), grid, blk, 0, s, m);
   return hipGetLastError();
 }
 
@@ -198,6 +277,10 @@ hipError_t launch_contract_fp32(const ContractArgs& c, bool contiguous, hipStrea
 
 hipError_t launch_contract_fp64(const ContractArgs& c, bool contiguous, hipStream_t s) {
   return launch_t<double>(c, contiguous, s);
+}
+
+hipError_t launch_contract_multi(bool dbl, const ContractArgs* c, const bool* contiguous, int count, hipStream_t s) {
+  return dbl ? launch_multi_t<double>(c, contiguous, count, s) : launch_multi_t<float>(c, contiguous, count, s);
 }
 
 }  // namespace pstd
