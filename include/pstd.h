@@ -249,15 +249,13 @@ int64_t pstd_plan_numel(pstd_plan plan, int32_t field /* -1 = p, 0..2 = u[axis] 
 
 int pstd_plan_destroy(pstd_plan plan);
 
-/* ---- Batched 2D solves: many independent boxes stepped by one persistent launch ----------------------
+/* ---- Batched 2D solves: many independent boxes stepped together ----------------------------------------
  * A batch holds `count` independent 2D FP32 solves of possibly different sizes, boundary faces,
  * spacings, time steps and sound speeds (density rho0 shared), all on the batch's stream.  Each solve is
  * the 2D scheme of §4.3; the paired Neumann/Dirichlet solves of one physical instance are two entries
  * combined afterwards with pstd_batch_combine_R.  Operators are built in FP64 once per distinct
- * (n, boundary pair) and shared.  pstd_batch_step runs all requested steps of all solves in one
- * persistent kernel launch of at most as many blocks as the GPU holds: per step a velocity phase over
- * every solve's velocity tiles, a grid-wide barrier, a pressure phase over every pressure tile, a second
- * barrier. */
+ * (n, boundary pair) and shared.  A step is two launches: every solve's velocity tiles, then every
+ * pressure tile. */
 typedef struct pstd_batch_s* pstd_batch;
 
 /* n: count x 2 (nx, ny) nodes per solve, each >= 3 and <= 512; bc: count x 4 faces {x-, x+, y-, y+};
@@ -275,8 +273,7 @@ int pstd_batch_set_c0_maps(pstd_batch batch, const float* const* c0_maps);
 /* Prepare caller-filled states (count of them, FP32 p and u[0], u[1]) as pstd_state_init does. */
 int pstd_batch_state_init(pstd_batch batch, pstd_state* states, int32_t u_mode);
 
-/* Advance every solve by n_steps: per 1024 steps one persistent launch (with the kernel that zeroes its
- * tile tickets and barrier counters) replayed from a captured HIP graph.  Asynchronous. */
+/* Advance every solve by n_steps, replaying captured HIP graphs of up to 64 steps.  Asynchronous. */
 int pstd_batch_step(pstd_batch batch, pstd_state* states, int64_t n_steps);
 
 /* out[i] = (1+R[i])/2 p_neumann + (1-R[i])/2 p_dirichlet for npairs pairs; pairs = npairs x 2 solve
@@ -284,24 +281,19 @@ int pstd_batch_step(pstd_batch batch, pstd_state* states, int64_t n_steps);
 int pstd_batch_combine_R(pstd_batch batch, const pstd_state* states, const int32_t* pairs, const double* R,
                          float* const* out, int32_t npairs);
 
-/* Launch configuration of pstd_batch_step: resident block count (0 = the occupancy maximum), tile
- * order within a phase (0 = longest contraction first, 1 = solve by solve) and output tile edge (32:
- * 32 x 32 tiles on FP32 MFMA 16x16x4; 64: 64 x 64 tiles on FP32 MFMA 32x32x2; 16: when every solve has
- * one shape of at most 512 x 512 nodes, no persistent launch but two fused phase launches per step over
- * all solves, each block one 16 x 16 tile of one solve, replayed from captured graphs; blocks and order
- * are then unused).  Returns PSTD_E_UNSUPPORTED for tile 16 on other batches. */
+/* Launch configuration of pstd_batch_step: blocks (accepted and kept; a launch has one block per tile), tile
+ * order within a phase (0 = longest contraction first, 1 = solve by solve) and output tile edge (32 or 64; 16: when
+ * every solve has one shape of at most 512 x 512 nodes, the fused phase launches of a single 2D plan over all
+ * solves; order is then unused).  Returns PSTD_E_UNSUPPORTED for tile 16 on other batches. */
 int pstd_batch_set_config(pstd_batch batch, int32_t blocks, int32_t order, int32_t tile);
 
-/* Autotuner: time every candidate configuration (tile edge x block count x order, and tile 16 where it
- * applies) for trial_steps steps on scratch state buffers (the caller's states are not touched), keep
+/* Autotuner: time every candidate configuration (tile edge x order, and tile 16 where it applies) for trial_steps steps on scratch state buffers (the caller's states are not touched), keep
  * the fastest and, if cache_path is not NULL, store it in a small JSON file keyed by a signature of the
  * batch; a later call with a matching file skips the timing.  config_out (nullable, 4 ints): blocks, order, tile, 1 if taken from the cache.
  * Synchronous. */
 int pstd_batch_autotune(pstd_batch batch, int32_t trial_steps, const char* cache_path, int32_t* config_out);
 
-/* Wait for the batch's stream and report whether every grid barrier of the launches since the last
- * call completed: PSTD_E_HIP if one gave up waiting (its blocks were not all resident, e.g. because other
- * work held the GPU), in which case the states are not valid. */
+/* Wait for the batch's stream. */
 int pstd_batch_synchronize(pstd_batch batch);
 
 int pstd_batch_destroy(pstd_batch batch);

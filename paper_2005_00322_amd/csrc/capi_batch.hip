@@ -1,4 +1,4 @@
-// libpstd C ABI, batched 2D solves: creation, initialisation, persistent stepping, pairing, autotuning.
+// libpstd C ABI, batched 2D solves: creation, initialisation, stepping, pairing, autotuning.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -27,22 +27,19 @@ struct pstd_batch_s {
   pstd::BatchSolve* d_solves = nullptr;
   std::vector<void*> key;                     // state pointers the device table was built for
   std::vector<pstd::BatchTask> tasksA, tasksB;
-  int segA[pstd::kBatchQueues + 1] = {}, segB[pstd::kBatchQueues + 1] = {};   // queue boundaries
+  pstd::BatchRuns runsA{}, runsB{};           // the XCDs' runs of either list
   pstd::BatchTask* d_tasks = nullptr;         // A then B
   int order_built = -1;
   int tile_built = -1;
-  unsigned* d_counters = nullptr;             // kBatchCountersPerStep per step of a launch, then the timeout flag
-  int blocks = 0;                             // 0 = occupancy maximum
+  int blocks = 0;                             // as configured (the launches have one block per tile)
   int order = 0;
-  int tile = 32;                              // output tile edge of the persistent kernel (32 or 64)
+  int tile = 32;                              // output tile edge (32 or 64; 16: the fused phase launches)
   hipStream_t capture = nullptr;              // private stream the launch graphs are captured on
-  std::map<std::tuple<int64_t, int, int>, hipGraphExec_t> graphs;   // (steps, blocks, tile) -> graph
+  std::map<std::pair<int64_t, int>, hipGraphExec_t> graphs;   // (steps, tile) -> graph
 };
 
 namespace pstd {
 namespace {
-
-constexpr int64_t kChunk = 1024;   // steps per persistent launch
 
 int upload_unscaled(const std::vector<double>& m, int M, int K, hipStream_t s, DevOperator* op) {
   op->M = M;
@@ -70,57 +67,52 @@ void free_batch(pstd_batch_s* B) {
   }
   if (B->d_solves) (void)hipFree(B->d_solves);
   if (B->d_tasks) (void)hipFree(B->d_tasks);
-  if (B->d_counters) (void)hipFree(B->d_counters);
   for (auto& kv : B->graphs) (void)hipGraphExecDestroy(kv.second);
   if (B->capture) (void)hipStreamDestroy(B->capture);
   delete B;
 }
 
-// Tile lists of both phases for output tiles of edge T, in the requested order.
-// Tile lists of both phases, split into one queue per XCD.  Solves go to queues greedily, most costly
-// first (cost: per-step multiply-adds, n_x n_y (n_x + n_y)), so each queue carries about 1/8 of the work
-// and all tiles of a solve share one L2.  Within a queue: order 0 longest contraction first (stable, so
-// a solve's tiles stay together), order 1 solve after solve.
+// Tile lists of both phases for output tiles of edge T: the tiles of the solves, most costly solve first, cut into one
+// run of equal cost per XCD (a tile's cost: its contracted length and a little for its start and end), so that a
+// solve's tiles share one L2, or two where a cut falls into it.  Within a run: order 0 longest contraction first
+// (stable, so a solve's tiles stay together), order 1 solve after solve.
 void build_tasks(pstd_batch_s* B, int order, int T) {
-  constexpr int Q = kBatchQueues;
-  B->tasksA.clear();
-  B->tasksB.clear();
   std::vector<int> by_cost(B->count);
   for (int s = 0; s < B->count; ++s) by_cost[s] = s;
   auto cost = [&](int s) { return static_cast<double>(B->nx[s]) * B->ny[s] * (B->nx[s] + B->ny[s]); };
   std::stable_sort(by_cost.begin(), by_cost.end(), [&](int x, int y) { return cost(x) > cost(y); });
-  std::vector<double> load(Q, 0.0);
-  std::vector<std::vector<int>> members(Q);
+  std::vector<std::pair<int, BatchTask>> a, b;   // (contracted length, task)
   for (int s : by_cost) {
-    const int q = static_cast<int>(std::min_element(load.begin(), load.end()) - load.begin());
-    members[q].push_back(s);
-    load[q] += cost(s);
+    const int nx = B->nx[s], ny = B->ny[s];
+    for (int i0 = 0; i0 < nx - 1; i0 += T)
+      for (int j0 = 0; j0 < ny; j0 += T) a.push_back({nx, BatchTask{s, 0, i0, j0}});
+    for (int i0 = 0; i0 < nx; i0 += T)
+      for (int j0 = 0; j0 < ny - 1; j0 += T) a.push_back({ny, BatchTask{s, 1, i0, j0}});
+    for (int i0 = 0; i0 < nx; i0 += T)
+      for (int j0 = 0; j0 < ny; j0 += T) b.push_back({nx + ny - 2, BatchTask{s, 2, i0, j0}});
   }
-  B->segA[0] = B->segB[0] = 0;
-  for (int q = 0; q < Q; ++q) {
-    std::sort(members[q].begin(), members[q].end());
-    std::vector<std::pair<int, BatchTask>> a, b;   // (contracted length, task)
-    for (int s : members[q]) {
-      const int nx = B->nx[s], ny = B->ny[s];
-      for (int i0 = 0; i0 < nx - 1; i0 += T)
-        for (int j0 = 0; j0 < ny; j0 += T) a.push_back({nx, BatchTask{s, 0, i0, j0}});
-      for (int i0 = 0; i0 < nx; i0 += T)
-        for (int j0 = 0; j0 < ny - 1; j0 += T) a.push_back({ny, BatchTask{s, 1, i0, j0}});
-      for (int i0 = 0; i0 < nx; i0 += T)
-        for (int j0 = 0; j0 < ny; j0 += T) b.push_back({nx + ny - 2, BatchTask{s, 2, i0, j0}});
+  auto cut = [&](std::vector<std::pair<int, BatchTask>>& v, std::vector<BatchTask>* out, BatchRuns* runs) {
+    constexpr int kTileOverhead = 64;   // of a tile's start and end, in k
+    double total = 0.0, sum = 0.0;
+    for (const auto& t : v) total += t.first + kTileOverhead;
+    int q = 0;
+    runs->beg[0] = 0;
+    for (size_t i = 0; i < v.size(); ++i) {
+      while (q + 1 < kBatchQueues && sum >= total * (q + 1) / kBatchQueues) runs->beg[++q] = static_cast<int>(i);
+      sum += v[i].first + kTileOverhead;
     }
-    if (order == 0) {
-      auto longest_first = [](const std::pair<int, BatchTask>& x, const std::pair<int, BatchTask>& y) {
-        return x.first > y.first;
-      };
-      std::stable_sort(a.begin(), a.end(), longest_first);
-      std::stable_sort(b.begin(), b.end(), longest_first);
-    }
-    for (auto& t : a) B->tasksA.push_back(t.second);
-    for (auto& t : b) B->tasksB.push_back(t.second);
-    B->segA[q + 1] = static_cast<int>(B->tasksA.size());
-    B->segB[q + 1] = static_cast<int>(B->tasksB.size());
-  }
+    while (q < kBatchQueues) runs->beg[++q] = static_cast<int>(v.size());
+    if (order == 0)
+      for (int r = 0; r < kBatchQueues; ++r)
+        std::stable_sort(v.begin() + runs->beg[r], v.begin() + runs->beg[r + 1],
+                         [](const std::pair<int, BatchTask>& x, const std::pair<int, BatchTask>& y) {
+                           return x.first > y.first;
+                         });
+    out->clear();
+    for (const auto& t : v) out->push_back(t.second);
+  };
+  cut(a, &B->tasksA, &B->runsA);
+  cut(b, &B->tasksB, &B->runsB);
 }
 
 int ensure_tasks(pstd_batch_s* B) {
@@ -166,68 +158,34 @@ int ensure_solves(pstd_batch_s* B, const pstd_state* st) {
   return PSTD_OK;
 }
 
-int resident_blocks(const pstd_batch_s* B, int* out) {
-  int maxb = 0;
-  if (batch2d_max_blocks(B->tile, &maxb) != 0 || maxb < 1) return fail(PSTD_E_HIP, "occupancy query failed");
-  *out = (B->blocks > 0 && B->blocks < maxb) ? B->blocks : maxb;
-  return PSTD_OK;
-}
-
-// The instantiated graph (counter fill + persistent launch) for `steps` steps on `blocks` blocks.  The
-// device tables it reads (solves, tasks, counters) keep their addresses for the batch's lifetime; their
-// contents are refreshed in place.
-int graph_for(pstd_batch_s* B, int64_t steps, int blocks, hipGraphExec_t* out) {
-  const auto key = std::make_tuple(steps, blocks, B->tile);
-  auto it = B->graphs.find(key);
-  if (it != B->graphs.end()) {
-    *out = it->second;
-    return PSTD_OK;
-  }
-  if (!B->capture) PSTD_HIP(hipStreamCreateWithFlags(&B->capture, hipStreamNonBlocking));
-  BatchArgs a;
-  a.solves = B->d_solves;
-  a.tasksA = B->d_tasks;
-  a.tasksB = B->d_tasks + B->tasksA.size();
-  for (int q = 0; q <= kBatchQueues; ++q) {
-    a.segA[q] = B->segA[q];
-    a.segB[q] = B->segB[q];
-  }
-  a.counters = B->d_counters;
-  a.timeout = B->d_counters + kBatchCountersPerStep * kChunk;
-  a.steps = steps;
-  hipGraph_t g = nullptr;
-  PSTD_HIP(hipStreamBeginCapture(B->capture, hipStreamCaptureModeThreadLocal));
-  const hipError_t le = launch_batch2d(a, B->tile, blocks, B->capture);
-  hipError_t e = hipStreamEndCapture(B->capture, &g);
-  if (le != hipSuccess) e = le;
-  hipGraphExec_t ex = nullptr;
-  if (e == hipSuccess) e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-  if (g) (void)hipGraphDestroy(g);
-  if (e != hipSuccess) return fail(PSTD_E_HIP, "capture of the persistent launch failed: %s", hipGetErrorString(e));
-  B->graphs[key] = ex;
-  *out = ex;
-  return PSTD_OK;
-}
-
-// Tile 16: every solve has one shape of at most 512 x 512 nodes, so a step is two fused phase launches
-// over all solves (block = (16 x 16 tile, solve)), as for a single 2D plan; no tasks, counters or grid
-// barriers.  Graphs of up to kPhaseChunk steps are captured and replayed.
-constexpr int64_t kPhaseChunk = 64;
-
+// Tile 16: every solve has one shape of at most 512 x 512 nodes, so the two launches of a step are the fused phases of a
+// single 2D plan over all solves (block = (tile, solve)); no tile lists.
 bool phase_eligible(const pstd_batch_s* B) {
   if (B->count < 1 || B->count > 65535 || B->solves.size() != static_cast<size_t>(B->count)) return false;
   for (int s = 0; s < B->count; ++s) {
     const BatchSolve& S = B->solves[s];
     if (B->nx[s] != B->nx[0] || B->ny[s] != B->ny[0]) return false;
-    if (!S.fGx || !S.fDx || !S.fGy || !S.fDy || !batch2d_phase_fits(S.ldgx, S.ldgy, S.lddx, S.lddy, S.nx, S.ny)) return false;
+    if (!S.fGx || !S.fDx || !S.fGy || !S.fDy || !batch2d_phase_fits(S.ldgx, S.ldgy, S.lddx, S.lddy, S.nx, S.ny))
+      return false;
   }
   return phase2d_supported(B->nx[0], B->ny[0]);
 }
 
-int launch_phase_steps(pstd_batch_s* B, int64_t n_steps, hipStream_t s) {
-  for (int64_t left = n_steps; left > 0; left -= kPhaseChunk) {
-    const int64_t steps = std::min(left, kPhaseChunk);
-    const auto key = std::make_tuple(steps, -1, 16);
+constexpr int64_t kChunk = 64;   // steps per captured graph
+
+hipError_t launch_phase(pstd_batch_s* B, int phase, hipStream_t s) {
+  if (B->tile == 16) return launch_phase2d_batch(phase, B->d_solves, B->count, B->nx[0], B->ny[0], false, s);
+  return launch_batch2d(phase, B->d_solves, phase == 0 ? B->d_tasks : B->d_tasks + B->tasksA.size(),
+                        phase == 0 ? B->runsA : B->runsB, B->tile, s);
+}
+
+// n_steps steps from captured graphs of up to kChunk of them.  The device tables a graph reads (solves, tasks) keep
+// their addresses for the batch's lifetime; their contents are refreshed in place, and the runs depend on the tile
+// alone.
+int launch_steps(pstd_batch_s* B, int64_t n_steps, hipStream_t s) {
+  for (int64_t left = n_steps; left > 0; left -= kChunk) {
+    const int64_t steps = std::min(left, kChunk);
+    const auto key = std::make_pair(steps, B->tile);
     auto it = B->graphs.find(key);
     if (it == B->graphs.end()) {
       if (!B->capture) PSTD_HIP(hipStreamCreateWithFlags(&B->capture, hipStreamNonBlocking));
@@ -235,8 +193,8 @@ int launch_phase_steps(pstd_batch_s* B, int64_t n_steps, hipStream_t s) {
       PSTD_HIP(hipStreamBeginCapture(B->capture, hipStreamCaptureModeThreadLocal));
       hipError_t le = hipSuccess;
       for (int64_t k = 0; k < steps && le == hipSuccess; ++k) {
-        le = launch_phase2d_batch(0, B->d_solves, B->count, B->nx[0], B->ny[0], false, B->capture);
-        if (le == hipSuccess) le = launch_phase2d_batch(1, B->d_solves, B->count, B->nx[0], B->ny[0], false, B->capture);
+        le = launch_phase(B, 0, B->capture);
+        if (le == hipSuccess) le = launch_phase(B, 1, B->capture);
       }
       hipError_t e = hipStreamEndCapture(B->capture, &g);
       if (le != hipSuccess) e = le;
@@ -247,19 +205,6 @@ int launch_phase_steps(pstd_batch_s* B, int64_t n_steps, hipStream_t s) {
       it = B->graphs.emplace(key, ex).first;
     }
     PSTD_HIP(hipGraphLaunch(it->second, s));
-  }
-  return PSTD_OK;
-}
-
-int launch_steps(pstd_batch_s* B, int64_t n_steps, hipStream_t s) {
-  int blocks = 0;
-  int st = resident_blocks(B, &blocks);
-  if (st != PSTD_OK) return st;
-  for (int64_t left = n_steps; left > 0; left -= kChunk) {
-    hipGraphExec_t ex = nullptr;
-    st = graph_for(B, std::min(left, kChunk), blocks, &ex);
-    if (st != PSTD_OK) return st;
-    PSTD_HIP(hipGraphLaunch(ex, s));
   }
   return PSTD_OK;
 }
@@ -398,14 +343,6 @@ int pstd_batch_create(int32_t count, const int64_t* n, const int32_t* bc, const 
     S.sD = -B->dt[s] * rho0 * B->c0[s] * B->c0[s] / B->dx[s];
     B->solves.push_back(S);
   }
-  if (hipMalloc(&B->d_counters, sizeof(unsigned) * (kBatchCountersPerStep * kChunk + 1)) != hipSuccess) {
-    free_batch(B);
-    return fail(PSTD_E_OOM, "hipMalloc of the phase counters failed");
-  }
-  if (hipMemset(B->d_counters, 0, sizeof(unsigned) * (kBatchCountersPerStep * kChunk + 1)) != hipSuccess) {
-    free_batch(B);
-    return fail(PSTD_E_HIP, "hipMemset of the phase counters failed");
-  }
   *out = B;
   return PSTD_OK;
 }
@@ -429,13 +366,6 @@ int pstd_batch_set_c0_maps(pstd_batch B, const float* const* c0_maps) {
 int pstd_batch_synchronize(pstd_batch B) {
   if (!B) return fail(PSTD_E_INVALID_ARG, "null batch");
   PSTD_HIP(B->stream ? hipStreamSynchronize(B->stream) : hipDeviceSynchronize());
-  unsigned flag = 0;
-  PSTD_HIP(hipMemcpy(&flag, B->d_counters + kBatchCountersPerStep * kChunk, sizeof(unsigned), hipMemcpyDeviceToHost));
-  if (flag) {
-    PSTD_HIP(hipMemset(B->d_counters + kBatchCountersPerStep * kChunk, 0, sizeof(unsigned)));
-    return fail(PSTD_E_HIP, "a grid barrier of the persistent launch timed out (blocks not all resident); "
-                            "the state is not valid");
-  }
   return PSTD_OK;
 }
 
@@ -512,12 +442,8 @@ int pstd_batch_step(pstd_batch B, pstd_state* st, int64_t n_steps) {
   if (n_steps < 0) return fail(PSTD_E_INVALID_ARG, "n_steps < 0");
   if (n_steps == 0) return PSTD_OK;
   int r = ensure_solves(B, st);
-  if (B->tile == 16) {
-    if (r == PSTD_OK) r = launch_phase_steps(B, n_steps, B->stream);
-  } else {
-    if (r == PSTD_OK) r = ensure_tasks(B);
-    if (r == PSTD_OK) r = launch_steps(B, n_steps, B->stream);
-  }
+  if (r == PSTD_OK && B->tile != 16) r = ensure_tasks(B);
+  if (r == PSTD_OK) r = launch_steps(B, n_steps, B->stream);
   if (r != PSTD_OK) return r;
   for (int s = 0; s < B->count; ++s) st[s].step += n_steps;
   return PSTD_OK;
@@ -591,72 +517,35 @@ int pstd_batch_autotune(pstd_batch B, int32_t trial_steps, const char* cache_pat
     scratch[s].u[2] = nullptr;
     scratch[s].step = 0;
   }
-  int cus = 0, dev = 0;
-  if (st == PSTD_OK && (hipGetDevice(&dev) != hipSuccess ||
-                        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess))
-    st = fail(PSTD_E_HIP, "device query failed");
   const std::vector<void*> saved_key = B->key;
   double best = 1e300;
-  int best_b = 0, best_o = 0, best_t = 32;
+  int best_o = 0, best_t = 32;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (st == PSTD_OK && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess))
     st = fail(PSTD_E_HIP, "event creation failed");
-  if (st == PSTD_OK && phase_eligible(B)) {
-    // the fused phase launches: one configuration
-    B->tile = 16;
-    B->blocks = 0;
-    B->order = 0;
-    st = ensure_solves(B, scratch.data());
-    if (st == PSTD_OK) st = launch_phase_steps(B, trial_steps, B->stream);   // warm (and capture the graph)
-    if (st == PSTD_OK && hipEventRecord(e0, B->stream) != hipSuccess) st = fail(PSTD_E_HIP, "event record failed");
-    if (st == PSTD_OK) st = launch_phase_steps(B, trial_steps, B->stream);
-    if (st == PSTD_OK && (hipEventRecord(e1, B->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess))
-      st = fail(PSTD_E_HIP, "event timing failed");
-    if (st == PSTD_OK) {
+  // the fused phase launches (one configuration), then both tile edges in both orders
+  for (int tile : {16, 32, 64})
+    for (int order = 0; order < (tile == 16 ? 1 : 2) && st == PSTD_OK; ++order) {
+      if (tile == 16 && !phase_eligible(B)) break;
+      B->blocks = 0;
+      B->order = order;
+      B->tile = tile;
+      st = ensure_solves(B, scratch.data());
+      if (st == PSTD_OK && tile != 16) st = ensure_tasks(B);
+      if (st == PSTD_OK) st = launch_steps(B, trial_steps, B->stream);   // warm (and capture the graph)
+      if (st == PSTD_OK && hipEventRecord(e0, B->stream) != hipSuccess) st = fail(PSTD_E_HIP, "event record failed");
+      if (st == PSTD_OK) st = launch_steps(B, trial_steps, B->stream);
+      if (st == PSTD_OK && (hipEventRecord(e1, B->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess))
+        st = fail(PSTD_E_HIP, "event timing failed");
+      if (st != PSTD_OK) break;
       float ms = 0.f;
       (void)hipEventElapsedTime(&ms, e0, e1);
-      best = ms;
-      best_b = 0;
-      best_o = 0;
-      best_t = 16;
-    }
-  }
-  for (int tile : {32, 64}) {
-    if (st != PSTD_OK) break;
-    int maxb = 0;
-    if (batch2d_max_blocks(tile, &maxb) != 0 || maxb < 1) {
-      st = fail(PSTD_E_HIP, "occupancy query failed");
-      break;
-    }
-    std::vector<int> cand;
-    for (int m = 1; m * cus <= maxb; ++m) cand.push_back(m * cus);
-    if (cand.empty() || cand.back() != maxb) cand.push_back(maxb);
-    for (int order = 0; order < 2 && st == PSTD_OK; ++order)
-      for (int b : cand) {
-        B->blocks = b == maxb ? 0 : b;
-        B->order = order;
-        B->tile = tile;
-        st = ensure_solves(B, scratch.data());
-        if (st == PSTD_OK) st = ensure_tasks(B);
-        if (st == PSTD_OK) st = launch_steps(B, trial_steps, B->stream);   // warm (and capture the graph)
-        if (st != PSTD_OK) break;
-        if (hipEventRecord(e0, B->stream) != hipSuccess) { st = fail(PSTD_E_HIP, "event record failed"); break; }
-        st = launch_steps(B, trial_steps, B->stream);
-        if (st != PSTD_OK) break;
-        if (hipEventRecord(e1, B->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
-          st = fail(PSTD_E_HIP, "event timing failed");
-          break;
-        }
-        float ms = 0.f;
-        (void)hipEventElapsedTime(&ms, e0, e1);
-        if (ms < best) {
-          best = ms;
-          best_b = B->blocks;
-          best_o = order;
-          best_t = tile;
-        }
+      if (ms < best) {
+        best = ms;
+        best_o = order;
+        best_t = tile;
       }
-  }
+    }
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   (void)(B->stream ? hipStreamSynchronize(B->stream) : hipDeviceSynchronize());
@@ -664,7 +553,7 @@ int pstd_batch_autotune(pstd_batch B, int32_t trial_steps, const char* cache_pat
   B->key.clear();   // the device solve table points at the freed scratch states
   (void)saved_key;
   if (st != PSTD_OK) return st;
-  B->blocks = best_b;
+  B->blocks = 0;
   B->order = best_o;
   B->tile = best_t;
   if (cache_path) {

@@ -190,23 +190,15 @@ struct BatchTask {
   int kind;                 // 0 u_x tile, 1 u_y tile, 2 p tile
   int i0, j0;
 };
-// Tiles of each phase are kept in kBatchQueues queues, one per XCD (blocks of XCD x are those with
-// blockIdx % 8 == x): queue q holds the tiles of the solves assigned to XCD q, so a solve's operator rows
-// and field strips are fetched into one L2; a block drains its own queue, then takes tiles from the others.
+// Tiles of each phase lie in kBatchQueues runs, one per XCD (blocks of XCD x are those with blockIdx % 8 == x): run q is
+// tasks[beg[q] .. beg[q + 1]).
 constexpr int kBatchQueues = 8;
-constexpr int kBatchCountersPerStep = 2 * kBatchQueues + 2;   // tickets per queue and phase, two arrivals
-struct BatchArgs {
-  const BatchSolve* solves;
-  const BatchTask* tasksA;  // velocity-phase tiles, queue after queue
-  int segA[kBatchQueues + 1];   // queue q is tasksA[segA[q] .. segA[q + 1])
-  const BatchTask* tasksB;  // pressure-phase tiles
-  int segB[kBatchQueues + 1];
-  unsigned* counters;       // kBatchCountersPerStep per step, zeroed by the launcher
-  unsigned* timeout;        // set to 1 when a grid barrier gives up waiting (sticky; cleared by the host)
-  int64_t steps;
+struct BatchRuns {
+  int beg[kBatchQueues + 1];
 };
-int batch2d_max_blocks(int tile, int* out);   // tile: 32 or 64 (output tile edge)
-hipError_t launch_batch2d(const BatchArgs& a, int tile, int blocks, hipStream_t s);
+// phase 0: velocity tiles, 1: pressure tiles; tile: 32 or 64 (output tile edge)
+hipError_t launch_batch2d(int phase, const BatchSolve* solves, const BatchTask* tasks, const BatchRuns& runs, int tile,
+                          hipStream_t s);
 
 hipError_t launch_nonfinite(int prec, const void* x, int64_t count, int* flag, hipStream_t s);
 

@@ -38,11 +38,11 @@ struct KArgs {
 };
 
 // PLAIN: beta = 1 and no map (the velocity update).
-template <typename T, bool ROWS, int MT, int WO, bool PLAIN>
+template <typename T, bool ROWS, int MT, bool PLAIN>
 __device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* lds) {
-  typedef Tile<T, MT, WO> TL;
-  const int m0 = (tile % a.mtiles) * TL::EO;
-  const int64_t l0 = static_cast<int64_t>(tile / a.mtiles) * TL::EL;
+  typedef Tile<T, MT> TL;
+  const int m0 = (tile % a.mtiles) * TL::E;
+  const int64_t l0 = static_cast<int64_t>(tile / a.mtiles) * TL::E;
   constexpr uint32_t ES = sizeof(T);
   const int lane = threadIdx.x & 63;
   typename TL::template Field<ROWS> X;
@@ -57,7 +57,7 @@ __device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* ld
   if constexpr (ROWS) {
     X.x = a.X + l0 * a.K;
     X.ld = a.K;
-    X.set_rows(static_cast<int>(min(a.lines - l0, static_cast<int64_t>(TL::EL))));
+    X.set_rows(static_cast<int>(min(a.lines - l0, static_cast<int64_t>(TL::E))));
   } else {
     X.x = a.X + b0 * a.x_bstride + c0;
     X.ld = a.inner;
@@ -66,8 +66,8 @@ __device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* ld
   // Outputs: value (row, column) of the tile, columns along the unit stride.  A lane's column gives a 32-bit offset, its
   // rows are row_step apart from a wave-uniform start.
   const int64_t row_step = ROWS ? a.M : a.inner;
-  const int64_t first = (ROWS ? l0 : m0) + (ROWS ? TL::line0() : TL::op0());
-  const int64_t ybase = first * row_step + (ROWS ? m0 + TL::op0() : b0 * a.y_bstride + c0);
+  const int64_t first = (ROWS ? l0 : m0) + TL::row0();
+  const int64_t ybase = first * row_step + (ROWS ? m0 + TL::template op0<ROWS>() : b0 * a.y_bstride + c0);
   const int lr = Mma<T>::lane_row(lane);
   const int rows_left = static_cast<int>(min((ROWS ? a.lines : a.M) - first, static_cast<int64_t>(16 * MT))) - lr;
   uint32_t coff[MT];
@@ -77,11 +77,11 @@ __device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* ld
     bool ok;
     int64_t o;
     if constexpr (ROWS) {
-      ok = m0 + TL::op0() + cl < a.M;
+      ok = m0 + TL::template op0<ROWS>() + cl < a.M;
       o = cl;
     } else {
-      ok = l0 + TL::line0() + cl < a.lines;
-      o = line_off(TL::line0() + cl, a.y_bstride);
+      ok = l0 + TL::template line0<ROWS>() + cl < a.lines;
+      o = line_off(TL::template line0<ROWS>() + cl, a.y_bstride);
     }
     coff[j] = ok ? ES * static_cast<uint32_t>(o + lr * row_step) : ~0u;
   }
@@ -90,7 +90,7 @@ __device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* ld
   auto valid = [&](int i, int j, int r) { return coff[j] != ~0u && 16 * i + Mma<T>::reg_row(r) < rows_left; };
   auto at = [&](int i, int r) { return ybase + (16 * i + Mma<T>::reg_row(r)) * row_step; };
   TL::template contract<ROWS>(a.op + static_cast<int64_t>(m0) * a.Kp, 16 * static_cast<int64_t>(a.Kp), X, lds,
-                               m0 + TL::op0() >= a.M || l0 + TL::line0() >= a.lines, acc, [&] {
+                               m0 + TL::template op0<ROWS>() >= a.M || l0 + TL::template line0<ROWS>() >= a.lines, acc, [&] {
     if (!PLAIN && a.beta == 0.0) return;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -133,8 +133,8 @@ __device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* ld
 
 template <typename T, bool ROWS, int MT>
 __global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_kernel(KArgs<T> a) {
-  __shared__ __attribute__((aligned(16))) T lds[Tile<T, MT, 2>::lds_values];
-  contract_tile<T, ROWS, MT, 2, false>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
+  __shared__ __attribute__((aligned(16))) T lds[Tile<T, MT>::lds_values];
+  contract_tile<T, ROWS, MT, false>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
 }
 
 // Up to three contractions (beta = 1, no map) with outputs of their own in one grid (the velocity terms of a step: all read p), so that
@@ -149,7 +149,7 @@ struct MultiArgs {
 
 template <typename T, int MT>
 __global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_multi_kernel(MultiArgs<T> m) {
-  __shared__ __attribute__((aligned(16))) T lds[Tile<T, MT, 2>::lds_values];
+  __shared__ __attribute__((aligned(16))) T lds[Tile<T, MT>::lds_values];
   int b = blockIdx.x;
   for (int i = 0; i < m.count; ++i) {
     const int n = (m.tiles[i] + 7) & ~7;
@@ -159,8 +159,8 @@ __global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_multi_kernel(Mu
     }
     const int tile = xcd_tile(b, n);
     if (tile >= m.tiles[i]) return;
-    if (m.rows[i]) contract_tile<T, true, MT, 2, true>(m.a[i], tile, lds);
-    else contract_tile<T, false, MT, 2, true>(m.a[i], tile, lds);
+    if (m.rows[i]) contract_tile<T, true, MT, true>(m.a[i], tile, lds);
+    else contract_tile<T, false, MT, true>(m.a[i], tile, lds);
     return;
   }
 }

@@ -70,26 +70,28 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
   return x * q + min(x, r) + (b >> 3);
 }
 
-// Four waves of (16 MT) x (16 MT) outputs (MT x MT MFMA blocks each), WO of them along the operator's rows and 4 / WO along
-// the field's lines.
-template <typename T, int MT, int WO>
+// A tile of edge 32 MT: four waves of (16 MT) x (16 MT) outputs, MT x MT MFMA blocks each.
+template <typename T, int MT>
 struct Tile {
   typedef typename Mma<T>::v4 v4;
-  static constexpr int EO = 16 * MT * WO, EL = 16 * MT * (4 / WO), NT = 256;   // operator rows, field lines of a tile
+  static constexpr int E = 32 * MT, NT = 256;
   static constexpr int BK = 128 / static_cast<int>(sizeof(T)), V = 16 / static_cast<int>(sizeof(T));
   static constexpr int LD = BK + V, CH = BK / 16;     // LDS row stride, chunks of a slice
-  static constexpr int NX = EL * BK / NT;             // field values a thread stages per slice
+  static constexpr int NX = E * BK / NT;             // field values a thread stages per slice
   static constexpr int NU = NX / V;                   // and 16-byte units of them
-  static constexpr size_t lds_values = 2 * EL * LD;   // two slices
+  static constexpr size_t lds_values = 2 * E * LD;    // two slices
 
-  // first operator row and first line of this thread's wave in the tile
-  static __device__ __forceinline__ int op0() { return wave_index() % WO * 16 * MT; }
-  static __device__ __forceinline__ int line0() { return wave_index() / WO * 16 * MT; }
+  // first row and column of this wave's quadrant of the output tile, and where they lie on the operator and the field: ROWS,
+  // the field's lines are the rows and the operator's rows the columns; otherwise the other way round
+  static __device__ __forceinline__ int row0() { return (wave_index() & 1) * 16 * MT; }
+  static __device__ __forceinline__ int col0() { return (wave_index() >> 1) * 16 * MT; }
+  template <bool ROWS> static __device__ __forceinline__ int op0() { return ROWS ? col0() : row0(); }
+  template <bool ROWS> static __device__ __forceinline__ int line0() { return ROWS ? row0() : col0(); }
 
-  // The field operand: lines 0 .. EL - 1 of the tile, of which `lines` exist.  ROWS: line l is the row at x + l * ld, k
+  // The field operand: lines 0 .. E - 1 of the tile, of which `lines` exist.  ROWS: line l is the row at x + l * ld, k
   // contiguous; otherwise value (l, k) lies at x + off + k * ld with off this thread's line offset in bytes.  A thread
-  // stages NX values of a slice: ROWS, one k of NX lines; otherwise NU units of V k of one line (EL is 64 or 128, or 32: the
-  // k of a unit are the same for a wave from 64 on).
+  // stages NX values of a slice: ROWS, one k of NX lines; otherwise NU units of V k of one line (E = 64: the k of a unit are
+  // the same for the whole wave).
   template <bool ROWS>
   struct Field {
     const T* x;      // wave-uniform
@@ -97,7 +99,7 @@ struct Tile {
     int K;
     uint32_t off[ROWS ? NX : 1];
     static __device__ __forceinline__ int line(int i) {
-      return ROWS ? static_cast<int>(threadIdx.x) / BK + i * (NT / BK) : static_cast<int>(threadIdx.x) % EL;
+      return ROWS ? static_cast<int>(threadIdx.x) / BK + i * (NT / BK) : static_cast<int>(threadIdx.x) % E;
     }
     // ROWS: the lines past `lines` read the last one
     __device__ __forceinline__ void set_rows(int lines) {
@@ -108,8 +110,8 @@ struct Tile {
     // the k this thread stages of a slice (ROWS), or k of value e of its unit i, and the LDS position of that unit
     static __device__ __forceinline__ int row_k() { return static_cast<int>(threadIdx.x) % BK; }
     static __device__ __forceinline__ int unit_pos(int i) {
-      const int g = EL >= 64 ? wave_index() / (EL / 64) : static_cast<int>(threadIdx.x) / EL;
-      return V * (g + i * (NT / EL));
+      const int g = E == 64 ? wave_index() : static_cast<int>(threadIdx.x) / E;
+      return V * (g + i * (NT / E));
     }
     static __device__ __forceinline__ int unit_k(int i, int e) {
       const int p = unit_pos(i) + e;
@@ -157,9 +159,9 @@ struct Tile {
                                                   double (&acc)[MT][MT][4], F&& before_last) {
     const int lane = threadIdx.x & 63;
     const int nsl = (X.K + BK - 1) / BK, nch = (X.K + 15) / 16;
-    const T* a0 = op + op0() / 16 * op_block;
+    const T* a0 = op + op0<ROWS>() / 16 * op_block;
     const uint32_t al = static_cast<uint32_t>(4 * sizeof(T)) * static_cast<uint32_t>(lane);
-    const T* xs = lds + (line0() + (lane & 15)) * LD + 4 * (lane >> 4);   // this lane's fragment in buffer 0
+    const T* xs = lds + (line0<ROWS>() + (lane & 15)) * LD + 4 * (lane >> 4);   // this lane's fragment in buffer 0
     v4 A[CH][MT];
     T xr[NX];
     auto load_op = [&](int c, int ch) {
@@ -180,12 +182,12 @@ struct Tile {
     }
     auto slice = [&](int s, auto last) {
       constexpr bool kLast = decltype(last)::value;
-      const int buf = (s & 1) * (EL * LD);
+      const int buf = (s & 1) * (E * LD);
       if constexpr (kLast) {
         before_last();
       } else {
-        if (s + 2 < nsl) X.template store<false>(s + 1, lds + (EL * LD - buf), xr);
-        else X.template store<true>(s + 1, lds + (EL * LD - buf), xr);
+        if (s + 2 < nsl) X.template store<false>(s + 1, lds + (E * LD - buf), xr);
+        else X.template store<true>(s + 1, lds + (E * LD - buf), xr);
         X.load(s + 2, xr);
       }
       v4 part[MT][MT];   // the slice's sum (FP64: the accumulators themselves)
@@ -228,7 +230,7 @@ struct Tile {
     };
     if (idle) {   // a loop of its own: a test inside the products' loop costs every wave its schedule
       for (int s = 0; s + 1 < nsl; ++s) {
-        X.template store<true>(s + 1, lds + (1 - (s & 1)) * (EL * LD), xr);
+        X.template store<true>(s + 1, lds + (1 - (s & 1)) * (E * LD), xr);
         X.load(s + 2, xr);
         lds_barrier();
       }

@@ -348,7 +348,7 @@ def solve_faces(shape, dx, dt, c0, R_faces, p0, n_steps, rho0=1000.0, precision=
 
 
 class Batch:
-    """Many independent 2D FP32 solves stepped by one persistent launch (include/pstd.h, pstd_batch_*).
+    """Many independent 2D FP32 solves stepped together (include/pstd.h, pstd_batch_*).
 
     solves: list of dicts with keys shape (nx, ny), bcs ((l, r), (l, r)), dx, dt, c0.
     """
@@ -440,7 +440,7 @@ class Batch:
         del keep
 
     def synchronize(self):
-        """Wait for the batch's work; raises if a grid barrier of the persistent launch timed out."""
+        """Wait for the batch's work."""
         check(load().pstd_batch_synchronize(self._h), "pstd_batch_synchronize")
 
     def set_config(self, blocks=0, order=0, tile=32):
