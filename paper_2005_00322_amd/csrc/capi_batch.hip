@@ -452,15 +452,37 @@ int pstd_batch_step(pstd_batch B, pstd_state* st, int64_t n_steps) {
 int pstd_batch_combine_R(pstd_batch B, const pstd_state* st, const int32_t* pairs, const double* R, float* const* out,
                          int32_t npairs) {
   if (!B || !st || !pairs || !R || !out || npairs < 0) return fail(PSTD_E_INVALID_ARG, "null argument");
+  std::vector<CombinePair> work(npairs);
   for (int i = 0; i < npairs; ++i) {
     const int d = pairs[2 * i], nn = pairs[2 * i + 1];
     if (d < 0 || d >= B->count || nn < 0 || nn >= B->count) return fail(PSTD_E_INVALID_ARG, "pair %d out of range", i);
     if (B->nx[d] != B->nx[nn] || B->ny[d] != B->ny[nn]) return fail(PSTD_E_INVALID_ARG, "pair %d: sizes differ", i);
     if (!out[i] || !st[d].p || !st[nn].p || !std::isfinite(R[i])) return fail(PSTD_E_INVALID_ARG, "pair %d: bad argument", i);
-    const float* f[2] = {static_cast<const float*>(st[nn].p), static_cast<const float*>(st[d].p)};
-    const float w[2] = {static_cast<float>(0.5 * (1.0 + R[i])), static_cast<float>(0.5 * (1.0 - R[i]))};
-    PSTD_HIP(launch_combine(f, w, 2, out[i], static_cast<int64_t>(B->nx[d]) * B->ny[d], B->stream));
+    work[i] = CombinePair{static_cast<const float*>(st[nn].p), static_cast<const float*>(st[d].p), out[i],
+                          static_cast<float>(0.5 * (1.0 + R[i])), static_cast<float>(0.5 * (1.0 - R[i])),
+                          static_cast<int64_t>(B->nx[d]) * B->ny[d]};
   }
+  // one launch unless an output overlaps another pair's fields (those pairs run one after another, in order)
+  struct Span {
+    const float *beg, *end;
+    int pair;
+  };
+  std::vector<Span> outs;
+  for (int i = 0; i < npairs; ++i) outs.push_back({work[i].out, work[i].out + work[i].count, i});
+  std::sort(outs.begin(), outs.end(), [](const Span& x, const Span& y) { return x.beg < y.beg; });
+  bool apart = true;
+  for (int i = 1; i < npairs; ++i) apart = apart && outs[i - 1].end <= outs[i].beg;
+  for (int i = 0; i < npairs && apart; ++i)
+    for (const float* in : {work[i].n, work[i].d}) {
+      // outputs are disjoint and sorted: the ones that overlap `in` follow the first that ends behind its start
+      auto o = std::lower_bound(outs.begin(), outs.end(), in, [](const Span& x, const float* v) { return x.end <= v; });
+      for (; o != outs.end() && o->beg < in + work[i].count; ++o) apart = apart && o->pair == i;
+    }
+  if (apart) {
+    PSTD_HIP(launch_combine_pairs(work.data(), npairs, B->stream));
+    return PSTD_OK;
+  }
+  for (const CombinePair& c : work) PSTD_HIP(launch_combine_pairs(&c, 1, B->stream));
   return PSTD_OK;
 }
 

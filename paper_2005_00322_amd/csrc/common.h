@@ -153,6 +153,15 @@ hipError_t launch_fill_zero(int prec, void* x, int64_t count, hipStream_t s);
 hipError_t launch_square(int prec, const float* in, void* out, int64_t count, hipStream_t s);
 hipError_t launch_combine(const float* const* f, const float* w, int nf, float* out, int64_t count,
                           hipStream_t s);
+// out = wn n + wd d elementwise over each pair's count values; out may alias its own n or d.
+struct CombinePair {
+  const float* n;
+  const float* d;
+  float* out;
+  float wn, wd;
+  int64_t count;
+};
+hipError_t launch_combine_pairs(const CombinePair* pairs, int count, hipStream_t s);
 bool phase2d_supported(int nx, int ny);
 // Fills op->frag from op->data on stream s.
 hipError_t build_fragments(bool dbl, const DevOperator& op, hipStream_t s);
