@@ -45,8 +45,13 @@ float bf16_to_float(uint16_t h) {
   return f;
 }
 
-// Round the FP64 matrix (M x K, already scaled) to the plan precision and upload it zero padded (FP64 and FP32: in
-// fragment order too).
+// Element offset of entry (i, k)'s hi part in a split operator's fragments (its lo part is 512 further on).
+inline size_t split_fragment_at(int Kp, unsigned i, unsigned k) {
+  return static_cast<size_t>((i >> 5) * (static_cast<unsigned>(Kp) >> 4) + (k >> 4)) * 1024 + (i & 31) * 8 + (k & 8) * 32 + (k & 7);
+}
+
+// Round the FP64 matrix (M x K, already scaled) to the plan precision and upload it zero padded, row-major and in
+// fragment order.
 int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, double scale, DevOperator* op) {
   op->M = M;
   op->K = K;
@@ -81,37 +86,38 @@ int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, 
     }
     return PSTD_OK;
   }
-  // split bf16: hi = bf16(v), lo = bf16(v - hi), both rounded from the FP64 value
+  // split bf16, in fragment order: hi = bf16(v), lo = bf16(v - hi), both rounded from the FP64 value
   std::vector<uint16_t> host(2 * cnt, 0);
   for (int i = 0; i < M; ++i)
     for (int k = 0; k < K; ++k) {
       const double v = scale * m[static_cast<size_t>(i) * K + k];
       const uint16_t hi = bf16_rne(static_cast<float>(v));
-      const uint16_t lo = bf16_rne(static_cast<float>(v - static_cast<double>(bf16_to_float(hi))));
-      host[static_cast<size_t>(i) * op->Kp + k] = hi;
-      host[cnt + static_cast<size_t>(i) * op->Kp + k] = lo;
+      uint16_t* at = host.data() + split_fragment_at(op->Kp, i, k);
+      at[0] = hi;
+      at[512] = bf16_rne(static_cast<float>(v - static_cast<double>(bf16_to_float(hi))));
     }
-  if (hipMalloc(&op->data, 2 * cnt * 2) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
-  PSTD_HIP(hipMemcpy(op->data, host.data(), 2 * cnt * 2, hipMemcpyHostToDevice));
-  // operators the contraction forms on the chip from f and g: windows Fr[i] = f(kThRowsMax - 1 - i) and
-  // G[i] = g(i), i < th_len, zero past the operator
+  // Operators of these sizes take the FP32 sum of their Toeplitz and Hankel parts as entry (the end weights, 0, 1/2
+  // or 1, are exact): the values that results of these sizes have always rested on.
   std::vector<double> f, g;
   double w[4], resid = 0.0;
-  if (M > kThRowsMin && M <= kThRowsMax && op->Kp <= kThColsMax &&
-      toeplitz_hankel(m.data(), M, K, kThTol, &f, &g, w, &resid)) {
-    const int len = kThRowsMax + op->Kp + 8;
-    std::vector<float> win(2 * static_cast<size_t>(len), 0.f);
-    for (int i = 0; i < len; ++i) {
-      const int d = kThRowsMax - 1 - i;
-      if (d >= 1 - K && d <= M - 1) win[i] = static_cast<float>(scale * f[d + K - 1]);
-      if (i <= M + K - 2) win[len + i] = static_cast<float>(scale * g[i]);
-    }
-    if (hipMalloc(&op->th, win.size() * sizeof(float)) != hipSuccess)
-      return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
-    PSTD_HIP(hipMemcpy(op->th, win.data(), win.size() * sizeof(float), hipMemcpyHostToDevice));
-    op->th_len = len;
-    for (int i = 0; i < 4; ++i) op->thw[i] = static_cast<float>(w[i]);
+  const bool formed = M > kThRowsMin && M <= kThRowsMax && op->Kp <= kThColsMax &&
+                      toeplitz_hankel(m.data(), M, K, kThTol, &f, &g, w, &resid);
+  if (formed) {
+    host.resize(4 * cnt, 0);
+    for (int i = 0; i < M; ++i)
+      for (int k = 0; k < K; ++k) {
+        const float wr = static_cast<float>(i == 0 ? w[0] : i == M - 1 ? w[1] : 1.0);
+        const float wc = static_cast<float>(k == 0 ? w[2] : k == K - 1 ? w[3] : 1.0);
+        const float v = wr * wc * (static_cast<float>(scale * f[i - k + K - 1]) + static_cast<float>(scale * g[i + k]));
+        const uint16_t hi = bf16_rne(v);
+        uint16_t* at = host.data() + 2 * cnt + split_fragment_at(op->Kp, i, k);
+        at[0] = hi;
+        at[512] = bf16_rne(v - bf16_to_float(hi));
+      }
   }
+  if (hipMalloc(&op->data, host.size() * 2) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
+  PSTD_HIP(hipMemcpy(op->data, host.data(), host.size() * 2, hipMemcpyHostToDevice));
+  op->frag = static_cast<uint16_t*>(op->data) + (formed ? 2 * cnt : 0);
   return PSTD_OK;
 }
 
@@ -128,15 +134,12 @@ void free_plan(pstd_plan_s* P) {
   for (int a = 0; a < 3; ++a) {
     if (P->G[a].data) (void)hipFree(P->G[a].data);
     if (P->G[a].dataT) (void)hipFree(P->G[a].dataT);
-    if (P->G[a].th) (void)hipFree(P->G[a].th);
     if (P->D[a].data) (void)hipFree(P->D[a].data);
     if (P->D[a].dataT) (void)hipFree(P->D[a].dataT);
-    if (P->D[a].th) (void)hipFree(P->D[a].th);
     fft_axis_free(&P->fft[a]);
     for (int k = 0; k < 4; ++k) {
       if (P->R[a][k].data) (void)hipFree(P->R[a][k].data);
       if (P->R[a][k].dataT) (void)hipFree(P->R[a][k].dataT);
-      if (P->R[a][k].th) (void)hipFree(P->R[a][k].th);
     }
   }
   if (P->c2map) (void)hipFree(P->c2map);
@@ -220,7 +223,6 @@ bool contract_args(const pstd_plan_s* P, const DevOperator& op, int a, const voi
   ContractArgs& c = *out;
   c = ContractArgs{};
   c.A = op.data;
-  c.A_lo = nullptr;
   c.frag = op.frag;
   c.lda = op.Kp;
   c.M = op.M;
@@ -255,12 +257,7 @@ hipError_t contract(const pstd_plan_s* P, const DevOperator& op, int a, const vo
   const bool contiguous = contract_args(P, op, a, X, Y, alpha, beta, scale, &c);
   if (P->prec == PSTD_FP64) return launch_contract_fp64(c, contiguous, s);
   if (P->prec == PSTD_FP32) return launch_contract_fp32(c, contiguous, s);
-  c.A_lo = static_cast<const uint16_t*>(op.data) + static_cast<size_t>(op.Mp) * op.Kp;
-  if (op.th && P->use_th) {
-    c.th = op.th;
-    c.th_len = op.th_len;
-    for (int i = 0; i < 4; ++i) c.thw[i] = op.thw[i];
-  }
+  if (P->stored) c.frag = op.data;
   return launch_contract_split(c, contiguous, s);
 }
 
@@ -670,7 +667,7 @@ int pstd_plan_set_path(pstd_plan P, int32_t path) {
     P->path = old;
     return pst;
   }
-  P->use_th = path != PSTD_PATH_STORED;
+  P->stored = path == PSTD_PATH_STORED;
   P->fft_pow2 = path != PSTD_PATH_FFT_GENERIC;
   drop_graphs(P);  // captured graphs may belong to the other path
   return PSTD_OK;
@@ -885,9 +882,9 @@ int pstd_plan_get_operator(pstd_plan P, int32_t axis, int32_t which, double* out
     PSTD_HIP(hipMemcpy(h.data(), op.data, cnt * 4, hipMemcpyDeviceToHost));
     for (int i = 0; i < op.M; ++i)
       for (int k = 0; k < op.K; ++k) {
-        const size_t a = static_cast<size_t>(i) * op.Kp + k;
+        const size_t a = split_fragment_at(op.Kp, i, k);
         out[static_cast<size_t>(i) * op.K + k] =
-            static_cast<double>(bf16_to_float(h[a])) + static_cast<double>(bf16_to_float(h[cnt + a]));
+            static_cast<double>(bf16_to_float(h[a])) + static_cast<double>(bf16_to_float(h[a + 512]));
       }
   }
   return PSTD_OK;

@@ -87,24 +87,19 @@ constexpr int kColPad = 64;
 struct DevOperator {
   int M = 0, K = 0;        // logical size
   int Mp = 0, Kp = 0;      // padded size (row stride = Kp)
-  void* data = nullptr;    // FP64: double[Mp*Kp]; FP32: float[Mp*Kp]; SPLIT: bf16 hi[Mp*Kp] then lo[Mp*Kp]
+  void* data = nullptr;    // FP64: double[Mp*Kp]; FP32: float[Mp*Kp]; SPLIT: bf16 hi and lo parts in fragment order
   void* dataT = nullptr;   // 1D plans: transposed copy, Kp x Mp (row stride Mp)
-  // FP64 / FP32: data in MFMA fragment order (in data's allocation): for every 16 rows and chunk of 16 columns the 64
-  // lanes' four values, lane l those of row l % 16, columns 4 e + l / 16 for e < 4
+  // The operator in MFMA fragment order, in data's allocation.  FP64 / FP32: for every 16 rows and chunk of 16 columns the
+  // 64 lanes' four values, lane l those of row l % 16, columns 4 e + l / 16 for e < 4.  SPLIT: for every 32 rows and chunk
+  // of 16 columns the hi and then the lo parts, lane l those of row l % 32, columns 8 (l / 32) + e for e < 8; data itself,
+  // or of operators of kThRowsMin..kThRowsMax rows the FP32 sums of their Toeplitz and Hankel parts.
   void* frag = nullptr;
-  // SPLIT only, operators with a Toeplitz-plus-Hankel form and kThRowsMin < M <= kThRowsMax, Kp <= kThColsMax:
-  // FP32 f and g windows of th_len values each (see kernels_split.hip) and the end weights
-  // {first row, last row, first column, last column}
-  float* th = nullptr;
-  int th_len = 0;
-  float thw[4] = {1.f, 1.f, 1.f, 1.f};
 };
 
-// Operators whose slices the split-bf16 contraction forms from their Toeplitz and Hankel parts.
+// Split-bf16 operators whose frag holds the FP32 sums of their Toeplitz and Hankel parts: rows in
+// (kThRowsMin, kThRowsMax], padded columns up to kThColsMax.
 constexpr int kThRowsMin = 192, kThRowsMax = 384, kThColsMax = 512;
-constexpr int kThLen = kThRowsMax + kThColsMax + 8;   // upper bound of th_len
-// Largest entry error of the form, relative to max|A|: far below FP32 rounding, so the slices formed on
-// the chip equal the stored operator to the rounding of their FP32 sum.
+// Largest entry error of that form, relative to max|A|: far below FP32 rounding.
 constexpr double kThTol = 1e-9;
 
 // A (R x C, row-major, FP64) = diag(wr) (F + H) diag(wc) with F[r][c] = f[r - c + C - 1],
@@ -114,9 +109,8 @@ bool toeplitz_hankel(const double* A, int R, int C, double tol, std::vector<doub
                      double w[4], double* resid);
 
 struct ContractArgs {
-  const void* A;        // operator, row-major, row stride lda, zero padded
-  const void* A_lo;     // SPLIT_BF16 only: low part
-  const void* frag;     // FP64 / FP32: DevOperator::frag
+  const void* A;        // FP64 / FP32: operator, row-major, row stride lda, zero padded
+  const void* frag;     // the operator in fragment order (DevOperator)
   int lda;
   int M, K;             // output length and input length along the contracted axis
   const void* X;        // input field
@@ -128,9 +122,6 @@ struct ContractArgs {
   float alpha, beta;    // Y = beta*Y + alpha * scale * (A X)
   double alpha_d, beta_d;
   const void* scale;    // optional per-point factor with Y's layout (c0(x)^2 map, state dtype), may be null
-  const float* th;      // SPLIT_BF16: Toeplitz/Hankel windows of the operator (null: read A and A_lo)
-  int th_len;
-  float thw[4];
 };
 
 // Launchers (kernels_*.hip).  contiguous = the contracted axis is the last (unit-stride) one.
@@ -357,7 +348,7 @@ struct pstd_plan_s {
   void* line_work = nullptr;   // 1D plans of 129 .. kLineMaxNodes nodes: workspace of launch_step1d (owned)
   unsigned line_spins = pstd::kLineSpins;
   int path = 0;                // PSTD_PATH_* (0 = automatic)
-  bool use_th = true;          // split-bf16 contractions form Toeplitz-plus-Hankel operators on the chip
+  bool stored = false;         // path "stored": split-bf16 contractions with the operators as rounded from FP64
   bool fft_pow2 = true;        // FP32 power-of-two FFT axes use fft_pow2_kernel
   // captured step graphs: slot 0 holds a full chunk of steps, slot 1 the last other length used
   struct StepGraph {
