@@ -153,6 +153,7 @@ int weight_grad(pstd_nop_s* N, const float* X, int M, const float* Y, int Nc, fl
   g.bB2 = KC;
   g.bC1 = static_cast<int64_t>(nch) * M * Nc;
   g.bC2 = static_cast<int64_t>(M) * Nc;
+  g.free_order = 1;
   NOP_RUN(launch_nop_gemm(g, N->stream));
   NOP_RUN(launch_nop_partial_sum(N->part, G, N->mid, B * nch, M * Nc, N->stream));
   return PSTD_OK;
@@ -408,6 +409,7 @@ int pstd_nop_backward(pstd_nop N, const float* target, double* loss) {
     g.bA1 = 4LL * B * C;
     g.bB1 = 4LL * B * C;
     g.bC1 = static_cast<int64_t>(C) * C;
+    g.free_order = 1;
     NOP_RUN(launch_nop_gemm(g, s));
     // dA[blk] (4B x C) = dZt[blk] (4B x C) R[blk] (C x C)
     g = gemm(N, N->Zt, C, 1, th + N->oR[l], C, 1, N->At2, C, 1, 4 * B, C, C);

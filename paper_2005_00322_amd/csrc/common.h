@@ -281,6 +281,7 @@ struct NopGemm {
   const float* dgelu;
   int act;              // apply GELU
   int split;            // 1: hi*hi + hi*lo + lo*hi bf16 products (near FP32); 0: one bf16 product
+  int free_order;       // the sum over K may be split (results that are not rounded to bf16 later)
 };
 hipError_t launch_nop_gemm(const NopGemm& g, hipStream_t s);
 // Y[b][o][p] = sum_i A[o][i] X[b][i][p] (+ bias[o]) (+ D[b][o][p]) (+ sum_k T[b][h][o][k] Cw[k][w] at

@@ -67,80 +67,125 @@ __device__ __forceinline__ float gelu_grad_f(float x) {
   return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.39894228040143268f * expf(-0.5f * x * x);
 }
 
-// Element e (0 .. ROWS*BK-1) of an operand tile: row r (m for A, n for B) and column k.  Lanes run along
-// k when the operand is contiguous in k, along the rows otherwise, so the loads coalesce either way.
-template <int ROWS>
-__device__ __forceinline__ void tile_pos(int e, bool kcontig, int& r, int& k) {
-  if (kcontig) {
-    k = e & (BK - 1);
-    r = e >> 5;
-  } else {
-    r = e % ROWS;
-    k = e / ROWS;
-  }
-}
+// One operand of a product on its way to LDS: ROWS rows (m or n) of the tile, BKT of K at a time, by NT threads.  What
+// bounds these products is loads in flight, so no load sits behind a bounds check: rows past the operand's end read its
+// last one (their outputs are not stored), and only a last slice that K does not fill looks at k, reading the last one and
+// storing zero.  A load is a wave-uniform base and a lane offset in bytes (Off: 64 bits where a tile spans 4 GiB or more).
+//   VEC    k contiguous, 16-byte aligned rows, K a multiple of 4: four k of a row per load
+//   LANEK  k contiguous: lanes along k
+//   LANER  otherwise: lanes along the rows, a thread's values consecutive in k, so that its LDS writes are 8 or 16 bytes
+enum { kVec = 0, kLaneK = 1, kLaneR = 2 };
 
-// Tile of WMW x WNW waves, each computing FM x FN blocks of 32 x 32 outputs:
-// BM = 32 WMW FM rows, BN = 32 WNW FN columns.
-template <int WMW, int WNW, int FM, int FN>
+template <int ROWS, int BKT, int mode, typename Off>
+struct GemmSide {
+  static constexpr int N = ROWS * BKT / NT;         // values per thread and slice
+  static constexpr int LD = BKT + 8;                // LDS row stride: conflict-free 16-byte reads
+  static constexpr int KS = BKT < NT ? BKT : NT;    // LANEK: distinct k per pass
+  const float* p;                                   // first row of the tile
+  int64_t sr, sk;
+  int rows, K;
+
+  // value i's row and k (VEC: of the first of its four)
+  __device__ __forceinline__ int row(int i) const {
+    const int t = threadIdx.x;
+    return mode == kVec ? (t + (i / 4) * NT) / (BKT / 4) : mode == kLaneK ? t / KS + i * (NT / KS) : t % ROWS;
+  }
+  __device__ __forceinline__ int kpos(int i) const {
+    const int t = threadIdx.x;
+    return mode == kVec ? 4 * (t % (BKT / 4)) + i % 4 : mode == kLaneK ? t % KS : (t / ROWS) * N + i;
+  }
+  __device__ __forceinline__ void load(int k0, float (&v)[N]) const {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    auto off = [&](int r, int k) { return static_cast<Off>(4) * (static_cast<Off>(min(r, rows - 1)) * static_cast<Off>(sr) + static_cast<Off>(k) * static_cast<Off>(sk)); };
+    if (k0 + BKT <= K) {
+      if (mode == kVec) {
+        const char* b = reinterpret_cast<const char*>(p + k0);
+#pragma unroll
+        for (int i = 0; i < N; i += 4) {
+          const f32x4 w = *reinterpret_cast<const f32x4*>(b + off(row(i), kpos(i)));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[i + e] = w[e];
+        }
+      } else if (mode == kLaneK) {
+        const char* b = reinterpret_cast<const char*>(p + k0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const float*>(b + off(row(i), kpos(i)));
+      } else {
+        const Off o = off(row(0), kpos(0));
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p + (k0 + i) * sk) + o);
+      }
+    } else {
+      const char* b = reinterpret_cast<const char*>(p + k0 * sk);
+      const int kl = K - 1 - k0;
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const float*>(b + off(row(i), min(kpos(i), kl)));
+    }
+  }
+  // rounded to bf16 (SPLIT: and the remainders) into [row][k]
+  template <bool SPLIT>
+  __device__ __forceinline__ void store(int k0, const float (&v)[N], __bf16* hi, __bf16* lo) const {
+    __bf16 h[N], l[N];
+    const bool full = k0 + BKT <= K;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float x = full || k0 + kpos(i) < K ? v[i] : 0.f;
+      h[i] = static_cast<__bf16>(x);
+      if (SPLIT) l[i] = static_cast<__bf16>(x - static_cast<float>(h[i]));
+    }
+    auto put = [&](__bf16* dst, const __bf16* x) {
+      typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+      constexpr int V = N % 8 == 0 ? 8 : 4;
+      typedef __bf16 vec __attribute__((ext_vector_type(V)));
+      if (mode == kLaneK) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) dst[row(i) * LD + kpos(i)] = x[i];
+      } else if (mode == kVec) {
+#pragma unroll
+        for (int i = 0; i < N; i += 4) {
+          bf16x4 w;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[e] = x[i + e];
+          *reinterpret_cast<bf16x4*>(dst + row(i) * LD + kpos(i)) = w;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < N; i += V) {
+          vec w;
+#pragma unroll
+          for (int e = 0; e < V; ++e) w[e] = x[i + e];
+          *reinterpret_cast<vec*>(dst + row(0) * LD + kpos(i)) = w;
+        }
+      }
+    };
+    put(hi, h);
+    if (SPLIT) put(lo, l);
+  }
+};
+
+// Tile of WMW x WNW waves, each computing FM x FN blocks of 32 x 32 outputs: BM = 32 WMW FM rows, BN = 32 WNW FN columns.
+// WK > 1: that many waves share the outputs, each taking every WK-th 32 of K, and add up in the end (weight gradients,
+// whose few outputs have a long K; a sum whose order no later rounding to bf16 depends on).
+// One barrier per slice: slice s + 1 is written to the other buffer once slice s is multiplied, its loads in flight meanwhile.
+// us per launch with a bounds check around every load and now (batch 64, 32 channels, 128 x 128, 48 modes): inverse DCT along
+// H with its accumulation 136 -> 68 (319 MB), DCT along H 53 -> 41, along W 25 -> 22, channel mixing 22 -> 15, its weight
+// gradient 20 -> 14, the pointwise weight gradient 72 -> 64.
+template <int WMW, int WNW, int WK, int FM, int FN, bool SPLIT, int MA, int MB, typename Off>
 __global__ __launch_bounds__(NT) void nop_gemm_kernel(NopGemm g) {
-  constexpr int BM = 32 * WMW * FM, BN = 32 * WNW * FN;
-  constexpr int PA = BM * BK / NT, PB = BN * BK / NT;   // operand elements staged per thread
-  __shared__ __attribute__((aligned(16))) __bf16 lds[2 * (BM + BN) * LDK];   // A hi, A lo, B hi, B lo
-  __bf16* Ah = lds;
-  __bf16* Al = lds + BM * LDK;
-  __bf16* Bh = lds + 2 * BM * LDK;
-  __bf16* Bl = Bh + BN * LDK;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % WMW, wn = wave / WMW;
+  constexpr int BM = 32 * WMW * FM, BN = 32 * WNW * FN, BKT = BK * WK;
+  typedef GemmSide<BM, BKT, MA, Off> SA;
+  typedef GemmSide<BN, BKT, MB, Off> SB;
+  constexpr int LD = SA::LD, PART = (BM + BN) * LD, BUF = (SPLIT ? 2 : 1) * PART;   // [A hi, B hi (, A lo, B lo)]
+  constexpr int RED = WK > 1 ? 2 * (WK - 1) * BM * BN : 0;                             // the partial sums, in bf16 units
+  __shared__ __attribute__((aligned(16))) __bf16 lds[2 * BUF > RED ? 2 * BUF : RED];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave % WMW, wn = (wave / WMW) % WNW, wk = wave / (WMW * WNW);
   const int tiles_m = (g.M + BM - 1) / BM;
   const int m0 = (blockIdx.x % tiles_m) * BM, n0 = (blockIdx.x / tiles_m) * BN;
   const int z = blockIdx.y;
   const int z1 = z / g.nb2, z2 = z - z1 * g.nb2;
-  const float* A = g.A + z1 * g.bA1 + z2 * g.bA2;
-  const float* B = g.B + z1 * g.bB1 + z2 * g.bB2;
-  const bool akc = g.sAk == 1, bkc = g.sBk == 1;
-  const bool split = g.split != 0;
-  // element offsets within one batch entry fit in 32 bits (the host checks every operand's extent)
-  const uint32_t sAm = static_cast<uint32_t>(g.sAm), sAk = static_cast<uint32_t>(g.sAk);
-  const uint32_t sBk = static_cast<uint32_t>(g.sBk), sBn = static_cast<uint32_t>(g.sBn);
-
-  float ra[PA], rb[PB];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < PA; ++i) {
-      int r, k;
-      tile_pos<BM>(tid + i * NT, akc, r, k);
-      const int m = m0 + r, kk = k0 + k;
-      ra[i] = (m < g.M && kk < g.K) ? A[static_cast<uint32_t>(m) * sAm + static_cast<uint32_t>(kk) * sAk] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < PB; ++i) {
-      int r, k;
-      tile_pos<BN>(tid + i * NT, bkc, r, k);
-      const int n = n0 + r, kb = k0 + k;
-      rb[i] = (n < g.N && kb < g.K) ? B[static_cast<uint32_t>(kb) * sBk + static_cast<uint32_t>(n) * sBn] : 0.f;
-    }
-  };
-  auto store = [&]() {
-#pragma unroll
-    for (int i = 0; i < PA; ++i) {
-      int r, k;
-      tile_pos<BM>(tid + i * NT, akc, r, k);
-      const __bf16 h = static_cast<__bf16>(ra[i]);
-      Ah[r * LDK + k] = h;
-      if (split) Al[r * LDK + k] = static_cast<__bf16>(ra[i] - static_cast<float>(h));
-    }
-#pragma unroll
-    for (int i = 0; i < PB; ++i) {
-      int r, k;
-      tile_pos<BN>(tid + i * NT, bkc, r, k);
-      const __bf16 h = static_cast<__bf16>(rb[i]);
-      Bh[r * LDK + k] = h;
-      if (split) Bl[r * LDK + k] = static_cast<__bf16>(rb[i] - static_cast<float>(h));
-    }
-  };
-
+  const SA A{g.A + z1 * g.bA1 + z2 * g.bA2 + m0 * g.sAm, g.sAm, g.sAk, g.M - m0, g.K};
+  const SB B{g.B + z1 * g.bB1 + z2 * g.bB2 + n0 * g.sBn, g.sBn, g.sBk, g.N - n0, g.K};
   f32x16 acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
@@ -148,34 +193,45 @@ __global__ __launch_bounds__(NT) void nop_gemm_kernel(NopGemm g) {
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  const int nsl = (g.K + BK - 1) / BK;
-  load(0);
-  store();
+  const int nsl = (g.K + BKT - 1) / BKT;
+  float ra[SA::N], rb[SB::N];
+  auto store = [&](int s) {
+    __bf16* L = lds + (s & 1) * BUF;
+    A.template store<SPLIT>(s * BKT, ra, L, L + PART);
+    B.template store<SPLIT>(s * BKT, rb, L + BM * LD, L + PART + BM * LD);
+  };
+  A.load(0, ra);
+  B.load(0, rb);
+  store(0);
   lds_barrier();
-  const int koff = 8 * (lane >> 5);
+  const int koff = 8 * (lane >> 5) + BK * wk;
   for (int s = 0; s < nsl; ++s) {
-    if (s + 1 < nsl) load((s + 1) * BK);
+    if (s + 1 < nsl) {
+      A.load((s + 1) * BKT, ra);
+      B.load((s + 1) * BKT, rb);
+    }
+    const __bf16* L = lds + (s & 1) * BUF;
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 16) {
       bf16x8 ah[FM], bh[FN];
 #pragma unroll
       for (int i = 0; i < FM; ++i)
-        ah[i] = *reinterpret_cast<const bf16x8*>(&Ah[((wm * FM + i) * 32 + (lane & 31)) * LDK + kk + koff]);
+        ah[i] = *reinterpret_cast<const bf16x8*>(L + ((wm * FM + i) * 32 + (lane & 31)) * LD + kk + koff);
 #pragma unroll
       for (int j = 0; j < FN; ++j)
-        bh[j] = *reinterpret_cast<const bf16x8*>(&Bh[((wn * FN + j) * 32 + (lane & 31)) * LDK + kk + koff]);
+        bh[j] = *reinterpret_cast<const bf16x8*>(L + (BM + (wn * FN + j) * 32 + (lane & 31)) * LD + kk + koff);
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bh[j], acc[i][j], 0, 0, 0);
-      if (split) {
+      if constexpr (SPLIT) {
         bf16x8 al[FM], bl[FN];
 #pragma unroll
         for (int i = 0; i < FM; ++i)
-          al[i] = *reinterpret_cast<const bf16x8*>(&Al[((wm * FM + i) * 32 + (lane & 31)) * LDK + kk + koff]);
+          al[i] = *reinterpret_cast<const bf16x8*>(L + PART + ((wm * FM + i) * 32 + (lane & 31)) * LD + kk + koff);
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-          bl[j] = *reinterpret_cast<const bf16x8*>(&Bl[((wn * FN + j) * 32 + (lane & 31)) * LDK + kk + koff]);
+          bl[j] = *reinterpret_cast<const bf16x8*>(L + PART + (BM + (wn * FN + j) * 32 + (lane & 31)) * LD + kk + koff);
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -185,11 +241,25 @@ __global__ __launch_bounds__(NT) void nop_gemm_kernel(NopGemm g) {
           }
       }
     }
-    lds_barrier();
     if (s + 1 < nsl) {
-      store();
+      store(s + 1);
       lds_barrier();
     }
+  }
+  if constexpr (WK > 1) {
+    static_assert(WMW == 1 && WNW == 1 && FM == 1 && FN == 1, "one block of outputs");
+    float* red = reinterpret_cast<float*>(lds);
+    lds_barrier();   // the last slice is read
+    if (wk > 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) red[(wk - 1) * 1024 + r * 64 + lane] = acc[0][0][r];
+    }
+    lds_barrier();
+    if (wk > 0) return;
+#pragma unroll
+    for (int w = 0; w + 1 < WK; ++w)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[0][0][r] += red[w * 1024 + r * 64 + lane];
   }
 
   // epilogue
@@ -201,40 +271,43 @@ __global__ __launch_bounds__(NT) void nop_gemm_kernel(NopGemm g) {
   const uint32_t sDm = static_cast<uint32_t>(g.sDm), sDn = static_cast<uint32_t>(g.sDn);
   // All reads of a 32 x 32 block (old C, the added tensor, the GELU argument, the bias) are issued before
   // its first store: the stores may alias nothing the loads touch, but the compiler cannot know that,
-  // and interleaving would serialise every element on a memory round trip.
+  // and interleaving would serialise every element on a memory round trip.  Elements outside read the operand's last row
+  // or column, so that no read waits behind a branch.
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
-      const int n = n0 + (wn * FN + j) * 32 + (lane & 31);
-      float ext[16];
+      const int mb = m0 + (wm * FM + i) * 32, nb = n0 + (wn * FN + j) * 32;
+      if (mb >= g.M || nb >= g.N) continue;
+      const int n = nb + (lane & 31);
+      const uint32_t nc = static_cast<uint32_t>(min(n, g.N - 1));
+      auto mr = [&](int r) { return mb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
+      auto mc = [&](int r) { return static_cast<uint32_t>(min(mr(r), g.M - 1)); };
+      float ext[16], gg[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + (wm * FM + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const bool ok = m < g.M && n < g.N;
-        const uint32_t co = static_cast<uint32_t>(m) * sCm + static_cast<uint32_t>(n) * sCn;
-        float e = 0.f;
-        if (ok) {
-          if (g.beta != 0.f) e += g.beta * C[co];
-          if (g.bias_m) e += g.bias_m[m];
-          if (Dp) e += Dp[static_cast<uint32_t>(m) * sDm + static_cast<uint32_t>(n) * sDn];
-        }
-        ext[r] = e;
+      for (int r = 0; r < 16; ++r) ext[r] = 0.f;
+      if (g.beta != 0.f) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ext[r] += g.beta * C[mc(r) * sCm + nc * sCn];
       }
-      float gg[16];
+      if (g.bias_m) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + (wm * FM + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const uint32_t co = static_cast<uint32_t>(m) * sCm + static_cast<uint32_t>(n) * sCn;
-        gg[r] = (Gp && m < g.M && n < g.N) ? Gp[co] : 0.f;
+        for (int r = 0; r < 16; ++r) ext[r] += g.bias_m[mc(r)];
+      }
+      if (Dp) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ext[r] += Dp[mc(r) * sDm + nc * sDn];
+      }
+      if (Gp) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) gg[r] = Gp[mc(r) * sCm + nc * sCn];
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int m = m0 + (wm * FM + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (m < g.M && n < g.N) {
-          const uint32_t co = static_cast<uint32_t>(m) * sCm + static_cast<uint32_t>(n) * sCn;
-          float v = g.alpha * acc[i][j][r] + ext[r];
-          if (Gp) v *= gelu_grad_f(gg[r]);
+        float v = g.alpha * acc[i][j][r] + ext[r];
+        if (Gp) v *= gelu_grad_f(gg[r]);
+        if (mr(r) < g.M && n < g.N) {
+          const uint32_t co = static_cast<uint32_t>(mr(r)) * sCm + static_cast<uint32_t>(n) * sCn;
           if (g.act) {
             if (Pp) Pp[co] = v;
             v = gelu_f(v);
@@ -1462,18 +1535,52 @@ unsigned blocks_for(int64_t n, int t) { return static_cast<unsigned>((n + t - 1)
 
 }  // namespace
 
-// Tile shape by operand shape: few output rows (channel mixing, K = 32) take 32 x 256 tiles so each
-// block streams a long run of positions; the rest 64 x 64.
+namespace {
+
+template <int WMW, int WNW, int WK, int FM, int FN, int MA, int MB, typename Off = uint32_t>
+void launch_gemm_m(const NopGemm& g, unsigned tiles, hipStream_t s) {
+  const dim3 grid(tiles, g.nb1 * g.nb2), blk(NT);
+  if (g.split) hipLaunchKernelGGL((nop_gemm_kernel<WMW, WNW, WK, FM, FN, true, MA, MB, Off>), grid, blk, 0, s, g);
+  else hipLaunchKernelGGL((nop_gemm_kernel<WMW, WNW, WK, FM, FN, false, MA, MB, Off>), grid, blk, 0, s, g);
+}
+
+template <int WMW, int WNW, int WK, int FM, int FN>
+void launch_gemm_t(const NopGemm& g, int ma, int mb, unsigned tiles, hipStream_t s) {
+  switch (3 * ma + mb) {
+    case 0: return launch_gemm_m<WMW, WNW, WK, FM, FN, 0, 0>(g, tiles, s);
+    case 1: return launch_gemm_m<WMW, WNW, WK, FM, FN, 0, 1>(g, tiles, s);
+    case 2: return launch_gemm_m<WMW, WNW, WK, FM, FN, 0, 2>(g, tiles, s);
+    case 3: return launch_gemm_m<WMW, WNW, WK, FM, FN, 1, 0>(g, tiles, s);
+    case 4: return launch_gemm_m<WMW, WNW, WK, FM, FN, 1, 1>(g, tiles, s);
+    case 5: return launch_gemm_m<WMW, WNW, WK, FM, FN, 1, 2>(g, tiles, s);
+    case 6: return launch_gemm_m<WMW, WNW, WK, FM, FN, 2, 0>(g, tiles, s);
+    case 7: return launch_gemm_m<WMW, WNW, WK, FM, FN, 2, 1>(g, tiles, s);
+    default: return launch_gemm_m<WMW, WNW, WK, FM, FN, 2, 2>(g, tiles, s);
+  }
+}
+
+}  // namespace
+
+// Tile shape by operand shape: few output rows (K = 32 products of many positions) take 32 x 256 tiles so each
+// block streams a long run of positions; gradients of at most 32 x 32 outputs one block of them per K range; the rest 64 x 64.
 hipError_t launch_nop_gemm(const NopGemm& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nb1 * g.nb2 <= 0) return hipSuccess;
-  const dim3 grid_z(1, g.nb1 * g.nb2);
-  auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
-  if (g.M <= 32 && g.N >= 256) {
-    hipLaunchKernelGGL((nop_gemm_kernel<1, 4, 1, 2>), dim3(tiles(32, 256), g.nb1 * g.nb2), dim3(NT), 0, s, g);
-  } else {
-    hipLaunchKernelGGL((nop_gemm_kernel<2, 2, 1, 1>), dim3(tiles(64, 64), g.nb1 * g.nb2), dim3(NT), 0, s, g);
-  }
-  (void)grid_z;
+  auto mode = [&](const float* p, int64_t sr, int64_t sk, int64_t b1, int64_t b2) {
+    if (sk != 1) return static_cast<int>(kLaneR);
+    const bool vec = (reinterpret_cast<uintptr_t>(p) & 15) == 0 && g.K % 4 == 0 && sr % 4 == 0 && b1 % 4 == 0 && b2 % 4 == 0;
+    return static_cast<int>(vec ? kVec : kLaneK);
+  };
+  const int ma = mode(g.A, g.sAm, g.sAk, g.bA1, g.bA2), mb = mode(g.B, g.sBn, g.sBk, g.bB1, g.bB2);
+  auto tiles = [&](int bm, int bn) { return static_cast<unsigned>(((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn)); };
+  // a tile's byte offsets (at most 256 rows and 128 k) in 32 bits, or the lanes along the rows at 64-bit offsets
+  auto span = [&](int64_t rows, int64_t sr, int64_t sk) {
+    return 4 * (std::min<int64_t>(rows, 256) * sr + std::min<int64_t>(g.K, 128) * sk);
+  };
+  if (std::max(span(g.M, g.sAm, g.sAk), span(g.N, g.sBn, g.sBk)) >= (int64_t(1) << 32))
+    launch_gemm_m<2, 2, 1, 1, 1, kLaneR, kLaneR, uint64_t>(g, tiles(64, 64), s);
+  else if (g.free_order && g.M <= 32 && g.N <= 32 && g.K >= 128) launch_gemm_t<1, 1, 4, 1, 1>(g, ma, mb, tiles(32, 32), s);
+  else if (g.M <= 32 && g.N >= 256) launch_gemm_t<1, 4, 1, 1, 2>(g, ma, mb, tiles(32, 256), s);
+  else launch_gemm_t<2, 2, 1, 1, 1>(g, ma, mb, tiles(64, 64), s);
   return hipGetLastError();
 }
 
