@@ -22,7 +22,7 @@ struct pstd_nop_s {
   void *dct2_img = nullptr, *idct_img = nullptr;   // bf16 LDS images of the tables
   float* F = nullptr;
   std::vector<float*> V, PRE, AT;
-  float *qpre = nullptr, *q = nullptr, *out = nullptr;
+  float *qpre = nullptr, *out = nullptr;
   float *Y1 = nullptr, *Ahat = nullptr, *Zt = nullptr, *At2 = nullptr, *T = nullptr;
   float *dv = nullptr, *dvn = nullptr, *dpre = nullptr, *dq = nullptr, *dout = nullptr, *part = nullptr;
   double *terms = nullptr, *mid = nullptr;
@@ -224,7 +224,6 @@ int pstd_nop_create(const pstd_nop_config* cfg, void* hip_stream, pstd_nop* out)
     A(&N->AT[l], spec);
   }
   A(&N->qpre, B * Hp * P);
-  A(&N->q, B * Hp * P);
   A(&N->out, B * P);
   A(&N->Y1, ysz);
   A(&N->Ahat, spec);
@@ -338,7 +337,7 @@ int forward_impl(pstd_nop N, const float* p0, const float* c0, float* out, int32
   }
   // projection: out = Q2 GELU(Q1 v + q1b) + q2b
   NOP_RUN(launch_nop_project(th + N->oQ1, th + N->oq1b, th + N->oQ2, th + N->oq2b, vin, N->out,
-                             keep ? N->qpre : nullptr, keep ? N->q : nullptr, C, Hp, P, B, c.split != 0, half, s));
+                             keep ? N->qpre : nullptr, C, Hp, P, B, c.split != 0, half, s));
   if (out != N->out)
     PSTD_HIP(hipMemcpyAsync(out, N->out, static_cast<size_t>(B) * P * sizeof(float), hipMemcpyDeviceToDevice, s));
   N->last_batch = B;
@@ -371,21 +370,14 @@ int pstd_nop_backward(pstd_nop N, const float* target, double* loss) {
   NOP_RUN(launch_nop_loss(N->out, target, N->terms, N->dout, B, P, s));
   // output layer
   NOP_RUN(launch_nop_rowsum(N->dout, gr + N->oq2b, N->mid, B, 1, P, s));
-  int st = weight_grad(N, N->dout, 1, N->q, Hp, gr + N->oQ2, B);
-  if (st != PSTD_OK) return st;
-  // dq = (Q2 outer dout) * GELU'(qpre)
-  NopGemm g = gemm(N, th + N->oQ2, 1, 1, N->dout, P, 1, N->dq, P, 1, Hp, static_cast<int>(P), 1);
-  g.nb1 = B;
-  g.bB1 = P;
-  g.bC1 = Hp * P;
-  g.dgelu = N->qpre;
-  NOP_RUN(launch_nop_gemm(g, s));
-  NOP_RUN(launch_nop_rowsum(N->dq, gr + N->oq1b, N->mid, B, Hp, P, s));
-  st = weight_grad(N, N->dq, Hp, N->V[c.layers], C, gr + N->oQ1, B);
+  // dq = (Q2 outer dout) * GELU'(qpre), with the gradients of q1b and Q2 (one after the other in theta)
+  NOP_RUN(launch_nop_hidden_bwd(th + N->oQ2, N->qpre, N->dout, N->dq, gr + N->oq1b, N->mid, B, Hp, P, c.split != 0, s));
+  int st = weight_grad(N, N->dq, Hp, N->V[c.layers], C, gr + N->oQ1, B);
   if (st != PSTD_OK) return st;
   // dv = Q1^T dq
   NOP_RUN(launch_nop_mix(th + N->oQ1, true, N->dq, N->dv, nullptr, nullptr, nullptr, nullptr, nullptr, 0, C, Hp, H, W,
                          B, false, c.split != 0, 0, s));
+  NopGemm g;
   for (int l = c.layers - 1; l >= 0; --l) {
     NOP_RUN(launch_nop_gelu_bwd(N->dv, N->PRE[l], N->dpre, gr + N->ob[l], N->mid, B, C, P, s));
     st = weight_grad(N, N->dpre, C, N->V[l], C, gr + N->oW[l], B);

@@ -263,10 +263,8 @@ hipError_t launch_fft_pow2(const FftArgs& a, hipStream_t s);
 hipError_t launch_fft_pow2_multi(const FftArgs* a, int count, hipStream_t s);
 
 // ---- neural-operator surrogate (kernels_nop.hip, capi_nop.hip) ----------------------------------------
-// C[z] = alpha A[z] B[z] (+ beta C[z]) (+ bias_m[m]) (+ D[z]) (* GELU'(dgelu[z])), then with act set
-// pre[z] = value (if pre is given) and C[z] = GELU(value).  A is M x K, B is K x N, C is M x N, all FP32
-// with element strides; the batch index z = z1 nb2 + z2 adds z1 b*1 + z2 b*2 to each operand.  pre and
-// dgelu use C's strides.
+// C[z] = alpha A[z] B[z] (+ beta C[z]).  A is M x K, B is K x N, C is M x N, all FP32 with element strides; the batch
+// index z = z1 nb2 + z2 adds z1 b*1 + z2 b*2 to each operand.
 struct NopGemm {
   const float* A; const float* B; float* C;
   int M, N, K;
@@ -274,12 +272,6 @@ struct NopGemm {
   int nb1, nb2;
   int64_t bA1, bA2, bB1, bB2, bC1, bC2;
   float alpha, beta;
-  const float* bias_m;
-  const float* add;
-  int64_t sDm, sDn, bD1, bD2;
-  float* pre;
-  const float* dgelu;
-  int act;              // apply GELU
   int split;            // 1: hi*hi + hi*lo + lo*hi bf16 products (near FP32); 0: one bf16 product
   int free_order;       // the sum over K may be split (results that are not rounded to bf16 later)
 };
@@ -292,10 +284,10 @@ hipError_t launch_nop_gemm(const NopGemm& g, hipStream_t s);
 hipError_t launch_nop_mix(const float* A, bool transA, const void* X, void* Y, const float* bias, const float* D,
                           float* pre, const void* T, const float* Cw, int Mm, int O, int I, int H, int W, int B, bool act,
                           bool split, int act_types, hipStream_t s);
-// out = Q2 GELU(Q1 v + q1b) + q2b per position (C <= 32); qpre and q stored when non-null; v in bf16 with
+// out = Q2 GELU(Q1 v + q1b) + q2b per position (C <= 32); qpre stored when non-null; v in bf16 with
 // half.
 hipError_t launch_nop_project(const float* Q1, const float* q1b, const float* Q2, const float* q2b, const void* v,
-                              float* out, float* qpre, float* q, int C, int Hp, int64_t P, int B, bool split, bool half,
+                              float* out, float* qpre, int C, int Hp, int64_t P, int B, bool split, bool half,
                               hipStream_t s);
 // A[pl][kh][kw] = sum_h sum_w Ch[kh][h] V[pl][h][w] Cw[kw][w] for every plane (the truncated 2D DCT, Ch:
 // Mm x H, Cw: Mm x W), one plane per wave on the bf16 matrix cores; W <= 128, Mm <= 64.
@@ -322,6 +314,9 @@ size_t nop_mid_count(int max_rows, int max_cols);
 hipError_t launch_nop_gelu_bwd(const float* gin, const float* pre, float* d, float* rowsum, double* mid, int nb, int rows,
                                int64_t P, hipStream_t s);
 hipError_t launch_nop_rowsum(const float* x, float* out, double* mid, int nb, int rows, int64_t P, hipStream_t s);
+// dq = (Q2 outer dout) GELU'(qpre); grads: the gradients of q1b (rows values) and Q2 (rows values).
+hipError_t launch_nop_hidden_bwd(const float* Q2, const float* qpre, const float* dout, float* dq, float* grads, double* mid,
+                                 int nb, int rows, int64_t P, bool split, hipStream_t s);
 hipError_t launch_nop_partial_sum(const float* part, float* out, double* mid, int nz, int n, hipStream_t s);
 hipError_t launch_nop_loss(const float* out, const float* tgt, double* terms, float* dout, int B, int64_t P,
                            hipStream_t s);

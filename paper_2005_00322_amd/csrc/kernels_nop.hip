@@ -3,7 +3,7 @@
 //
 // Every contraction of the network (the truncated DCT along each axis, the per-mode channel mixing, the
 // inverse DCT, the pointwise channel mixing, the lift and projection, and all their backward products)
-// is  C[z] = alpha A[z] B[z] (+ beta C[z]) (+ bias[m]) (+ D[z]) (-> GELU)  with arbitrary element
+// is  C[z] = alpha A[z] B[z] (+ beta C[z])  with arbitrary element
 // strides, so one kernel serves all of them without transposes in HBM.  Operands are FP32 in HBM and
 // rounded to bf16 while they are staged into LDS; with `split` each operand is also kept as a bf16
 // remainder and the product is formed as hi*hi + hi*lo + lo*hi (close to FP32 accuracy; used by the
@@ -264,15 +264,10 @@ __global__ __launch_bounds__(NT) void nop_gemm_kernel(NopGemm g) {
 
   // epilogue
   float* C = g.C + z1 * g.bC1 + z2 * g.bC2;
-  const float* Dp = g.add ? g.add + z1 * g.bD1 + z2 * g.bD2 : nullptr;
-  float* Pp = g.pre ? g.pre + z1 * g.bC1 + z2 * g.bC2 : nullptr;
-  const float* Gp = g.dgelu ? g.dgelu + z1 * g.bC1 + z2 * g.bC2 : nullptr;
   const uint32_t sCm = static_cast<uint32_t>(g.sCm), sCn = static_cast<uint32_t>(g.sCn);
-  const uint32_t sDm = static_cast<uint32_t>(g.sDm), sDn = static_cast<uint32_t>(g.sDn);
-  // All reads of a 32 x 32 block (old C, the added tensor, the GELU argument, the bias) are issued before
-  // its first store: the stores may alias nothing the loads touch, but the compiler cannot know that,
-  // and interleaving would serialise every element on a memory round trip.  Elements outside read the operand's last row
-  // or column, so that no read waits behind a branch.
+  // All reads of a 32 x 32 block of old C are issued before its first store: the stores may alias nothing the loads
+  // touch, but the compiler cannot know that, and interleaving would serialise every element on a memory round trip.
+  // Elements outside read the last row or column, so that no read waits behind a branch.
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -283,38 +278,17 @@ __global__ __launch_bounds__(NT) void nop_gemm_kernel(NopGemm g) {
       const uint32_t nc = static_cast<uint32_t>(min(n, g.N - 1));
       auto mr = [&](int r) { return mb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
       auto mc = [&](int r) { return static_cast<uint32_t>(min(mr(r), g.M - 1)); };
-      float ext[16], gg[16];
+      float ext[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) ext[r] = 0.f;
       if (g.beta != 0.f) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) ext[r] += g.beta * C[mc(r) * sCm + nc * sCn];
       }
-      if (g.bias_m) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) ext[r] += g.bias_m[mc(r)];
-      }
-      if (Dp) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) ext[r] += Dp[mc(r) * sDm + nc * sDn];
-      }
-      if (Gp) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) gg[r] = Gp[mc(r) * sCm + nc * sCn];
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float v = g.alpha * acc[i][j][r] + ext[r];
-        if (Gp) v *= gelu_grad_f(gg[r]);
-        if (mr(r) < g.M && n < g.N) {
-          const uint32_t co = static_cast<uint32_t>(mr(r)) * sCm + static_cast<uint32_t>(n) * sCn;
-          if (g.act) {
-            if (Pp) Pp[co] = v;
-            v = gelu_f(v);
-          }
-          C[co] = v;
-        }
-      }
+      for (int r = 0; r < 16; ++r)
+        if (mr(r) < g.M && n < g.N)
+          C[static_cast<uint32_t>(mr(r)) * sCm + static_cast<uint32_t>(n) * sCn] = g.alpha * acc[i][j][r] + ext[r];
     }
 }
 
@@ -435,6 +409,71 @@ __global__ __launch_bounds__(256) void nop_rowsum_kernel(const float* __restrict
   }
   s = block_sum(s);
   if (threadIdx.x == 0) part[static_cast<int64_t>(z) * rows + j] = s;
+}
+
+// Backward through the hidden layer, one pass over its pre-activations (qpre: [b][rows][P]): dq = (Q2[j] dout) GELU'(qpre)
+// is stored, and the gradients of q1b (the sum of dq) and Q2 (the sum of GELU(qpre) dout, the activation formed again
+// as the forward pass formed it) are summed on the way, in double: part[z][j] and part[z][rows + j] over chunk z of the
+// (sample, kHidSeg positions) pairs.  The factors are rounded to bf16 (SPLIT: with their remainders) as operands of a
+// matrix product.  Bound by the vector ALU (the error function); a product for dq, one for Q2 that read the stored activation
+// and a row sum of dq before: 641 us (batch 64, 128 rows, 128 x 128), and 100 us of the forward pass to store the activation.
+constexpr int kHidSeg = 4096;
+
+template <bool SPLIT, bool VEC>
+__global__ __launch_bounds__(256) void nop_hidden_bwd_kernel(const float* __restrict__ Q2, const float* __restrict__ qpre,
+                                                             const float* __restrict__ dout, float* __restrict__ dq,
+                                                             double* __restrict__ part, int nb, int rows, int64_t P) {
+  const int j = blockIdx.x, z = blockIdx.y, nz = gridDim.y;
+  const int64_t npc = (P + kHidSeg - 1) / kHidSeg, nseg = npc * nb;
+  const int64_t s0 = z * nseg / nz, s1 = (z + 1) * nseg / nz;
+  const float w = Q2[j], wh = static_cast<float>(static_cast<__bf16>(w)), wl = static_cast<float>(static_cast<__bf16>(w - wh));
+  double sb = 0.0, sw = 0.0;
+  auto one = [&](float pre, float d, float& sq) {   // returns dq
+    const float dh = static_cast<float>(static_cast<__bf16>(d));
+    const float g = gelu_f(pre), gh = static_cast<float>(static_cast<__bf16>(g));
+    float x = wh * dh;
+    sq = gh * dh;
+    if constexpr (SPLIT) {
+      const float dl = static_cast<float>(static_cast<__bf16>(d - dh)), gl = static_cast<float>(static_cast<__bf16>(g - gh));
+      x = fmaf(wl, dh, x);
+      x = fmaf(wh, dl, x);
+      sq = fmaf(dl, gh, sq);
+      sq = fmaf(dh, gl, sq);
+    }
+    return x * gelu_grad_f(pre);
+  };
+  for (int64_t sg = s0; sg < s1; ++sg) {
+    const int64_t b = sg / npc, p0 = (sg - b * npc) * kHidSeg, o = (b * rows + j) * P, od = b * P;
+    const int64_t pe = min(P, p0 + kHidSeg);
+    if constexpr (VEC) {
+#pragma unroll 2
+      for (int64_t p = p0 + 4 * threadIdx.x; p < pe; p += 1024) {
+        const f32x4 q = *reinterpret_cast<const f32x4*>(qpre + o + p), d = *reinterpret_cast<const f32x4*>(dout + od + p);
+        f32x4 v;
+        float t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = one(q[k], d[k], t[k]);
+        *reinterpret_cast<f32x4*>(dq + o + p) = v;
+        sb += (static_cast<double>(v[0]) + v[1]) + (static_cast<double>(v[2]) + v[3]);
+        sw += (static_cast<double>(t[0]) + t[1]) + (static_cast<double>(t[2]) + t[3]);
+      }
+    } else {
+      for (int64_t p = p0 + threadIdx.x; p < pe; p += 256) {
+        float t;
+        const float v = one(qpre[o + p], dout[od + p], t);
+        dq[o + p] = v;
+        sb += v;
+        sw += t;
+      }
+    }
+  }
+  sb = block_sum(sb);
+  __syncthreads();
+  sw = block_sum(sw);
+  if (threadIdx.x == 0) {
+    part[2 * static_cast<int64_t>(z) * rows + j] = sb;
+    part[(2 * static_cast<int64_t>(z) + 1) * rows + j] = sw;
+  }
 }
 
 // mid[y n + j] = sum over chunk y of the nz partial products part[z n + j] (the split-K sums), in double:
@@ -917,13 +956,13 @@ __global__ __launch_bounds__(256) void nop_mixrows_kernel(const float* __restric
 // Fused projection on the bf16 matrix cores (FP32 accumulation): out[b][p] = sum_j Q2[j] GELU(sum_c
 // Q1[j][c] v[b][c][p] + q1b[j]) + q2b (C <= 32 channels), 32 hidden rows per pass; each lane sums its
 // rows, the two halves of the wave are added with a lane exchange.  Q1, q1b and Q2 are staged in LDS once
-// per block.  With keep (qpre non-null), qpre and q ([b][Hp][P]) are stored.
+// per block.  With qpre ([b][Hp][P]) the pre-activations are stored.
 template <typename TV>
 __global__ __launch_bounds__(256) void nop_project_kernel(const float* __restrict__ Q1, const float* __restrict__ q1b,
                                                           const float* __restrict__ Q2, const float* __restrict__ q2b,
                                                           const TV* __restrict__ v, float* __restrict__ out,
-                                                          float* __restrict__ qpre, float* __restrict__ q, int C,
-                                                          int Hp, int64_t P, int split) {
+                                                          float* __restrict__ qpre, int C, int Hp, int64_t P,
+                                                          int split) {
   extern __shared__ float sm[];
   const int ldq = C + 1;
   float* sQ1 = sm;                  // [Hp][C + 1]
@@ -981,11 +1020,7 @@ __global__ __launch_bounds__(256) void nop_project_kernel(const float* __restric
       if (jj < Hp) {
         const float hv = acc[r] + sb[jj];
         const float g = gelu_f(hv);
-        if (qpre && nok) {
-          const int64_t off = (b * Hp + jj) * P + n;
-          qpre[off] = hv;
-          q[off] = g;
-        }
+        if (qpre && nok) qpre[(b * Hp + jj) * P + n] = hv;
         part = fmaf(s2[jj], g, part);
       }
     }
@@ -1000,13 +1035,13 @@ __global__ __launch_bounds__(256) void nop_project_kernel(const float* __restric
 // hidden tiles of a chunk run one after the other, so one tile's accumulators are live at a time.  The
 // MFMA sequence, the epilogue arithmetic and the order of the Q2 dot product are those of
 // nop_project_kernel, so both forms give the same bits for finite activations.  KFULL: C == 32 (no channel masks); KEEP: the
-// pre-activations and activations are stored for the backward pass.
+// pre-activations are stored for the backward pass.
 template <typename TV, bool SPLIT, bool KFULL, bool KEEP>
 __global__ __launch_bounds__(256) void nop_projrows_kernel(const float* __restrict__ Q1, const float* __restrict__ q1b,
                                                            const float* __restrict__ Q2, const float* __restrict__ q2b,
                                                            const TV* __restrict__ v, float* __restrict__ out,
-                                                           float* __restrict__ qpre, float* __restrict__ q, int C,
-                                                           int Hp, int P, int B, int rpb) {
+                                                           float* __restrict__ qpre, int C, int Hp, int P, int B,
+                                                           int rpb) {
   constexpr int MAXT = 4;                          // hidden tiles of 32
   __shared__ float sb[32 * MAXT], s2[32 * MAXT];
   __shared__ bf16x8 sah[2 * MAXT][64], sal[SPLIT ? 2 * MAXT : 1][64];
@@ -1046,8 +1081,6 @@ __global__ __launch_bounds__(256) void nop_projrows_kernel(const float* __restri
   const int nxs = C > 16 ? 2 : 1;
   const rsrc_t rV = wave_rsrc(v, static_cast<uint32_t>(B * C * P) * VS);
   const rsrc_t rQp = wave_rsrc(KEEP ? static_cast<void*>(qpre) : static_cast<void*>(out),
-                               KEEP ? static_cast<uint32_t>(B * Hp * P) * 4u : 0u);
-  const rsrc_t rQg = wave_rsrc(KEEP ? static_cast<void*>(q) : static_cast<void*>(out),
                                KEEP ? static_cast<uint32_t>(B * Hp * P) * 4u : 0u);
   const rsrc_t rO = wave_rsrc(out, static_cast<uint32_t>(B * P) * 4u);
 
@@ -1115,7 +1148,6 @@ __global__ __launch_bounds__(256) void nop_projrows_kernel(const float* __restri
         if (KEEP) {
           const uint32_t off = (4u * static_cast<uint32_t>(jj * P + n)) | ((nok && jj < Hp) ? 0u : kOOB);
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, hv), rQp, off, 4u * qrow, 0);
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, g), rQg, off, 4u * qrow, 0);
         }
         // rows past Hp have zero Q1 rows, bias and Q2 entries: they add 0 * GELU(0) = 0
         part = fmaf(s2[jj], g, part);
@@ -1693,7 +1725,7 @@ hipError_t launch_nop_mix(const float* A, bool transA, const void* X, void* Y, c
 }
 
 hipError_t launch_nop_project(const float* Q1, const float* q1b, const float* Q2, const float* q2b, const void* v,
-                              float* out, float* qpre, float* q, int C, int Hp, int64_t P, int B, bool split, bool half,
+                              float* out, float* qpre, int C, int Hp, int64_t P, int B, bool split, bool half,
                               hipStream_t s) {
   const size_t lds = sizeof(float) * (static_cast<size_t>(Hp) * (C + 1) + 2 * Hp);
   if (C > 32 || lds > 65536) return hipErrorInvalidValue;
@@ -1702,7 +1734,7 @@ hipError_t launch_nop_project(const float* Q1, const float* q1b, const float* Q2
                     static_cast<int64_t>(B) * P * 4 < (int64_t(1) << 31) &&
                     (!qpre || static_cast<int64_t>(B) * Hp * P * 4 < (int64_t(1) << 31));
   const bool keep = qpre != nullptr;
-  if (Hp >= 1 && Hp <= 128 && C >= 1 && fits && keep == (q != nullptr) && !(half && (split || keep))) {
+  if (Hp >= 1 && Hp <= 128 && C >= 1 && fits && !(half && (split || keep))) {
     // the chunk-walking form: about 1024 blocks of 4 waves
     const int64_t chunks = static_cast<int64_t>(B) * ((P + 127) / 128);
     const int rpb = static_cast<int>(std::max<int64_t>(1, (chunks + 1023) / 1024));
@@ -1710,9 +1742,9 @@ hipError_t launch_nop_project(const float* Q1, const float* q1b, const float* Q2
     const int Pi = static_cast<int>(P);
 #define PSTD_PROJ_K(TVV, SPV, KPV)                                                                                \
   if (C == 32) hipLaunchKernelGGL((nop_projrows_kernel<TVV, SPV, true, KPV>), grid, blk, 0, s, Q1, q1b, Q2, q2b,    \
-                                  static_cast<const TVV*>(v), out, qpre, q, C, Hp, Pi, B, rpb);                   \
+                                  static_cast<const TVV*>(v), out, qpre, C, Hp, Pi, B, rpb);                   \
   else hipLaunchKernelGGL((nop_projrows_kernel<TVV, SPV, false, KPV>), grid, blk, 0, s, Q1, q1b, Q2, q2b,          \
-                          static_cast<const TVV*>(v), out, qpre, q, C, Hp, Pi, B, rpb);
+                          static_cast<const TVV*>(v), out, qpre, C, Hp, Pi, B, rpb);
     if (half) {        // the inference form: bf16 activations
       PSTD_PROJ_K(__bf16, false, false)
     } else if (split) {
@@ -1725,10 +1757,10 @@ hipError_t launch_nop_project(const float* Q1, const float* q1b, const float* Q2
   }
   if (half)
     hipLaunchKernelGGL(nop_project_kernel<__bf16>, dim3(blocks_for(P, 128), B), dim3(256), lds, s, Q1, q1b, Q2, q2b,
-                       static_cast<const __bf16*>(v), out, qpre, q, C, Hp, P, split ? 1 : 0);
+                       static_cast<const __bf16*>(v), out, qpre, C, Hp, P, split ? 1 : 0);
   else
     hipLaunchKernelGGL(nop_project_kernel<float>, dim3(blocks_for(P, 128), B), dim3(256), lds, s, Q1, q1b, Q2, q2b,
-                       static_cast<const float*>(v), out, qpre, q, C, Hp, P, split ? 1 : 0);
+                       static_cast<const float*>(v), out, qpre, C, Hp, P, split ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -1852,6 +1884,21 @@ hipError_t launch_nop_gelu_bwd(const float* gin, const float* pre, float* d, flo
 
 hipError_t launch_nop_rowsum(const float* x, float* out, double* mid, int nb, int rows, int64_t P, hipStream_t s) {
   return launch_rowsum_t<false>(x, nullptr, nullptr, out, mid, nb, rows, P, s);
+}
+
+hipError_t launch_nop_hidden_bwd(const float* Q2, const float* qpre, const float* dout, float* dq, float* grads, double* mid,
+                                 int nb, int rows, int64_t P, bool split, hipStream_t s) {
+  const int64_t nseg = nb * ((P + kHidSeg - 1) / kHidSeg);
+  const int nz = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({nseg, kNopMidChunks, (2048 + rows - 1) / rows})));
+  const uintptr_t align = reinterpret_cast<uintptr_t>(qpre) | reinterpret_cast<uintptr_t>(dout) | reinterpret_cast<uintptr_t>(dq);
+  const bool vec = (P & 3) == 0 && (align & 15) == 0;
+  const dim3 grid(rows, nz), blk(256);
+  if (split && vec) hipLaunchKernelGGL((nop_hidden_bwd_kernel<true, true>), grid, blk, 0, s, Q2, qpre, dout, dq, mid, nb, rows, P);
+  else if (split) hipLaunchKernelGGL((nop_hidden_bwd_kernel<true, false>), grid, blk, 0, s, Q2, qpre, dout, dq, mid, nb, rows, P);
+  else if (vec) hipLaunchKernelGGL((nop_hidden_bwd_kernel<false, true>), grid, blk, 0, s, Q2, qpre, dout, dq, mid, nb, rows, P);
+  else hipLaunchKernelGGL((nop_hidden_bwd_kernel<false, false>), grid, blk, 0, s, Q2, qpre, dout, dq, mid, nb, rows, P);
+  hipLaunchKernelGGL(nop_mid_sum_kernel, dim3(blocks_for(2 * rows, 256)), blk, 0, s, mid, grads, nz, 2 * rows);
+  return hipGetLastError();
 }
 
 hipError_t launch_nop_partial_sum(const float* part, float* out, double* mid, int nz, int n, hipStream_t s) {
