@@ -92,7 +92,7 @@ int chunks_of(int64_t P) {
   } while (0)
 
 // Spectral term of one layer up to its last stage: T = (inverse DCT along H of) R . DCT(vin), laid out
-// [b][h][c][kw]; keeps the blocked DCT in `at`.
+// [b][h][c][kw]; keeps the blocked DCT in `at` (not null).
 int spectral_fwd(pstd_nop_s* N, const void* vin, const float* R, float* at, int B, bool half) {
   const pstd_nop_config& c = N->cfg;
   const int H = c.H, W = c.W, C = c.channels, Mm = c.modes;
@@ -113,21 +113,14 @@ int spectral_fwd(pstd_nop_s* N, const void* vin, const float* R, float* at, int 
     g = gemm(N, N->Y1, W, 1, N->Cw, 1, W, N->Ahat, Mm, 1, B * C * Mm, Mm, W);
     NOP_RUN(launch_nop_gemm(g, s));
   }
-  NOP_RUN(launch_nop_mode_transpose(N->Ahat, at, B, C, Mm, true, s));
-  // mixing per 2 x 2 mode block: Zt[blk] (4B x C) = at[blk] (4B x C) R[blk]^T
-  g = gemm(N, at, C, 1, R, 1, C, N->Zt, C, 1, 4 * B, C, C);
-  g.nb1 = (Mm / 2) * (Mm / 2);
-  g.bA1 = 4LL * B * C;
-  g.bB1 = static_cast<int64_t>(C) * C;
-  g.bC1 = 4LL * B * C;
-  NOP_RUN(launch_nop_gemm(g, s));
-  NOP_RUN(launch_nop_mode_transpose(N->Zt, N->Ahat, B, C, Mm, false, s));
+  if (at) NOP_RUN(launch_nop_mode_transpose(N->Ahat, at, B, C, Mm, s));
+  NOP_RUN(launch_nop_modemix(N->Ahat, R, N->Zt, B, C, Mm, false, c.split != 0, s));
   // inverse along H: T[b][h][c][kw] = sum_kh Ch[kh][h] Z[b][c][kh][kw]; the inverse along W is the
   // second K segment of the channel-mixing kernel that consumes T
   if (Mm <= 64 && H <= 512) {
-    NOP_RUN(launch_nop_idct_h(N->Ahat, N->T, N->idct_img, B, C, H, Mm, c.split != 0, half, s));
+    NOP_RUN(launch_nop_idct_h(N->Zt, N->T, N->idct_img, B, C, H, Mm, c.split != 0, half, s));
   } else {
-    g = gemm(N, N->Ch, 1, H, N->Ahat, Mm, 1, N->T, static_cast<int64_t>(C) * Mm, 1, H, Mm, Mm);
+    g = gemm(N, N->Ch, 1, H, N->Zt, Mm, 1, N->T, static_cast<int64_t>(C) * Mm, 1, H, Mm, Mm);
     g.nb1 = B;
     g.bB1 = static_cast<int64_t>(C) * Mm * Mm;
     g.bC1 = static_cast<int64_t>(H) * C * Mm;
@@ -328,7 +321,7 @@ int forward_impl(pstd_nop N, const float* p0, const float* c0, float* out, int32
   float* vin = N->V[0];
   for (int l = 0; l < c.layers; ++l) {
     float* vout = keep ? N->V[l + 1] : N->V[(l + 1) & 1];
-    const int st = spectral_fwd(N, vin, th + N->oR[l], keep ? N->AT[l] : N->At2, B, half);
+    const int st = spectral_fwd(N, vin, th + N->oR[l], keep ? N->AT[l] : nullptr, B, half);
     if (st != PSTD_OK) return st;
     // vout = GELU(W vin + b + S), pre-activation kept for the backward pass
     NOP_RUN(launch_nop_mix(th + N->oW[l], false, vin, vout, th + N->ob[l], nullptr, keep ? N->PRE[l] : nullptr, N->T,
@@ -393,7 +386,7 @@ int pstd_nop_backward(pstd_nop N, const float* target, double* loss) {
     NOP_RUN(launch_nop_gemm(g, s));
     g = gemm(N, N->Y1, W, 1, N->Cw, 1, W, N->Ahat, Mm, 1, B * C * Mm, Mm, W);
     NOP_RUN(launch_nop_gemm(g, s));
-    NOP_RUN(launch_nop_mode_transpose(N->Ahat, N->Zt, B, C, Mm, true, s));
+    NOP_RUN(launch_nop_mode_transpose(N->Ahat, N->Zt, B, C, Mm, s));
     // dR[blk] (C x C) = dZt[blk]^T (C x 4B) AT[l][blk] (4B x C)
     const int nblk = (Mm / 2) * (Mm / 2);
     g = gemm(N, N->Zt, 1, C, N->AT[l], C, 1, gr + N->oR[l], C, 1, C, C, 4 * B);
@@ -403,16 +396,10 @@ int pstd_nop_backward(pstd_nop N, const float* target, double* loss) {
     g.bC1 = static_cast<int64_t>(C) * C;
     g.free_order = 1;
     NOP_RUN(launch_nop_gemm(g, s));
-    // dA[blk] (4B x C) = dZt[blk] (4B x C) R[blk] (C x C)
-    g = gemm(N, N->Zt, C, 1, th + N->oR[l], C, 1, N->At2, C, 1, 4 * B, C, C);
-    g.nb1 = nblk;
-    g.bA1 = 4LL * B * C;
-    g.bB1 = static_cast<int64_t>(C) * C;
-    g.bC1 = 4LL * B * C;
-    NOP_RUN(launch_nop_gemm(g, s));
-    NOP_RUN(launch_nop_mode_transpose(N->At2, N->Ahat, B, C, Mm, false, s));
+    // dA = R^T dZ per mode
+    NOP_RUN(launch_nop_modemix(N->Ahat, th + N->oR[l], N->At2, B, C, Mm, true, c.split != 0, s));
     // dvn += IDCT(dA) (the DCT's adjoint)
-    g = gemm(N, N->Ahat, Mm, 1, N->Cw, W, 1, N->Y1, W, 1, B * C * Mm, W, Mm);
+    g = gemm(N, N->At2, Mm, 1, N->Cw, W, 1, N->Y1, W, 1, B * C * Mm, W, Mm);
     NOP_RUN(launch_nop_gemm(g, s));
     g = gemm(N, N->Ch, 1, H, N->Y1, W, 1, N->dvn, W, 1, H, W, Mm);
     g.nb1 = B * C;

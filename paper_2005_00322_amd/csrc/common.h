@@ -303,7 +303,9 @@ hipError_t launch_nop_dct2(const void* V, float* A, const void* img, int planes,
 // bf16 matrix cores; Mm <= 64 and H <= 512 (LDS).
 hipError_t launch_nop_idct_h(const float* Z, void* T, const void* img, int B, int C, int H, int Mm, bool split,
                              bool half, hipStream_t s);   // T in bf16 with half
-hipError_t launch_nop_mode_transpose(const float* in, float* out, int B, int C, int Mm, bool to_block, hipStream_t s);
+hipError_t launch_nop_modemix(const float* in, const float* R, float* out, int B, int C, int Mm, bool trans, bool split,
+                              hipStream_t s);   // channel mixing in the natural layout, R per 2 x 2 block of modes
+hipError_t launch_nop_mode_transpose(const float* in, float* out, int B, int C, int Mm, hipStream_t s);
 hipError_t launch_nop_features(const float* p0, const float* c0, float* f, int B, int H, int W, hipStream_t s);
 // Sums over the batch run in two stages; `mid` holds the first one's doubles (nop_mid_count of them, for the
 // largest row and column count the caller passes).  gelu_bwd: d = gin GELU'(pre), rowsum[j] = the sum of

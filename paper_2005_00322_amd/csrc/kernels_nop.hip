@@ -292,13 +292,158 @@ __global__ __launch_bounds__(NT) void nop_gemm_kernel(NopGemm g) {
     }
 }
 
-// Natural spectral layout [b][c][kh][kw] <-> block layout [blk][q][b][c] (blk = (kh/2)(Mm/2) + kw/2,
-// q = 2 (kh%2) + kw%2): the modes that share one mixing matrix become one contiguous GEMM operand.
+// Channel mixing of the modes in their natural layout [b][c][kh][kw]: out[b][o][m] = sum_c R[blk][o][c] in[b][c][m] (TRANS:
+// R[blk][c][o]) with blk = (kh/2)(Mm/2) + kw/2 the 2 x 2 block of modes that shares a matrix.  A block takes four samples,
+// one pair of kh and up to 48 kw: its input rows of one channel are contiguous in memory, go through LDS as [blk][(q, b)][c]
+// (q the mode of its 2 x 2 block) and come back as 16 rows of products per blk, four blks at a time on four waves; the results
+// leave through LDS along kw.  Bound by HBM (the modes once in and once out) and by the latency of one round of loads, so a
+// thread's loads are all issued first (two blocks per CU; with loads as they are needed 102 us, with one block 72).  A
+// product in block layout with a transposing pass before and after it moved the modes three times: 115 us against 49
+// (batch 256, 32 channels, 48 modes: 151 MB), 41 against 24 (batch 64).
+// The bf16 products and their order are those of nop_gemm_kernel.
+constexpr int kMixB = 4, kMixKw = 48;
+constexpr int kMixRow = 40, kMixBlk = 16 * kMixRow + 8;   // bf16: LDS strides of a row and of a blk (its 16 rows)
+
+// C32: C == 32 and R 16-byte aligned.
+template <bool SPLIT, bool TRANS, bool C32>
+__global__ __launch_bounds__(256, 2) void nop_modemix_kernel(const float* __restrict__ in, const float* __restrict__ R,
+                                                          float* __restrict__ out, int B, int C, int Mm, int chunk) {
+  extern __shared__ __attribute__((aligned(16))) char mix_lds[];
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  __bf16* sa = reinterpret_cast<__bf16*>(mix_lds);
+  float* so = reinterpret_cast<float*>(mix_lds);     // the results, once the operands are read
+  constexpr int MAXW = kMixKw / 2 / 4;               // blks of a wave
+  const int nch = (Mm + chunk - 1) / chunk;
+  const int kp = blockIdx.x / nch, kw0 = (blockIdx.x - kp * nch) * chunk, kwn = min(chunk, Mm - kw0), nblk = kwn >> 1;
+  const int b0 = blockIdx.y * kMixB, nb = min(kMixB, B - b0);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t M2 = static_cast<int64_t>(Mm) * Mm, base = static_cast<int64_t>(b0) * C * M2 + static_cast<int64_t>(2 * kp) * Mm + kw0;
+  __bf16* sl = sa + nblk * kMixBlk;                  // SPLIT: the remainders
+  // item u: pair of modes (kw even and odd) blk of row khp of channel c of sample b
+  const int step_r = 256 / nblk, step_b = 256 - step_r * nblk;
+  auto next = [&](int& rest, int& blk) {
+    rest += step_r;
+    blk += step_b;
+    if (blk >= nblk) {
+      blk -= nblk;
+      ++rest;
+    }
+  };
+  auto at = [&](int rest, int blk) {
+    const int khp = rest & 1, c = min((rest >> 1) & 31, C - 1), b = min(rest >> 6, nb - 1);
+    return base + (static_cast<int64_t>(b) * C + c) * M2 + khp * Mm + 2 * blk;
+  };
+  // one item per blk and thread; all of a thread's loads, the matrices' too, are in flight before the first is used
+  const int rest0 = threadIdx.x / nblk, blk0 = threadIdx.x - rest0 * nblk;
+  constexpr int U = kMixKw / 2;
+  f32x2 v[U];
+  float rf[MAXW][2][8];
+  {
+    int rest = rest0, blk = blk0;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      v[i] = *reinterpret_cast<const f32x2*>(in + at(rest, blk));   // past the items: clamped to the last sample
+      next(rest, blk);
+    }
+  }
+  const int o = lane & 31, kh = 8 * (lane >> 5);
+#pragma unroll
+  for (int w = 0; w < MAXW; ++w) {
+    const float* Rb = R + static_cast<int64_t>(kp * (Mm >> 1) + (kw0 >> 1) + min(wave + 4 * w, nblk - 1)) * C * C;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      if (C32 && !TRANS) {
+#pragma unroll
+        for (int e = 0; e < 8; e += 4) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(Rb + o * 32 + 16 * c + kh + e);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) rf[w][c][e + k] = x[k];
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int k = 16 * c + kh + e, kc = C32 ? k : min(k, C - 1), oc = C32 ? o : min(o, C - 1);
+          rf[w][c][e] = Rb[TRANS ? kc * C + oc : oc * C + kc];
+        }
+      }
+  }
+  {
+    int rest = rest0, blk = blk0;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int khp = rest & 1, c = (rest >> 1) & 31, b = rest >> 6;
+      if (i < nblk) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float x = c < C && b < nb ? v[i][j] : 0.f;
+          const int p = blk * kMixBlk + ((2 * khp + j) * kMixB + b) * kMixRow + c;
+          const __bf16 h = static_cast<__bf16>(x);
+          sa[p] = h;
+          if (SPLIT) sl[p] = static_cast<__bf16>(x - static_cast<float>(h));
+        }
+      }
+      next(rest, blk);
+    }
+  }
+  lds_barrier();
+  float res[MAXW][8];                                // rows 0 .. 15 of a blk's product: registers 0 .. 7
+#pragma unroll
+  for (int w = 0; w < MAXW; ++w) {
+    const int blk = wave + 4 * w;
+    if (blk >= nblk) break;
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      if (!C32 && 16 * c >= C) break;
+      bf16x8 bh, bl, al;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float x = C32 || (16 * c + kh + e < C && o < C) ? rf[w][c][e] : 0.f;
+        bh[e] = static_cast<__bf16>(x);
+        if (SPLIT) bl[e] = static_cast<__bf16>(x - static_cast<float>(bh[e]));
+      }
+      const int p = blk * kMixBlk + (lane & 15) * kMixRow + 16 * c + kh;
+      const bf16x8 ah = *reinterpret_cast<const bf16x8*>(sa + p);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
+      if (SPLIT) {
+        al = *reinterpret_cast<const bf16x8*>(sl + p);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 8; ++r) res[w][r] = acc[r];
+  }
+  lds_barrier();
+  // row 8 (r / 4) + 4 (lane / 32) + r % 4 is mode q = 2 (r / 4) + lane / 32 of sample r % 4
+  const int ldo = 2 * kwn + 2;                       // twice an odd number: the lanes of a store on 64 banks
+#pragma unroll
+  for (int w = 0; w < MAXW; ++w) {
+    const int blk = wave + 4 * w;
+    if (blk >= nblk) break;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) so[((r & 3) * 32 + o) * ldo + (r >> 2) * kwn + 2 * blk + (lane >> 5)] = res[w][r];
+  }
+  lds_barrier();
+  int rest = rest0, blk = blk0;
+#pragma unroll 4
+  for (int i = 0; i < nblk; ++i) {
+    const int khp = rest & 1, c = (rest >> 1) & 31, b = rest >> 6;
+    if (c < C && b < nb)
+      *reinterpret_cast<f32x2*>(out + at(rest, blk)) = *reinterpret_cast<const f32x2*>(so + (b * 32 + c) * ldo + khp * kwn + 2 * blk);
+    next(rest, blk);
+  }
+}
+
+// Natural spectral layout [b][c][kh][kw] -> block layout [blk][q][b][c] (blk = (kh/2)(Mm/2) + kw/2,
+// q = 2 (kh%2) + kw%2): the modes that share one mixing matrix become one contiguous GEMM operand (of its gradient).
 // One block moves the C x 64 slab of modes m0 .. m0+63 (m = kh Mm + kw) of one sample through LDS: the
-// natural side is read or written as 64 consecutive modes per channel, the block side as C consecutive
+// natural side is read as 64 consecutive modes per channel, the block side written as C consecutive
 // channels per mode.  C <= 32.
 __global__ __launch_bounds__(256) void nop_mode_transpose_kernel(const float* __restrict__ in, float* __restrict__ out,
-                                                                 int B, int C, int Mm, int to_block) {
+                                                                 int B, int C, int Mm) {
   __shared__ float tile[32][65];
   const int M2 = Mm * Mm;
   const int m0 = blockIdx.x * 64;
@@ -316,27 +461,15 @@ __global__ __launch_bounds__(256) void nop_mode_transpose_kernel(const float* __
     const int blk = (kh >> 1) * (Mm >> 1) + (kw >> 1), q = 2 * (kh & 1) + (kw & 1);
     boff[u] = m < M2 ? ((static_cast<int64_t>(blk) * 4 + q) * B + b) * C + bc : -1;
   }
-  if (to_block) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int c = (t >> 6) + 4 * u;
-      if (c < C && nm < M2) tile[c][t & 63] = in[(b * C + c) * M2 + nm];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (bc < C && boff[u] >= 0) out[boff[u]] = tile[bc][(t >> 5) + 8 * u];
-  } else {
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (bc < C && boff[u] >= 0) tile[bc][(t >> 5) + 8 * u] = in[boff[u]];
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int c = (t >> 6) + 4 * u;
-      if (c < C && nm < M2) out[(b * C + c) * M2 + nm] = tile[c][t & 63];
-    }
+  for (int u = 0; u < 8; ++u) {
+    const int c = (t >> 6) + 4 * u;
+    if (c < C && nm < M2) tile[c][t & 63] = in[(b * C + c) * M2 + nm];
   }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    if (bc < C && boff[u] >= 0) out[boff[u]] = tile[bc][(t >> 5) + 8 * u];
 }
 
 // Input features [b][4][H][W]: p0, (c0 - 1500)/100, x = i/(H-1), y = j/(W-1).
@@ -1839,10 +1972,31 @@ hipError_t launch_nop_idct_h(const float* Z, void* T, const void* img, int B, in
   return hipGetLastError();
 }
 
-hipError_t launch_nop_mode_transpose(const float* in, float* out, int B, int C, int Mm, bool to_block, hipStream_t s) {
+hipError_t launch_nop_modemix(const float* in, const float* R, float* out, int B, int C, int Mm, bool trans, bool split,
+                              hipStream_t s) {
+  if (B < 1 || C < 1 || C > 32 || Mm < 2 || Mm % 2) return hipErrorInvalidValue;
+  const int nch = (Mm + kMixKw - 1) / kMixKw, chunk = ((Mm / 2 + nch - 1) / nch) * 2;   // even, at most kMixKw
+  const size_t ops = static_cast<size_t>(chunk / 2) * kMixBlk * 2 * (split ? 2 : 1);
+  const size_t res = static_cast<size_t>(kMixB) * 32 * (2 * chunk + 2) * sizeof(float);
+  const size_t lds = std::max(ops, res);                                                     // below 64 KB
+  const dim3 grid((Mm / 2) * ((Mm + chunk - 1) / chunk), (B + kMixB - 1) / kMixB), blk(256);
+  const bool c32 = C == 32 && (reinterpret_cast<uintptr_t>(R) & 15) == 0;
+  auto launch = [&](auto sp, auto tr, auto c) {
+    hipLaunchKernelGGL((nop_modemix_kernel<decltype(sp)::value, decltype(tr)::value, decltype(c)::value>), grid, blk, lds, s, in, R,
+                       out, B, C, Mm, chunk);
+  };
+  auto with = [&](auto sp, auto tr) { c32 ? launch(sp, tr, std::true_type{}) : launch(sp, tr, std::false_type{}); };
+  if (split && trans) with(std::true_type{}, std::true_type{});
+  else if (split) with(std::true_type{}, std::false_type{});
+  else if (trans) with(std::false_type{}, std::true_type{});
+  else with(std::false_type{}, std::false_type{});
+  return hipGetLastError();
+}
+
+hipError_t launch_nop_mode_transpose(const float* in, float* out, int B, int C, int Mm, hipStream_t s) {
   if (C > 32) return hipErrorInvalidValue;
   hipLaunchKernelGGL(nop_mode_transpose_kernel, dim3(blocks_for(static_cast<int64_t>(Mm) * Mm, 64), B), dim3(256), 0,
-                     s, in, out, B, C, Mm, to_block ? 1 : 0);
+                     s, in, out, B, C, Mm);
   return hipGetLastError();
 }
 
