@@ -888,13 +888,16 @@ __global__ __launch_bounds__(256) void nop_mix_kernel(const float* __restrict__ 
 
 // Register-resident form of the same product for O <= 32, I <= 32 and at most KT K-steps of modes (no D
 // term): each block walks `rpb` consecutive rows r = b H + h of up to 128 positions.  A, the bias and the
-// Cw columns of the block's positions are loaded once and kept in registers; bf16 T rows arrive as
-// 16-byte vectors when TVEC (Mm % 8 == 0).  Three register sets form a ring: the X and T operands of
+// Cw columns of the block's positions are loaded once and kept in registers; T rows arrive 16 bytes at a time with TVEC (Mm a
+// multiple of 8 in bf16, of 4 in FP32), two values at a time otherwise.  KF: 1 all 32 inputs, 2 at most 4 (the lift), 3 at most
+// 16, else 0; loads whose input no lane has are left out.  Three register sets form a ring: the X and T operands of
 // rows r + 1 and r + 2 are in flight while row r is multiplied and stored.
+// FP32 with 48 modes (batch 64, 32 channels, 128 x 128: 452 MB, 96 us at the rate of a large copy): T rows one value at a time,
+// 24 loads of 64 lines each a row, 167 us; now 103.
 // The MFMA sequence (X K-steps, then T K-steps, each hi/lo-split when split) is the one of
 // nop_mix_kernel, so both forms give the same bits.
 typedef unsigned u32x4r __attribute__((ext_vector_type(4)));
-template <typename TX, typename TY, typename TT, int KT, bool TVEC, bool SPLIT, bool KFULL>
+template <typename TX, typename TY, typename TT, int KT, bool TVEC, bool SPLIT, int KF>
 __global__ __launch_bounds__(256) void nop_mixrows_kernel(const float* __restrict__ A, const TX* __restrict__ X,
                                                           TY* __restrict__ Y, const float* __restrict__ bias,
                                                           float* __restrict__ pre, const TT* __restrict__ T,
@@ -959,9 +962,10 @@ __global__ __launch_bounds__(256) void nop_mixrows_kernel(const float* __restric
   constexpr bool XH = sizeof(TX) == 2;
   float xr[3][2][XH ? 1 : 8];
   bf16x8 xb[3][2];
-  u32x4r tr[3][KT > 0 ? KT : 1];
-  float te[3][KT > 0 ? KT : 1][TVEC ? 1 : 8];
-  static_assert(!TVEC || TS == 2, "16-byte T rows are read for bf16 storage only");
+  // a row of T (32 lanes 4 Mm or 2 Mm bytes apart) is read TW values at a time: lanes so far apart cost the address
+  // unit a line each per load
+  constexpr int TW = TVEC ? 16 / static_cast<int>(TS) : 2, TD = 2 * static_cast<int>(TS);
+  uint32_t td[3][KT > 0 ? KT : 1][TD];
   const uint32_t xlane = XS * static_cast<uint32_t>(kh * P + w);
   const uint32_t xlane_ok = xlane | (nok ? 0u : kOOB);
   const uint32_t tlane = TS * static_cast<uint32_t>(o * Mm + kh);
@@ -973,11 +977,16 @@ __global__ __launch_bounds__(256) void nop_mixrows_kernel(const float* __restric
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int k = 16 * c + kh + e;
+        if ((KF == 2 && 16 * c + e >= 4) || (KF == 3 && c == 1)) {   // no input there in any lane
+          if (XH) xb[set][c][e] = static_cast<__bf16>(0.f);
+          else xr[set][c][XH ? 0 : e] = 0.f;
+          continue;
+        }
         // with all 32 inputs present the per-lane offset is one register and the channel goes into the
         // scalar offset; otherwise each element carries its own range mask
         const uint32_t kst = XS * static_cast<uint32_t>((16 * c + e) * P);
-        const uint32_t off = KFULL ? xlane_ok : (xlane + kst) | ((nok && k < I) ? 0u : kOOB);
-        const uint32_t so = KFULL ? xrow + kst : xrow;
+        const uint32_t off = KF == 1 ? xlane_ok : (xlane + kst) | ((nok && k < I) ? 0u : kOOB);
+        const uint32_t so = KF == 1 ? xrow + kst : xrow;
         if (XH)
           xb[set][c][e] = __builtin_bit_cast(__bf16, __builtin_amdgcn_raw_buffer_load_b16(rX, off, so, 0));
         else
@@ -987,18 +996,21 @@ __global__ __launch_bounds__(256) void nop_mixrows_kernel(const float* __restric
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
       const int m0 = 16 * t + kh;
-      if (TVEC) {
-        const uint32_t off = (tlane + TS * 16u * t) | ((o < O && m0 < Mm) ? 0u : kOOB);
-        tr[set][t] = __builtin_bit_cast(u32x4r, __builtin_amdgcn_raw_buffer_load_b128(rT, off, trow, 0));
-      } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t off = (tlane + TS * static_cast<uint32_t>(16 * t + e)) | ((o < O && m0 + e < Mm) ? 0u : kOOB);
-          if (TS == 4)
-            te[set][t][TVEC ? 0 : e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rT, off, trow, 0));
-          else
-            te[set][t][TVEC ? 0 : e] = static_cast<float>(
-                __builtin_bit_cast(__bf16, __builtin_amdgcn_raw_buffer_load_b16(rT, off, trow, 0)));
+      for (int e = 0; e < 8; e += TW) {
+        const uint32_t off = (tlane + TS * static_cast<uint32_t>(16 * t + e)) | ((o < O && m0 + e < Mm) ? 0u : kOOB);
+        constexpr int D = TW * static_cast<int>(TS) / 4;
+        const int d = e * static_cast<int>(TS) / 4;
+        if constexpr (D == 4) {
+          const u32x4r v = __builtin_amdgcn_raw_buffer_load_b128(rT, off, trow, 0);
+#pragma unroll
+          for (int x = 0; x < 4; ++x) td[set][t][d + x] = v[x];
+        } else if constexpr (D == 2) {
+          const auto v = __builtin_amdgcn_raw_buffer_load_b64(rT, off, trow, 0);
+          td[set][t][d] = v[0];
+          td[set][t][d + 1] = v[1];
+        } else {
+          td[set][t][d] = __builtin_amdgcn_raw_buffer_load_b32(rT, off, trow, 0);
         }
       }
     }
@@ -1032,14 +1044,17 @@ __global__ __launch_bounds__(256) void nop_mixrows_kernel(const float* __restric
     for (int t = 0; t < KT; ++t) {
       if (t >= nts) break;
       bf16x8 th, tl;
-      if (TVEC) {   // bf16 storage: the loaded words are the hi operand, the lo part is zero
-        th = __builtin_bit_cast(bf16x8, tr[set][t]);
+      if constexpr (TS == 2) {   // bf16 storage: the loaded words are the hi operand, the lo part is zero
+        u32x4r w;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) w[x] = td[set][t][x];
+        th = __builtin_bit_cast(bf16x8, w);
 #pragma unroll
         for (int e = 0; e < 8; ++e) tl[e] = static_cast<__bf16>(0.f);
       } else {
         float tf[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) tf[e] = te[set][t][TVEC ? 0 : e];
+        for (int e = 0; e < 8; ++e) tf[e] = __builtin_bit_cast(float, td[set][t][e]);
         to_bf16x8(tf, th, tl, sp);
       }
       if (sp) {
@@ -1762,45 +1777,36 @@ void launch_mixrows_t(const float* A, bool transA, const void* X, void* Y, const
   const TT* t = static_cast<const TT*>(T);
   TY* y = static_cast<TY*>(Y);
   const int a = act ? 1 : 0, ta = transA ? 1 : 0;
-  // bf16 activations come with plain products only; the lift (FP32 features into bf16) has four inputs
+  // bf16 activations come with plain products only; the lift (four inputs) has no T
   constexpr bool half_act = sizeof(TX) == 2, lift = sizeof(TX) == 4 && sizeof(TY) == 2;
+  auto run = [&](auto sp, auto kf) {
+    hipLaunchKernelGGL((nop_mixrows_kernel<TX, TY, TT, KT, TVEC, decltype(sp)::value, decltype(kf)::value>), dim3(nblk), dim3(256), 0,
+                       s, A, x, y, bias, pre, t, Cw, O, I, H, W, Mm, B, rpb, a, ta);
+  };
+  auto with = [&](auto sp) {
+    if constexpr (!lift) {
+      if (I == 32) return run(sp, std::integral_constant<int, 1>{});
+    }
+    if constexpr (KT == 0) {
+      if (I <= 4) return run(sp, std::integral_constant<int, 2>{});
+    }
+    if (I <= 16) return run(sp, std::integral_constant<int, 3>{});
+    run(sp, std::integral_constant<int, 0>{});
+  };
   if constexpr (!half_act) {
-    if (split) {
-      if constexpr (!lift) {
-        if (I == 32) {
-          hipLaunchKernelGGL((nop_mixrows_kernel<TX, TY, TT, KT, TVEC, true, true>), dim3(nblk), dim3(256), 0, s, A, x,
-                             y, bias, pre, t, Cw, O, I, H, W, Mm, B, rpb, a, ta);
-          return;
-        }
-      }
-      hipLaunchKernelGGL((nop_mixrows_kernel<TX, TY, TT, KT, TVEC, true, false>), dim3(nblk), dim3(256), 0, s, A, x, y,
-                         bias, pre, t, Cw, O, I, H, W, Mm, B, rpb, a, ta);
-      return;
-    }
+    if (split) return with(std::true_type{});
   }
-  if constexpr (!lift) {
-    if (I == 32) {
-      hipLaunchKernelGGL((nop_mixrows_kernel<TX, TY, TT, KT, TVEC, false, true>), dim3(nblk), dim3(256), 0, s, A, x, y,
-                         bias, pre, t, Cw, O, I, H, W, Mm, B, rpb, a, ta);
-      return;
-    }
-  }
-  hipLaunchKernelGGL((nop_mixrows_kernel<TX, TY, TT, KT, TVEC, false, false>), dim3(nblk), dim3(256), 0, s, A, x, y,
-                     bias, pre, t, Cw, O, I, H, W, Mm, B, rpb, a, ta);
+  with(std::false_type{});
 }
 
 template <typename TX, typename TY, typename TT>
 void launch_mixrows(const float* A, bool transA, const void* X, void* Y, const float* bias, float* pre, const void* T,
                     const float* Cw, int Mm, int O, int I, int H, int W, int B, bool act, bool split, hipStream_t s) {
   const int kt = T ? (Mm + 15) / 16 : 0;
-  const bool vec = T && Mm % 8 == 0 && sizeof(TT) == 2;
+  const bool vec = T && Mm % (16 / sizeof(TT)) == 0 && (reinterpret_cast<uintptr_t>(T) & 15) == 0;
 #define PSTD_MIXROWS(KTV)                                                                                        \
-  if constexpr (sizeof(TT) == 2) {                                                                               \
-    if (vec) launch_mixrows_t<TX, TY, TT, KTV, true>(A, transA, X, Y, bias, pre, T, Cw, Mm, O, I, H, W, B, act, split, s); \
-    else launch_mixrows_t<TX, TY, TT, KTV, false>(A, transA, X, Y, bias, pre, T, Cw, Mm, O, I, H, W, B, act, split, s); \
-  } else {                                                                                                       \
-    launch_mixrows_t<TX, TY, TT, KTV, false>(A, transA, X, Y, bias, pre, T, Cw, Mm, O, I, H, W, B, act, split, s); \
-  }
+  if (vec) launch_mixrows_t<TX, TY, TT, KTV, true>(A, transA, X, Y, bias, pre, T, Cw, Mm, O, I, H, W, B, act, split, s); \
+  else launch_mixrows_t<TX, TY, TT, KTV, false>(A, transA, X, Y, bias, pre, T, Cw, Mm, O, I, H, W, B, act, split, s);
   switch (kt) {
     case 0: launch_mixrows_t<TX, TY, TT, 0, false>(A, transA, X, Y, bias, pre, T, Cw, Mm, O, I, H, W, B, act, split, s); break;
     case 1: PSTD_MIXROWS(1) break;
@@ -1824,7 +1830,7 @@ hipError_t launch_nop_mix(const float* A, bool transA, const void* X, void* Y, c
     const bool fits = static_cast<int64_t>(B) * I * P * xs < (int64_t(1) << 31) &&
                       static_cast<int64_t>(B) * O * P * 4 < (int64_t(1) << 31) &&
                       (!T || static_cast<int64_t>(B) * H * O * Mm * ts < (int64_t(1) << 31));
-    if (!D && I <= 32 && (!T || (Mm >= 1 && Mm <= 64)) && fits) {
+    if (!D && I <= 32 && (!T || (Mm >= 2 && Mm <= 64 && Mm % 2 == 0)) && fits) {
       typedef __bf16 bf;
       switch (act_types) {
         case 0: launch_mixrows<float, float, float>(A, transA, X, Y, bias, pre, T, Cw, Mm, O, I, H, W, B, act, split, s); break;
