@@ -214,12 +214,13 @@ __device__ __forceinline__ void run_wave(const FArgs& a, Stage<FMODE>& X, __bf16
     // a row step past a small field's end would wrap the range check; no lane's value lies there
     auto step = [&](int r) { return min(rr(r) * row_step, bytes); };
     constexpr bool kAhead = CONTIG || NW < 3;   // strided with 96 accumulators: 161 registers without, 182 with
-    float y[2][16], sc[16];
+    float y[2][16] = {}, sc[16];
     auto load_y = [&](int set, int i, int j) {
+      if (a.beta == 0.f) return;   // (the same for the whole grid)
 #pragma unroll
       for (int r = 0; r < 16; ++r) y[set][r] = ld_f32(rY, at(i, j, r), step(r));
     };
-    // the old values of the next block are on their way while this one is updated (read even where beta = 0 drops them)
+    // the old values of the next block are on their way while this one is updated
     if constexpr (kAhead) load_y(0, 0, 0);
 #pragma unroll
     for (int n = 0; n < NW * JL; ++n) {
