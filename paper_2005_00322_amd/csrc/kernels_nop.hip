@@ -1,11 +1,12 @@
 // Kernels of the DCT-basis neural-operator surrogate: one strided batched GEMM on the bf16 matrix
-// cores (FP32 accumulation) with fused epilogues, and the small elementwise/reduction kernels around it.
+// cores (FP32 accumulation), kernels for the products that a layer repeats, and the small elementwise/reduction
+// kernels around them.
 //
 // Every contraction of the network (the truncated DCT along each axis, the per-mode channel mixing, the
 // inverse DCT, the pointwise channel mixing, the lift and projection, and all their backward products)
-// is  C[z] = alpha A[z] B[z] (+ beta C[z])  with arbitrary element
-// strides, so one kernel serves all of them without transposes in HBM.  Operands are FP32 in HBM and
-// rounded to bf16 while they are staged into LDS; with `split` each operand is also kept as a bf16
+// is  C[z] = alpha A[z] B[z] (+ beta C[z])  with arbitrary element strides; the general kernel takes those that
+// have none of their own.  Operands are FP32 in HBM (inference: layer fields in bf16) and
+// rounded to bf16 while they are staged into LDS or registers; with `split` each operand is also kept as a bf16
 // remainder and the product is formed as hi*hi + hi*lo + lo*hi (close to FP32 accuracy; used by the
 // parity tests).
 //
