@@ -860,6 +860,27 @@ int pstd_test_line_spins(pstd_plan P, uint32_t spins) {
   return PSTD_OK;
 }
 
+// For tests (host only): taken[b] = how often a split-bf16 launch of M operator rows over `lines` lines computes row
+// block b (of (M + 31) / 32), by the rule that its kernel and launcher follow.
+int pstd_test_split_blocks(int32_t M, int64_t lines, int32_t* taken) {
+  if (M < 1 || lines < 1 || !taken) return fail(PSTD_E_INVALID_ARG, "bad argument");
+  const SplitTiles t = split_tiles(M, lines);
+  if (t.per_wave < 1 || t.per_wave > 3) return fail(PSTD_E_UNSUPPORTED, "%d row blocks per wave", t.per_wave);
+  for (int b = 0; b < t.rb; ++b) taken[b] = 0;
+  for (int tile = 0; tile < t.tiles; ++tile) {
+    const int first = split_first(t.rb, t.tiles, tile), blocks = split_first(t.rb, t.tiles, tile + 1) - first;
+    for (int wave = 0; wave < kSplitWaves; ++wave) {
+      const int computes = split_wave_blocks(blocks, wave) == t.per_wave ? t.per_wave : t.per_wave - 1;
+      for (int i = 0; i < computes; ++i) {
+        const int b = first + wave + kSplitWaves * i;
+        if (b >= t.rb) return fail(PSTD_E_INVALID_ARG, "row block %d past the operator", b);
+        ++taken[b];
+      }
+    }
+  }
+  return PSTD_OK;
+}
+
 int pstd_plan_get_operator(pstd_plan P, int32_t axis, int32_t which, double* out) {
   if (!P || !out) return fail(PSTD_E_INVALID_ARG, "null pointer");
   if (axis < 0 || axis >= P->ndim || which < 0 || which > 1) return fail(PSTD_E_INVALID_ARG, "bad axis/which");

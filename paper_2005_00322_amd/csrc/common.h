@@ -130,6 +130,20 @@ hipError_t launch_contract_fp64(const ContractArgs& a, bool contiguous, hipStrea
 // up to three FP32 / FP64 contractions with different outputs, beta = 1 and no map as one grid
 hipError_t launch_contract_multi(bool dbl, const ContractArgs* a, const bool* contiguous, int count, hipStream_t s);
 hipError_t launch_contract_split(const ContractArgs& a, bool contiguous, hipStream_t s);
+// How a split-bf16 launch deals out an operator's `rb` row blocks (of 32 rows) to its row tiles and their four waves.  Tile t
+// takes blocks [split_first(t), split_first(t + 1)), so tiles differ by one block at most and a wave has
+// `per_wave` of them or one fewer (a kernel knows both counts, no other).
+struct SplitTiles {
+  int rb, tiles, per_wave;
+  int64_t line_tiles;      // tiles of kSplitLines field lines
+};
+constexpr int kSplitLines = 64, kSplitWaves = 4;
+inline __host__ __device__ int split_first(int rb, int tiles, int tile) { return rb * tile / tiles; }
+// blocks wave, wave + 4, .. of a tile of `blocks`
+inline __host__ __device__ int split_wave_blocks(int blocks, int wave) {
+  return (blocks - wave + kSplitWaves - 1) / kSplitWaves;
+}
+SplitTiles split_tiles(int M, int64_t lines);
 // The 1D time loop of lines of at most kLineMaxNodes nodes.  work: step1d_work_bytes of device memory, zeroed
 // once, kept by the plan; spins: polls a workgroup makes for a half step's values before it gives up (the steps
 // then run in one workgroup).

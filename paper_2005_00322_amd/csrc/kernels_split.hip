@@ -31,7 +31,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int NT = 256, BK = 32, LD = BK + 8;      // LDS row stride in bf16: 80 bytes, conflict-free 16-byte accesses
-constexpr int JL = 2, LINES = 32 * JL;             // field lines of a block
+constexpr int JL = 2, LINES = kSplitLines;         // field lines of a block
+static_assert(LINES == 32 * JL && NT == 64 * kSplitWaves, "block shape");
 constexpr int PART = LINES * LD;                   // hi or lo part of a slice
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -52,7 +53,7 @@ struct FArgs {
   int64_t inner, lines, x_bstride, y_bstride;
   float alpha, beta;
   const float* scale;
-  int mtiles, rb_tile, rb; // operator row tiles, row blocks (of 32 rows) of a tile and of the operator
+  int mtiles, rb;          // operator row tiles and row blocks (of 32 rows)
 };
 
 // FMODE: 0 strided lines; 1 contiguous rows, lanes along k; 2 contiguous rows, 16-byte loads (aligned, K a multiple of 4).
@@ -242,12 +243,12 @@ __device__ __forceinline__ void run_wave(const FArgs& a, Stage<FMODE>& X, __bf16
   }
 }
 
-// NB: row blocks of the waves that have most; the others have one fewer (a branch per wave, not per product).
+// NB: row blocks of the waves that have most; the others have one fewer (SplitTiles; a branch per wave, not per product).
 template <int FMODE, int NB>
 __global__ __launch_bounds__(NT, 3) void split_kernel(FArgs a) {
   __shared__ __attribute__((aligned(16))) __bf16 lds[4 * PART];
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int rb0 = (tile % a.mtiles) * a.rb_tile;
+  const int mt = tile % a.mtiles, rb0 = split_first(a.rb, a.mtiles, mt);
   const int64_t l0 = static_cast<int64_t>(tile / a.mtiles) * LINES;
   Stage<FMODE> X;
   X.K = a.K;
@@ -267,29 +268,37 @@ __global__ __launch_bounds__(NT, 3) void split_kernel(FArgs a) {
   X.template store<true>(0, lds);
   X.load(1);
   lds_barrier();
-  const int rb = min(a.rb_tile, a.rb - rb0);                 // row blocks of this tile
-  const int mine = (rb - wave_index() + 3) / 4;
-  if (mine == NB) run_wave<FMODE, NB>(a, X, lds, rb0, l0);
-  else if constexpr (NB > 1) {
-    if (mine == NB - 1) run_wave<FMODE, NB - 1>(a, X, lds, rb0, l0);
-    else run_wave<FMODE, 0>(a, X, lds, rb0, l0);
-  } else {
-    run_wave<FMODE, 0>(a, X, lds, rb0, l0);
-  }
+  if (split_wave_blocks(split_first(a.rb, a.mtiles, mt + 1) - rb0, wave_index()) == NB) run_wave<FMODE, NB>(a, X, lds, rb0, l0);
+  else run_wave<FMODE, NB - 1>(a, X, lds, rb0, l0);
 }
 
 template <int FMODE>
-hipError_t launch_f(const FArgs& a, unsigned blocks, hipStream_t s) {
+hipError_t launch_f(const FArgs& a, int per_wave, unsigned blocks, hipStream_t s) {
   const dim3 grid(blocks), blk(NT);
-  switch ((a.rb_tile + 3) / 4) {
+  switch (per_wave) {
     case 1: hipLaunchKernelGGL((split_kernel<FMODE, 1>), grid, blk, 0, s, a); break;
     case 2: hipLaunchKernelGGL((split_kernel<FMODE, 2>), grid, blk, 0, s, a); break;
-    default: hipLaunchKernelGGL((split_kernel<FMODE, 3>), grid, blk, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((split_kernel<FMODE, 3>), grid, blk, 0, s, a); break;
+    default: return hipErrorInvalidConfiguration;
   }
   return hipGetLastError();
 }
 
 }  // namespace
+
+// All rows in one tile up to 384 (three row blocks per wave: 96 accumulators), so that the field is read once; shorter
+// row tiles where that leaves CUs without a block (256 x 256 plane: 10.5 us with all rows, 8.1 with 128;
+// 700 x 1000: 41 and 30; with 500 x 40 x 500, 313 blocks of all rows, 39.8 and 42.7).
+SplitTiles split_tiles(int M, int64_t lines) {
+  SplitTiles t;
+  t.rb = (M + 31) / 32;
+  t.line_tiles = (lines + kSplitLines - 1) / kSplitLines;
+  int most = 3 * kSplitWaves;
+  while (most > kSplitWaves && t.line_tiles * ((t.rb + most - 1) / most) < 256) most -= kSplitWaves;
+  t.tiles = (t.rb + most - 1) / most;
+  t.per_wave = ((t.rb + t.tiles - 1) / t.tiles + kSplitWaves - 1) / kSplitWaves;
+  return t;
+}
 
 hipError_t launch_contract_split(const ContractArgs& c, bool contiguous, hipStream_t s) {
   if (!c.frag || c.batch < 1 || c.ncols < 1 || c.M < 1 || c.K < 1) return hipErrorInvalidValue;
@@ -308,22 +317,17 @@ hipError_t launch_contract_split(const ContractArgs& c, bool contiguous, hipStre
   a.alpha = c.alpha;
   a.beta = c.beta;
   a.scale = static_cast<const float*>(c.scale);
-  a.rb = (c.M + 31) / 32;
-  // All rows in one block up to 384 (three row blocks per wave: 96 accumulators), so that the field is read once; shorter
-  // row tiles where that leaves CUs without a block (256 x 256 plane: 10.5 us with all rows, 8.1 with 128;
-  // 700 x 1000: 41 and 30; with 500 x 40 x 500, 313 blocks of all rows, 39.8 and 42.7).
-  const int64_t ltiles = (a.lines + LINES - 1) / LINES;
-  int most = 12;
-  while (most > 4 && ltiles * ((a.rb + most - 1) / most) < 256) most -= 4;
-  a.mtiles = (a.rb + most - 1) / most;
-  a.rb_tile = (a.rb + a.mtiles - 1) / a.mtiles;
-  const int64_t blocks = ltiles * a.mtiles;
+  const SplitTiles t = split_tiles(c.M, a.lines);
+  a.rb = t.rb;
+  a.mtiles = t.tiles;
+  const int64_t blocks = t.line_tiles * t.tiles;
   // 32-bit byte offsets from a block's first line: a whole field stays below 2 GiB (checked at plan creation)
   const int64_t xb = 4 * a.lines * c.K, yb = 4 * a.lines * c.M;
   if (blocks > 0x7fffffff || xb >= (int64_t(1) << 31) || yb >= (int64_t(1) << 31)) return hipErrorInvalidValue;
   const unsigned n = static_cast<unsigned>(blocks);
-  if (!contiguous) return launch_f<0>(a, n, s);
-  return c.K % 4 == 0 && (reinterpret_cast<uintptr_t>(c.X) & 15) == 0 ? launch_f<2>(a, n, s) : launch_f<1>(a, n, s);
+  if (!contiguous) return launch_f<0>(a, t.per_wave, n, s);
+  return c.K % 4 == 0 && (reinterpret_cast<uintptr_t>(c.X) & 15) == 0 ? launch_f<2>(a, t.per_wave, n, s)
+                                                                              : launch_f<1>(a, t.per_wave, n, s);
 }
 
 }  // namespace pstd
