@@ -860,6 +860,15 @@ int pstd_test_line_spins(pstd_plan P, uint32_t spins) {
   return PSTD_OK;
 }
 
+// For tests (host only): workgroups of a long line's time loop, their rows, and the words of u that they exchange.
+int pstd_test_line_shape(int32_t n, int32_t* workgroups, int32_t* rows, int32_t* u_words) {
+  if (n < 3 || !workgroups || !rows || !u_words) return fail(PSTD_E_INVALID_ARG, "bad argument");
+  *workgroups = line_workgroups(n);
+  *rows = kLineRows;
+  *u_words = line_u_words(n);
+  return PSTD_OK;
+}
+
 // For tests (host only): taken[b] = how often a split-bf16 launch of M operator rows over `lines` lines computes row
 // block b (of (M + 31) / 32), by the rule that its kernel and launcher follow.
 int pstd_test_split_blocks(int32_t M, int64_t lines, int32_t* taken) {

@@ -149,6 +149,10 @@ SplitTiles split_tiles(int M, int64_t lines);
 // then run in one workgroup).
 constexpr int kLineMaxNodes = 1365;
 constexpr unsigned kLineSpins = 1u << 16;
+// Its workgroups, of kLineRows rows each, and the words of u that they exchange (n of p): every workgroup owns some of both.
+constexpr int kLineRows = 16;
+inline __host__ __device__ int line_workgroups(int n) { return (n + kLineRows - 1) / kLineRows; }
+inline __host__ __device__ int line_u_words(int n) { return n; }
 size_t step1d_work_bytes(int prec, int n);
 hipError_t launch_step1d(int prec, const DevOperator& G, const DevOperator& D, void* p, void* u, int n,
                          int64_t steps, const void* scale, void* work, unsigned spins, hipStream_t s);

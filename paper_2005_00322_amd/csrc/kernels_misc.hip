@@ -66,7 +66,9 @@ __device__ void step1d_one_block(const T* __restrict__ GT, int ldg, const T* __r
 // CUs: a value travels as one 64-bit word holding the float and the half step's number (FP64: two words with half
 // the bits each), so readers poll the values themselves and no barrier, fence or second round trip is needed.
 // A buffer per field is enough: a workgroup publishes step t + 1 of a field only after it has read all of
-// the other field, each value of which was published after its owner had read all of step t.
+// the other field, each value of which was published after its owner had read all of step t.  That holds a reader's
+// values only if it owns a word of the other field itself, so u has n words too, the last of them a zero: with n - 1 the last
+// workgroup of n = 16 m + 1 nodes owns row n - 1 of p alone, and nobody waits for it before p moves on.
 // n = 1000, FP32 with a map, 50 steps: 25.5 ms in one workgroup, 0.265 ms here (2.5 us per half step).
 //
 // The workgroups have to be resident together.  A wait is bounded: a workgroup that gives up sets
@@ -77,7 +79,7 @@ __device__ void step1d_one_block(const T* __restrict__ GT, int ldg, const T* __r
 struct LineHead {
   unsigned epoch, abort;
 };
-constexpr int kLineThreads = 512, kLineRows = 16;
+constexpr int kLineThreads = 32 * kLineRows;
 
 template <typename T>
 __device__ __forceinline__ void line_publish(unsigned long long* x, int n, int i, T v, unsigned tag) {
@@ -193,8 +195,8 @@ __global__ __launch_bounds__(kLineThreads) void step1d_multi_kernel(const T* __r
     }
     ui = static_cast<T>(static_cast<double>(ui) + dot(g, sp));
     ++tag;
-    if (l == 0 && i < nm) line_publish<T>(xu, n, i, ui, tag);
-    if (!line_gather<T, PER>(xu, n, nm, tag, su, spins)) gave_up[1] = 1;
+    if (l == 0 && i < line_u_words(n)) line_publish<T>(xu, n, i, i < nm ? ui : T(0), tag);
+    if (!line_gather<T, PER>(xu, n, line_u_words(n), tag, su, spins)) gave_up[1] = 1;
     __syncthreads();
     if ((stop = gave_up[1] != 0)) break;
     pi = static_cast<T>(static_cast<double>(pi) + dot(d, su) * sc);
@@ -417,7 +419,7 @@ hipError_t launch_step1d_t(int prec, const DevOperator& Go, const DevOperator& D
   unsigned long long* xu = xp + line_words(prec, n);
   T* po = reinterpret_cast<T*>(xu + line_words(prec, n));
   T* uo = po + n;
-  const dim3 grid((n + kLineRows - 1) / kLineRows), blk(kLineThreads);
+  const dim3 grid(line_workgroups(n)), blk(kLineThreads);
 #define PSTD_LINE(KPL)                                                                                                \
   hipLaunchKernelGGL((step1d_multi_kernel<T, KPL>), grid, blk, 0, s, G, Go.Kp, D, Do.Kp, p, u, n, steps, scale, head, \
                      xp, xu, po, uo, spins)
