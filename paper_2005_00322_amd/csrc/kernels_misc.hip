@@ -231,6 +231,56 @@ __global__ __launch_bounds__(1024) void step1d_commit_kernel(const T* __restrict
   for (int i = threadIdx.x; i < n - 1; i += blockDim.x) u[i] = u_out[i];
 }
 
+// A single step of a line of at most kOnceNodes nodes in one workgroup: half wave w takes rows w, w + 32, .., the sums in the
+// order of step1d_multi_kernel's (so a call of one step and one of many give the same bits).  A call of one step is bound by
+// its launches and one round trip for the operators; the two launches of the general path cost more than they spread.
+constexpr int kOnceNodes = 160, kOnceRows = kOnceNodes / 32;
+
+template <typename T>
+__global__ __launch_bounds__(1024) void step1d_once_kernel(const T* __restrict__ G, int ldg, const T* __restrict__ D, int ldd,
+                                                           T* __restrict__ p, T* __restrict__ u, int n,
+                                                           const T* __restrict__ scale) {
+  __shared__ double sp[kOnceNodes], su[kOnceNodes];
+  const int tid = threadIdx.x, l = tid & 31, w = tid >> 5, nm = n - 1;
+  T g[kOnceRows][kOnceRows], d[kOnceRows][kOnceRows];   // [row][column l + 32 k]
+#pragma unroll
+  for (int r = 0; r < kOnceRows; ++r)
+#pragma unroll
+    for (int k = 0; k < kOnceRows; ++k) {
+      const int i = w + 32 * r, c = l + 32 * k;
+      g[r][k] = (i < nm && c < n) ? G[static_cast<int64_t>(i) * ldg + c] : T(0);
+      d[r][k] = (i < n && c < nm) ? D[static_cast<int64_t>(i) * ldd + c] : T(0);
+    }
+  if (tid < kOnceNodes) {
+    sp[tid] = tid < n ? static_cast<double>(p[tid]) : 0.0;
+    su[tid] = 0.0;
+  }
+  auto dot = [&](const T (&a)[kOnceRows], const double* x) {
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < kOnceRows; ++k) acc[k & 3] = fma(static_cast<double>(a[k]), x[l + 32 * k], acc[k & 3]);
+    return half_wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
+  };
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kOnceRows; ++r) {
+    const int i = w + 32 * r;
+    const double s = dot(g[r], sp);
+    if (l == 0 && i < nm) {
+      const T v = static_cast<T>(static_cast<double>(u[i]) + s);
+      u[i] = v;
+      su[i] = static_cast<double>(v);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kOnceRows; ++r) {
+    const int i = w + 32 * r;
+    const double s = dot(d[r], su);
+    if (l == 0 && i < n) p[i] = static_cast<T>(sp[i] + s * (scale ? static_cast<double>(scale[i]) : 1.0));
+  }
+}
+
 // The whole time loop of a line of n <= 128 nodes in one workgroup, both operators in registers for all steps:
 // thread t owns row t / 8 of each operator and its 16 entries in columns t % 8 + 8 j, so a step reads no
 // global memory and the eight addresses that a wave reads from the state in LDS lie in different banks.  A row's
@@ -410,6 +460,12 @@ hipError_t launch_step1d_t(int prec, const DevOperator& Go, const DevOperator& D
   const T *G = static_cast<const T*>(Go.data), *D = static_cast<const T*>(Do.data);
   if (n <= 128) {
     hipLaunchKernelGGL(step1d_reg_kernel<T>, dim3(1), dim3(1024), 0, s, G, Go.Kp, D, Do.Kp, p, u, n, steps, scale);
+    return hipGetLastError();
+  }
+  // one step, us a call with this kernel / with the two launches below: 130 nodes 8.8 / 11.5 (FP32), 7.9 / 12.1 (FP64), 160
+  // nodes 9.5 / 11.8, 8.9 / 11.2; beyond, the rows of a sixth pass would not fit the registers
+  if (steps == 1 && n <= kOnceNodes) {
+    hipLaunchKernelGGL(step1d_once_kernel<T>, dim3(1), dim3(1024), 0, s, G, Go.Kp, D, Do.Kp, p, u, n, scale);
     return hipGetLastError();
   }
   const size_t shmem = ((sizeof(T) * 2 * static_cast<size_t>(n) + 7) & ~static_cast<size_t>(7)) + 8 * static_cast<size_t>(4) * n;
