@@ -112,7 +112,10 @@ int pstd_state_init(pstd_plan plan, pstd_state* state, int32_t u_mode);
  * p^n first, then p^{n+1} from all u_a^{n+1/2}.  Asynchronous on the plan's stream.  The steps replay
  * captured HIP graphs (whole chunks of 50 steps, then one graph of the remaining steps; 1D plans of at most
  * 1365 nodes with walls on nodes run the whole call in one or two kernels instead); a graph is captured on first use for the
- * state's buffers and kept by the plan (one full-chunk graph and one of the last other length). */
+ * state's buffers and kept by the plan (one full-chunk graph and one of the last other length).
+ * Calls of 1D plans of 129 to 1365 nodes use a workspace of the plan.  Recorded by the caller into graphs of its own, the
+ * calls of one capture share one; a plan's first seven captures have one each, so their replays may overlap
+ * (on different states); the calls of further captures run in one workgroup, without a workspace and slowly. */
 int pstd_step(pstd_plan plan, pstd_state* state, int64_t n_steps);
 
 /* Capture, without running anything, the graphs a later pstd_step(plan, state, n_steps) replays, so that

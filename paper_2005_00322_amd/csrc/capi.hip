@@ -210,10 +210,33 @@ int prepare_axes(pstd_plan_s* P) {
     }
   const size_t wb = use_step1d(P) && !P->line_work ? step1d_work_bytes(P->prec, static_cast<int>(P->n[0])) : 0;
   if (wb) {
-    if (hipMalloc(&P->line_work, wb) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of the 1D workspace failed");
-    PSTD_HIP(hipMemset(P->line_work, 0, wb));
+    if (hipMalloc(&P->line_work, kLineSlots * wb) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of the 1D workspaces failed");
+    PSTD_HIP(hipMemset(P->line_work, 0, kLineSlots * wb));
     PSTD_HIP(hipStreamSynchronize(nullptr));
   }
+  return PSTD_OK;
+}
+
+// The workspace of a pstd_step call on a line: the plan's own, or that of the capture the call is recorded into.  The calls
+// of one capture follow one another, but replays of different captures may run at the same time, so each has a
+// workspace to itself while there are some left, and none after that (*work null).
+int line_workspace(pstd_plan_s* P, void** work) {
+  *work = P->line_work;
+  if (!P->line_work || !P->stream) return PSTD_OK;   // (the null stream cannot be captured)
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  PSTD_HIP(hipStreamGetCaptureInfo(P->stream, &st, &id));
+  if (st != hipStreamCaptureStatusActive) return PSTD_OK;
+  int slot = 0;
+  while (slot < P->line_captures && P->line_capture[slot] != id) ++slot;
+  if (slot == P->line_captures) {
+    if (slot == kLineSlots - 1) {
+      *work = nullptr;
+      return PSTD_OK;
+    }
+    P->line_capture[P->line_captures++] = id;
+  }
+  *work = static_cast<unsigned char*>(P->line_work) + (slot + 1) * step1d_work_bytes(P->prec, static_cast<int>(P->n[0]));
   return PSTD_OK;
 }
 
@@ -609,8 +632,11 @@ int pstd_step(pstd_plan P, pstd_state* st, int64_t n_steps) {
   const int pst = prepare_axes(P);
   if (pst != PSTD_OK) return pst;
   if (use_step1d(P)) {
+    void* work = nullptr;
+    const int wst = line_workspace(P, &work);
+    if (wst != PSTD_OK) return wst;
     PSTD_HIP(launch_step1d(P->prec, P->G[0], P->D[0], st->p, st->u[0], static_cast<int>(P->n[0]), n_steps,
-                           P->c2map, P->line_work, P->line_spins, P->stream));
+                           P->c2map, work, P->line_spins, P->stream));
     st->step += n_steps;
     return PSTD_OK;
   }
@@ -859,6 +885,9 @@ int pstd_test_line_spins(pstd_plan P, uint32_t spins) {
   P->line_spins = spins;
   return PSTD_OK;
 }
+
+// For tests: captures of a long line's steps that have a workspace of their own.
+int pstd_test_line_captures(pstd_plan P) { return P ? P->line_captures : -1; }
 
 // For tests (host only): workgroups of a long line's time loop, their rows, and the words of u that they exchange.
 int pstd_test_line_shape(int32_t n, int32_t* workgroups, int32_t* rows, int32_t* u_words) {

@@ -145,9 +145,12 @@ inline __host__ __device__ int split_wave_blocks(int blocks, int wave) {
 }
 SplitTiles split_tiles(int M, int64_t lines);
 // The 1D time loop of lines of at most kLineMaxNodes nodes.  work: step1d_work_bytes of device memory, zeroed
-// once, kept by the plan; spins: polls a workgroup makes for a half step's values before it gives up (the steps
-// then run in one workgroup).
+// once, kept by the plan, for calls that run one after another (null: all steps in one workgroup, which needs
+// none); spins: polls a workgroup makes for a half step's values before it gives up (the steps then run in one workgroup).
 constexpr int kLineMaxNodes = 1365;
+// Workspaces of a plan: one for its own calls, which its stream orders, and one for each of the first captures that its caller
+// makes of them, whose replays no stream orders (at most 70 KB each).
+constexpr int kLineSlots = 8;
 constexpr unsigned kLineSpins = 1u << 16;
 // Its workgroups, of kLineRows rows each, and the words of u that they exchange (n of p): every workgroup owns some of both.
 constexpr int kLineRows = 16;
@@ -361,7 +364,9 @@ struct pstd_plan_s {
   pstd::FftAxis fft[3];
   void* c2map = nullptr;       // c0(x)^2 in the state dtype (owned), null for a homogeneous medium
   int* flag = nullptr;         // device int for reductions (owned)
-  void* line_work = nullptr;   // 1D plans of 129 .. kLineMaxNodes nodes: workspace of launch_step1d (owned)
+  void* line_work = nullptr;   // 1D plans of 129 .. kLineMaxNodes nodes: kLineSlots workspaces of launch_step1d (owned)
+  unsigned long long line_capture[pstd::kLineSlots - 1] = {};   // captures that have slots 1, 2, ..
+  int line_captures = 0;
   unsigned line_spins = pstd::kLineSpins;
   int path = 0;                // PSTD_PATH_* (0 = automatic)
   bool stored = false;         // path "stored": split-bf16 contractions with the operators as rounded from FP64

@@ -12,7 +12,7 @@ namespace {
 // c0(x)^2 when a sound-speed map is given).  Threads split every dot product 4 ways; the sums and the
 // update are formed in FP64 for both state types and rounded once into the state.  One CU reads its
 // operators at well under the L2 rate (n = 1000, FP32: 509 us per step), so this is only the fallback of
-// step1d_multi_kernel below.
+// step1d_multi_kernel below, and for calls without a workspace.
 template <typename T>
 __device__ void step1d_one_block(const T* __restrict__ GT, int ldg, const T* __restrict__ DT, int ldd, T* __restrict__ p,
                                  T* __restrict__ u, int n, int64_t steps, const T* __restrict__ scale) {
@@ -229,6 +229,14 @@ __global__ __launch_bounds__(1024) void step1d_commit_kernel(const T* __restrict
   }
   for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = p_out[i];
   for (int i = threadIdx.x; i < n - 1; i += blockDim.x) u[i] = u_out[i];
+}
+
+// All steps in one workgroup, without a workspace.
+template <typename T>
+__global__ __launch_bounds__(1024) void step1d_one_kernel(const T* __restrict__ GT, int ldg, const T* __restrict__ DT, int ldd,
+                                                          T* __restrict__ p, T* __restrict__ u, int n, int64_t steps,
+                                                          const T* __restrict__ scale) {
+  step1d_one_block<T>(GT, ldg, DT, ldd, p, u, n, steps, scale);
 }
 
 // A single step of a line of at most kOnceNodes nodes in one workgroup: half wave w takes rows w, w + 32, .., the sums in the
@@ -469,7 +477,12 @@ hipError_t launch_step1d_t(int prec, const DevOperator& Go, const DevOperator& D
     return hipGetLastError();
   }
   const size_t shmem = ((sizeof(T) * 2 * static_cast<size_t>(n) + 7) & ~static_cast<size_t>(7)) + 8 * static_cast<size_t>(4) * n;
-  if (shmem > 64 * 1024 || !work || n > kLineMaxNodes) return hipErrorInvalidConfiguration;
+  if (shmem > 64 * 1024 || n > kLineMaxNodes) return hipErrorInvalidConfiguration;
+  if (!work) {
+    hipLaunchKernelGGL(step1d_one_kernel<T>, dim3(1), dim3(1024), shmem, s, static_cast<const T*>(Go.dataT), Go.Mp,
+                       static_cast<const T*>(Do.dataT), Do.Mp, p, u, n, steps, scale);
+    return hipGetLastError();
+  }
   LineHead* head = static_cast<LineHead*>(work);
   unsigned long long* xp = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(work) + 256);
   unsigned long long* xu = xp + line_words(prec, n);
@@ -496,7 +509,7 @@ hipError_t launch_step1d_t(int prec, const DevOperator& Go, const DevOperator& D
 
 size_t step1d_work_bytes(int prec, int n) {
   if (n <= 128) return 0;
-  return 256 + 2 * line_words(prec, n) * 8 + 2 * static_cast<size_t>(prec == PSTD_FP64 ? 8 : 4) * n;
+  return round_up(256 + 2 * line_words(prec, n) * 8 + 2 * static_cast<size_t>(prec == PSTD_FP64 ? 8 : 4) * n, 256);
 }
 
 hipError_t launch_step1d(int prec, const DevOperator& G, const DevOperator& D, void* p, void* u, int n,
