@@ -24,10 +24,13 @@ namespace {
 
 constexpr int NT = 256;
 
+// FP32 sums of 16 k in 32-wide tiles and of 32 k in 64-wide ones
+template <int MT> using BatchTile = Tile<float, MT, MT>;
+
 // PH 0: a velocity tile (T.kind 0 or 1), PH 1: a pressure tile (T.kind 2).
 template <int MT, int PH>
 __device__ __forceinline__ void run_task(const BatchSolve& S, const BatchTask& T, float* lds) {
-  typedef Tile<float, MT> TL;
+  typedef BatchTile<MT> TL;
   const int lane = threadIdx.x & 63;
   const int nx = S.nx, ny = S.ny, i0 = T.i0, j0 = T.j0;
   float* const Y = PH == 1 ? S.p : T.kind == 0 ? S.ux : S.uy;
@@ -118,7 +121,7 @@ __device__ __forceinline__ void run_task(const BatchSolve& S, const BatchTask& T
 template <int TILE, int PH>
 __global__ __launch_bounds__(NT, TILE == 64 ? 3 : 6) void batch2d_kernel(const BatchSolve* __restrict__ solves,
                                                         const BatchTask* __restrict__ tasks, BatchRuns runs) {
-  __shared__ __attribute__((aligned(16))) float lds[Tile<float, TILE / 32>::lds_values];
+  __shared__ __attribute__((aligned(16))) float lds[BatchTile<TILE / 32>::lds_values];
   const int q = blockIdx.x % kBatchQueues, t = runs.beg[q] + static_cast<int>(blockIdx.x) / kBatchQueues;
   if (t >= runs.beg[q + 1]) return;
   const BatchTask T = tasks[t];

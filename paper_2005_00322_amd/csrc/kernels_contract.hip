@@ -24,6 +24,9 @@
 namespace pstd {
 namespace {
 
+// FP32 sums of one chunk, 16 k
+template <typename T, int MT> using ContractTile = Tile<T, MT, 1>;
+
 template <typename T>
 struct KArgs {
   const T* op;          // operator fragments
@@ -40,7 +43,7 @@ struct KArgs {
 // PLAIN: beta = 1 and no map (the velocity update).
 template <typename T, bool ROWS, int MT, bool PLAIN>
 __device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* lds) {
-  typedef Tile<T, MT> TL;
+  typedef ContractTile<T, MT> TL;
   const int m0 = (tile % a.mtiles) * TL::E;
   const int64_t l0 = static_cast<int64_t>(tile / a.mtiles) * TL::E;
   constexpr uint32_t ES = sizeof(T);
@@ -133,14 +136,16 @@ __device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* ld
 
 template <typename T, bool ROWS, int MT>
 __global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_kernel(KArgs<T> a) {
-  __shared__ __attribute__((aligned(16))) T lds[Tile<T, MT>::lds_values];
+  __shared__ __attribute__((aligned(16))) T lds[ContractTile<T, MT>::lds_values];
   contract_tile<T, ROWS, MT, false>(a, xcd_tile(blockIdx.x, gridDim.x), lds);
 }
 
 // Up to three contractions (beta = 1, no map) with outputs of their own in one grid (the velocity terms of a step: all read p), so that
 // the partly filled last round of blocks comes once instead of once per axis.  tiles[i]: tiles of contraction i; every
 // XCD takes its run of each contraction's tiles in turn (xcd_tile; the counts are rounded up to whole rounds of the
-// XCDs by blocks that end at once).  161 x 200 x 129 FP32: a step of 184 us with one launch per axis takes 178.
+// XCDs by blocks that end at once).  161 x 200 x 129 FP32: a step of 184 us with one launch per axis takes 178 (with FP32 sums
+// of 32 k; 190 with 16).  Three waves per SIMD for 64-wide tiles: with four the two forms of the tile in one kernel leave no
+// register free (192).
 template <typename T>
 struct MultiArgs {
   KArgs<T> a[3];
@@ -148,8 +153,8 @@ struct MultiArgs {
 };
 
 template <typename T, int MT>
-__global__ __launch_bounds__(256, MT == 2 ? 4 : 6) void contract_multi_kernel(MultiArgs<T> m) {
-  __shared__ __attribute__((aligned(16))) T lds[Tile<T, MT>::lds_values];
+__global__ __launch_bounds__(256, MT == 2 ? 3 : 6) void contract_multi_kernel(MultiArgs<T> m) {
+  __shared__ __attribute__((aligned(16))) T lds[ContractTile<T, MT>::lds_values];
   int b = blockIdx.x;
   for (int i = 0; i < m.count; ++i) {
     const int n = (m.tiles[i] + 7) & ~7;

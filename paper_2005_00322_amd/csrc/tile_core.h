@@ -11,9 +11,10 @@
 //     non-finite value times zero would not be);
 //   - one barrier per slice of 128 bytes of k: slice s + 1 is written while slice s is multiplied, the loads of
 //     s + 2 are in flight.
-// FP32 products are summed on the MFMA for one chunk (16 k), the two chunks of a slice added, and that sum added to FP64
-// registers (every chunk on its own: 10% slower, the FP64 adds take the issue slots of other waves' MFMAs): a long FP32 sum of the
-// cancelling terms of a spectral derivative loses more than the rounding of operator and state together.
+// FP32 products are summed on the MFMA for one chunk (16 k), and FL chunks (1 or 2) are added to FP64 registers at a time:
+// a long FP32 sum of the cancelling terms of a spectral derivative loses more than the rounding of operator and
+// state together.  The FP64 adds of FL = 1 take issue slots of other waves' MFMAs (161 x 200 x 129: 180 us per step with
+// FL = 2, 190 with FL = 1; held back one chunk, to issue among its own wave's MFMAs, they cost 16 more registers and no less time).
 //
 // MFMA v_mfma_{f32,f64}_16x16x4: lane l supplies P[l%16][l/16] and Q[l%16][l/16] and receives C[4*(l/16)+r][l%16]
 // (f32) or C[4*r+l/16][l%16] (f64) in register r (measured on gfx950).  A lane holds the k 4 e + l / 16, e < 4, of a
@@ -70,9 +71,10 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
   return x * q + min(x, r) + (b >> 3);
 }
 
-// A tile of edge 32 MT: four waves of (16 MT) x (16 MT) outputs, MT x MT MFMA blocks each.
-template <typename T, int MT>
+// A tile of edge 32 MT: four waves of (16 MT) x (16 MT) outputs, MT x MT MFMA blocks each.  FL: chunks of an FP32 sum.
+template <typename T, int MT, int FL>
 struct Tile {
+  static_assert(FL == 1 || FL == 2, "chunks of an FP32 sum");
   typedef typename Mma<T>::v4 v4;
   static constexpr int E = 32 * MT, NT = 256;
   static constexpr int BK = 128 / static_cast<int>(sizeof(T)), V = 16 / static_cast<int>(sizeof(T));
@@ -180,6 +182,15 @@ struct Tile {
       X.template store<true>(0, lds, x0);
       lds_barrier();
     }
+    constexpr bool kEach = sizeof(T) == 4 && FL == 1;   // every chunk's sum goes to the accumulators by itself
+    auto add = [&](const v4 (&c)[MT][MT]) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[i][j][r] += static_cast<double>(c[i][j][r]);
+    };
     auto slice = [&](int s, auto last) {
       constexpr bool kLast = decltype(last)::value;
       const int buf = (s & 1) * (E * LD);
@@ -190,7 +201,7 @@ struct Tile {
         else X.template store<true>(s + 1, lds + (E * LD - buf), xr);
         X.load(s + 2, xr);
       }
-      v4 part[MT][MT];   // the slice's sum (FP64: the accumulators themselves)
+      v4 part[MT][MT];   // the slice's sum (FP64: the accumulators themselves; kEach: unused)
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         if (kLast && s * CH + c >= nch) break;
@@ -211,21 +222,27 @@ struct Tile {
             for (int j = 0; j < MT; ++j)
               c4[i][j] = ROWS ? Mma<T>::mma(x[i][e], A[c][j][e], c4[i][j]) : Mma<T>::mma(A[c][i][e], x[j][e], c4[i][j]);
         if constexpr (!kLast) load_op(c, (s + 1) * CH + c);
+        if constexpr (kEach) {
+          add(c4);
+        } else {
+#pragma unroll
+          for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) part[i][j][r] = c == 0 ? c4[i][j][r] : part[i][j][r] + c4[i][j][r];
+        }
+      }
+      if constexpr (sizeof(T) == 8) {
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
           for (int j = 0; j < MT; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) part[i][j][r] = c == 0 ? c4[i][j][r] : part[i][j][r] + c4[i][j][r];
+            for (int r = 0; r < 4; ++r) acc[i][j][r] = static_cast<double>(part[i][j][r]);
+      } else if constexpr (!kEach) {
+        add(part);
       }
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < MT; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            acc[i][j][r] =
-                sizeof(T) == 8 ? static_cast<double>(part[i][j][r]) : acc[i][j][r] + static_cast<double>(part[i][j][r]);
       if constexpr (!kLast) lds_barrier();
     };
     if (idle) {   // a loop of its own: a test inside the products' loop costs every wave its schedule
