@@ -40,3 +40,17 @@ def test_per_axis_contractions_sum_16_products(shape, phase):
         for near, far in ((0, 16), (47, 48), (64, 95)):
             got, want = _residues(plan, axis, near, far, phase)
             assert torch.equal(got, want), (near, far)
+
+
+@pytest.mark.parametrize("shape", [(200, 130), (130, 200), (512, 300), (300, 512), (400, 400)])
+def test_fused_phases_sum_8_products(shape):
+    import torch
+    from paper_2005_00322_amd import Plan
+
+    print("partial sums", shape, flush=True)
+    with Plan(shape, workloads.DX, 0.2 * workloads.DX / 1500.0, 1500.0, ((0, 0),) * 2) as plan:
+        plan.set_path("fused")
+        for axis in range(2):
+            for near, far in ((0, 8), (7, 15), (16, 25), (33, 56), (64, 72)):
+                got, want = _residues(plan, axis, near, far, True)
+                assert torch.equal(got, want), (axis, near, far)
