@@ -28,6 +28,57 @@ int fail(int status, const char* fmt, ...) {
   return status;
 }
 
+// Operators go into one allocation and one copy up to this size: three axes of 161, 200 and 129 nodes take 160 us so and 220 with
+// one each; an allocation of more than 1 MB costs 25 us more than two smaller ones.
+constexpr size_t kOneAllocation = 1 << 20;
+
+template <typename T>
+int upload_plain(const OperatorSource* src, int count, int copies) {
+  size_t total = 0;
+  for (int i = 0; i < count; ++i) {
+    DevOperator& op = *src[i].op;
+    op.M = src[i].M;
+    op.K = src[i].K;
+    op.Mp = static_cast<int>(round_up(op.M, kRowPad));
+    op.Kp = static_cast<int>(round_up(op.K, kColPad));
+    total += (1 + copies) * static_cast<size_t>(op.Mp) * op.Kp;
+  }
+  if (count > 1 && total * sizeof(T) > kOneAllocation) {
+    for (int i = 0; i < count; ++i) {
+      const int st = upload_plain<T>(src + i, 1, copies);
+      if (st != PSTD_OK) return st;
+    }
+    return PSTD_OK;
+  }
+  const HostZeros<T> host(total);
+  if (!host.get()) return fail(PSTD_E_OOM, "no host memory for the operators");
+  T* h = host.get();
+  for (int i = 0; i < count; ++i) {
+    const DevOperator& op = *src[i].op;
+    const size_t cnt = static_cast<size_t>(op.Mp) * op.Kp;
+    fill_operator(src[i].m->data(), op.M, op.K, src[i].scale, op.Mp, op.Kp, h, copies >= 1 ? h + cnt : nullptr,
+                  copies >= 2 ? h + 2 * cnt : nullptr);
+    h += (1 + copies) * cnt;
+  }
+  void* data = nullptr;
+  if (hipMalloc(&data, total * sizeof(T)) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of the operators failed");
+  src[0].op->data = data;
+  PSTD_HIP(hipMemcpy(data, host.get(), total * sizeof(T), hipMemcpyHostToDevice));
+  T* d = static_cast<T*>(data);
+  for (int i = 0; i < count; ++i) {
+    DevOperator& op = *src[i].op;
+    const size_t cnt = static_cast<size_t>(op.Mp) * op.Kp;
+    op.bytes = (1 + copies) * cnt * sizeof(T);
+    op.frag = d;
+    if (copies >= 1) op.rows = d + cnt;
+    if (copies >= 2) op.cols = d + 2 * cnt;
+    d += (1 + copies) * cnt;
+  }
+  return PSTD_OK;
+}
+template int upload_plain<float>(const OperatorSource*, int, int);
+template int upload_plain<double>(const OperatorSource*, int, int);
+
 namespace {
 
 uint16_t bf16_rne(float f) {
@@ -50,42 +101,13 @@ inline size_t split_fragment_at(int Kp, unsigned i, unsigned k) {
   return static_cast<size_t>((i >> 5) * (static_cast<unsigned>(Kp) >> 4) + (k >> 4)) * 1024 + (i & 31) * 8 + (k & 8) * 32 + (k & 7);
 }
 
-// Round the FP64 matrix (M x K, already scaled) to the plan precision and upload it zero padded, row-major and in
-// fragment order.
-int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, double scale, DevOperator* op) {
+// The matrix m (M x K) times scale as a split operator, uploaded in fragment order.
+int upload_split(const std::vector<double>& m, int M, int K, double scale, DevOperator* op) {
   op->M = M;
   op->K = K;
   op->Mp = static_cast<int>(round_up(M, kRowPad));
   op->Kp = static_cast<int>(round_up(K, kColPad));
   const size_t cnt = static_cast<size_t>(op->Mp) * op->Kp;
-  const bool want_t = (P->ndim == 1);
-  if (P->prec == PSTD_FP64 || P->prec == PSTD_FP32) {
-    const size_t esz = P->prec == PSTD_FP64 ? 8 : 4;
-    std::vector<unsigned char> host(cnt * esz, 0), hostT(want_t ? cnt * esz : 0, 0);
-    for (int i = 0; i < M; ++i)
-      for (int k = 0; k < K; ++k) {
-        const double v = scale * m[static_cast<size_t>(i) * K + k];
-        const size_t a = static_cast<size_t>(i) * op->Kp + k;
-        const size_t t = static_cast<size_t>(k) * op->Mp + i;
-        if (esz == 8) {
-          reinterpret_cast<double*>(host.data())[a] = v;
-          if (want_t) reinterpret_cast<double*>(hostT.data())[t] = v;
-        } else {
-          reinterpret_cast<float*>(host.data())[a] = static_cast<float>(v);
-          if (want_t) reinterpret_cast<float*>(hostT.data())[t] = static_cast<float>(v);
-        }
-      }
-    if (hipMalloc(&op->data, 2 * cnt * esz) != hipSuccess)
-      return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
-    PSTD_HIP(hipMemcpy(op->data, host.data(), cnt * esz, hipMemcpyHostToDevice));
-    op->frag = static_cast<unsigned char*>(op->data) + cnt * esz;
-    PSTD_HIP(build_fragments(esz == 8, *op, P->stream));
-    if (want_t) {
-      if (hipMalloc(&op->dataT, cnt * esz) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
-      PSTD_HIP(hipMemcpy(op->dataT, hostT.data(), cnt * esz, hipMemcpyHostToDevice));
-    }
-    return PSTD_OK;
-  }
   // split bf16, in fragment order: hi = bf16(v), lo = bf16(v - hi), both rounded from the FP64 value
   std::vector<uint16_t> host(2 * cnt, 0);
   for (int i = 0; i < M; ++i)
@@ -116,8 +138,20 @@ int upload_operator(pstd_plan_s* P, const std::vector<double>& m, int M, int K, 
       }
   }
   if (hipMalloc(&op->data, host.size() * 2) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
-  PSTD_HIP(hipMemcpy(op->data, host.data(), host.size() * 2, hipMemcpyHostToDevice));
+  op->bytes = host.size() * 2;
+  PSTD_HIP(hipMemcpy(op->data, host.data(), op->bytes, hipMemcpyHostToDevice));
   op->frag = static_cast<uint16_t*>(op->data) + (formed ? 2 * cnt : 0);
+  return PSTD_OK;
+}
+
+// Matrices times scale in the plan's precision.
+int upload_operators(const pstd_plan_s* P, const OperatorSource* src, int count, int copies) {
+  if (P->prec == PSTD_FP64) return upload_plain<double>(src, count, copies);
+  if (P->prec == PSTD_FP32) return upload_plain<float>(src, count, copies);
+  for (int i = 0; i < count; ++i) {
+    const int st = upload_split(*src[i].m, src[i].M, src[i].K, src[i].scale, src[i].op);
+    if (st != PSTD_OK) return st;
+  }
   return PSTD_OK;
 }
 
@@ -133,14 +167,10 @@ void free_plan(pstd_plan_s* P) {
   if (!P) return;
   for (int a = 0; a < 3; ++a) {
     if (P->G[a].data) (void)hipFree(P->G[a].data);
-    if (P->G[a].dataT) (void)hipFree(P->G[a].dataT);
     if (P->D[a].data) (void)hipFree(P->D[a].data);
-    if (P->D[a].dataT) (void)hipFree(P->D[a].dataT);
     fft_axis_free(&P->fft[a]);
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < 4; ++k)
       if (P->R[a][k].data) (void)hipFree(P->R[a][k].data);
-      if (P->R[a][k].dataT) (void)hipFree(P->R[a][k].dataT);
-    }
   }
   if (P->c2map) (void)hipFree(P->c2map);
   if (P->flag) (void)hipFree(P->flag);
@@ -173,15 +203,16 @@ double const_D(const pstd_plan_s* P) { return -P->dt * P->rho0 * (P->c2map ? 1.0
 
 // Dense operators of axis a, built on first use for axes that start on the FFT path.
 int ensure_dense(pstd_plan_s* P, int a) {
-  if (P->G[a].data) return PSTD_OK;
+  if (P->D[a].frag) return PSTD_OK;
   const int n = static_cast<int>(P->n[a]);
   if (n > 4097) return fail(PSTD_E_UNSUPPORTED, "axis %d: dense operators are limited to 4097 nodes", a);
   const AxisCase c = axis_case(P->bc[2 * a], P->bc[2 * a + 1]);
   const AxisTables& t = axis_tables(n, c);
   const int m = staggered_points(n, c);
-  int st = upload_operator(P, t.G, m, n, const_G(P), &P->G[a]);
-  if (st == PSTD_OK) st = upload_operator(P, t.D, n, m, const_D(P), &P->D[a]);
-  return st;
+  // the 1D time loops read rows, the longer ones' fallback columns
+  const int copies = P->ndim > 1 || c >= CASE_PP || n > kLineMaxNodes ? 0 : n > 128 ? 2 : 1;
+  const OperatorSource src[2] = {{&t.G, m, n, const_G(P), &P->G[a]}, {&t.D, n, m, const_D(P), &P->D[a]}};
+  return upload_operators(P, src, 2, copies);
 }
 
 // Whether axis a runs on the FFT path under the plan's current path setting.  AUTO: axes above 512
@@ -245,7 +276,6 @@ bool contract_args(const pstd_plan_s* P, const DevOperator& op, int a, const voi
                    const void* scale, ContractArgs* out) {
   ContractArgs& c = *out;
   c = ContractArgs{};
-  c.A = op.data;
   c.frag = op.frag;
   c.lda = op.Kp;
   c.M = op.M;
@@ -868,11 +898,12 @@ int pstd_apply_axis_operator(pstd_plan P, int32_t axis, int32_t which, const voi
   const int n = static_cast<int>(P->n[axis]);
   if (n > 4097) return fail(PSTD_E_UNSUPPORTED, "axis %d: dense operators are limited to 4097 nodes", axis);
   DevOperator& op = P->R[axis][which - 2];
-  if (!op.data) {
+  if (!op.frag) {
     int rows = 0, cols = 0;
     const std::vector<double> m =
         resample_table(n, axis_case(P->bc[2 * axis], P->bc[2 * axis + 1]), which, &rows, &cols);
-    const int st = upload_operator(P, m, rows, cols, which <= 3 ? 1.0 / P->dx : 1.0, &op);
+    const OperatorSource src{&m, rows, cols, which <= 3 ? 1.0 / P->dx : 1.0, &op};
+    const int st = upload_operators(P, &src, 1, 0);
     if (st != PSTD_OK) return st;
   }
   PSTD_HIP(contract(P, op, axis, in, out, 1.0, 0.0, nullptr, P->stream));
@@ -888,6 +919,17 @@ int pstd_test_line_spins(pstd_plan P, uint32_t spins) {
 
 // For tests: captures of a long line's steps that have a workspace of their own.
 int pstd_test_line_captures(pstd_plan P) { return P ? P->line_captures : -1; }
+
+// For tests: bytes of device memory that the plan's operators hold.
+int64_t pstd_test_operator_bytes(pstd_plan P) {
+  if (!P) return -1;
+  size_t b = 0;
+  for (int a = 0; a < 3; ++a) {
+    b += P->G[a].bytes + P->D[a].bytes;
+    for (const DevOperator& r : P->R[a]) b += r.bytes;
+  }
+  return static_cast<int64_t>(b);
+}
 
 // For tests (host only): workgroups of a long line's time loop, their rows, and the words of u that they exchange.
 int pstd_test_line_shape(int32_t n, int32_t* workgroups, int32_t* rows, int32_t* u_words) {
@@ -928,14 +970,14 @@ int pstd_plan_get_operator(pstd_plan P, int32_t axis, int32_t which, double* out
   const size_t cnt = static_cast<size_t>(op.Mp) * op.Kp;
   if (P->prec == PSTD_FP64) {
     std::vector<double> h(cnt);
-    PSTD_HIP(hipMemcpy(h.data(), op.data, cnt * 8, hipMemcpyDeviceToHost));
+    PSTD_HIP(hipMemcpy(h.data(), op.frag, cnt * 8, hipMemcpyDeviceToHost));
     for (int i = 0; i < op.M; ++i)
-      for (int k = 0; k < op.K; ++k) out[static_cast<size_t>(i) * op.K + k] = h[static_cast<size_t>(i) * op.Kp + k];
+      for (int k = 0; k < op.K; ++k) out[static_cast<size_t>(i) * op.K + k] = h[fragment_at(op.Kp, i, k)];
   } else if (P->prec == PSTD_FP32) {
     std::vector<float> h(cnt);
-    PSTD_HIP(hipMemcpy(h.data(), op.data, cnt * 4, hipMemcpyDeviceToHost));
+    PSTD_HIP(hipMemcpy(h.data(), op.frag, cnt * 4, hipMemcpyDeviceToHost));
     for (int i = 0; i < op.M; ++i)
-      for (int k = 0; k < op.K; ++k) out[static_cast<size_t>(i) * op.K + k] = h[static_cast<size_t>(i) * op.Kp + k];
+      for (int k = 0; k < op.K; ++k) out[static_cast<size_t>(i) * op.K + k] = h[fragment_at(op.Kp, i, k)];
   } else {
     std::vector<uint16_t> h(2 * cnt);
     PSTD_HIP(hipMemcpy(h.data(), op.data, cnt * 4, hipMemcpyDeviceToHost));

@@ -41,22 +41,6 @@ struct pstd_batch_s {
 namespace pstd {
 namespace {
 
-int upload_unscaled(const std::vector<double>& m, int M, int K, hipStream_t s, DevOperator* op) {
-  op->M = M;
-  op->K = K;
-  op->Mp = static_cast<int>(round_up(M, kRowPad));
-  op->Kp = static_cast<int>(round_up(K, kColPad));
-  std::vector<float> h(static_cast<size_t>(op->Mp) * op->Kp, 0.f);
-  for (int i = 0; i < M; ++i)
-    for (int k = 0; k < K; ++k) h[static_cast<size_t>(i) * op->Kp + k] = static_cast<float>(m[static_cast<size_t>(i) * K + k]);
-  if (hipMalloc(&op->data, 2 * h.size() * sizeof(float)) != hipSuccess)
-    return fail(PSTD_E_OOM, "hipMalloc failed");
-  PSTD_HIP(hipMemcpy(op->data, h.data(), h.size() * sizeof(float), hipMemcpyHostToDevice));
-  op->frag = static_cast<float*>(op->data) + h.size();
-  PSTD_HIP(build_fragments(false, *op, s));
-  return PSTD_OK;
-}
-
 void free_batch(pstd_batch_s* B) {
   if (!B) return;
   for (void* p : B->c2maps)
@@ -309,8 +293,8 @@ int pstd_batch_create(int32_t count, const int64_t* n, const int32_t* bc, const 
       if (B->ops.count(k)) continue;
       const AxisTables& t = axis_tables(k.first, static_cast<AxisCase>(k.second));
       pstd_batch_s::Op op;
-      int st = upload_unscaled(t.G, k.first - 1, k.first, B->stream, &op.G);
-      if (st == PSTD_OK) st = upload_unscaled(t.D, k.first, k.first - 1, B->stream, &op.D);
+      const OperatorSource src[2] = {{&t.G, k.first - 1, k.first, 1.0, &op.G}, {&t.D, k.first, k.first - 1, 1.0, &op.D}};
+      const int st = upload_plain<float>(src, 2, 0);
       B->ops[k] = op;
       if (st != PSTD_OK) {
         free_batch(B);
@@ -320,10 +304,6 @@ int pstd_batch_create(int32_t count, const int64_t* n, const int32_t* bc, const 
     const pstd_batch_s::Op& ox = B->ops[keys[0]];
     const pstd_batch_s::Op& oy = B->ops[keys[1]];
     BatchSolve S{};
-    S.Gx = static_cast<const float*>(ox.G.data);
-    S.Dx = static_cast<const float*>(ox.D.data);
-    S.Gy = static_cast<const float*>(oy.G.data);
-    S.Dy = static_cast<const float*>(oy.D.data);
     S.fGx = static_cast<const float*>(ox.G.frag);
     S.fDx = static_cast<const float*>(ox.D.frag);
     S.fGy = static_cast<const float*>(oy.G.frag);
@@ -408,7 +388,6 @@ int pstd_batch_state_init(pstd_batch B, pstd_state* st, int32_t u_mode) {
       }
       // u^{-1/2} = +(dt / (2 rho0)) G p = -1/2 sG (unscaled G) p
       ContractArgs c{};
-      c.A = a == 0 ? S.Gx : S.Gy;
       c.frag = a == 0 ? S.fGx : S.fGy;
       c.lda = a == 0 ? S.ldgx : S.ldgy;
       c.M = (a == 0 ? S.nx : S.ny) - 1;

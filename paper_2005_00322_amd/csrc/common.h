@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <cstdlib>
 #include <string>
 #include <vector>
 
@@ -83,17 +84,83 @@ inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 constexpr int kRowPad = 128;
 constexpr int kColPad = 64;
 
-// One operator (an M x K row-major matrix, zero padded) in the precision of its plan.
+// One operator (an M x K matrix, zero padded) in the precision of its plan, in MFMA fragment order: the kernels load it
+// straight into MFMA registers.  It is brought into that order on the host, once per plan, and kept in that order alone, except
+// for 1D time loops.
 struct DevOperator {
   int M = 0, K = 0;        // logical size
-  int Mp = 0, Kp = 0;      // padded size (row stride = Kp)
-  void* data = nullptr;    // FP64: double[Mp*Kp]; FP32: float[Mp*Kp]; SPLIT: bf16 hi and lo parts in fragment order
-  void* dataT = nullptr;   // 1D plans: transposed copy, Kp x Mp (row stride Mp)
-  // The operator in MFMA fragment order, in data's allocation.  FP64 / FP32: for every 16 rows and chunk of 16 columns the
-  // 64 lanes' four values, lane l those of row l % 16, columns 4 e + l / 16 for e < 4.  SPLIT: for every 32 rows and chunk
-  // of 16 columns the hi and then the lo parts, lane l those of row l % 32, columns 8 (l / 32) + e for e < 8; data itself,
-  // or of operators of kThRowsMin..kThRowsMax rows the FP32 sums of their Toeplitz and Hankel parts.
+  int Mp = 0, Kp = 0;      // padded size
+  void* data = nullptr;    // its allocation (null where another operator's holds this one too)
+  size_t bytes = 0;        // of it, this operator's share
+  // FP64 / FP32: for every 16 rows and chunk of 16 columns the 64 lanes' four values, lane l those of row l % 16, columns
+  // 4 e + l / 16 for e < 4 (fragment_at).  SPLIT: for every 32 rows and chunk of 16 columns the hi and then the lo parts,
+  // lane l those of row l % 32, columns 8 (l / 32) + e for e < 8; data itself, or of operators of
+  // kThRowsMin..kThRowsMax rows the FP32 sums of their Toeplitz and Hankel parts.
   void* frag = nullptr;
+  void* rows = nullptr;    // 1D time loops: row-major, row stride Kp
+  void* cols = nullptr;    // 1D time loops above 128 nodes: transposed, Kp x Mp
+};
+// Element offset of entry (i, k) in FP64 / FP32 fragments of padded width Kp.
+inline size_t fragment_at(int Kp, int i, int k) {
+  return (static_cast<size_t>(i >> 4) * (Kp >> 4) + (k >> 4)) * 256 + 4 * ((i & 15) + 16 * (k & 3)) + ((k & 15) >> 2);
+}
+// The M x K row-major matrix m times scale, as T, into zeroed fragments of padded width Kp, and where given into zeroed rows
+// (row stride Kp) and columns (stride Mp).  Whole rows of a chunk are transposed as 4 x 4 values, since a plan's operators are formed
+// each time it is created (256 x 256 values in FP32: 27 us, 59 entry by entry, 25 without reordering).
+template <typename T>
+void fill_operator(const double* m, int M, int K, double scale, int Mp, int Kp, T* frag, T* rows, T* cols) {
+  typedef T v4 __attribute__((ext_vector_type(4)));
+  typedef double d4 __attribute__((ext_vector_type(4), aligned(8)));
+  for (int i0 = 0; i0 < M; i0 += 16)
+    for (int k0 = 0; k0 < K; k0 += 16) {
+      T* o = frag + fragment_at(Kp, i0, k0);
+      const int ni = M - i0 < 16 ? M - i0 : 16, nk = K - k0 < 16 ? K - k0 : 16;
+      const double* r = m + static_cast<size_t>(i0) * K + k0;
+      for (int i = 0; i < ni; ++i, r += K) {
+        if (nk == 16) {
+          const v4 a = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r), v4);
+          const v4 b = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 4), v4);
+          const v4 c = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 8), v4);
+          const v4 d = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 12), v4);
+          const v4 ab0 = __builtin_shufflevector(a, b, 0, 4, 1, 5), ab1 = __builtin_shufflevector(a, b, 2, 6, 3, 7);
+          const v4 cd0 = __builtin_shufflevector(c, d, 0, 4, 1, 5), cd1 = __builtin_shufflevector(c, d, 2, 6, 3, 7);
+          v4* q = reinterpret_cast<v4*>(o + 4 * i);
+          q[0] = __builtin_shufflevector(ab0, cd0, 0, 1, 4, 5);
+          q[16] = __builtin_shufflevector(ab0, cd0, 2, 3, 6, 7);
+          q[32] = __builtin_shufflevector(ab1, cd1, 0, 1, 4, 5);
+          q[48] = __builtin_shufflevector(ab1, cd1, 2, 3, 6, 7);
+        } else {
+          for (int k = 0; k < nk; ++k) o[4 * (i + 16 * (k & 3)) + (k >> 2)] = static_cast<T>(scale * r[k]);
+        }
+        if (rows)
+          for (int k = 0; k < nk; ++k) rows[static_cast<size_t>(i0 + i) * Kp + k0 + k] = static_cast<T>(scale * r[k]);
+        if (cols)
+          for (int k = 0; k < nk; ++k) cols[static_cast<size_t>(k0 + k) * Mp + i0 + i] = static_cast<T>(scale * r[k]);
+      }
+    }
+}
+// Matrices times scale as T on the device, zero padded, in fragment order, with `copies` more of each (1: its rows, 2: and its
+// columns).
+struct OperatorSource {
+  const std::vector<double>* m;
+  int M, K;
+  double scale;
+  DevOperator* op;
+};
+template <typename T>
+int upload_plain(const OperatorSource* src, int count, int copies);
+// A zeroed host array (pages that stay zero are not touched); get() is null where there is no memory for it.
+template <typename T>
+class HostZeros {
+ public:
+  explicit HostZeros(size_t n) : p_(static_cast<T*>(std::calloc(n, sizeof(T)))) {}
+  ~HostZeros() { std::free(p_); }
+  HostZeros(const HostZeros&) = delete;
+  HostZeros& operator=(const HostZeros&) = delete;
+  T* get() const { return p_; }
+
+ private:
+  T* p_;
 };
 
 // Split-bf16 operators whose frag holds the FP32 sums of their Toeplitz and Hankel parts: rows in
@@ -109,9 +176,8 @@ bool toeplitz_hankel(const double* A, int R, int C, double tol, std::vector<doub
                      double w[4], double* resid);
 
 struct ContractArgs {
-  const void* A;        // FP64 / FP32: operator, row-major, row stride lda, zero padded
   const void* frag;     // the operator in fragment order (DevOperator)
-  int lda;
+  int lda;              // and its padded width
   int M, K;             // output length and input length along the contracted axis
   const void* X;        // input field
   void* Y;              // output field (read-modify-write)
@@ -175,8 +241,6 @@ struct CombinePair {
 };
 hipError_t launch_combine_pairs(const CombinePair* pairs, int count, hipStream_t s);
 bool phase2d_supported(int nx, int ny);
-// Fills op->frag from op->data on stream s.
-hipError_t build_fragments(bool dbl, const DevOperator& op, hipStream_t s);
 // Two fused phases per 2D step (fields and operators double with dbl, float otherwise).
 hipError_t launch_phase2d(bool dbl, const DevOperator& Gx, const DevOperator& Gy, const DevOperator& Dx,
                           const DevOperator& Dy, void* p, void* ux, void* uy, const void* c2, int nx, int ny,
@@ -189,10 +253,9 @@ struct BatchSolve {
   float* p;                 // nx x ny
   float* ux;                // (nx-1) x ny
   float* uy;                // nx x (ny-1)
-  const float* Gx; const float* Dx; const float* Gy; const float* Dy;   // unscaled (dx = 1) operators
-  const float* fGx; const float* fDx; const float* fGy; const float* fDy;   // the same in fragment order (tile 16)
-  int ldgx, lddx, ldgy, lddy;                                          // their row strides
-  int mgx, mdx, mgy, mdy;                                              // their allocated (padded) rows
+  const float* fGx; const float* fDx; const float* fGy; const float* fDy;   // unscaled (dx = 1) operators in fragment order
+  int ldgx, lddx, ldgy, lddy;                                          // their padded widths
+  int mgx, mdx, mgy, mdy;                                              // their padded rows
   int nx, ny;
   double sG;                // -dt / (rho0 dx)
   double sD;                // -dt rho0 c0^2 / dx, or -dt rho0 / dx with a c0^2 map

@@ -251,30 +251,7 @@ hipError_t launch_multi_t(const ContractArgs* c, const bool* contiguous, int cou
   return hipGetLastError();
 }
 
-// dst: the Mp x Kp matrix src in fragment order (DevOperator::frag).
-template <typename T>
-__global__ __launch_bounds__(256) void fragment_kernel(const T* __restrict__ src, T* __restrict__ dst, int Mp, int Kp) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= static_cast<int64_t>(Mp) * Kp) return;
-  const int e = static_cast<int>(i & 3), l = static_cast<int>(i >> 2) & 63, nc = Kp >> 4;
-  const int blk = static_cast<int>(i >> 8);
-  dst[i] = src[static_cast<int64_t>(16 * (blk / nc) + (l & 15)) * Kp + 16 * (blk % nc) + chunk_k(4 * (l >> 4) + e)];
-}
-
 }  // namespace
-
-hipError_t build_fragments(bool dbl, const DevOperator& op, hipStream_t s) {
-  const int64_t cnt = static_cast<int64_t>(op.Mp) * op.Kp;
-  if (!op.frag || op.Mp % 16 || op.Kp % 16) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>((cnt + 255) / 256)), blk(256);
-  if (dbl)
-    hipLaunchKernelGGL(fragment_kernel<double>, grid, blk, 0, s, static_cast<const double*>(op.data),
-                       static_cast<double*>(op.frag), op.Mp, op.Kp);
-  else
-    hipLaunchKernelGGL(fragment_kernel<float>, grid, blk, 0, s, static_cast<const float*>(op.data),
-                       static_cast<float*>(op.frag), op.Mp, op.Kp);
-  return hipGetLastError();
-}
 
 hipError_t launch_contract_fp32(const ContractArgs& c, bool contiguous, hipStream_t s) {
   return launch_t<float>(c, contiguous, s);

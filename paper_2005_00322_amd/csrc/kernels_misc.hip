@@ -465,7 +465,8 @@ size_t line_words(int prec, int n) { return static_cast<size_t>(prec == PSTD_FP6
 template <typename T>
 hipError_t launch_step1d_t(int prec, const DevOperator& Go, const DevOperator& Do, T* p, T* u, int n, int64_t steps,
                            const T* scale, void* work, unsigned spins, hipStream_t s) {
-  const T *G = static_cast<const T*>(Go.data), *D = static_cast<const T*>(Do.data);
+  const T *G = static_cast<const T*>(Go.rows), *D = static_cast<const T*>(Do.rows);
+  if (!G || !D || (n > 128 && (!Go.cols || !Do.cols))) return hipErrorInvalidValue;
   if (n <= 128) {
     hipLaunchKernelGGL(step1d_reg_kernel<T>, dim3(1), dim3(1024), 0, s, G, Go.Kp, D, Do.Kp, p, u, n, steps, scale);
     return hipGetLastError();
@@ -479,8 +480,8 @@ hipError_t launch_step1d_t(int prec, const DevOperator& Go, const DevOperator& D
   const size_t shmem = ((sizeof(T) * 2 * static_cast<size_t>(n) + 7) & ~static_cast<size_t>(7)) + 8 * static_cast<size_t>(4) * n;
   if (shmem > 64 * 1024 || n > kLineMaxNodes) return hipErrorInvalidConfiguration;
   if (!work) {
-    hipLaunchKernelGGL(step1d_one_kernel<T>, dim3(1), dim3(1024), shmem, s, static_cast<const T*>(Go.dataT), Go.Mp,
-                       static_cast<const T*>(Do.dataT), Do.Mp, p, u, n, steps, scale);
+    hipLaunchKernelGGL(step1d_one_kernel<T>, dim3(1), dim3(1024), shmem, s, static_cast<const T*>(Go.cols), Go.Mp,
+                       static_cast<const T*>(Do.cols), Do.Mp, p, u, n, steps, scale);
     return hipGetLastError();
   }
   LineHead* head = static_cast<LineHead*>(work);
@@ -500,8 +501,8 @@ hipError_t launch_step1d_t(int prec, const DevOperator& Go, const DevOperator& D
 #undef PSTD_LINE
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(step1d_commit_kernel<T>, dim3(1), dim3(1024), shmem, s, static_cast<const T*>(Go.dataT), Go.Mp,
-                     static_cast<const T*>(Do.dataT), Do.Mp, p, u, n, steps, scale, head, po, uo);
+  hipLaunchKernelGGL(step1d_commit_kernel<T>, dim3(1), dim3(1024), shmem, s, static_cast<const T*>(Go.cols), Go.Mp,
+                     static_cast<const T*>(Do.cols), Do.Mp, p, u, n, steps, scale, head, po, uo);
   return hipGetLastError();
 }
 
