@@ -81,15 +81,15 @@ template int upload_plain<double>(const OperatorSource*, int, int);
 
 namespace {
 
-uint16_t bf16_rne(float f) {
+// (selects and no branch: the loops that form operators call it 2 M K times)
+inline uint16_t bf16_rne(float f) {
   uint32_t u;
   std::memcpy(&u, &f, 4);
-  if ((u & 0x7f800000u) == 0x7f800000u) return static_cast<uint16_t>(u >> 16);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return static_cast<uint16_t>(u >> 16);
+  const uint32_t up = (u & 0x7f800000u) == 0x7f800000u ? 0u : 0x7fffu + ((u >> 16) & 1u);
+  return static_cast<uint16_t>((u + up) >> 16);
 }
 
-float bf16_to_float(uint16_t h) {
+inline float bf16_to_float(uint16_t h) {
   uint32_t u = static_cast<uint32_t>(h) << 16;
   float f;
   std::memcpy(&f, &u, 4);
@@ -101,46 +101,79 @@ inline size_t split_fragment_at(int Kp, unsigned i, unsigned k) {
   return static_cast<size_t>((i >> 5) * (static_cast<unsigned>(Kp) >> 4) + (k >> 4)) * 1024 + (i & 31) * 8 + (k & 8) * 32 + (k & 7);
 }
 
-// The matrix m (M x K) times scale as a split operator, uploaded in fragment order.
+// hi and lo of an entry: hi = bf16(v), lo = bf16(v - hi), both rounded from v
+inline void split_entry(double v, uint16_t* at) {
+  const uint16_t hi = bf16_rne(static_cast<float>(v));
+  at[0] = hi;
+  at[512] = bf16_rne(static_cast<float>(v - static_cast<double>(bf16_to_float(hi))));
+}
+inline void split_entry(float v, uint16_t* at) {
+  const uint16_t hi = bf16_rne(v);
+  at[0] = hi;
+  at[512] = bf16_rne(v - bf16_to_float(hi));
+}
+
+// The entries entry(i, k) of op as a split operator in fragment order, zero padded, in an allocation of its own.  Runs of eight k
+// lie side by side in both orders.
+template <typename F>
+int upload_split_entries(const DevOperator& op, F&& entry, void** out) {
+  const size_t words = 2 * static_cast<size_t>(op.Mp) * op.Kp;
+  const HostZeros<uint16_t> host(words);
+  if (!host.get()) return fail(PSTD_E_OOM, "no host memory for an operator");
+  for (int i0 = 0; i0 < op.M; i0 += 32)
+    for (int k0 = 0; k0 < op.K; k0 += 8)
+      for (int i = i0; i < std::min(i0 + 32, op.M); ++i) {
+        uint16_t* at = host.get() + split_fragment_at(op.Kp, i, k0);
+        if (k0 + 8 <= op.K)
+          for (int k = 0; k < 8; ++k) split_entry(entry(i, k0 + k), at + k);
+        else
+          for (int k = 0; k0 + k < op.K; ++k) split_entry(entry(i, k0 + k), at + k);
+      }
+  if (hipMalloc(out, words * 2) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
+  PSTD_HIP(hipMemcpy(*out, host.get(), words * 2, hipMemcpyHostToDevice));
+  return PSTD_OK;
+}
+
+// The entries of m times scale as rounded from FP64.
+int upload_split_exact(const std::vector<double>& m, double scale, const DevOperator& op, void** out) {
+  const double* a = m.data();
+  const size_t K = op.K;
+  return upload_split_entries(op, [=](int i, int k) { return scale * a[i * K + k]; }, out);
+}
+
+// The matrix m (M x K) times scale as a split operator.
 int upload_split(const std::vector<double>& m, int M, int K, double scale, DevOperator* op) {
   op->M = M;
   op->K = K;
   op->Mp = static_cast<int>(round_up(M, kRowPad));
   op->Kp = static_cast<int>(round_up(K, kColPad));
-  const size_t cnt = static_cast<size_t>(op->Mp) * op->Kp;
-  // split bf16, in fragment order: hi = bf16(v), lo = bf16(v - hi), both rounded from the FP64 value
-  std::vector<uint16_t> host(2 * cnt, 0);
-  for (int i = 0; i < M; ++i)
-    for (int k = 0; k < K; ++k) {
-      const double v = scale * m[static_cast<size_t>(i) * K + k];
-      const uint16_t hi = bf16_rne(static_cast<float>(v));
-      uint16_t* at = host.data() + split_fragment_at(op->Kp, i, k);
-      at[0] = hi;
-      at[512] = bf16_rne(static_cast<float>(v - static_cast<double>(bf16_to_float(hi))));
-    }
+  const size_t bytes = 4 * static_cast<size_t>(op->Mp) * op->Kp;
   // Operators of these sizes take the FP32 sum of their Toeplitz and Hankel parts as entry (the end weights, 0, 1/2
   // or 1, are exact): the values that results of these sizes have always rested on.
   std::vector<double> f, g;
   double w[4], resid = 0.0;
-  const bool formed = M > kThRowsMin && M <= kThRowsMax && op->Kp <= kThColsMax &&
-                      toeplitz_hankel(m.data(), M, K, kThTol, &f, &g, w, &resid);
-  if (formed) {
-    host.resize(4 * cnt, 0);
-    for (int i = 0; i < M; ++i)
-      for (int k = 0; k < K; ++k) {
-        const float wr = static_cast<float>(i == 0 ? w[0] : i == M - 1 ? w[1] : 1.0);
-        const float wc = static_cast<float>(k == 0 ? w[2] : k == K - 1 ? w[3] : 1.0);
-        const float v = wr * wc * (static_cast<float>(scale * f[i - k + K - 1]) + static_cast<float>(scale * g[i + k]));
-        const uint16_t hi = bf16_rne(v);
-        uint16_t* at = host.data() + 2 * cnt + split_fragment_at(op->Kp, i, k);
-        at[0] = hi;
-        at[512] = bf16_rne(v - bf16_to_float(hi));
-      }
+  op->formed = M > kThRowsMin && M <= kThRowsMax && op->Kp <= kThColsMax &&
+               toeplitz_hankel(m.data(), M, K, kThTol, &f, &g, w, &resid);
+  int st;
+  if (op->formed) {
+    // the parts in FP32, f by k - i + M - 1
+    std::vector<float> ff(f.size()), gg(g.size());
+    for (size_t t = 0; t < ff.size(); ++t) {
+      ff[t] = static_cast<float>(scale * f[ff.size() - 1 - t]);
+      gg[t] = static_cast<float>(scale * g[t]);
+    }
+    const float *fp = ff.data() + M - 1, *gp = gg.data();
+    const float w0 = static_cast<float>(w[0]), w1 = static_cast<float>(w[1]), w2 = static_cast<float>(w[2]), w3 = static_cast<float>(w[3]);
+    st = upload_split_entries(*op, [=](int i, int k) {
+      const float wr = i == 0 ? w0 : i == M - 1 ? w1 : 1.f, wc = k == 0 ? w2 : k == K - 1 ? w3 : 1.f;
+      return wr * wc * (fp[k - i] + gp[i + k]);
+    }, &op->data);
+  } else {
+    st = upload_split_exact(m, scale, *op, &op->data);
   }
-  if (hipMalloc(&op->data, host.size() * 2) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
-  op->bytes = host.size() * 2;
-  PSTD_HIP(hipMemcpy(op->data, host.data(), op->bytes, hipMemcpyHostToDevice));
-  op->frag = static_cast<uint16_t*>(op->data) + (formed ? 2 * cnt : 0);
+  if (st != PSTD_OK) return st;
+  op->bytes = bytes;
+  op->frag = op->data;
   return PSTD_OK;
 }
 
@@ -166,11 +199,11 @@ void drop_graphs(pstd_plan_s* P) {
 void free_plan(pstd_plan_s* P) {
   if (!P) return;
   for (int a = 0; a < 3; ++a) {
-    if (P->G[a].data) (void)hipFree(P->G[a].data);
-    if (P->D[a].data) (void)hipFree(P->D[a].data);
+    for (DevOperator* op : {&P->G[a], &P->D[a], &P->R[a][0], &P->R[a][1], &P->R[a][2], &P->R[a][3]}) {
+      if (op->data) (void)hipFree(op->data);
+      if (op->exact) (void)hipFree(op->exact);
+    }
     fft_axis_free(&P->fft[a]);
-    for (int k = 0; k < 4; ++k)
-      if (P->R[a][k].data) (void)hipFree(P->R[a][k].data);
   }
   if (P->c2map) (void)hipFree(P->c2map);
   if (P->flag) (void)hipFree(P->flag);
@@ -215,6 +248,31 @@ int ensure_dense(pstd_plan_s* P, int a) {
   return upload_operators(P, src, 2, copies);
 }
 
+// Path "stored": the entries as rounded from FP64 of the operators along axis a that do not have those (dense ones, and the
+// collocated and interpolating ones built so far).
+int ensure_exact(pstd_plan_s* P, int a) {
+  const int n = static_cast<int>(P->n[a]);
+  const AxisCase c = axis_case(P->bc[2 * a], P->bc[2 * a + 1]);
+  auto exact = [&](const std::vector<double>& m, double scale, DevOperator* op) {
+    if (!op->formed || op->exact) return static_cast<int>(PSTD_OK);
+    const int st = upload_split_exact(m, scale, *op, &op->exact);
+    if (st == PSTD_OK) op->bytes *= 2;
+    return st;
+  };
+  int st = PSTD_OK;
+  if (P->G[a].formed || P->D[a].formed) {
+    const AxisTables& t = axis_tables(n, c);
+    st = exact(t.G, const_G(P), &P->G[a]);
+    if (st == PSTD_OK) st = exact(t.D, const_D(P), &P->D[a]);
+  }
+  for (int k = 0; k < 4 && st == PSTD_OK; ++k)
+    if (P->R[a][k].formed && !P->R[a][k].exact) {
+      int rows = 0, cols = 0;
+      st = exact(resample_table(n, c, k + 2, &rows, &cols), k + 2 <= 3 ? 1.0 / P->dx : 1.0, &P->R[a][k]);
+    }
+  return st;
+}
+
 // Whether axis a runs on the FFT path under the plan's current path setting.  AUTO: axes above 512
 // nodes (1D plans keep the line kernels up to kLineMaxNodes nodes).
 bool axis_fft(const pstd_plan_s* P, int a) {
@@ -236,7 +294,8 @@ bool use_step1d(const pstd_plan_s* P) {
 int prepare_axes(pstd_plan_s* P) {
   for (int a = 0; a < P->ndim; ++a)
     if (!axis_fft(P, a)) {
-      const int st = ensure_dense(P, a);
+      int st = ensure_dense(P, a);
+      if (st == PSTD_OK && P->path == PSTD_PATH_STORED) st = ensure_exact(P, a);
       if (st != PSTD_OK) return st;
     }
   const size_t wb = use_step1d(P) && !P->line_work ? step1d_work_bytes(P->prec, static_cast<int>(P->n[0])) : 0;
@@ -310,7 +369,7 @@ hipError_t contract(const pstd_plan_s* P, const DevOperator& op, int a, const vo
   const bool contiguous = contract_args(P, op, a, X, Y, alpha, beta, scale, &c);
   if (P->prec == PSTD_FP64) return launch_contract_fp64(c, contiguous, s);
   if (P->prec == PSTD_FP32) return launch_contract_fp32(c, contiguous, s);
-  if (P->stored) c.frag = op.data;
+  if (P->stored && op.formed) c.frag = op.exact;
   return launch_contract_split(c, contiguous, s);
 }
 
@@ -903,7 +962,8 @@ int pstd_apply_axis_operator(pstd_plan P, int32_t axis, int32_t which, const voi
     const std::vector<double> m =
         resample_table(n, axis_case(P->bc[2 * axis], P->bc[2 * axis + 1]), which, &rows, &cols);
     const OperatorSource src{&m, rows, cols, which <= 3 ? 1.0 / P->dx : 1.0, &op};
-    const int st = upload_operators(P, &src, 1, 0);
+    int st = upload_operators(P, &src, 1, 0);
+    if (st == PSTD_OK && P->stored) st = ensure_exact(P, axis);
     if (st != PSTD_OK) return st;
   }
   PSTD_HIP(contract(P, op, axis, in, out, 1.0, 0.0, nullptr, P->stream));
@@ -979,13 +1039,20 @@ int pstd_plan_get_operator(pstd_plan P, int32_t axis, int32_t which, double* out
     for (int i = 0; i < op.M; ++i)
       for (int k = 0; k < op.K; ++k) out[static_cast<size_t>(i) * op.K + k] = h[fragment_at(op.Kp, i, k)];
   } else {
-    std::vector<uint16_t> h(2 * cnt);
-    PSTD_HIP(hipMemcpy(h.data(), op.data, cnt * 4, hipMemcpyDeviceToHost));
+    // as rounded from FP64, whether or not the plan has those entries on the device
+    const int n = static_cast<int>(P->n[axis]);
+    const AxisTables& t = axis_tables(n, axis_case(P->bc[2 * axis], P->bc[2 * axis + 1]));
+    const double* m = (which == 0 ? t.G : t.D).data();
+    const double scale = which == 0 ? const_G(P) : const_D(P);
+    std::vector<uint16_t> h(op.formed ? 0 : 2 * cnt);
+    if (!op.formed) PSTD_HIP(hipMemcpy(h.data(), op.frag, cnt * 4, hipMemcpyDeviceToHost));
     for (int i = 0; i < op.M; ++i)
       for (int k = 0; k < op.K; ++k) {
-        const size_t a = split_fragment_at(op.Kp, i, k);
-        out[static_cast<size_t>(i) * op.K + k] =
-            static_cast<double>(bf16_to_float(h[a])) + static_cast<double>(bf16_to_float(h[a + 512]));
+        uint16_t e[513];
+        const size_t at = static_cast<size_t>(i) * op.K + k;
+        if (op.formed) split_entry(scale * m[at], e);
+        const uint16_t* v = op.formed ? e : h.data() + split_fragment_at(op.Kp, i, k);
+        out[at] = static_cast<double>(bf16_to_float(v[0])) + static_cast<double>(bf16_to_float(v[512]));
       }
   }
   return PSTD_OK;

@@ -94,9 +94,10 @@ struct DevOperator {
   size_t bytes = 0;        // of it, this operator's share
   // FP64 / FP32: for every 16 rows and chunk of 16 columns the 64 lanes' four values, lane l those of row l % 16, columns
   // 4 e + l / 16 for e < 4 (fragment_at).  SPLIT: for every 32 rows and chunk of 16 columns the hi and then the lo parts,
-  // lane l those of row l % 32, columns 8 (l / 32) + e for e < 8; data itself, or of operators of
-  // kThRowsMin..kThRowsMax rows the FP32 sums of their Toeplitz and Hankel parts.
+  // lane l those of row l % 32, columns 8 (l / 32) + e for e < 8.
   void* frag = nullptr;
+  bool formed = false;     // SPLIT: the entries are FP32 sums of the operator's Toeplitz and Hankel parts
+  void* exact = nullptr;   // and those rounded from FP64, which path "stored" reads (built when it is chosen)
   void* rows = nullptr;    // 1D time loops: row-major, row stride Kp
   void* cols = nullptr;    // 1D time loops above 128 nodes: transposed, Kp x Mp
 };
@@ -163,7 +164,7 @@ class HostZeros {
   T* p_;
 };
 
-// Split-bf16 operators whose frag holds the FP32 sums of their Toeplitz and Hankel parts: rows in
+// Split-bf16 operators whose entries are the FP32 sums of their Toeplitz and Hankel parts: rows in
 // (kThRowsMin, kThRowsMax], padded columns up to kThColsMax.
 constexpr int kThRowsMin = 192, kThRowsMax = 384, kThColsMax = 512;
 // Largest entry error of that form, relative to max|A|: far below FP32 rounding.
