@@ -56,8 +56,8 @@ int upload_plain(const OperatorSource* src, int count, int copies) {
   for (int i = 0; i < count; ++i) {
     const DevOperator& op = *src[i].op;
     const size_t cnt = static_cast<size_t>(op.Mp) * op.Kp;
-    fill_operator(src[i].m->data(), op.M, op.K, src[i].scale, op.Mp, op.Kp, h, copies >= 1 ? h + cnt : nullptr,
-                  copies >= 2 ? h + 2 * cnt : nullptr);
+    fill_fragments(src[i].m->data(), op.M, op.K, src[i].scale, op.Kp, h);
+    if (copies) fill_lines(src[i].m->data(), op.M, op.K, src[i].scale, op.Mp, op.Kp, h + cnt, copies >= 2 ? h + 2 * cnt : nullptr);
     h += (1 + copies) * cnt;
   }
   void* data = nullptr;

@@ -105,40 +105,44 @@ struct DevOperator {
 inline size_t fragment_at(int Kp, int i, int k) {
   return (static_cast<size_t>(i >> 4) * (Kp >> 4) + (k >> 4)) * 256 + 4 * ((i & 15) + 16 * (k & 3)) + ((k & 15) >> 2);
 }
-// The M x K row-major matrix m times scale, as T, into zeroed fragments of padded width Kp, and where given into zeroed rows
-// (row stride Kp) and columns (stride Mp).  Whole rows of a chunk are transposed as 4 x 4 values, since a plan's operators are formed
-// each time it is created (256 x 256 values in FP32: 27 us, 59 entry by entry, 25 without reordering).
+// The M x K row-major matrix m times scale, as T, into zeroed fragments of padded width Kp.  A row at a time, its chunks
+// transposed as 4 x 4 values: plans and batches form their operators from tables that lie in host memory, and what bounds it is the
+// one stream that it reads (300 x 300 in FP32: 41 us, 59 with sixteen rows at a time, 28 without reordering).
 template <typename T>
-void fill_operator(const double* m, int M, int K, double scale, int Mp, int Kp, T* frag, T* rows, T* cols) {
+void fill_fragments(const double* m, int M, int K, double scale, int Kp, T* out) {
   typedef T v4 __attribute__((ext_vector_type(4)));
   typedef double d4 __attribute__((ext_vector_type(4), aligned(8)));
-  for (int i0 = 0; i0 < M; i0 += 16)
-    for (int k0 = 0; k0 < K; k0 += 16) {
-      T* o = frag + fragment_at(Kp, i0, k0);
-      const int ni = M - i0 < 16 ? M - i0 : 16, nk = K - k0 < 16 ? K - k0 : 16;
-      const double* r = m + static_cast<size_t>(i0) * K + k0;
-      for (int i = 0; i < ni; ++i, r += K) {
-        if (nk == 16) {
-          const v4 a = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r), v4);
-          const v4 b = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 4), v4);
-          const v4 c = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 8), v4);
-          const v4 d = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 12), v4);
-          const v4 ab0 = __builtin_shufflevector(a, b, 0, 4, 1, 5), ab1 = __builtin_shufflevector(a, b, 2, 6, 3, 7);
-          const v4 cd0 = __builtin_shufflevector(c, d, 0, 4, 1, 5), cd1 = __builtin_shufflevector(c, d, 2, 6, 3, 7);
-          v4* q = reinterpret_cast<v4*>(o + 4 * i);
-          q[0] = __builtin_shufflevector(ab0, cd0, 0, 1, 4, 5);
-          q[16] = __builtin_shufflevector(ab0, cd0, 2, 3, 6, 7);
-          q[32] = __builtin_shufflevector(ab1, cd1, 0, 1, 4, 5);
-          q[48] = __builtin_shufflevector(ab1, cd1, 2, 3, 6, 7);
-        } else {
-          for (int k = 0; k < nk; ++k) o[4 * (i + 16 * (k & 3)) + (k >> 2)] = static_cast<T>(scale * r[k]);
-        }
-        if (rows)
-          for (int k = 0; k < nk; ++k) rows[static_cast<size_t>(i0 + i) * Kp + k0 + k] = static_cast<T>(scale * r[k]);
-        if (cols)
-          for (int k = 0; k < nk; ++k) cols[static_cast<size_t>(k0 + k) * Mp + i0 + i] = static_cast<T>(scale * r[k]);
-      }
+  for (int i = 0; i < M; ++i) {
+    const double* r = m + static_cast<size_t>(i) * K;
+    T* o = out + fragment_at(Kp, i, 0);
+    int k0 = 0;
+    for (; k0 + 16 <= K; k0 += 16, r += 16, o += 256) {
+      const v4 a = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r), v4);
+      const v4 b = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 4), v4);
+      const v4 c = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 8), v4);
+      const v4 d = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 12), v4);
+      const v4 ab0 = __builtin_shufflevector(a, b, 0, 4, 1, 5), ab1 = __builtin_shufflevector(a, b, 2, 6, 3, 7);
+      const v4 cd0 = __builtin_shufflevector(c, d, 0, 4, 1, 5), cd1 = __builtin_shufflevector(c, d, 2, 6, 3, 7);
+      v4* q = reinterpret_cast<v4*>(o);
+      q[0] = __builtin_shufflevector(ab0, cd0, 0, 1, 4, 5);
+      q[16] = __builtin_shufflevector(ab0, cd0, 2, 3, 6, 7);
+      q[32] = __builtin_shufflevector(ab1, cd1, 0, 1, 4, 5);
+      q[48] = __builtin_shufflevector(ab1, cd1, 2, 3, 6, 7);
     }
+    for (int k = 0; k0 + k < K; ++k) o[64 * (k & 3) + (k >> 2)] = static_cast<T>(scale * r[k]);
+  }
+}
+// The same into rows (stride Kp) and, where given, columns (stride Mp), in blocks so that either side stays in cache.
+template <typename T>
+void fill_lines(const double* m, int M, int K, double scale, int Mp, int Kp, T* rows, T* cols) {
+  for (int i0 = 0; i0 < M; i0 += 16)
+    for (int k0 = 0; k0 < K; k0 += 16)
+      for (int i = i0; i < M && i < i0 + 16; ++i)
+        for (int k = k0; k < K && k < k0 + 16; ++k) {
+          const T v = static_cast<T>(scale * m[static_cast<size_t>(i) * K + k]);
+          rows[static_cast<size_t>(i) * Kp + k] = v;
+          if (cols) cols[static_cast<size_t>(k) * Mp + i] = v;
+        }
 }
 // Matrices times scale as T on the device, zero padded, in fragment order, with `copies` more of each (1: its rows, 2: and its
 // columns).
