@@ -25,7 +25,7 @@ struct pstd_batch_s {
   std::map<std::pair<int, int>, Op> ops;
   std::vector<pstd::BatchSolve> solves;       // host copy (pointers filled per state set)
   pstd::BatchSolve* d_solves = nullptr;
-  std::vector<void*> key;                     // state pointers the device table was built for
+  std::vector<void*> key;                     // state pointers the device table holds (empty: out of date)
   std::vector<pstd::BatchTask> tasksA, tasksB;
   pstd::BatchRuns runsA{}, runsB{};           // the XCDs' runs of either list
   pstd::BatchTask* d_tasks = nullptr;         // A then B
@@ -127,17 +127,19 @@ int ensure_solves(pstd_batch_s* B, const pstd_state* st) {
     key.push_back(st[s].u[0]);
     key.push_back(st[s].u[1]);
   }
-  if (key == B->key && B->d_solves) return PSTD_OK;
+  if (key == B->key) return PSTD_OK;
+  // The update travels in kernel arguments, in stream order behind the launches that still read the previous states: no wait,
+  // no copy.  A capture would only record it.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (B->stream) PSTD_HIP(hipStreamIsCapturing(B->stream, &cap));
+  if (cap != hipStreamCaptureStatusNone) return fail(PSTD_E_HIP, "new states cannot be introduced while the stream is captured");
+  B->key.clear();
   for (int s = 0; s < B->count; ++s) {
     B->solves[s].p = static_cast<float*>(st[s].p);
     B->solves[s].ux = static_cast<float*>(st[s].u[0]);
     B->solves[s].uy = static_cast<float*>(st[s].u[1]);
   }
-  if (!B->d_solves && hipMalloc(&B->d_solves, B->solves.size() * sizeof(BatchSolve)) != hipSuccess)
-    return fail(PSTD_E_OOM, "hipMalloc of the solve table failed");
-  // the stream may still run kernels reading the previous table
-  PSTD_HIP(B->stream ? hipStreamSynchronize(B->stream) : hipDeviceSynchronize());
-  PSTD_HIP(hipMemcpy(B->d_solves, B->solves.data(), B->solves.size() * sizeof(BatchSolve), hipMemcpyHostToDevice));
+  PSTD_HIP(launch_batch_states(B->solves.data(), B->count, B->d_solves, B->stream));
   B->key = key;
   return PSTD_OK;
 }
@@ -323,6 +325,15 @@ int pstd_batch_create(int32_t count, const int64_t* n, const int32_t* bc, const 
     S.sD = -B->dt[s] * rho0 * B->c0[s] * B->c0[s] / B->dx[s];
     B->solves.push_back(S);
   }
+  const size_t table = B->solves.size() * sizeof(BatchSolve);
+  if (hipMalloc(&B->d_solves, table) != hipSuccess) {
+    free_batch(B);
+    return fail(PSTD_E_OOM, "hipMalloc of the solve table failed");
+  }
+  if (hipMemcpy(B->d_solves, B->solves.data(), table, hipMemcpyHostToDevice) != hipSuccess) {
+    free_batch(B);
+    return fail(PSTD_E_HIP, "copy of the solve table failed");
+  }
   *out = B;
   return PSTD_OK;
 }
@@ -339,7 +350,7 @@ int pstd_batch_set_c0_maps(pstd_batch B, const float* const* c0_maps) {
     B->solves[s].c2 = static_cast<const float*>(B->c2maps[s]);
     B->solves[s].sD = -B->dt[s] * B->rho0 / B->dx[s];
   }
-  B->key.clear();   // the device solve table is rebuilt with the maps on the next step
+  B->key.clear();   // the device solve table takes the maps with the next step's states
   return PSTD_OK;
 }
 
@@ -363,7 +374,7 @@ int pstd_batch_state_init(pstd_batch B, pstd_state* st, int32_t u_mode) {
   if (B->stream) PSTD_HIP(hipStreamIsCapturing(B->stream, &cap));
   if (B->tile == 16 && u_mode == 0 && cap == hipStreamCaptureStatusNone) {
     // one shape: two launches over all solves (three per solve otherwise; 16 solves of 256 x 256: 0.62 -> 0.03 ms).
-    // A captured call takes the launches per solve: they need no copy of the solve table.
+    // A captured call takes the launches per solve: they do not read the solve table.
     const int r = ensure_solves(B, st);
     if (r != PSTD_OK) return r;
     PSTD_HIP(launch_batch_walls(B->d_solves, B->count, B->nx[0], B->ny[0], B->stream));
@@ -518,7 +529,6 @@ int pstd_batch_autotune(pstd_batch B, int32_t trial_steps, const char* cache_pat
     scratch[s].u[2] = nullptr;
     scratch[s].step = 0;
   }
-  const std::vector<void*> saved_key = B->key;
   double best = 1e300;
   int best_o = 0, best_t = 32;
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -552,7 +562,6 @@ int pstd_batch_autotune(pstd_batch B, int32_t trial_steps, const char* cache_pat
   (void)(B->stream ? hipStreamSynchronize(B->stream) : hipDeviceSynchronize());
   for (void* p : bufs) (void)hipFree(p);
   B->key.clear();   // the device solve table points at the freed scratch states
-  (void)saved_key;
   if (st != PSTD_OK) return st;
   B->blocks = 0;
   B->order = best_o;

@@ -267,6 +267,8 @@ struct BatchSolve {
   const float* c2;          // nx x ny map of c0(x)^2, or null for a homogeneous medium
   int walls;                // Dirichlet faces: bit f for face f of {x-, x+, y-, y+}
 };
+// Writes the states (p, ux, uy, c2, sD) of `count` host solves into the device table, in stream order.
+hipError_t launch_batch_states(const BatchSolve* solves, int count, BatchSolve* table, hipStream_t s);
 // One fused phase of many solves of one shape (kernels_phase2d.hip).  start (which = 0): the centred start
 // u^{-1/2} instead of an update.
 hipError_t launch_phase2d_batch(int which, const BatchSolve* solves, int count, int nx, int ny, bool start,

@@ -128,6 +128,27 @@ __global__ __launch_bounds__(NT, TILE == 64 ? 3 : 6) void batch2d_kernel(const B
   run_task<TILE / 32, PH>(solves[T.solve], T, lds);
 }
 
+// What of a solve changes between steps: the caller's states and maps.
+struct BatchState {
+  float *p, *ux, *uy;
+  const float* c2;
+  double sD;
+};
+constexpr int kMaxStates = 96;   // 40 bytes each, within a launch's 4 KB of arguments
+struct StateArgs {
+  BatchState s[kMaxStates];
+};
+
+__global__ __launch_bounds__(128) void batch_states_kernel(StateArgs a, int count, BatchSolve* table) {
+  const int i = threadIdx.x;
+  if (i >= count) return;
+  table[i].p = a.s[i].p;
+  table[i].ux = a.s[i].ux;
+  table[i].uy = a.s[i].uy;
+  table[i].c2 = a.s[i].c2;
+  table[i].sD = a.s[i].sD;
+}
+
 template <int TILE>
 hipError_t launch_t(int phase, const BatchSolve* solves, const BatchTask* tasks, const BatchRuns& runs, unsigned blocks,
                     hipStream_t s) {
@@ -137,6 +158,18 @@ hipError_t launch_t(int phase, const BatchSolve* solves, const BatchTask* tasks,
 }
 
 }  // namespace
+
+hipError_t launch_batch_states(const BatchSolve* solves, int count, BatchSolve* table, hipStream_t s) {
+  for (int i = 0; i < count; i += kMaxStates) {
+    StateArgs a{};
+    const int n = std::min(count - i, kMaxStates);
+    for (int k = 0; k < n; ++k) a.s[k] = BatchState{solves[i + k].p, solves[i + k].ux, solves[i + k].uy, solves[i + k].c2, solves[i + k].sD};
+    hipLaunchKernelGGL(batch_states_kernel, dim3(1), dim3(128), 0, s, a, n, table + i);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 hipError_t launch_batch2d(int phase, const BatchSolve* solves, const BatchTask* tasks, const BatchRuns& runs, int tile,
                           hipStream_t s) {
