@@ -201,8 +201,17 @@ uint64_t fnv1a(uint64_t h, const void* p, size_t n) {
   return h;
 }
 
+// What a tuned configuration depends on: the kernels (kBatchKernels, raised with every change of them that moves their
+// times), the solves, which of them have a sound-speed map, and the GPU.
+constexpr int kBatchKernels = 2;
+
 std::string signature(const pstd_batch_s* B) {
   uint64_t h = 1469598103934665603ull;
+  h = fnv1a(h, &kBatchKernels, sizeof(kBatchKernels));
+  for (const BatchSolve& S : B->solves) {
+    const unsigned char map = S.c2 != nullptr;
+    h = fnv1a(h, &map, 1);
+  }
   h = fnv1a(h, &B->count, sizeof(B->count));
   h = fnv1a(h, B->nx.data(), B->nx.size() * sizeof(int));
   h = fnv1a(h, B->ny.data(), B->ny.size() * sizeof(int));
