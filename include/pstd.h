@@ -282,10 +282,10 @@ int pstd_batch_step(pstd_batch batch, pstd_state* states, int64_t n_steps);
 int pstd_batch_combine_R(pstd_batch batch, const pstd_state* states, const int32_t* pairs, const double* R,
                          float* const* out, int32_t npairs);
 
-/* Launch configuration of pstd_batch_step: blocks (accepted and kept; a launch has one block per tile), tile
- * order within a phase (0 = longest contraction first, 1 = solve by solve) and output tile edge (32 or 64; 16: when
- * every solve has one shape of at most 512 x 512 nodes, the fused phase launches of a single 2D plan over all
- * solves; order is then unused).  Returns PSTD_E_UNSUPPORTED for tile 16 on other batches. */
+/* Launch configuration of pstd_batch_step: blocks (0 = one per tile; otherwise a launch has at most so many, each with several
+ * tiles, and leaves the rest of the GPU to other work), tile order within a phase (0 = longest contraction first, 1 = solve
+ * by solve) and output tile edge (32 or 64; 16: when every solve has one shape of at most 512 x 512 nodes, the fused phase launches of a
+ * single 2D plan over all solves; blocks and order are then unused).  Returns PSTD_E_UNSUPPORTED for tile 16 on other batches. */
 int pstd_batch_set_config(pstd_batch batch, int32_t blocks, int32_t order, int32_t tile);
 
 /* Autotuner: time every candidate configuration (tile edge x order, and tile 16 where it applies) for

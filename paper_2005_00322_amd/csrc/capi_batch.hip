@@ -31,11 +31,11 @@ struct pstd_batch_s {
   pstd::BatchTask* d_tasks = nullptr;         // A then B
   int order_built = -1;
   int tile_built = -1;
-  int blocks = 0;                             // as configured (the launches have one block per tile)
+  int blocks = 0;                             // of a launch, at most (0: one per tile)
   int order = 0;
   int tile = 32;                              // output tile edge (32 or 64; 16: the fused phase launches)
   hipStream_t capture = nullptr;              // private stream the launch graphs are captured on
-  std::map<std::pair<int64_t, int>, hipGraphExec_t> graphs;   // (steps, tile) -> graph
+  std::map<std::tuple<int64_t, int, int>, hipGraphExec_t> graphs;   // (steps, tile, blocks) -> graph
 };
 
 namespace pstd {
@@ -162,7 +162,7 @@ constexpr int64_t kChunk = 64;   // steps per captured graph
 hipError_t launch_phase(pstd_batch_s* B, int phase, hipStream_t s) {
   if (B->tile == 16) return launch_phase2d_batch(phase, B->d_solves, B->count, B->nx[0], B->ny[0], false, s);
   return launch_batch2d(phase, B->d_solves, phase == 0 ? B->d_tasks : B->d_tasks + B->tasksA.size(),
-                        phase == 0 ? B->runsA : B->runsB, B->tile, s);
+                        phase == 0 ? B->runsA : B->runsB, B->tile, B->blocks, s);
 }
 
 // n_steps steps from captured graphs of up to kChunk of them.  The device tables a graph reads (solves, tasks) keep
@@ -171,7 +171,7 @@ hipError_t launch_phase(pstd_batch_s* B, int phase, hipStream_t s) {
 int launch_steps(pstd_batch_s* B, int64_t n_steps, hipStream_t s) {
   for (int64_t left = n_steps; left > 0; left -= kChunk) {
     const int64_t steps = std::min(left, kChunk);
-    const auto key = std::make_pair(steps, B->tile);
+    const auto key = std::make_tuple(steps, B->tile, B->tile == 16 ? 0 : B->blocks);
     auto it = B->graphs.find(key);
     if (it == B->graphs.end()) {
       if (!B->capture) PSTD_HIP(hipStreamCreateWithFlags(&B->capture, hipStreamNonBlocking));

@@ -287,9 +287,9 @@ constexpr int kBatchQueues = 8;
 struct BatchRuns {
   int beg[kBatchQueues + 1];
 };
-// phase 0: velocity tiles, 1: pressure tiles; tile: 32 or 64 (output tile edge)
+// phase 0: velocity tiles, 1: pressure tiles; tile: 32 or 64 (output tile edge); blocks: at most so many (0: one per tile)
 hipError_t launch_batch2d(int phase, const BatchSolve* solves, const BatchTask* tasks, const BatchRuns& runs, int tile,
-                          hipStream_t s);
+                          int blocks, hipStream_t s);
 
 hipError_t launch_nonfinite(int prec, const void* x, int64_t count, int* flag, hipStream_t s);
 

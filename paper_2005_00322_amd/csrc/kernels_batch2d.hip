@@ -12,8 +12,8 @@
 //
 // Operators are unscaled (dx = 1) FP32 matrices shared by all solves with the same (n, boundary pair);
 // each solve's constants -dt/(rho0 dx) and -dt rho0 c0^2/dx are applied in the FP64 epilogue.  The tile product is
-// tile_core.h's (a pressure tile runs it once per axis into the same accumulators); four blocks per CU keep the
-// matrix cores busy while others stage, load or wait.
+// tile_core.h's (a pressure tile runs it once per axis into the same accumulators); three (64-wide tiles) or more blocks per CU keep
+// the matrix cores busy while others stage, load or wait.
 #include <algorithm>
 
 #include "tile_core.h"
@@ -116,16 +116,21 @@ __device__ __forceinline__ void run_task(const BatchSolve& S, const BatchTask& T
               static_cast<float>(fma(scale, acc[i][j][r], static_cast<double>(yv[i][j][r])));
 }
 
-// One phase: block b takes tile b / 8 of the run of XCD b % 8.  64-wide tiles at three blocks per CU: a fourth costs 38
-// spilled registers (256 uneven solves 1028 against 923 us per step).
-template <int TILE, int PH>
+// One phase: slot b takes tile b / 8 of the run of XCD b % 8; a block has one slot, or with a limit on the blocks (LIMIT, `slots` in
+// all) every gridDim.x-th.  64-wide tiles at three blocks per CU: a fourth costs 38 spilled registers (256 uneven solves
+// 1028 against 923 us per step).
+template <int TILE, int PH, bool LIMIT>
 __global__ __launch_bounds__(NT, TILE == 64 ? 3 : 6) void batch2d_kernel(const BatchSolve* __restrict__ solves,
-                                                        const BatchTask* __restrict__ tasks, BatchRuns runs) {
+                                                        const BatchTask* __restrict__ tasks, BatchRuns runs, int slots) {
   __shared__ __attribute__((aligned(16))) float lds[BatchTile<TILE / 32>::lds_values];
-  const int q = blockIdx.x % kBatchQueues, t = runs.beg[q] + static_cast<int>(blockIdx.x) / kBatchQueues;
-  if (t >= runs.beg[q + 1]) return;
-  const BatchTask T = tasks[t];
-  run_task<TILE / 32, PH>(solves[T.solve], T, lds);
+  for (int b = blockIdx.x; b < (LIMIT ? slots : static_cast<int>(gridDim.x)); b += gridDim.x) {
+    const int q = b % kBatchQueues, t = runs.beg[q] + b / kBatchQueues;
+    if (t < runs.beg[q + 1]) {
+      const BatchTask T = tasks[t];
+      run_task<TILE / 32, PH>(solves[T.solve], T, lds);
+    }
+    if (!LIMIT) break;
+  }
 }
 
 // What of a solve changes between steps: the caller's states and maps.
@@ -149,12 +154,12 @@ __global__ __launch_bounds__(128) void batch_states_kernel(StateArgs a, int coun
   table[i].sD = a.s[i].sD;
 }
 
-template <int TILE>
-hipError_t launch_t(int phase, const BatchSolve* solves, const BatchTask* tasks, const BatchRuns& runs, unsigned blocks,
-                    hipStream_t s) {
-  if (phase == 0) hipLaunchKernelGGL((batch2d_kernel<TILE, 0>), dim3(blocks), dim3(NT), 0, s, solves, tasks, runs);
-  else hipLaunchKernelGGL((batch2d_kernel<TILE, 1>), dim3(blocks), dim3(NT), 0, s, solves, tasks, runs);
-  return hipGetLastError();
+template <int TILE, int PH>
+void launch_t(const BatchSolve* solves, const BatchTask* tasks, const BatchRuns& runs, int slots, int blocks, hipStream_t s) {
+  if (blocks > 0 && blocks < slots)
+    hipLaunchKernelGGL((batch2d_kernel<TILE, PH, true>), dim3(blocks), dim3(NT), 0, s, solves, tasks, runs, slots);
+  else
+    hipLaunchKernelGGL((batch2d_kernel<TILE, PH, false>), dim3(slots), dim3(NT), 0, s, solves, tasks, runs, slots);
 }
 
 }  // namespace
@@ -172,12 +177,16 @@ hipError_t launch_batch_states(const BatchSolve* solves, int count, BatchSolve* 
 }
 
 hipError_t launch_batch2d(int phase, const BatchSolve* solves, const BatchTask* tasks, const BatchRuns& runs, int tile,
-                          hipStream_t s) {
+                          int blocks, hipStream_t s) {
   int most = 0;
   for (int q = 0; q < kBatchQueues; ++q) most = std::max(most, runs.beg[q + 1] - runs.beg[q]);
-  if (most < 1 || most > 0x7fffffff / kBatchQueues || (tile != 32 && tile != 64)) return hipErrorInvalidValue;
-  const unsigned blocks = static_cast<unsigned>(most) * kBatchQueues;
-  return tile == 64 ? launch_t<64>(phase, solves, tasks, runs, blocks, s) : launch_t<32>(phase, solves, tasks, runs, blocks, s);
+  if (most < 1 || most > 0x7fffffff / kBatchQueues / 2 || (tile != 32 && tile != 64)) return hipErrorInvalidValue;
+  const int slots = most * kBatchQueues;
+  if (tile == 64 && phase == 0) launch_t<64, 0>(solves, tasks, runs, slots, blocks, s);
+  else if (tile == 64) launch_t<64, 1>(solves, tasks, runs, slots, blocks, s);
+  else if (phase == 0) launch_t<32, 0>(solves, tasks, runs, slots, blocks, s);
+  else launch_t<32, 1>(solves, tasks, runs, slots, blocks, s);
+  return hipGetLastError();
 }
 
 }  // namespace pstd
