@@ -3,6 +3,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 
 #include "common.h"
@@ -28,20 +29,143 @@ int fail(int status, const char* fmt, ...) {
   return status;
 }
 
-// Operators go into one allocation and one copy up to this size: three axes of 161, 200 and 129 nodes take 160 us so and 220 with
+namespace {
+
+// Operators go into one allocation up to this size: three axes of 161, 200 and 129 nodes take 160 us so and 220 with
 // one each; an allocation of more than 1 MB costs 25 us more than two smaller ones.
 constexpr size_t kOneAllocation = 1 << 20;
+// They are formed and copied piece by piece through a host buffer of at most this size (or one unit's, where that is more): whole
+// images of large operators were fresh pages, cleared first and gone from the caches when they were copied (a line of 1365 nodes
+// in FP64 took 25 ms, and 5 now), and pieces below 4 MB are copied more slowly (1500 x 30 in FP64: 2.95 ms with 1 MB, 2.7 with 4).
+constexpr size_t kStageBytes = 4 << 20;
+
+// A host buffer, aligned for vector stores; get() is null where there is no memory for it.  (malloc gives a program that makes plans
+// one after another the same pages again; aligned_alloc maps new ones each time: 4 MB of those cost 0.3 ms.)
+template <typename T>
+class Stage {
+ public:
+  explicit Stage(size_t n) : p_(std::malloc(n * sizeof(T) + 64)) {}
+  ~Stage() { std::free(p_); }
+  Stage(const Stage&) = delete;
+  Stage& operator=(const Stage&) = delete;
+  T* get() const { return p_ ? reinterpret_cast<T*>((reinterpret_cast<uintptr_t>(p_) + 63) & ~uintptr_t(63)) : nullptr; }
+
+ private:
+  void* p_;
+};
+
+// A unit of an operator's images: 16 rows of its fragments (image 0) or as they are (image 1), zero padded.
+inline size_t unit_values(const DevOperator& op) { return 16 * static_cast<size_t>(op.Kp); }
+
+// `rows` rows (at most 16) of a row-major matrix of K columns times scale, as T, into the fragments of one row block, each row's
+// chunks transposed as 4 x 4 values.  In FP32 four rows at a time, whose values fill whole cache lines of the fragments; what
+// bounds it is reading the tables, which lie in memory, so the rows that follow are fetched ahead (a 1500 x 30 plan in FP32: 3.3 ms
+// with one row at a time, 2.3 with four, 1.7 with their lines fetched ahead; FP64 2.7 with one, 3.4 with four).
+template <typename T>
+void fill_fragments(const double* m, int rows, int K, double scale, T* out) {
+  typedef T v4 __attribute__((ext_vector_type(4)));
+  typedef double d4 __attribute__((ext_vector_type(4), aligned(8)));
+  constexpr int R = sizeof(T) == 4 ? 4 : 1;   // rows at a time
+  for (int i0 = 0; i0 < rows; i0 += R) {
+    const int n = std::min(R, rows - i0);
+    const double* r0 = m + static_cast<size_t>(i0) * K;
+    T* o = out + 4 * i0;
+    int k0 = 0;
+    for (; k0 + 16 <= K; k0 += 16, r0 += 16, o += 256)
+      for (int i = 0; i < n; ++i) {
+        const double* r = r0 + static_cast<size_t>(i) * K;
+        __builtin_prefetch(r + R * static_cast<size_t>(K));
+        __builtin_prefetch(r + R * static_cast<size_t>(K) + 8);
+        const v4 a = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r), v4);
+        const v4 b = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 4), v4);
+        const v4 c = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 8), v4);
+        const v4 d = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 12), v4);
+        const v4 ab0 = __builtin_shufflevector(a, b, 0, 4, 1, 5), ab1 = __builtin_shufflevector(a, b, 2, 6, 3, 7);
+        const v4 cd0 = __builtin_shufflevector(c, d, 0, 4, 1, 5), cd1 = __builtin_shufflevector(c, d, 2, 6, 3, 7);
+        v4* q = reinterpret_cast<v4*>(o) + i;
+        q[0] = __builtin_shufflevector(ab0, cd0, 0, 1, 4, 5);
+        q[16] = __builtin_shufflevector(ab0, cd0, 2, 3, 6, 7);
+        q[32] = __builtin_shufflevector(ab1, cd1, 0, 1, 4, 5);
+        q[48] = __builtin_shufflevector(ab1, cd1, 2, 3, 6, 7);
+      }
+    for (int i = 0; i < n; ++i)
+      for (int k = 0; k0 + k < K; ++k) o[4 * i + 64 * (k & 3) + (k >> 2)] = static_cast<T>(scale * r0[static_cast<size_t>(i) * K + k]);
+  }
+}
+
+template <typename T>
+void fill_unit(const OperatorSource& src, int image, int unit, T* out) {
+  const DevOperator& op = *src.op;
+  const size_t values = unit_values(op), K = src.K;
+  const int n = std::max(0, std::min(16, src.M - 16 * unit));
+  const double* m = src.m->data() + 16 * unit * K;
+  if (n < 16) std::memset(out, 0, values * sizeof(T));
+  if (image == 0) {
+    const size_t whole = K / 16 * 256;   // of the chunks that K fills
+    if (n == 16) std::memset(out + whole, 0, (values - whole) * sizeof(T));
+    fill_fragments(m, n, src.K, src.scale, out);
+  } else {
+    for (int i = 0; i < n; ++i, m += K, out += op.Kp) {
+      for (size_t k = 0; k < K; ++k) out[k] = static_cast<T>(src.scale * m[k]);
+      std::memset(out + K, 0, (op.Kp - K) * sizeof(T));
+    }
+  }
+}
+
+// The first `images` images of `count` operators one behind the other, handed in pieces of at most `cap` values (or one unit) to
+// put(piece, values).
+template <typename T, typename Put>
+int form_images(const OperatorSource* src, int count, int images, size_t cap, Put&& put) {
+  size_t total = 0, unit = 0;
+  for (int i = 0; i < count; ++i) {
+    unit = std::max(unit, unit_values(*src[i].op));
+    total += images * static_cast<size_t>(src[i].op->Mp) * src[i].op->Kp;
+  }
+  cap = std::min(total, std::max(cap, unit));
+  const Stage<T> stage(cap);
+  if (!stage.get()) return fail(PSTD_E_OOM, "no host memory for the operators");
+  size_t held = 0;
+  for (int i = 0; i < count; ++i)
+    for (int image = 0; image < images; ++image)
+      for (int u = 0; u < src[i].op->Mp / 16; ++u) {
+        const size_t values = unit_values(*src[i].op);
+        if (held + values > cap) {
+          const int st = put(stage.get(), held);
+          if (st != PSTD_OK) return st;
+          held = 0;
+        }
+        fill_unit(src[i], image, u, stage.get() + held);
+        held += values;
+      }
+  return put(stage.get(), held);
+}
+
+// put for form_images: pieces one behind the other to device memory
+template <typename T>
+struct CopyUp {
+  T* to;
+  int operator()(const T* piece, size_t values) {
+    PSTD_HIP(hipMemcpy(to, piece, values * sizeof(T), hipMemcpyHostToDevice));
+    to += values;
+    return PSTD_OK;
+  }
+};
+
+inline void set_shape(const OperatorSource& s) {
+  s.op->M = s.M;
+  s.op->K = s.K;
+  s.op->Mp = static_cast<int>(round_up(s.M, kRowPad));
+  s.op->Kp = static_cast<int>(round_up(s.K, kColPad));
+}
+
+}  // namespace
 
 template <typename T>
 int upload_plain(const OperatorSource* src, int count, int copies) {
   size_t total = 0;
   for (int i = 0; i < count; ++i) {
-    DevOperator& op = *src[i].op;
-    op.M = src[i].M;
-    op.K = src[i].K;
-    op.Mp = static_cast<int>(round_up(op.M, kRowPad));
-    op.Kp = static_cast<int>(round_up(op.K, kColPad));
-    total += (1 + copies) * static_cast<size_t>(op.Mp) * op.Kp;
+    set_shape(src[i]);
+    total += (1 + copies) * static_cast<size_t>(src[i].op->Mp) * src[i].op->Kp;
   }
   if (count > 1 && total * sizeof(T) > kOneAllocation) {
     for (int i = 0; i < count; ++i) {
@@ -50,30 +174,27 @@ int upload_plain(const OperatorSource* src, int count, int copies) {
     }
     return PSTD_OK;
   }
-  const HostZeros<T> host(total);
-  if (!host.get()) return fail(PSTD_E_OOM, "no host memory for the operators");
-  T* h = host.get();
-  for (int i = 0; i < count; ++i) {
-    const DevOperator& op = *src[i].op;
-    const size_t cnt = static_cast<size_t>(op.Mp) * op.Kp;
-    fill_fragments(src[i].m->data(), op.M, op.K, src[i].scale, op.Kp, h);
-    if (copies) fill_lines(src[i].m->data(), op.M, op.K, src[i].scale, op.Mp, op.Kp, h + cnt, copies >= 2 ? h + 2 * cnt : nullptr);
-    h += (1 + copies) * cnt;
-  }
   void* data = nullptr;
   if (hipMalloc(&data, total * sizeof(T)) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of the operators failed");
   src[0].op->data = data;
-  PSTD_HIP(hipMemcpy(data, host.get(), total * sizeof(T), hipMemcpyHostToDevice));
+  // the images that the host forms, one operator's behind the other's, and behind them the columns, which the GPU forms from the rows
+  const int host = std::min(copies, 1) + 1;
   T* d = static_cast<T*>(data);
+  T* cols = d + total / (1 + copies) * host;
+  const int st = form_images<T>(src, count, host, kStageBytes / sizeof(T), CopyUp<T>{d});
+  if (st != PSTD_OK) return st;
   for (int i = 0; i < count; ++i) {
     DevOperator& op = *src[i].op;
     const size_t cnt = static_cast<size_t>(op.Mp) * op.Kp;
+    if (copies >= 2) PSTD_HIP(launch_transpose(sizeof(T) == 8, d + cnt, op.Mp, op.Kp, cols, nullptr));
     op.bytes = (1 + copies) * cnt * sizeof(T);
     op.frag = d;
     if (copies >= 1) op.rows = d + cnt;
-    if (copies >= 2) op.cols = d + 2 * cnt;
-    d += (1 + copies) * cnt;
+    if (copies >= 2) op.cols = cols;
+    d += host * cnt;
+    cols += cnt;
   }
+  if (copies >= 2) PSTD_HIP(hipStreamSynchronize(nullptr));
   return PSTD_OK;
 }
 template int upload_plain<float>(const OperatorSource*, int, int);
@@ -113,32 +234,45 @@ inline void split_entry(float v, uint16_t* at) {
   at[512] = bf16_rne(v - bf16_to_float(hi));
 }
 
-// The entries entry(i, k) of op as a split operator in fragment order, zero padded, in an allocation of its own.  Runs of eight k
-// lie side by side in both orders.
+// The entries entry(i, k) of op as a split operator in fragment order, zero padded, in an allocation of its own, formed and copied by
+// units of 32 rows.  Runs of eight k lie side by side in both orders.
 template <typename F>
-int upload_split_entries(const DevOperator& op, F&& entry, void** out) {
-  const size_t words = 2 * static_cast<size_t>(op.Mp) * op.Kp;
-  const HostZeros<uint16_t> host(words);
-  if (!host.get()) return fail(PSTD_E_OOM, "no host memory for an operator");
-  for (int i0 = 0; i0 < op.M; i0 += 32)
-    for (int k0 = 0; k0 < op.K; k0 += 8)
-      for (int i = i0; i < std::min(i0 + 32, op.M); ++i) {
-        uint16_t* at = host.get() + split_fragment_at(op.Kp, i, k0);
-        if (k0 + 8 <= op.K)
-          for (int k = 0; k < 8; ++k) split_entry(entry(i, k0 + k), at + k);
-        else
-          for (int k = 0; k0 + k < op.K; ++k) split_entry(entry(i, k0 + k), at + k);
-      }
+int upload_split_entries(const DevOperator& op, const double* table, F&& entry, void** out) {
+  const size_t unit = 64 * static_cast<size_t>(op.Kp), words = op.Mp / 32 * unit;
+  const size_t cap = std::min(words, std::max<size_t>(1, kStageBytes / 2 / unit) * unit);
+  const Stage<uint16_t> stage(cap);
+  if (!stage.get()) return fail(PSTD_E_OOM, "no host memory for an operator");
   if (hipMalloc(out, words * 2) != hipSuccess) return fail(PSTD_E_OOM, "hipMalloc of an operator failed");
-  PSTD_HIP(hipMemcpy(*out, host.get(), words * 2, hipMemcpyHostToDevice));
-  return PSTD_OK;
+  CopyUp<uint16_t> put{static_cast<uint16_t*>(*out)};
+  size_t held = 0;
+  for (int i0 = 0; i0 < op.Mp; i0 += 32) {
+    if (held == cap) {
+      const int st = put(stage.get(), held);
+      if (st != PSTD_OK) return st;
+      held = 0;
+    }
+    uint16_t* const u = stage.get() + held;
+    std::memset(u, 0, unit * 2);
+    for (int i1 = i0; i1 < std::min(i0 + 32, op.M); i1 += 4)
+      for (int k0 = 0; k0 < op.K; k0 += 8)
+        for (int i = i1; i < std::min(i1 + 4, op.M); ++i) {
+          uint16_t* at = u + split_fragment_at(op.Kp, i - i0, k0);
+          if (table) __builtin_prefetch(table + static_cast<size_t>(i + 4) * op.K + k0);
+          if (k0 + 8 <= op.K)
+            for (int k = 0; k < 8; ++k) split_entry(entry(i, k0 + k), at + k);
+          else
+            for (int k = 0; k0 + k < op.K; ++k) split_entry(entry(i, k0 + k), at + k);
+        }
+    held += unit;
+  }
+  return put(stage.get(), held);
 }
 
 // The entries of m times scale as rounded from FP64.
 int upload_split_exact(const std::vector<double>& m, double scale, const DevOperator& op, void** out) {
   const double* a = m.data();
   const size_t K = op.K;
-  return upload_split_entries(op, [=](int i, int k) { return scale * a[i * K + k]; }, out);
+  return upload_split_entries(op, a, [=](int i, int k) { return scale * a[i * K + k]; }, out);
 }
 
 // The matrix m (M x K) times scale as a split operator.
@@ -164,7 +298,7 @@ int upload_split(const std::vector<double>& m, int M, int K, double scale, DevOp
     }
     const float *fp = ff.data() + M - 1, *gp = gg.data();
     const float w0 = static_cast<float>(w[0]), w1 = static_cast<float>(w[1]), w2 = static_cast<float>(w[2]), w3 = static_cast<float>(w[3]);
-    st = upload_split_entries(*op, [=](int i, int k) {
+    st = upload_split_entries(*op, nullptr, [=](int i, int k) {
       const float wr = i == 0 ? w0 : i == M - 1 ? w1 : 1.f, wc = k == 0 ? w2 : k == K - 1 ? w3 : 1.f;
       return wr * wc * (fp[k - i] + gp[i + k]);
     }, &op->data);
@@ -989,6 +1123,29 @@ int64_t pstd_test_operator_bytes(pstd_plan P) {
     for (const DevOperator& r : P->R[a]) b += r.bytes;
   }
   return static_cast<int64_t>(b);
+}
+
+// For tests (host only): the first `images` images of the M x K matrix m times scale in FP32 (or FP64), formed in pieces of at most
+// `cap` values (0: as for a plan) into out; *largest: the values of the largest piece.
+int pstd_test_operator_images(int32_t M, int32_t K, const double* m, double scale, int32_t dbl, int32_t images, int64_t cap,
+                              void* out, int64_t* largest) {
+  if (M < 1 || K < 1 || M > 4097 || K > 4097 || !m || !out || !largest || images < 1 || images > 2 || cap < 0)
+    return fail(PSTD_E_INVALID_ARG, "bad argument");
+  const std::vector<double> mat(m, m + static_cast<size_t>(M) * K);
+  DevOperator op;
+  const OperatorSource src{&mat, M, K, scale, &op};
+  set_shape(src);
+  *largest = 0;
+  auto run = [&](auto* to) {
+    typedef std::remove_reference_t<decltype(*to)> T;
+    return form_images<T>(&src, 1, images, cap ? static_cast<size_t>(cap) : kStageBytes / sizeof(T), [&](const T* piece, size_t values) {
+      *largest = std::max(*largest, static_cast<int64_t>(values));
+      std::memcpy(to, piece, values * sizeof(T));
+      to += values;
+      return static_cast<int>(PSTD_OK);
+    });
+  };
+  return dbl ? run(static_cast<double*>(out)) : run(static_cast<float*>(out));
 }
 
 // For tests (host only): workgroups of a long line's time loop, their rows, and the words of u that they exchange.

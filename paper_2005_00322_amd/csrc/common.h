@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <cstdlib>
 #include <string>
 #include <vector>
 
@@ -105,45 +104,6 @@ struct DevOperator {
 inline size_t fragment_at(int Kp, int i, int k) {
   return (static_cast<size_t>(i >> 4) * (Kp >> 4) + (k >> 4)) * 256 + 4 * ((i & 15) + 16 * (k & 3)) + ((k & 15) >> 2);
 }
-// The M x K row-major matrix m times scale, as T, into zeroed fragments of padded width Kp.  A row at a time, its chunks
-// transposed as 4 x 4 values: plans and batches form their operators from tables that lie in host memory, and what bounds it is the
-// one stream that it reads (300 x 300 in FP32: 41 us, 59 with sixteen rows at a time, 28 without reordering).
-template <typename T>
-void fill_fragments(const double* m, int M, int K, double scale, int Kp, T* out) {
-  typedef T v4 __attribute__((ext_vector_type(4)));
-  typedef double d4 __attribute__((ext_vector_type(4), aligned(8)));
-  for (int i = 0; i < M; ++i) {
-    const double* r = m + static_cast<size_t>(i) * K;
-    T* o = out + fragment_at(Kp, i, 0);
-    int k0 = 0;
-    for (; k0 + 16 <= K; k0 += 16, r += 16, o += 256) {
-      const v4 a = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r), v4);
-      const v4 b = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 4), v4);
-      const v4 c = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 8), v4);
-      const v4 d = __builtin_convertvector(scale * *reinterpret_cast<const d4*>(r + 12), v4);
-      const v4 ab0 = __builtin_shufflevector(a, b, 0, 4, 1, 5), ab1 = __builtin_shufflevector(a, b, 2, 6, 3, 7);
-      const v4 cd0 = __builtin_shufflevector(c, d, 0, 4, 1, 5), cd1 = __builtin_shufflevector(c, d, 2, 6, 3, 7);
-      v4* q = reinterpret_cast<v4*>(o);
-      q[0] = __builtin_shufflevector(ab0, cd0, 0, 1, 4, 5);
-      q[16] = __builtin_shufflevector(ab0, cd0, 2, 3, 6, 7);
-      q[32] = __builtin_shufflevector(ab1, cd1, 0, 1, 4, 5);
-      q[48] = __builtin_shufflevector(ab1, cd1, 2, 3, 6, 7);
-    }
-    for (int k = 0; k0 + k < K; ++k) o[64 * (k & 3) + (k >> 2)] = static_cast<T>(scale * r[k]);
-  }
-}
-// The same into rows (stride Kp) and, where given, columns (stride Mp), in blocks so that either side stays in cache.
-template <typename T>
-void fill_lines(const double* m, int M, int K, double scale, int Mp, int Kp, T* rows, T* cols) {
-  for (int i0 = 0; i0 < M; i0 += 16)
-    for (int k0 = 0; k0 < K; k0 += 16)
-      for (int i = i0; i < M && i < i0 + 16; ++i)
-        for (int k = k0; k < K && k < k0 + 16; ++k) {
-          const T v = static_cast<T>(scale * m[static_cast<size_t>(i) * K + k]);
-          rows[static_cast<size_t>(i) * Kp + k] = v;
-          if (cols) cols[static_cast<size_t>(k) * Mp + i] = v;
-        }
-}
 // Matrices times scale as T on the device, zero padded, in fragment order, with `copies` more of each (1: its rows, 2: and its
 // columns).
 struct OperatorSource {
@@ -154,20 +114,6 @@ struct OperatorSource {
 };
 template <typename T>
 int upload_plain(const OperatorSource* src, int count, int copies);
-// A zeroed host array (pages that stay zero are not touched); get() is null where there is no memory for it.
-template <typename T>
-class HostZeros {
- public:
-  explicit HostZeros(size_t n) : p_(static_cast<T*>(std::calloc(n, sizeof(T)))) {}
-  ~HostZeros() { std::free(p_); }
-  HostZeros(const HostZeros&) = delete;
-  HostZeros& operator=(const HostZeros&) = delete;
-  T* get() const { return p_; }
-
- private:
-  T* p_;
-};
-
 // Split-bf16 operators whose entries are the FP32 sums of their Toeplitz and Hankel parts: rows in
 // (kThRowsMin, kThRowsMax], padded columns up to kThColsMax.
 constexpr int kThRowsMin = 192, kThRowsMax = 384, kThColsMax = 512;
@@ -230,6 +176,8 @@ inline __host__ __device__ int line_u_words(int n) { return n; }
 size_t step1d_work_bytes(int prec, int n);
 hipError_t launch_step1d(int prec, const DevOperator& G, const DevOperator& D, void* p, void* u, int n,
                          int64_t steps, const void* scale, void* work, unsigned spins, hipStream_t s);
+// The columns (Kp x Mp) of an operator from its padded rows (Mp x Kp), both extents multiples of 64.
+hipError_t launch_transpose(bool dbl, const void* rows, int Mp, int Kp, void* cols, hipStream_t s);
 hipError_t launch_zero_dirichlet(int prec, void* p, int ndim, const int64_t* n, const int* dir_lo,
                                  const int* dir_hi, hipStream_t s);
 hipError_t launch_fill_zero(int prec, void* x, int64_t count, hipStream_t s);

@@ -336,6 +336,17 @@ __global__ __launch_bounds__(1024) void step1d_reg_kernel(const T* __restrict__ 
   if (q == 0 && i < nm) u[i] = ui;
 }
 
+// cols = rows^T by tiles of 64 x 64 (a long line's operators, once per plan: 1365 nodes in FP64 take the host 8 ms, bound by the
+// strided side).
+template <typename T>
+__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ rows, int Mp, int Kp, T* __restrict__ cols) {
+  __shared__ T tile[64][65];
+  const int i0 = blockIdx.y * 64, k0 = blockIdx.x * 64, l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int r = w; r < 64; r += 4) tile[r][l] = rows[static_cast<int64_t>(i0 + r) * Kp + k0 + l];
+  __syncthreads();
+  for (int r = w; r < 64; r += 4) cols[static_cast<int64_t>(k0 + r) * Mp + i0 + l] = tile[l][r];
+}
+
 template <typename T>
 __global__ void zero_dirichlet_kernel(T* p, int ndim, int64_t n0, int64_t n1, int64_t n2, int lo0, int hi0, int lo1,
                                       int hi1, int lo2, int hi2) {
@@ -520,6 +531,16 @@ hipError_t launch_step1d(int prec, const DevOperator& G, const DevOperator& D, v
                                    static_cast<const double*>(scale), work, spins, s);
   return launch_step1d_t<float>(prec, G, D, static_cast<float*>(p), static_cast<float*>(u), n, steps,
                                 static_cast<const float*>(scale), work, spins, s);
+}
+
+hipError_t launch_transpose(bool dbl, const void* rows, int Mp, int Kp, void* cols, hipStream_t s) {
+  if (Mp < 64 || Kp < 64 || Mp % 64 || Kp % 64) return hipErrorInvalidValue;
+  const dim3 grid(Kp / 64, Mp / 64), blk(256);
+  if (dbl)
+    hipLaunchKernelGGL(transpose_kernel<double>, grid, blk, 0, s, static_cast<const double*>(rows), Mp, Kp, static_cast<double*>(cols));
+  else
+    hipLaunchKernelGGL(transpose_kernel<float>, grid, blk, 0, s, static_cast<const float*>(rows), Mp, Kp, static_cast<float*>(cols));
+  return hipGetLastError();
 }
 
 hipError_t launch_zero_dirichlet(int prec, void* p, int ndim, const int64_t* n, const int* lo, const int* hi,
