@@ -126,15 +126,16 @@ int pstd_step_prepare(pstd_plan plan, const pstd_state* state, int64_t n_steps);
 /* Execution path of pstd_step.
  *   PER_AXIS: one dense contraction kernel per axis and half step (axes up to 4097 nodes).
  *   FUSED:    2D FP32 grids of at most 512 x 512 nodes, walls or periodic axes: two kernels per step
- *             (every velocity tile, then every pressure tile with both axes' terms).
+ *             (every velocity tile, then every pressure tile with both axes' terms).  FP64 plans step so
+ *             under AUTO; FUSED by name is refused for them.
  *   FFT:      every axis whose extended period 2(n-1) is 16 x 2^a 3^b 5^c (up to 16384 for a float state,
  *             8192 for FP64) applies its operators as LDS-resident FFTs of the field's symmetric
  *             extension (§3.2: each DTT is a DFT of an evenly or oddly extended sequence), one kernel per
  *             axis and half step, and so does a periodic axis of a float state whose n is a power of two
  *             from 256 to 8192 (the DFT of the line itself, Eq. (fourier_pstd_solution)); other axes stay
  *             dense.
- *   AUTO:     FUSED where it applies; otherwise FFT on axes above 512 nodes (1D plans: above 1365) and
- *             dense contractions elsewhere.
+ *   AUTO:     the two kernels of FUSED on every 2D FP32 or FP64 grid of at most 512 x 512 nodes; otherwise FFT on
+ *             axes above 512 nodes (1D plans: above 1365) and dense contractions elsewhere.
  *   FFT_GENERIC: FFT, with every axis on the mixed-radix kernel.  Under the other paths an FP32 axis
  *             whose 2(n-1) is a power of two from 256 to 8192 runs a kernel specialised to that length
  *             (radix-16 passes, twiddles and spectral multipliers from tables formed in FP64).
@@ -155,9 +156,9 @@ int pstd_plan_set_path(pstd_plan plan, int32_t path);
  * u_a += -(dt/rho0) G_a p (Eq. (dtt_pstd_solution_a) along that axis); which = 1 applies that axis's share
  * of the pressure update, p += -(dt rho0 c0^2) D_a u_a (one summand of Eq. (dtt_pstd_solution_b) in the
  * form of §4.3).  A full step is every which = 0 term followed by every which = 1 term.  axis = -1
- * applies the whole phase (every axis) the way pstd_step does it: one kernel on the FUSED path; one for
+ * applies the whole phase (every axis) the way pstd_step does it: one kernel where the step is two; one for
  * the velocity terms of all axes when every axis runs on the FFT path with one power-of-two transform
- * length (float state); one per axis otherwise.  Asynchronous on the plan's stream; state->step is not
+ * length (float state) or none does (FP32, FP64); one per axis otherwise.  Asynchronous on the plan's stream; state->step is not
  * changed. */
 int pstd_apply_axis(pstd_plan plan, pstd_state* state, int32_t axis, int32_t which);
 

@@ -50,8 +50,10 @@ __device__ __forceinline__ void contract_tile(const KArgs<T>& a, int tile, T* ld
   const int lane = threadIdx.x & 63;
   typename TL::template Field<ROWS> X;
   X.K = a.K;
-  // the first line's batch (strided; every later line's offset from it fits 32 bits: a batch of 4 GiB has no neighbour
-  // within the 2^31 points of a plan)
+  // the first line's batch (strided).  A lane's offsets from there fit 32 bits through the limits on an axis, 4097 nodes along a
+  // dense one and 8193 (FP64: 4097) along any: a middle axis has batches of at most 4097 x 8193 values, and a tile's lines
+  // span at most two of them or 128 x 4097 values; the first axis is one batch, with rows at most 8193^2 values apart, and a
+  // lane's first row is 12 from its wave's at most (FP64: 3 of 4097^2): 3.2 GB.
   const int64_t b0 = ROWS ? 0 : l0 / a.inner, c0 = ROWS ? 0 : l0 - b0 * a.inner;
   auto line_off = [&](int64_t l, int64_t bstride) {   // elements from line l0 to line l0 + l (clamped)
     const int64_t c = c0 + min(l, a.lines - 1 - l0), b = c / a.inner;

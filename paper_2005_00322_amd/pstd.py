@@ -185,8 +185,8 @@ class Plan:
     PATHS = {"auto": 0, "per_axis": 1, "fused": 2, "fft": 3, "stored": 4, "fft_generic": 5}
 
     def set_path(self, path: str) -> None:
-        """Execution path of later steps: "auto", "per_axis" (dense contractions), "fused" (2D FP32: two
-        kernels per step), "fft" (LDS-resident FFTs on every axis whose 2(n-1) is 16 x 2^a 3^b 5^c),
+        """Execution path of later steps: "auto" (which gives 2D FP32 and FP64 plans of at most 512 x 512 nodes
+        two kernels per step), "per_axis" (dense contractions), "fused" (those two kernels, 2D FP32 only), "fft" (LDS-resident FFTs on every axis whose 2(n-1) is 16 x 2^a 3^b 5^c),
         "fft_generic" (fft with every axis on the mixed-radix kernel, also where an FP32 power-of-two
         length has its own) or "stored" (per_axis with split-bf16 operators as rounded from FP64
         rather than formed from their Toeplitz and Hankel parts)."""
