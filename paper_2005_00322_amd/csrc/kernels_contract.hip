@@ -15,8 +15,10 @@
 //               Y[r][m] += sum_k X[r][k] A[m][k]
 // The tile product is tile_core.h's; the columns of its output run along the unit stride of Y in both layouts.
 // us per launch before (64 x 64 tiles, 16-deep slices, both operands through LDS, one tile range per batch) and now, axes
-// x / y / z: 256^3 FP32 159 / 154 / 196 -> 99 / 98 / 89 (86-96 TFLOP/s of the 150 a large FP32 product reaches here);
-// 161 x 200 x 129 FP32 44 / 71 / 36 -> 28 / 36 / 18; 161 x 200 x 129 FP64 63 / 99 / 53 -> 39 / 50 / 27.
+// x / y / z: 256^3 FP32 159 / 154 / 196 -> 105 / 105 / 97 (82-89 TFLOP/s of the 150 a large FP32 product reaches here);
+// 161 x 200 x 129 FP32 44 / 71 / 36 -> 30 / 38 / 20; 161 x 200 x 129 FP64 63 / 99 / 53 -> 38 / 50 / 27.  Counters at the latter size in
+// FP32 with a map: matrix cores 26-38% busy, vector ALU 20-26%, 1.5-1.8 TB/s.  A launch of one axis has about 1250 blocks, four per
+// CU and a fifth of a second round.
 #include <algorithm>
 
 #include "tile_core.h"
@@ -197,8 +199,8 @@ int64_t tiles_of(const KArgs<T>& a, int edge) {
 }
 
 // 64 x 64 tiles from about 400 of them on (1.5 per CU), 32 x 32 before that: four times the blocks, twice the operand
-// traffic for a product.  us at 32 / 64, FP32: 314 tiles (100 x 100^2) 9.9 / 11.2, 400 (128 x 100^2) 11.9 / 11.0,
-// 512 (128^3) 14.1 / 12.0; FP64: 314 12.1 / 13.9, 512 19.1 / 16.5.
+// traffic for a product.  us at 32 / 64, middle axis: 314 tiles (100^3) FP32 9.8 / 12.4, FP64 11.9 / 13.8; 400 (128 x 100^2)
+// 11.6 / 12.2 and 14.5 / 13.9; 512 (128^3) 13.6 / 13.3 and 18.0 / 16.2: the sides cross at about 390 tiles in FP64 and 470 in FP32.
 constexpr int64_t kBigTiles = 400;
 
 template <typename T>

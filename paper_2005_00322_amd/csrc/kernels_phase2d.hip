@@ -321,8 +321,8 @@ int tiles_of(int nx, int ny, int edge) { return ((nx + edge - 1) / edge) * ((ny 
 
 // Tile edge for `count` boxes of nx x ny nodes: 16 while its tiles are at most two per CU (each tile is then little more
 // than one round trip to memory), 32 beyond.  us per phase at 16 / 32, FP32 and FP64: 256 x 256 (256 tiles)
-// 4.2 / 6.2 and 4.9 / 8.5; 320 x 320 (400) 6.7 / 7.3 and 8.2 / 10.2; 512 x 300 (608) 10.0 / 8.6 and 12.4 / 12.4;
-// 512 x 512 (1024) 14.1 / 10.3 and 19.9 / 13.8.
+// 3.9 / 6.8 and 4.6 / 7.7; 320 x 320 (400) 6.5 / 8.1 and 7.6 / 9.0; 360 x 360 (529) 9.6 / 9.0 and 10.8 / 10.1; 512 x 300 (608)
+// 9.8 / 9.2 and 11.4 / 10.3; 512 x 512 (1024) 14.0 / 11.0 and 18.4 / 14.4.
 int tile_edge(int nx, int ny, int count) { return static_cast<int64_t>(tiles_of(nx, ny, 16)) * count > 512 ? 32 : 16; }
 
 // Chunks per round: 256 / MT bytes of a row, or half of that where it covers a wave's whole share (chunks past the share

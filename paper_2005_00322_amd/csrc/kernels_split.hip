@@ -7,7 +7,7 @@
 // A launch has to move the field once and the output twice through HBM; the matrix cores need about 40% of that time, and what
 // costs more is a poor overlap of the two (one block of eight waves per CU, K loop and update one after the other, the
 // operator through LDS: 184-195 us a launch at 384^3, 75-84 at 260^3, 13-15 at 128^3, 16-18 for a 256 x 256 plane).  Here
-// (171-190, 49-51, 6.8 and 8):
+// (173-190, 50-51, 6.8-7.8 and 8-10):
 //   - the four waves of a block split the operator's rows, so no two of them need the same operator fragment: it
 //     comes straight from L2 into the MFMA registers (16 bytes per lane, runs of 1 KB, one chunk of 16 k ahead) and
 //     nothing of it passes through LDS or the vector ALU;
@@ -30,7 +30,9 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int NT = 256, BK = 32, LD = BK + 8;      // LDS row stride in bf16: 80 bytes, conflict-free 16-byte accesses
+// LDS row stride in bf16: 80 bytes.  16-byte accesses of a strided field are free of conflicts; the stores of contiguous rows
+// are not (a quarter of the LDS cycles, 1.5% of the time).
+constexpr int NT = 256, BK = 32, LD = BK + 8;
 constexpr int JL = 2, LINES = kSplitLines;         // field lines of a block
 static_assert(LINES == 32 * JL && NT == 64 * kSplitWaves, "block shape");
 constexpr int PART = LINES * LD;                   // hi or lo part of a slice
